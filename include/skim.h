@@ -372,8 +372,9 @@ skim_status skim_ic_query_batch(const uint32_t *positions, uint32_t n, uint32_t 
  *   reach_pairs [q] out, device.
  *   qstatus     [q] out, device, may be NULL: 0, or -1 when the set holds a
  *               node >= n (its reach_pairs is then 0).
- * Scratch: the live out-lists of the graph (8 (64 n + 1) bytes plus 4 bytes
- * per live edge-instance) and up to 2 GiB of per-query search state.
+ * Scratch: the live out-lists of the graph (8 (l n + 1) bytes plus 4 bytes
+ * per live edge-instance) and, above 26,000 nodes, up to 2 GiB of search
+ * state (8 workgroups' worth, about 8.1 n bytes each, at least).
  */
 skim_status skim_influence_batch(const skim_graph *g, uint32_t ell, uint64_t seed, uint64_t q,
                                  const uint64_t *qoff, const uint32_t *qnodes,

@@ -5,27 +5,27 @@
 // or any other) on the instances of a given seed, typically fresh ones that
 // the sketches never saw.
 //
-// One coin pass builds the live out-list of every node-instance pair
-// (64 v + i), so the searches never evaluate a coin.  Each query is then a
-// breadth-first search over pairs run by one 1024-thread workgroup: a visited
-// bitmap of 64 bits per node and an append-only queue of pair ids (every pair
-// enters at most once, so the queue never overflows).  The queue is consumed
-// in chunks of one pair per thread; appends reserve queue slots with one LDS
-// atomic per wave.  The number of pairs appended is the query's answer.  The
-// workgroup then clears the words its pairs set, so the next query on the
-// same slot starts from a clean bitmap at a cost proportional to what was
-// visited.  Queries run in parallel, one per workgroup slot.
+// One coin pass builds the live out-lists, so the searches never evaluate a
+// coin.  A batch (skim_influence_batch) is cut into units of one instance and
+// 32 queries, each searched by one workgroup for its 32 queries at once
+// (k_eval_sets, see there); the lists are laid out instance by instance, so
+// the units of an instance read the same few hundred kilobytes.
 //
-// Exact greedy (skim_greedy_exact, the reference of a quality harness) reuses
-// the search with a bitmap of covered pairs: the pairs the seeds so far
-// reach.  That set is closed under reachability, so a search that skips
-// covered pairs counts exactly a node's marginal gain.  Each step scores every
-// node this way (n singleton queries), takes the largest gain on the device
-// (smallest id on ties, among unselected nodes), searches once more from the
-// winner and adds the pairs it reached to the covered bitmap.
+// Exact greedy (skim_greedy_exact, the reference of a quality harness) scores
+// one node per workgroup (k_eval): a breadth-first search over all instances'
+// pairs with a visited bitmap of 64 bits per node and an append-only queue of
+// pair ids (every pair enters at most once, so the queue never overflows),
+// consumed in chunks of one pair per thread.  The workgroup then clears the
+// words its pairs set.  The search skips the pairs the seeds so far reach, a
+// bitmap of covered pairs.  That set is closed under reachability, so a search
+// that skips covered pairs counts exactly a node's marginal gain.  Each step
+// scores every node this way (n singleton queries), takes the largest gain on
+// the device (smallest id on ties, among unselected nodes), searches once more
+// from the winner and adds the pairs it reached to the covered bitmap.
 #include "skim_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace skim {
 
@@ -154,6 +154,262 @@ __global__ void __launch_bounds__(kEvalBlock) k_eval(EvalArgs A) {
         // clean the bitmap words this query set
         for (uint64_t t = tid; t < total; t += kEvalBlock) st(bm + (ld(Q + t) >> 5), 0u);
         __syncthreads();
+    }
+}
+
+// --------------------------------------------- batches: 32 queries at once
+// A unit is one instance i and one word of 32 queries.  Its workgroup keeps a
+// 32-bit mask per node, the queries of the word that reach the node, and a
+// queue of the nodes whose mask grew since they were last expanded (a node is
+// in the queue at most once: its `dirty` bit).  Expanding v sends its mask
+// along its live out-edges; a head whose mask grows is queued again.  Queries
+// whose searches meet in a node (the prefixes of one seed sequence, any sets
+// that reach the same component) go on as one from there, where a search per
+// query walks the shared part once for each.
+//
+// What bounds it: LDS atomics and dependent list reads, with a workgroup per
+// unit.  Masks, dirty bits and a ring of 16-bit node ids take 6.125 n bytes of
+// LDS, which fits up to kSetsLdsNodes nodes; above that they are in global
+// memory (device atomics, 32-bit ids, slots within kEvalSlotBudget).  The 200
+// prefixes of a seed sequence on a 20,000-node weighted-cascade graph
+// (l = 64): one workgroup per query over all pairs 34.9 ms a call, this 0.52 ms,
+// most of it the lists.
+constexpr uint32_t kSetsLdsNodes = 26000;   // 6.125 n + 2 KiB of LDS
+constexpr uint32_t kSetsSmallNodes = 4096;  // up to here 256 threads: several units per CU
+
+struct SetsArgs {
+    uint32_t n, ell;
+    const uint64_t *fptr;  // [l n + 1] live out-lists, instance-major
+    const uint32_t *fadj;
+    uint64_t q, words;     // queries, words of 32 of them
+    const uint64_t *qoff;
+    const uint32_t *qnodes;
+    const uint8_t *bad;    // [q] the query names a node >= n
+    uint64_t *reach;       // [q] added to
+    uint32_t *masks;       // [slots][n], zero between units (global state)
+    uint32_t *dirty;       // [slots][(n + 31) / 32], zero between units
+    uint32_t *ring;        // [slots][n + NT]
+};
+
+// Per query: the status and a zero count (one wave each).
+__global__ void __launch_bounds__(256) k_sets_begin(uint32_t n, uint64_t q, const uint64_t *qoff,
+                                                    const uint32_t *qnodes, uint8_t *bad,
+                                                    uint64_t *reach, int32_t *status) {
+    const uint32_t lane = lane_id();
+    const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x / 64);
+    for (uint64_t j = blockIdx.x * (uint64_t)(blockDim.x / 64) + threadIdx.x / 64; j < q;
+         j += waves) {
+        bool b = false;
+        for (uint64_t t = qoff[j] + lane; t < qoff[j + 1]; t += 64) b |= qnodes[t] >= n;
+        const bool any = __ballot(b) != 0;
+        if (lane == 0) {
+            bad[j] = any;
+            reach[j] = 0;
+            if (status) status[j] = any ? -1 : 0;
+        }
+    }
+}
+
+// State words: LDS at workgroup scope, global memory at agent scope (as the
+// rest of this file, so no stale line of the L1 is read).
+template <bool kLds> struct SetWord {
+    static constexpr int kScope = kLds ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT;
+    static __device__ __forceinline__ uint32_t get(const uint32_t *p) {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, kScope);
+    }
+    static __device__ __forceinline__ uint32_t set_bits(uint32_t *p, uint32_t v) {
+        return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, kScope);
+    }
+    static __device__ __forceinline__ uint32_t keep_bits(uint32_t *p, uint32_t v) {
+        return __hip_atomic_fetch_and(p, v, __ATOMIC_RELAXED, kScope);
+    }
+    static __device__ __forceinline__ uint32_t take(uint32_t *p) {
+        return __hip_atomic_exchange(p, 0u, __ATOMIC_RELAXED, kScope);
+    }
+};
+
+// What came before (in program order) has reached the state words before
+// anything after is issued.
+__device__ __forceinline__ void sets_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+}
+
+// Adds the wave's counts of the 32 mask bits to out[0..32): c[j] holds the
+// bytes of bits j, j + 8, j + 16, j + 24 (at most 255 masks per lane).
+__device__ __forceinline__ void sets_flush(uint32_t (&c)[8], uint32_t *out) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        uint32_t lo = c[j] & 0x00FF00FFu, hi = (c[j] >> 8) & 0x00FF00FFu;  // sums < 2^14
+        for (int off = 32; off > 0; off >>= 1) {
+            lo += __shfl_xor(lo, off);
+            hi += __shfl_xor(hi, off);
+        }
+        if (lane_id() == 0) {
+            if (lo & 0xFFFFu) atomicAdd(out + j, lo & 0xFFFFu);
+            if (hi & 0xFFFFu) atomicAdd(out + j + 8, hi & 0xFFFFu);
+            if (lo >> 16) atomicAdd(out + j + 16, lo >> 16);
+            if (hi >> 16) atomicAdd(out + j + 24, hi >> 16);
+        }
+        c[j] = 0;
+    }
+}
+
+template <bool kLds, int NT>
+__global__ void __launch_bounds__(NT) k_eval_sets(SetsArgs A) {
+    using W = SetWord<kLds>;
+    using Id = typename std::conditional<kLds, uint16_t, uint32_t>::type;
+    extern __shared__ uint32_t s_mem[];
+    __shared__ uint64_t s_off[33];
+    __shared__ uint32_t s_cnt[32];
+    __shared__ uint32_t s_tail, s_bad;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), n = A.n;
+    const uint32_t dwords = (n + 31) / 32, cap = n + NT;
+    uint32_t *M = kLds ? s_mem : A.masks + (uint64_t)blockIdx.x * n;
+    uint32_t *D = kLds ? s_mem + n : A.dirty + (uint64_t)blockIdx.x * dwords;
+    Id *R = kLds ? (Id *)(s_mem + n + dwords) : (Id *)(A.ring + (uint64_t)blockIdx.x * cap);
+    if (kLds)
+        for (uint32_t v = tid; v < n + dwords; v += NT) s_mem[v] = 0;
+    // Workgroups go to the 8 XCDs in turn: every unit of instance i runs on
+    // XCD i mod 8, whose L2 then holds that instance's lists.
+    const uint64_t units = 8ull * ((A.ell + 7) / 8) * A.words;
+    for (uint64_t u = blockIdx.x; u < units; u += gridDim.x) {
+        const uint32_t inst = (uint32_t)(u % 8 + 8 * (u / 8 / A.words));
+        if (inst >= A.ell) continue;  // uniform
+        const uint64_t j0 = 32 * (u / 8 % A.words);
+        const uint32_t nq = A.q - j0 < 32 ? (uint32_t)(A.q - j0) : 32u;
+        const uint64_t *ptr = A.fptr + (uint64_t)inst * n;
+        __syncthreads();  // the previous unit is done (and the first one's state is clear)
+        if (tid <= 32) s_off[tid] = A.qoff[j0 + (tid < nq ? tid : nq)];
+        if (tid < 32) s_cnt[tid] = 0;
+        if (tid == 0) {
+            s_tail = 0;
+            s_bad = 0;
+        }
+        __syncthreads();
+        if (tid < nq && A.bad[j0 + tid]) atomicOr(&s_bad, 1u << tid);
+        __syncthreads();
+        // new bits m for node w; true if w has to be queued (called by lanes
+        // with something to send; the queueing itself is wave-wide)
+        auto send = [&](uint32_t w, uint32_t m) {
+            if ((m & ~W::get(M + w)) == 0) return false;
+            if ((m & ~W::set_bits(M + w, m)) == 0) return false;
+            sets_order();  // the mask before the dirty bit
+            const uint32_t bit = 1u << (w & 31);
+            return (W::set_bits(D + (w >> 5), bit) & bit) == 0;
+        };
+        auto queue = [&](bool add, uint32_t w) {
+            const unsigned long long b = __ballot(add);
+            if (!b) return;
+            const int leader = __ffsll((long long)b) - 1;
+            uint32_t base = 0;
+            if ((int)lane == leader) base = atomicAdd(&s_tail, (uint32_t)__popcll(b));
+            base = (uint32_t)__shfl((int)base, leader);
+            if (add) {
+                Id *slot = R + (base + (uint32_t)__popcll(b & ((1ull << lane) - 1ull))) % cap;
+                if (kLds) *slot = (Id)w;
+                else st((uint32_t *)slot, w);
+            }
+        };
+        // the members of the word's sets
+        const uint64_t b0 = s_off[0], b1 = s_off[32];
+        for (uint64_t t0 = b0; t0 < b1; t0 += NT) {
+            const uint64_t t = t0 + tid;
+            bool add = false;
+            uint32_t w = 0;
+            if (t < b1) {
+                uint32_t lo = 0, hi = 32;  // s_off[lo] <= t < s_off[hi]
+                while (hi - lo > 1) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if (s_off[mid] <= t) lo = mid;
+                    else hi = mid;
+                }
+                if (!((s_bad >> lo) & 1u)) {
+                    w = A.qnodes[t];
+                    add = send(w, 1u << lo);
+                }
+            }
+            queue(add, w);
+        }
+        __syncthreads();
+        for (uint32_t head = 0;;) {
+            const uint32_t tail = s_tail;
+            __syncthreads();  // every thread has the same tail before any append
+            if (head == tail) break;
+            const uint32_t cnt = tail - head < (uint32_t)NT ? tail - head : (uint32_t)NT;
+            if ((tid & ~63u) < cnt) {  // waves with an entry
+                uint32_t m = 0, d = 0;
+                uint64_t e0 = 0;
+                if (tid < cnt) {
+                    const Id *slot = R + (head + tid) % cap;
+                    const uint32_t v = kLds ? (uint32_t)*slot : ld((const uint32_t *)slot);
+                    e0 = ptr[v];
+                    d = (uint32_t)(ptr[v + 1] - e0);
+                    W::keep_bits(D + (v >> 5), ~(1u << (v & 31)));
+                    sets_order();  // the dirty bit is off before the mask is read
+                    m = W::get(M + v);
+                }
+                // the wave's out-edges laid end to end, 64 at a time
+                uint32_t incl = d;
+#pragma unroll
+                for (uint32_t off = 1; off < 64; off <<= 1) {
+                    const uint32_t y = __shfl_up(incl, off);
+                    if (lane >= off) incl += y;
+                }
+                const uint32_t tot = (uint32_t)__shfl((int)incl, 63);
+                for (uint32_t base = 0; base < tot; base += 64) {
+                    const uint32_t j = base + lane;
+                    uint32_t r = 0;
+#pragma unroll
+                    for (uint32_t step = 32; step > 0; step >>= 1) {
+                        const uint32_t y = (uint32_t)__shfl((int)incl, (int)(r + step - 1));
+                        if (y <= j) r += step;
+                    }
+                    r &= 63u;
+                    const uint32_t first =
+                        (uint32_t)__shfl((int)incl, (int)r) - (uint32_t)__shfl((int)d, (int)r);
+                    const uint64_t re0 =
+                        ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(e0 >> 32), (int)r) << 32) |
+                        (uint32_t)__shfl((int)(uint32_t)e0, (int)r);
+                    const uint32_t rm = (uint32_t)__shfl((int)m, (int)r);
+                    bool add = false;
+                    uint32_t w = 0;
+                    if (j < tot) {
+                        w = A.fadj[re0 + (j - first)];
+                        add = send(w, rm);
+                    }
+                    queue(add, w);
+                }
+            }
+            head += cnt;
+            __syncthreads();  // this round's entries are in the ring and s_tail
+        }
+        // count the masks' bits and clear them: over the ring when it still
+        // holds every entry (a repeated node counts once: its mask is taken),
+        // else over all nodes
+        {
+            const uint32_t tail = s_tail;
+            const bool sparse = tail <= cap && tail < n;
+            const uint32_t items = sparse ? tail : n;
+            uint32_t c[8] = {0, 0, 0, 0, 0, 0, 0, 0}, held = 0;
+            for (uint32_t t0 = 0; t0 < items; t0 += NT) {  // uniform
+                if (t0 + tid < items) {
+                    uint32_t v = t0 + tid;
+                    if (sparse) v = kLds ? (uint32_t)R[v] : ld((const uint32_t *)R + v);
+                    const uint32_t m = W::take(M + v);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) c[j] += (m >> j) & 0x01010101u;
+                }
+                if (++held == 255) {
+                    sets_flush(c, s_cnt);
+                    held = 0;
+                }
+            }
+            if (held) sets_flush(c, s_cnt);
+        }
+        __syncthreads();
+        if (tid < nq && s_cnt[tid])
+            atomicAdd((unsigned long long *)A.reach + j0 + tid, (unsigned long long)s_cnt[tid]);
     }
 }
 
@@ -310,31 +566,48 @@ extern "C" skim_status skim_influence_batch(const skim_graph *g, uint32_t ell, u
         read_back(&total, qoff + q, sizeof total, hs);
         SKIM_REQUIRE(total == 0 || qnodes, "qnodes is NULL");
         const uint32_t n = g->n;
-        LiveLists fwd = build_live_lists(g, ell, seed, esrc, /*forward=*/true, T);
-        const uint64_t qcap = (uint64_t)ell * n;
-        const uint64_t per_slot = (2ull * n + qcap) * sizeof(uint32_t);
-        uint64_t slots = std::max<uint64_t>(1, kEvalSlotBudget / per_slot);
-        slots = std::min<uint64_t>(std::min<uint64_t>(slots, kEvalMaxSlots), q);
-        EvalArgs A{};
+        const LiveLists fwd = build_live_lists(g, ell, seed, esrc, /*forward=*/true, T, nullptr,
+                                               /*instance_major=*/true);
+        SetsArgs A{};
         A.n = n;
         A.ell = ell;
         A.fptr = fwd.ptr;
         A.fadj = fwd.adj;
         A.q = q;
+        A.words = (q + 31) / 32;
         A.qoff = qoff;
         A.qnodes = qnodes;  // never read when every set is empty
         A.reach = reach_pairs;
-        A.status = qstatus;
-        A.bitmaps = T.alloc<uint32_t>(slots * 2 * n);
-        A.queues = T.alloc<uint32_t>(slots * qcap);
-        A.qcap = qcap;
-        A.covered = nullptr;
-        fill_u32(A.bitmaps, 0, slots * 2 * n, hs);
-        {
-            LaunchTimer t("k_eval", hs);
-            k_eval<<<(unsigned)slots, kEvalBlock, 0, hs>>>(A);
-            SKIM_LAUNCH_CHECK();
+        uint8_t *bad = T.alloc<uint8_t>(q);
+        A.bad = bad;
+        k_sets_begin<<<grid_for(q, 4, 4096), 256, 0, hs>>>(n, q, qoff, qnodes, bad, reach_pairs,
+                                                           qstatus);
+        SKIM_LAUNCH_CHECK();
+        const uint64_t units = 8ull * ((ell + 7) / 8) * A.words;
+        LaunchTimer t("k_eval_sets", hs);
+        if (n <= kSetsLdsNodes) {
+            const bool small = n <= kSetsSmallNodes;
+            const uint64_t nt = small ? 256 : 1024;
+            const size_t lds = 4ull * n + 4ull * ((n + 31) / 32) + 2ull * (n + nt);
+            const void *f = small ? (const void *)k_eval_sets<true, 256>
+                                  : (const void *)k_eval_sets<true, 1024>;
+            SKIM_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            const unsigned grid = (unsigned)std::min<uint64_t>(units, 4096);  // multiples of 8
+            if (small) k_eval_sets<true, 256><<<grid, 256, lds, hs>>>(A);
+            else k_eval_sets<true, 1024><<<grid, 1024, lds, hs>>>(A);
+        } else {
+            const uint64_t dwords = (n + 31) / 32, cap = (uint64_t)n + 1024;
+            const uint64_t per_slot = (n + dwords + cap) * sizeof(uint32_t);
+            uint64_t slots = std::max<uint64_t>(8, kEvalSlotBudget / per_slot / 8 * 8);
+            slots = std::min<uint64_t>(std::min<uint64_t>(slots, kEvalMaxSlots), units);
+            A.masks = T.alloc<uint32_t>(slots * n);
+            A.dirty = T.alloc<uint32_t>(slots * dwords);
+            A.ring = T.alloc<uint32_t>(slots * cap);
+            fill_u32(A.masks, 0, slots * n, hs);
+            fill_u32(A.dirty, 0, slots * dwords, hs);
+            k_eval_sets<false, 1024><<<(unsigned)slots, 1024, 0, hs>>>(A);
         }
+        SKIM_LAUNCH_CHECK();
         SKIM_HIP(hipStreamSynchronize(hs));
         return SKIM_OK;
     } catch (const Fail &f) {

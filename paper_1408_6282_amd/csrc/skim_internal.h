@@ -193,14 +193,23 @@ inline unsigned grid_for(uint64_t work, unsigned block, unsigned cap = 65536) {
 
 // Live in- (or out-) lists of every pair p = 64 v + i, as one CSR over pair
 // ids: adj[ptr[p] .. ptr[p+1]) = sources u of edges (u -> v) live in
-// instance i (forward: heads v of edges (v -> w) live in i).
+// instance i (forward: heads v of edges (v -> w) live in i).  With
+// instance_major the CSR is over i n + v instead (ptr [l n + 1]): the lists of
+// one instance are contiguous, for searches that stay in one instance.
 struct LiveLists {
     uint64_t *ptr = nullptr;  // [64 n + 1]
     uint32_t *adj = nullptr;
     uint64_t nlive = 0;
 };
+struct PairIndex {  // place of (node v, instance i) in a CSR over pairs
+    uint64_t node, inst;
+    __device__ __forceinline__ uint64_t at(uint32_t v, uint32_t i) const {
+        return v * node + i * inst;
+    }
+};
 LiveLists build_live_lists(const skim_graph *g, uint32_t ell, uint64_t seed, const uint32_t *esrc,
-                           bool forward, Arena &a, LiveLists *also_other = nullptr);
+                           bool forward, Arena &a, LiveLists *also_other = nullptr,
+                           bool instance_major = false);
 
 // Live-list word of a pair: 0 for no live in-edge, kLiveOne | u for the
 // single source u, else begin << kLiveCountBits | count into the sources.

@@ -38,7 +38,7 @@ __device__ __forceinline__ bool wave_one_source(bool valid, uint32_t u, uint32_t
 
 __global__ void k_live_masks(const uint32_t *esrc, const uint32_t *col, const uint32_t *thr,
                              uint64_t m, uint32_t n, uint32_t ell, uint64_t seed, uint64_t *masks,
-                             uint32_t *rcnt, uint32_t *fcnt) {
+                             uint32_t *rcnt, uint32_t *fcnt, PairIndex ix) {
     const uint32_t lane = lane_id();
     for (uint64_t base = blockIdx.x * (uint64_t)blockDim.x; base < m;
          base += (uint64_t)gridDim.x * blockDim.x) {
@@ -52,17 +52,14 @@ __global__ void k_live_masks(const uint32_t *esrc, const uint32_t *col, const ui
         if (one) {
             for (uint32_t i = 0; i < ell; ++i) {
                 const unsigned long long b = __ballot((mask >> i) & 1ull);
-                if (lane == i && b) atomicAdd(fcnt + (uint64_t)u0 * kPairStride + i,
-                                              (uint32_t)__popcll(b));
+                if (lane == i && b) atomicAdd(fcnt + ix.at(u0, i), (uint32_t)__popcll(b));
             }
         }
-        uint32_t *rrow = rcnt ? rcnt + (uint64_t)v * kPairStride : nullptr;
-        uint32_t *frow = fcnt && !one ? fcnt + (uint64_t)u * kPairStride : nullptr;
         while (mask) {
             const int i = __ffsll((long long)mask) - 1;
             mask &= mask - 1;
-            if (rrow) atomicAdd(rrow + i, 1u);
-            if (frow) atomicAdd(frow + i, 1u);
+            if (rcnt) atomicAdd(rcnt + ix.at(v, i), 1u);
+            if (fcnt && !one) atomicAdd(fcnt + ix.at(u, i), 1u);
         }
     }
 }
@@ -72,7 +69,8 @@ __global__ void k_live_masks(const uint32_t *esrc, const uint32_t *col, const ui
 // a one-source wave reserves each instance's entries with one atomic.
 __global__ void k_live_fill(const uint32_t *esrc, const uint32_t *col, const uint64_t *masks,
                             uint64_t m, uint32_t ell, const uint64_t *rptr, uint32_t *rcnt,
-                            uint32_t *radj, const uint64_t *fptr, uint32_t *fcnt, uint32_t *fadj) {
+                            uint32_t *radj, const uint64_t *fptr, uint32_t *fcnt, uint32_t *fadj,
+                            PairIndex ix) {
     const uint32_t lane = lane_id();
     for (uint64_t base = blockIdx.x * (uint64_t)blockDim.x; base < m;
          base += (uint64_t)gridDim.x * blockDim.x) {
@@ -87,7 +85,7 @@ __global__ void k_live_fill(const uint32_t *esrc, const uint32_t *col, const uin
                 const unsigned long long b = __ballot((mask >> i) & 1ull);
                 if (!b) continue;  // uniform
                 const int leader = __ffsll((long long)b) - 1;
-                const uint64_t p = (uint64_t)u0 * kPairStride + i;
+                const uint64_t p = ix.at(u0, i);
                 const uint32_t c = (uint32_t)__popcll(b);
                 uint32_t old = 0;
                 if ((int)lane == leader) old = atomicSub(fcnt + p, c);
@@ -100,12 +98,12 @@ __global__ void k_live_fill(const uint32_t *esrc, const uint32_t *col, const uin
             const int i = __ffsll((long long)mask) - 1;
             mask &= mask - 1;
             if (radj) {
-                const uint64_t p = (uint64_t)v * kPairStride + i;
+                const uint64_t p = ix.at(v, i);
                 const uint32_t c = atomicSub(rcnt + p, 1u);
                 radj[rptr[p] + c - 1] = u;
             }
             if (fadj && !one) {
-                const uint64_t p = (uint64_t)u * kPairStride + i;
+                const uint64_t p = ix.at(u, i);
                 const uint32_t c = atomicSub(fcnt + p, 1u);
                 fadj[fptr[p] + c - 1] = v;
             }
@@ -458,11 +456,13 @@ LiveLists build_out_lists(const skim_graph *g, uint32_t ell, uint64_t seed, cons
 }
 
 LiveLists build_live_lists(const skim_graph *g, uint32_t ell, uint64_t seed, const uint32_t *esrc,
-                           bool forward, Arena &a, LiveLists *also_other) {
+                           bool forward, Arena &a, LiveLists *also_other,
+                           bool instance_major) {
     hipStream_t s = a.stream();
     const uint32_t n = g->n;
     const uint64_t m = g->m;
-    const uint64_t npairs = (uint64_t)n * kPairStride;
+    const PairIndex ix = instance_major ? PairIndex{1, n} : PairIndex{kPairStride, 1};
+    const uint64_t npairs = (uint64_t)n * (instance_major ? ell : kPairStride);
     // `forward` selects the list returned; `also_other` (optional) receives
     // the opposite direction from the same coin pass.
     const bool want_rev = !forward || also_other;
@@ -476,7 +476,8 @@ LiveLists build_live_lists(const skim_graph *g, uint32_t ell, uint64_t seed, con
     if (m) {
         masks = a.alloc<uint64_t>(m);
         LaunchTimer t("k_live_masks", s);
-        k_live_masks<<<grid, 256, 0, s>>>(esrc, g->col, g->thr, m, n, ell, seed, masks, rcnt, fcnt);
+        k_live_masks<<<grid, 256, 0, s>>>(esrc, g->col, g->thr, m, n, ell, seed, masks, rcnt, fcnt,
+                                          ix);
         SKIM_LAUNCH_CHECK();
     }
     LiveLists rev, fwd;
@@ -498,7 +499,7 @@ LiveLists build_live_lists(const skim_graph *g, uint32_t ell, uint64_t seed, con
     if (m) {
         LaunchTimer t("k_live_fill", s);
         k_live_fill<<<grid, 256, 0, s>>>(esrc, g->col, masks, m, ell, rev.ptr, rcnt, rev.adj,
-                                         fwd.ptr, fcnt, fwd.adj);
+                                         fwd.ptr, fcnt, fwd.adj, ix);
         SKIM_LAUNCH_CHECK();
         a.release(masks);
     }

@@ -166,3 +166,38 @@ def test_greedy_exact_served_config(oracle_lib):
                         status=False)
     cum = np.cumsum(gains)
     assert [int(v) for v in got] == [int(cum[0]), int(cum[9]), int(cum[49])]
+
+
+@pytest.mark.parametrize("n,q", [(1, 1), (64, 31), (4096, 32), (4097, 33), (25999, 65),
+                                 (26000, 2), (26001, 40)])
+def test_words_of_32_queries_at_state_limits(oracle_lib, n, q):
+    """The masks' places (LDS at 256 and at 1024 threads, global memory) and the
+    words of 32 queries at their edges: nested prefixes, lone nodes (few pushes:
+    counted over the ring), and sets that reach a dense core (counted over all
+    nodes)."""
+    rng = np.random.default_rng(n + q)
+    m = 0 if n == 1 else 3 * n
+    e = np.unique(rng.integers(0, n, size=(m, 2)), axis=0)
+    e = e[e[:, 0] != e[:, 1]]
+    g = from_edges(n, e[:, 0], e[:, 1], 0xFFFFFFFF // 2)
+    order = rng.permutation(n)
+    sets = []
+    for j in range(q):
+        kind = j % 3
+        if kind == 0:
+            sets.append(order[:1 + j].tolist())
+        elif kind == 1:
+            sets.append([int(rng.integers(n))])
+        else:
+            sets.append([] if j == 2 else rng.integers(0, n, size=5).tolist())
+    if q > 32:
+        sets[32] = [0, n]  # a bad member leaves the other queries of its word alone
+    for ell in (1, 9):
+        log(f"influence words n={n} q={q} ell={ell}")
+        got, st = gpu_influence(g, ell, 11, sets)
+        for j, S in enumerate(sets):
+            if max(S, default=-1) >= n:
+                assert st[j] == -1 and got[j] == 0
+                continue
+            assert st[j] == 0
+            assert int(got[j]) == oracle_lib.influence(g, 11, ell, sorted(set(S))), (j, S)
