@@ -1,21 +1,22 @@
 // skim_query.hip -- influence queries from the sketches (Section 5.1).
 //
-// One wave per query.  The member sketches are sorted, so the distinct ranks
-// of their union come out in increasing order from a k-way merge: each step
-// takes the minimum head over the members (lane-local minimum, then a wave
-// minimum), then advances every member whose head equals it.
+// The member sketches are sorted, so the distinct ranks of their union come
+// out in increasing order from a k-way merge: each step takes the minimum head
+// over the members, then advances every member whose head equals it.
 //  * bottom-k estimator: stop at the k-th distinct value tau (or when the
-//    union runs out), estimate as for a single sketch;
-//  * Cohen-Kaplan (eq. unionest): run over every distinct non-threshold
-//    value; its weight is 1/rho(max tau_u over the members holding it), a
-//    non-full member counting as rho = 1; lane 0 adds the weights in
-//    increasing order of the value.
-// Each lane keeps its members' current heads in registers, so a merge step
-// touches global memory only for the members that advance.
-// The batched path is one persistent launch whose waves pull queries from a
-// device counter; the plain path launches the same device code once per
-// query.
+//    union runs out), estimate as for a single sketch.  A set of up to 64
+//    members is merged by a group of 4 to 16 lanes (merge_group), so a wave
+//    answers 4 to 16 sets at once; a larger one by the whole wave;
+//  * Cohen-Kaplan (eq. unionest): every distinct non-threshold value of the
+//    union weighs 1/rho(max tau_u over the members holding it), a non-full
+//    member counting as rho = 1; the weights are added in increasing order of
+//    the value.  Sets of up to 64 members over sketches of k <= 64 are sorted
+//    in registers (ck_sorted); others are merged by the whole wave.
+// The batched path is one persistent launch whose waves pull runs of queries
+// from a device counter; the plain path launches the same device code once
+// per query.
 #include "skim_internal.h"
+#include "skim_wave.h"
 
 #include <atomic>
 #include <memory>
@@ -27,52 +28,51 @@ namespace {
 constexpr uint32_t kMaxMembers = 1024;  // members per query (LDS state)
 constexpr int kQBlock = 64;             // one wave per block
 constexpr int kPerLane = kMaxMembers / 64;
+constexpr uint32_t kRun = 64;           // most queries a wave takes at once
 
 using QArgs = QueryArgs;
 
-__device__ __forceinline__ uint64_t wave_min_u64(uint64_t x) {
-    for (int off = 32; off > 0; off >>= 1) {
-        const uint32_t lo = __shfl_xor((uint32_t)x, off);
-        const uint32_t hi = __shfl_xor((uint32_t)(x >> 32), off);
-        const uint64_t y = ((uint64_t)hi << 32) | lo;
-        x = y < x ? y : x;
-    }
-    return x;
+// Members of a set merged by the whole wave.
+struct MergeLds {
+    uint32_t mnode[kMaxMembers];
+    uint16_t mpos[kMaxMembers];
+    uint16_t mlim[kMaxMembers];
+};
+
+// LDS written by some lanes of the wave, then read by others of it (the
+// block is one wave).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t x) {
-    for (int off = 32; off > 0; off >>= 1) {
-        const uint32_t lo = __shfl_xor((uint32_t)x, off);
-        const uint32_t hi = __shfl_xor((uint32_t)(x >> 32), off);
-        const uint64_t y = ((uint64_t)hi << 32) | lo;
-        x = y > x ? y : x;
-    }
-    return x;
+__device__ __forceinline__ uint64_t shfl_u64(uint64_t x, uint32_t src) {
+    const uint32_t lo = __shfl((uint32_t)x, (int)src), hi = __shfl((uint32_t)(x >> 32), (int)src);
+    return ((uint64_t)hi << 32) | lo;
 }
 
 // The k-way merge over S members (R >= S / 64 register slots per lane).
 // Each lane keeps the current head of its members t = lane + 64 r in
 // registers; a step reads global memory only for the members that advance.
 // Bottom-k stops at the k-th distinct value (d, tau); Cohen-Kaplan adds each
-// distinct value's weight in increasing order on lane 0 (sum).
+// distinct value's weight in increasing order (sum).
 template <int R>
-__device__ __forceinline__ void merge_members(const QArgs &Q, uint64_t S, uint32_t k,
-                                              const uint32_t *mnode, uint16_t *mpos,
-                                              const uint16_t *mlim, uint32_t &d, uint64_t &tau,
-                                              double &sum) {
+__device__ __forceinline__ void merge_members(const QArgs &Q, uint64_t S, uint32_t k, MergeLds &X,
+                                              uint32_t &d, uint64_t &tau, double &sum) {
     const uint32_t lane = lane_id();
     uint64_t head[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const uint32_t t = lane + 64u * r;
         head[r] = kNone;
-        if (t < S && mlim[t] > 0) head[r] = Q.ranks[(uint64_t)mnode[t] * k];
+        if (t < S && X.mlim[t] > 0) head[r] = Q.ranks[(uint64_t)X.mnode[t] * k];
     }
     for (;;) {
         uint64_t lmin = kNone;
 #pragma unroll
         for (int r = 0; r < R; ++r) lmin = head[r] < lmin ? head[r] : lmin;
-        const uint64_t g = wave_min_u64(lmin);
+        const uint64_t g = group_min_u64<64>(lmin);
         if (g == kNone) break;
         // advance the holders of g; for CK also find their largest threshold
         uint64_t tmax = 0;
@@ -80,10 +80,10 @@ __device__ __forceinline__ void merge_members(const QArgs &Q, uint64_t S, uint32
         for (int r = 0; r < R; ++r) {
             if (head[r] == g) {
                 const uint32_t t = lane + 64u * r;
-                const uint32_t u = mnode[t];
-                const uint32_t p = mpos[t] + 1u;
-                mpos[t] = (uint16_t)p;
-                head[r] = p < mlim[t] ? Q.ranks[(uint64_t)u * k + p] : kNone;
+                const uint32_t u = X.mnode[t];
+                const uint32_t p = X.mpos[t] + 1u;
+                X.mpos[t] = (uint16_t)p;
+                head[r] = p < X.mlim[t] ? Q.ranks[(uint64_t)u * k + p] : kNone;
                 if (Q.estimator == 1) {
                     const uint64_t tu = Q.size[u] >= k ? Q.ranks[(uint64_t)u * k + k - 1] : kNone;
                     tmax = tu > tmax ? tu : tmax;
@@ -91,13 +91,12 @@ __device__ __forceinline__ void merge_members(const QArgs &Q, uint64_t S, uint32
             }
         }
         if (Q.estimator == 1) {
-            tmax = wave_max_u64(tmax);
+            tmax = ~group_min_u64<64>(~tmax);
             // the weight 1/r of the largest holder threshold: r = rho(T) for
             // hashed ranks, (T - 1)/(l n - 1) for permutation positions
-            if (lane == 0)
-                sum += tmax == kNone ? 1.0
-                       : Q.perm_d    ? ((double)Q.perm_d - 1.0) / (double)(tmax - 1)
-                                     : 1.0 / rank_real(tmax);
+            sum += tmax == kNone ? 1.0
+                   : Q.perm_d    ? ((double)Q.perm_d - 1.0) / (double)(tmax - 1)
+                                 : 1.0 / rank_real(tmax);
         } else {
             ++d;
             if (d == k) {
@@ -108,110 +107,484 @@ __device__ __forceinline__ void merge_members(const QArgs &Q, uint64_t S, uint32
     }
 }
 
-// Answer query j with the calling wave (all 64 lanes, converged).
-__device__ void answer_query(const QArgs &Q, uint64_t j, uint32_t *mnode, uint16_t *mpos,
-                             uint16_t *mlim) {
+__device__ __forceinline__ double union_estimate(const QArgs &Q, uint32_t d, uint64_t tau) {
+    return Q.perm_d ? perm_estimate(d, tau, Q.k, Q.ell, Q.perm_d)
+                    : bottomk_estimate(d, tau, Q.k, Q.ell);
+}
+
+__device__ __forceinline__ void put_answer(const QArgs &Q, uint64_t j, double est, int32_t status) {
+    Q.est[j] = est;
+    if (Q.qstatus) Q.qstatus[j] = status;
+}
+
+// Answer query j (members qnodes[a .. a + S), S >= 1) with the whole wave.
+__device__ void answer_wave(const QArgs &Q, uint64_t j, uint64_t a, uint64_t S, MergeLds &X) {
     const uint32_t lane = lane_id();
-    const uint64_t a = Q.qoff[j], b = Q.qoff[j + 1];
     const uint32_t k = Q.k;
-    // Offsets are validated before a batch; a replayed plan re-checks its
-    // own set here (non-decreasing, within qoff[q]) and never reads outside.
-    if (b < a || b > Q.qoff[Q.q] || b > Q.nodes_cap || (j == 0 && a != 0)) {
-        if (lane == 0) {
-            Q.est[j] = 0.0;
-            if (Q.qstatus) Q.qstatus[j] = -3;
-        }
-        return;
-    }
-    const uint64_t S = b - a;
     // membership checks (node ids are validated per query)
     bool bad = false;
-    for (uint64_t t = a + lane; t < b; t += 64) bad |= Q.qnodes[t] >= Q.n;
+    for (uint64_t t = a + lane; t < a + S; t += 64) bad |= Q.qnodes[t] >= Q.n;
     bad = __ballot(bad) != 0;
     if (bad || S > kMaxMembers) {
-        if (lane == 0) {
-            Q.est[j] = 0.0;
-            if (Q.qstatus) Q.qstatus[j] = bad ? -1 : -2;
-        }
-        return;
-    }
-    if (S == 0) {
-        if (lane == 0) {
-            Q.est[j] = 0.0;
-            if (Q.qstatus) Q.qstatus[j] = 0;
-        }
-        return;
-    }
-    if (S == 1 && Q.estimator == 0) {
-        if (lane == 0) {
-            const uint32_t u = Q.qnodes[a];
-            const uint32_t sz = Q.size[u];
-            const uint64_t T = sz >= k ? Q.ranks[(uint64_t)u * k + k - 1] : 0;
-            Q.est[j] = Q.perm_d ? perm_estimate(sz, T, k, Q.ell, Q.perm_d)
-                                : bottomk_estimate(sz, T, k, Q.ell);
-            if (Q.qstatus) Q.qstatus[j] = 0;
-        }
+        if (lane == 0) put_answer(Q, j, 0.0, bad ? -1 : -2);
         return;
     }
     // member state: node, next position, usable length
     for (uint32_t t = lane; t < S; t += 64) {
         const uint32_t u = Q.qnodes[a + t];
         const uint32_t sz = Q.size[u];
-        mnode[t] = u;
-        mpos[t] = 0;
+        X.mnode[t] = u;
+        X.mpos[t] = 0;
         // CK ignores the threshold element of a full sketch
-        mlim[t] = (uint16_t)(Q.estimator == 1 && sz >= k ? k - 1 : (sz < k ? sz : k));
+        X.mlim[t] = (uint16_t)(Q.estimator == 1 && sz >= k ? k - 1 : (sz < k ? sz : k));
     }
-    __syncthreads();
+    wave_sync();
     uint32_t d = 0;
     uint64_t tau = 0;
     double sum = 0.0;
-    if (S <= 64)
-        merge_members<1>(Q, S, k, mnode, mpos, mlim, d, tau, sum);
-    else if (S <= 256)
-        merge_members<4>(Q, S, k, mnode, mpos, mlim, d, tau, sum);
-    else
-        merge_members<kPerLane>(Q, S, k, mnode, mpos, mlim, d, tau, sum);
-    if (lane == 0) {
-        Q.est[j] = Q.estimator == 1 ? sum / (double)Q.ell
-                   : Q.perm_d          ? perm_estimate(d, tau, k, Q.ell, Q.perm_d)
-                                       : bottomk_estimate(d, tau, k, Q.ell);
-        if (Q.qstatus) Q.qstatus[j] = 0;
-    }
-    __syncthreads();
+    if (S <= 64) merge_members<1>(Q, S, k, X, d, tau, sum);
+    else if (S <= 256) merge_members<4>(Q, S, k, X, d, tau, sum);
+    else merge_members<kPerLane>(Q, S, k, X, d, tau, sum);
+    if (lane == 0)
+        put_answer(Q, j, Q.estimator == 1 ? sum / (double)Q.ell : union_estimate(Q, d, tau), 0);
+    wave_sync();  // X is refilled by the next query
 }
 
+// --------------------------------------------------- bottom-k, small sets
+// One query per aligned group of G lanes, S <= G R members (member t = lane
+// in group + G r).  The group's minimum is 2 log2(G) vector-unit steps; each
+// member keeps its head and the rank after it in registers, so a member that
+// advances does not wait for memory unless it advances twice in a row.
+// Groups without a query (S = 0) idle.
+template <int G, int R>
+__device__ __forceinline__ void merge_group(const QArgs &Q, uint64_t j, uint64_t a, uint32_t S) {
+    const uint32_t gl = lane_id() & (G - 1), k = Q.k;
+    uint32_t node[R];
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t t = gl + G * r;
+        node[r] = t < S ? Q.qnodes[a + t] : 0u;
+        bad |= t < S && node[r] >= Q.n;
+    }
+    {
+        const unsigned long long m = __ballot(bad);
+        const uint32_t g0 = lane_id() & ~(uint32_t)(G - 1);
+        bad = ((m >> g0) & ((1ull << G) - 1ull)) != 0;
+    }
+    const bool mine = S > 0;
+    uint64_t head[R], next[R];
+    const uint64_t *at[R];  // the rank after `next`
+    uint32_t left[R];       // ranks from there on
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        head[r] = next[r] = kNone;
+        left[r] = 0;
+        at[r] = Q.ranks;
+        if (gl + G * r < S && !bad) {
+            const uint32_t sz = Q.size[node[r]], lim = sz < k ? sz : k;
+            const uint64_t *row = Q.ranks + (uint64_t)node[r] * k;
+            if (lim > 0) head[r] = row[0];
+            if (lim > 1) next[r] = row[1];
+            left[r] = lim > 2 ? lim - 2 : 0;
+            at[r] = row + 2;
+        }
+    }
+    uint32_t d = 0;
+    uint64_t tau = 0;
+    bool open = mine && !bad;
+    for (;;) {
+        uint64_t lmin = head[0];
+#pragma unroll
+        for (int r = 1; r < R; ++r) lmin = head[r] < lmin ? head[r] : lmin;
+        const uint64_t g = group_min_u64<G>(lmin);
+        if (open) {
+            if (g == kNone) {
+                open = false;
+            } else if (++d == k) {
+                tau = g;
+                open = false;
+            }
+        }
+        if (!__any(open)) break;
+        if (open) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (head[r] == g) {
+                    head[r] = next[r];
+                    next[r] = kNone;
+                    if (left[r]) {
+                        next[r] = *at[r]++;
+                        --left[r];
+                    }
+                }
+        }
+    }
+    if (mine && gl == 0) put_answer(Q, j, bad ? 0.0 : union_estimate(Q, d, tau), bad ? -1 : 0);
+}
+
+// A run of queries' offsets, one per lane, and the lanes of one size class.
+struct Run {
+    uint64_t j0, a, S;  // first query; this lane's set
+    uint8_t *list;      // [64] LDS
+};
+
+// The lanes with `in` set, in order, into the list; their number.
+__device__ __forceinline__ uint32_t list_class(const Run &run, bool in) {
+    const uint32_t lane = lane_id();
+    const unsigned long long m = __ballot(in);
+    wave_sync();  // the previous class has been read
+    if (in) run.list[__popcll(m & ((1ull << lane) - 1ull))] = (uint8_t)lane;
+    wave_sync();
+    return (uint32_t)__popcll(m);
+}
+
+template <int G, int R>
+__device__ __forceinline__ void run_class(const QArgs &Q, const Run &run, bool in) {
+    const uint32_t total = list_class(run, in);
+    for (uint32_t base = 0; base < total; base += 64 / G) {
+        const uint32_t x = base + lane_id() / G;
+        const uint32_t src = x < total ? run.list[x] : 0u;
+        const uint64_t a = shfl_u64(run.a, src);
+        const uint32_t S = (uint32_t)__shfl((int)(uint32_t)run.S, (int)src);
+        merge_group<G, R>(Q, run.j0 + src, a, x < total ? S : 0u);
+    }
+}
+
+// Offsets of query j0 + lane (lane < cnt).  Offsets are validated before a
+// batch; a replayed plan re-checks its own sets here (non-decreasing, within
+// qoff[q]) and never reads outside.  Empty sets and bad offsets are answered;
+// returns whether a set with members is left.
+__device__ __forceinline__ bool load_run(const QArgs &Q, uint32_t cnt, Run &run) {
+    const uint32_t lane = lane_id();
+    run.a = run.S = 0;
+    if (lane >= cnt) return false;
+    const uint64_t j = run.j0 + lane;
+    const uint64_t a = Q.qoff[j], b = Q.qoff[j + 1];
+    if (b < a || b > Q.qoff[Q.q] || b > Q.nodes_cap || (j == 0 && a != 0)) {
+        put_answer(Q, j, 0.0, -3);
+        return false;
+    }
+    if (a == b) {
+        put_answer(Q, j, 0.0, 0);
+        return false;
+    }
+    run.a = a;
+    run.S = b - a;
+    return true;
+}
+
+// Bottom-k answers of queries j0 .. j0 + cnt (cnt <= 64), by set size: one
+// lane for a single node, groups of 4, 8 and 16 lanes up to 64 members (16
+// lanes with 2 or 4 members each measured faster than a wave with one each),
+// the wave above.
+__device__ __forceinline__ void answer_bottomk(const QArgs &Q, uint64_t j0, uint32_t cnt,
+                                               MergeLds &X, uint8_t *list) {
+    Run run{j0, 0, 0, list};
+    const bool set = load_run(Q, cnt, run);
+    if (set && run.S == 1) {
+        const uint32_t u = Q.qnodes[run.a];
+        if (u >= Q.n) {
+            put_answer(Q, j0 + lane_id(), 0.0, -1);
+        } else {
+            const uint32_t sz = Q.size[u];
+            const uint64_t T = sz >= Q.k ? Q.ranks[(uint64_t)u * Q.k + Q.k - 1] : 0;
+            put_answer(Q, j0 + lane_id(), union_estimate(Q, sz, T), 0);
+        }
+    }
+    run_class<4, 1>(Q, run, set && run.S >= 2 && run.S <= 4);
+    run_class<8, 1>(Q, run, set && run.S >= 5 && run.S <= 8);
+    run_class<16, 1>(Q, run, set && run.S >= 9 && run.S <= 16);
+    run_class<16, 2>(Q, run, set && run.S >= 17 && run.S <= 32);
+    run_class<16, 4>(Q, run, set && run.S >= 33 && run.S <= 64);
+    unsigned long long rest = __ballot(set && run.S > 64);
+    while (rest) {
+        const uint32_t src = (uint32_t)__ffsll((long long)rest) - 1;
+        rest &= rest - 1;
+        answer_wave(Q, j0 + src, shfl_u64(run.a, src), shfl_u64(run.S, src), X);
+    }
+}
+
+// ------------------------------------------- Cohen-Kaplan, sorted in registers
+// A set of S <= 2^LG <= 64 members over sketches of k <= R ranks: one lane per
+// member holds its R ranks (ascending) in registers; 2^LG lanes merge theirs
+// by LG levels of a bitonic network (the first step of a level meets the
+// mirrored partner, the steps inside a lane need no cross-lane move), after
+// which lane t of the group holds the group's ranks R t .. R t + R - 1 in
+// order.  A wave sorts 64 >> LG sets at once.
+//
+// The keys are the ranks' leading 52 bits (after dropping the zeros common to
+// the group) over a 12-bit index (member lane, place), which finds the
+// holder's weight afterwards.  Two ranks that agree in those 52 bits and
+// differ below could come out in the wrong order: the dropped bits, kept in
+// LDS, are compared for every pair of neighbours, and such a set (about one
+// in 10^9 for hashed ranks) is answered by the merge instead.
+//
+// What bounds it: vector-unit instructions.  The merge it replaces made one
+// serial step of two wave-wide reductions and three dependent loads per
+// distinct value.
+struct CkLds {
+    uint64_t stage[64 * 17];  // 16 ranks of every lane, rows padded to 17
+    double w[64];             // 1/r of each lane's member threshold
+};
+
+template <int R, int kMask> __device__ __forceinline__ void ck_flip(uint64_t (&x)[R], bool low) {
+#pragma unroll
+    for (int r = 0; r < R / 2; ++r) {
+        const uint64_t a = x[r], b = x[R - 1 - r];
+        const uint64_t pa = lane_xor64<kMask>(b), pb = lane_xor64<kMask>(a);
+        x[r] = keep_of(a, pa, low);
+        x[R - 1 - r] = keep_of(b, pb, low);
+    }
+}
+template <int R, int kMask> __device__ __forceinline__ void ck_step(uint64_t (&x)[R], bool low) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[r] = keep_of(x[r], lane_xor64<kMask>(x[r]), low);
+}
+template <int R> __device__ __forceinline__ void ck_inside(uint64_t (&x)[R]) {
+#pragma unroll
+    for (int s = R / 2; s > 0; s >>= 1)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if ((r & s) == 0) {
+                const uint64_t a = x[r], b = x[r | s];
+                const bool c = a < b;
+                x[r] = c ? a : b;
+                x[r | s] = c ? b : a;
+            }
+}
+
+// Lanes of a group of 2^LG: node u (S valid lanes from the group's first; S =
+// 0: no query), all ids valid.  Returns the group's weight sum in every lane
+// and whether it must be merged instead.
+template <int R>
+__device__ __forceinline__ double ck_sorted(const QArgs &Q, uint32_t LG, uint32_t u, bool member,
+                                            CkLds &L, bool &redo) {
+    const uint32_t lane = lane_id(), k = Q.k, G = 1u << LG;
+    uint32_t lim = 0;
+    uint64_t last = 0;  // the member's largest usable rank
+    {
+        double w = 0.0;
+        if (member) {
+            const uint32_t sz = Q.size[u];
+            const uint64_t *row = Q.ranks + (uint64_t)u * k;
+            lim = sz >= k ? k - 1 : sz;  // a full sketch's threshold does not count
+            if (lim) last = row[lim - 1];
+            w = 1.0;
+            if (sz >= k) {
+                const uint64_t t = row[k - 1];
+                w = Q.perm_d ? ((double)Q.perm_d - 1.0) / (double)(t - 1) : 1.0 / rank_real(t);
+            }
+        }
+        L.w[lane] = w;
+    }
+    // 16 places of every lane's row at a time through LDS, so that the loads
+    // take whole lines
+    uint64_t x[R];
+#pragma unroll
+    for (int c = 0; c < R / 16; ++c) {
+        uint64_t v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const uint32_t src = 4 * i + (lane >> 4), p = 16 * c + (lane & 15);
+            const uint32_t ur = (uint32_t)__shfl((int)u, (int)src);
+            const uint32_t lr = (uint32_t)__shfl((int)lim, (int)src);
+            v[i] = p < lr ? Q.ranks[(uint64_t)ur * k + p] : kNone;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) L.stage[(4 * i + (lane >> 4)) * 17 + (lane & 15)] = v[i];
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q < 16; ++q) x[16 * c + q] = L.stage[lane * 17 + q];
+        wave_sync();
+    }
+    uint32_t total = lim;
+    for (uint32_t off = 1; off < G; off <<= 1) {
+        last |= ((uint64_t)__shfl_xor((uint32_t)(last >> 32), (int)off) << 32) |
+                __shfl_xor((uint32_t)last, (int)off);
+        total += __shfl_xor(total, (int)off);
+    }
+    const uint32_t sh = last ? (uint32_t)__clzll((long long)last) : 0u;
+    uint16_t *low12 = (uint16_t *)L.stage;  // [64][64] by index
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint64_t z = x[r] << sh;
+        low12[lane * 64 + r] = (uint16_t)(z & 0xFFFu);
+        // a valid key is never all ones: place 63 is never usable
+        x[r] = r < (int)lim ? (z & ~0xFFFull) | (lane << 6) | r : kNone;
+    }
+    wave_sync();
+    for (uint32_t lv = 1; lv <= LG; ++lv) {  // uniform
+        const bool lowhalf = (lane & (1u << (lv - 1))) == 0;
+        if (lv == 1) ck_flip<R, 1>(x, lowhalf);
+        else if (lv == 2) ck_flip<R, 3>(x, lowhalf);
+        else if (lv == 3) ck_flip<R, 7>(x, lowhalf);
+        else if (lv == 4) ck_flip<R, 15>(x, lowhalf);
+        else if (lv == 5) ck_flip<R, 31>(x, lowhalf);
+        else ck_flip<R, 63>(x, lowhalf);
+        for (int st = (int)lv - 2; st >= 0; --st) {
+            const bool low = (lane & (1u << st)) == 0;
+            if (st == 4) ck_step<R, 16>(x, low);
+            else if (st == 3) ck_step<R, 8>(x, low);
+            else if (st == 2) ck_step<R, 4>(x, low);
+            else if (st == 1) ck_step<R, 2>(x, low);
+            else ck_step<R, 1>(x, low);
+        }
+        ck_inside<R>(x);
+    }
+    // eq bit r: place r holds the same rank as the place before it
+    uint64_t eq = 0;
+    redo = false;
+    {
+        uint64_t prev = shfl_u64(x[R - 1], lane ? lane - 1 : 0);
+        if ((lane & (G - 1)) == 0) prev = kNone;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint64_t cur = x[r];
+            if (((cur ^ prev) >> 12) == 0 && cur != kNone && prev != kNone) {
+                if (low12[cur & 0xFFFu] == low12[prev & 0xFFFu]) eq |= 1ull << r;
+                else redo = true;
+            }
+            prev = cur;
+        }
+    }
+    // weights; the smallest of a run of equal ranks (the largest threshold
+    // among its holders) counts, at the run's last place
+    double run = __builtin_huge_val();  // of a run that began in an earlier lane
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const double w = x[r] == kNone ? 0.0 : L.w[(x[r] >> 6) & 63u];
+        x[r] = (uint64_t)__double_as_longlong(w);
+        run = ((eq >> r) & 1ull) ? fmin(run, w) : w;
+    }
+    {   // runs that continue from earlier lanes: segmented minimum over lanes
+        const uint64_t all = R == 64 ? ~0ull : (1ull << R) - 1ull;
+        double v = run;                      // of the lane's last run
+        uint32_t open = (eq & all) == all;   // which began in an earlier lane
+        for (uint32_t off = 1; off < G; off <<= 1) {
+            const uint64_t vu = shfl_u64((uint64_t)__double_as_longlong(v), lane >= off ? lane - off : 0);
+            const uint32_t ou = (uint32_t)__shfl((int)open, (int)(lane >= off ? lane - off : 0));
+            if (open && (lane & (G - 1)) >= off) {
+                v = fmin(v, __longlong_as_double((long long)vu));
+                open = ou;
+            }
+        }
+        run = __longlong_as_double(
+            (long long)shfl_u64((uint64_t)__double_as_longlong(v), lane ? lane - 1 : 0));
+    }
+    const uint32_t eq_next = (uint32_t)__shfl((int)((uint32_t)eq & 1u), (int)((lane + 1) & 63u));
+    const bool goes_on = eq_next && ((lane + 1) & (G - 1)) != 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const double w = __longlong_as_double((long long)x[r]);
+        run = ((eq >> r) & 1ull) ? fmin(run, w) : w;
+        const bool ends = r < R - 1 ? !((eq >> (r + 1)) & 1ull) : !goes_on;
+        x[r] = (uint64_t)__double_as_longlong(ends ? run : 0.0);
+    }
+    // the sum in increasing order of the ranks, lane after lane (a place
+    // inside a run adds 0.0, which changes nothing)
+    double sum = 0.0;
+    for (uint32_t t = 0; t < G; ++t) {
+        if (!__any(t * R < total)) break;
+        double s = sum;
+#pragma unroll
+        for (int r = 0; r < R; ++r) s += __longlong_as_double((long long)x[r]);
+        sum = __longlong_as_double((long long)shfl_u64((uint64_t)__double_as_longlong(s),
+                                                       (lane & ~(G - 1)) + t));
+    }
+    wave_sync();  // L is refilled by the next sets
+    return sum;
+}
+
+template <int R>
+__device__ __forceinline__ void answer_ck(const QArgs &Q, uint64_t j0, uint32_t cnt, MergeLds &X,
+                                          CkLds &L, uint8_t *list) {
+    const uint32_t lane = lane_id();
+    Run run{j0, 0, 0, list};
+    const bool set = load_run(Q, cnt, run);
+    unsigned long long rest = __ballot(set && (R == 0 || run.S > 64));
+    if constexpr (R > 0) {
+        for (uint32_t LG = 0; LG <= 6; ++LG) {
+            const uint32_t G = 1u << LG;
+            const uint32_t total =
+                list_class(run, set && run.S <= G && (LG == 0 || run.S > G / 2));
+            for (uint32_t base = 0; base < total; base += 64 >> LG) {
+                const uint32_t x = base + (lane >> LG), gl = lane & (G - 1);
+                const bool mine = x < total;
+                const uint32_t src = mine ? list[x] : 0u;
+                const uint64_t a = shfl_u64(run.a, src);
+                const uint32_t S = (uint32_t)__shfl((int)(uint32_t)run.S, (int)src);
+                const bool member = mine && gl < S;
+                uint32_t u = member ? Q.qnodes[a + gl] : 0u;
+                const unsigned long long gm = (LG == 6 ? ~0ull : (1ull << G) - 1ull)
+                                              << (lane & ~(G - 1));
+                const bool bad = (__ballot(member && u >= Q.n) & gm) != 0;
+                if (bad) u = 0;
+                bool redo = false;
+                const double sum = ck_sorted<R>(Q, LG, u, member && !bad, L, redo);
+                redo = (__ballot(redo) & gm) != 0;
+                if (mine && gl == 0 && !redo)
+                    put_answer(Q, j0 + src, bad ? 0.0 : sum / (double)Q.ell, bad ? -1 : 0);
+                for (unsigned long long m = __ballot(mine && gl == 0 && redo); m; m &= m - 1)
+                    rest |= 1ull << list[base + ((uint32_t)(__ffsll((long long)m) - 1) >> LG)];
+            }
+        }
+    }
+    while (rest) {
+        const uint32_t src = (uint32_t)__ffsll((long long)rest) - 1;
+        rest &= rest - 1;
+        answer_wave(Q, j0 + src, shfl_u64(run.a, src), shfl_u64(run.S, src), X);
+    }
+}
+
+// kCk: -1 bottom-k, else Cohen-Kaplan with kCk registers per lane (0: only
+// the merge, for k > 64).
+template <int kCk> struct QueryLds {
+    union {
+        MergeLds merge;
+        CkLds ck;
+    };
+    uint8_t list[64];
+};
+template <int kCk>
+__device__ __forceinline__ void answer_run(const QArgs &Q, uint64_t j0, uint32_t cnt,
+                                           QueryLds<kCk> &X) {
+    if constexpr (kCk < 0) answer_bottomk(Q, j0, cnt, X.merge, X.list);
+    else answer_ck<kCk>(Q, j0, cnt, X.merge, X.ck, X.list);
+}
+
+// `next` NULL: one query per workgroup (a batch that does not exceed the
+// grid needs no counter).
+template <int kCk>
 __global__ void __launch_bounds__(kQBlock) k_query_persistent(QArgs Q, uint64_t q,
                                                                unsigned long long *next) {
-    __shared__ uint32_t mnode[kMaxMembers];
-    __shared__ uint16_t mpos[kMaxMembers];
-    __shared__ uint16_t mlim[kMaxMembers];
-    __shared__ unsigned long long jcur;
-    // Queries are taken in runs that shrink as the batch drains (at most 32,
-    // about a quarter of an even share of what is left): takes from
+    __shared__ QueryLds<kCk> X;
+    if (!next) {
+        if (blockIdx.x < q) answer_run<kCk>(Q, blockIdx.x, 1, X);
+        return;
+    }
+    // Queries are taken in runs that shrink as the batch drains (at most
+    // kRun, about a quarter of an even share of what is left): takes from
     // different waves on the one counter are serialised by the hardware, so
     // one query per take would cap the batch at the counter's rate.
     const uint64_t share = 4ull * gridDim.x;
     uint64_t g = q / share;
-    g = g < 1 ? 1 : g > 32 ? 32 : g;
+    g = g < 1 ? 1 : g > kRun ? kRun : g;
     for (;;) {
-        if (threadIdx.x == 0) jcur = atomicAdd(next, (unsigned long long)g);
-        __syncthreads();
-        const uint64_t j0 = jcur;
-        __syncthreads();
+        unsigned long long j0 = 0;
+        if (threadIdx.x == 0) j0 = atomicAdd(next, (unsigned long long)g);
+        j0 = shfl_u64(j0, 0);
         if (j0 >= q) break;
         const uint64_t j1 = j0 + g < q ? j0 + g : q;
-        for (uint64_t j = j0; j < j1; ++j) answer_query(Q, j, mnode, mpos, mlim);
+        answer_run<kCk>(Q, j0, (uint32_t)(j1 - j0), X);
         g = (q - j1) / share;
-        g = g < 1 ? 1 : g > 32 ? 32 : g;
+        g = g < 1 ? 1 : g > kRun ? kRun : g;
     }
 }
 
-__global__ void __launch_bounds__(kQBlock) k_query_one(QArgs Q, uint64_t j) {
-    __shared__ uint32_t mnode[kMaxMembers];
-    __shared__ uint16_t mpos[kMaxMembers];
-    __shared__ uint16_t mlim[kMaxMembers];
-    answer_query(Q, j, mnode, mpos, mlim);
+template <int kCk> __global__ void __launch_bounds__(kQBlock) k_query_one(QArgs Q, uint64_t j) {
+    __shared__ QueryLds<kCk> X;
+    answer_run<kCk>(Q, j, 1, X);
 }
 
 __global__ void k_check_offsets(const uint64_t *qoff, uint64_t q, uint32_t *err) {
@@ -238,8 +611,14 @@ unsigned query_grid(uint64_t q) {
 }
 
 void launch_queries_async(const QueryArgs &Q, uint64_t q, unsigned long long *next, hipStream_t s) {
-    fill_u64((uint64_t *)next, 0, 1, s);
-    k_query_persistent<<<query_grid(q), kQBlock, 0, s>>>(Q, q, next);
+    const unsigned grid = query_grid(q);
+    if (q > grid) fill_u64((uint64_t *)next, 0, 1, s);
+    else next = nullptr;
+    if (Q.estimator == 0) k_query_persistent<-1><<<grid, kQBlock, 0, s>>>(Q, q, next);
+    else if (Q.k <= 16) k_query_persistent<16><<<grid, kQBlock, 0, s>>>(Q, q, next);
+    else if (Q.k <= 32) k_query_persistent<32><<<grid, kQBlock, 0, s>>>(Q, q, next);
+    else if (Q.k <= 64) k_query_persistent<64><<<grid, kQBlock, 0, s>>>(Q, q, next);
+    else k_query_persistent<0><<<grid, kQBlock, 0, s>>>(Q, q, next);
     SKIM_LAUNCH_CHECK();
 }
 
@@ -273,7 +652,11 @@ static void query_batch(const uint64_t *ranks, const uint32_t *size, uint32_t n,
         launch_queries_async(Q, q, next, s);
     } else {
         for (uint64_t j = 0; j < q; ++j) {
-            k_query_one<<<1, kQBlock, 0, s>>>(Q, j);
+            if (estimator == 0) k_query_one<-1><<<1, kQBlock, 0, s>>>(Q, j);
+            else if (k <= 16) k_query_one<16><<<1, kQBlock, 0, s>>>(Q, j);
+            else if (k <= 32) k_query_one<32><<<1, kQBlock, 0, s>>>(Q, j);
+            else if (k <= 64) k_query_one<64><<<1, kQBlock, 0, s>>>(Q, j);
+            else k_query_one<0><<<1, kQBlock, 0, s>>>(Q, j);
             SKIM_LAUNCH_CHECK();
         }
     }

@@ -155,3 +155,66 @@ def test_graph_plan_replays_match_batches(oracle_lib, tiny):
         qo.copy_(to_dev_u64(off))
         qn.copy_(to_dev_u32(nodes))
         plan.free()
+
+
+def _pool_tables(rng, n, k, low_bits):
+    """Sorted sketches drawn from a shared pool (so sets overlap), some of them
+    short.  low_bits > 0: ranks that share their leading bits and differ only
+    in the last `low_bits` (neighbours a truncated key would confuse)."""
+    pool = rng.integers(1, 2 ** 63, size=max(4 * k, 40), dtype=np.uint64) * np.uint64(2)
+    if low_bits:
+        base = np.repeat(pool[:max(2, len(pool) // 8)], 8)[:len(pool)]
+        pool = (base & ~np.uint64((1 << low_bits) - 1)) + \
+            rng.integers(0, 1 << low_bits, size=len(base), dtype=np.uint64)
+    pool = np.unique(pool)
+    R = np.full((n, k), 2 ** 64 - 1, dtype=np.uint64)
+    S = np.zeros(n, dtype=np.uint32)
+    for v in range(n):
+        c = int(rng.integers(0, k)) if v % 3 == 0 else k
+        c = min(c, len(pool))
+        R[v, :c] = np.sort(rng.choice(pool, size=c, replace=False))
+        S[v] = c
+    return R, S
+
+
+@pytest.mark.parametrize("k", [2, 15, 16, 17, 32, 33, 64, 65])
+@pytest.mark.parametrize("low_bits", [0, 10])
+def test_set_sizes_at_class_edges(oracle_lib, k, low_bits):
+    """Every size class of both estimators at its edges (lane groups of 2 to 64,
+    2 and 4 members a lane, the wave), over the register widths of the sorted
+    path, with members repeated; bit for bit, hashed and permutation readings.
+    Batches below and above the grid (one query a workgroup; runs of 64)."""
+    from gpu_util import to_dev_u32, to_dev_u64
+    import torch
+    import paper_1408_6282_amd as sk
+    rng = np.random.default_rng(100 * k + low_bits)
+    n, ell = 300, 8
+    R, S = _pool_tables(rng, n, k, low_bits)
+    rt, st = to_dev_u64(R.reshape(-1)), to_dev_u32(S)
+    edges = [0, 1, 2, 3, 4, 5, 8, 9, 16, 17, 31, 32, 33, 63, 64, 65, 256, 257, 1024, 1025]
+    few = [rng.integers(0, n, size=s).tolist() for s in edges] + [[n, 1], [1, 2, n + 5]]
+    many = [rng.integers(0, n, size=int(rng.choice(edges[:16]))).tolist() for _ in range(20000)]
+    for sets in (few, few + many):
+        off, nodes = _sets(sets)
+        for estimator, fn in [(0, oracle_lib.union_query), (1, oracle_lib.ck_query)]:
+            log(f"classes k={k} low={low_bits} q={len(sets)} est={estimator}")
+            want, wst = fn(R, S, k, ell, off, nodes)
+            over = np.diff(off.astype(np.int64)) > 1024  # the library's limit, not the oracle's
+            want, wst = np.where(over, 0.0, want), np.where(over, -2, wst)
+            got, status = gpu_query(rt, st, n, k, ell, off, nodes, estimator)
+            assert np.array_equal(status, wst)
+            assert np.array_equal(got, want)
+    # permutation positions: small integers (below 2^32)
+    P = np.where(R == np.uint64(2 ** 64 - 1), R, (R >> np.uint64(44)) + np.uint64(2))
+    if low_bits == 0 and all(np.all(np.diff(P[v, :S[v]].astype(np.int64)) > 0) for v in range(n)):
+        few = [x for x in few if len(x) <= 1024]
+        off, nodes = _sets(few)
+        pt = to_dev_u64(P.reshape(-1))
+        est = torch.empty(len(few), dtype=torch.float64, device="cuda:0")
+        for estimator in (0, 1):
+            sk.skim_perm_query_batch(pt, st, 1 << 17, k, ell, to_dev_u64(off),
+                                     to_dev_u32(np.minimum(nodes, n - 1)), est,
+                                     estimator=estimator)
+            want, _ = oracle_lib.perm_union_query(P, S, 1 << 17, k, ell, off,
+                                                  np.minimum(nodes, n - 1), estimator)
+            assert np.array_equal(est.cpu().numpy(), want)
