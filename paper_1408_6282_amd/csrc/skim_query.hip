@@ -29,6 +29,7 @@ constexpr uint32_t kMaxMembers = 1024;  // members per query (LDS state)
 constexpr int kQBlock = 64;             // one wave per block
 constexpr int kPerLane = kMaxMembers / 64;
 constexpr uint32_t kRun = 64;           // most queries a wave takes at once
+constexpr uint64_t kTakeMembers = 48;   // mean set size from which the counter balances
 
 using QArgs = QueryArgs;
 
@@ -117,8 +118,9 @@ __device__ __forceinline__ void put_answer(const QArgs &Q, uint64_t j, double es
     if (Q.qstatus) Q.qstatus[j] = status;
 }
 
-// Answer query j (members qnodes[a .. a + S), S >= 1) with the whole wave.
-__device__ void answer_wave(const QArgs &Q, uint64_t j, uint64_t a, uint64_t S, MergeLds &X) {
+// Cohen-Kaplan answer of query j (members qnodes[a .. a + S), S >= 1) by the
+// whole wave's merge.
+__device__ void ck_wave(const QArgs &Q, uint64_t j, uint64_t a, uint64_t S, MergeLds &X) {
     const uint32_t lane = lane_id();
     const uint32_t k = Q.k;
     // membership checks (node ids are validated per query)
@@ -135,8 +137,7 @@ __device__ void answer_wave(const QArgs &Q, uint64_t j, uint64_t a, uint64_t S, 
         const uint32_t sz = Q.size[u];
         X.mnode[t] = u;
         X.mpos[t] = 0;
-        // CK ignores the threshold element of a full sketch
-        X.mlim[t] = (uint16_t)(Q.estimator == 1 && sz >= k ? k - 1 : (sz < k ? sz : k));
+        X.mlim[t] = (uint16_t)(sz >= k ? k - 1 : sz);  // without a full sketch's threshold
     }
     wave_sync();
     uint32_t d = 0;
@@ -145,8 +146,7 @@ __device__ void answer_wave(const QArgs &Q, uint64_t j, uint64_t a, uint64_t S, 
     if (S <= 64) merge_members<1>(Q, S, k, X, d, tau, sum);
     else if (S <= 256) merge_members<4>(Q, S, k, X, d, tau, sum);
     else merge_members<kPerLane>(Q, S, k, X, d, tau, sum);
-    if (lane == 0)
-        put_answer(Q, j, Q.estimator == 1 ? sum / (double)Q.ell : union_estimate(Q, d, tau), 0);
+    if (lane == 0) put_answer(Q, j, sum / (double)Q.ell, 0);
     wave_sync();  // X is refilled by the next query
 }
 
@@ -157,20 +157,21 @@ __device__ void answer_wave(const QArgs &Q, uint64_t j, uint64_t a, uint64_t S, 
 // advances does not wait for memory unless it advances twice in a row.
 // Groups without a query (S = 0) idle.
 template <int G, int R>
-__device__ __forceinline__ void merge_group(const QArgs &Q, uint64_t j, uint64_t a, uint32_t S) {
+__device__ __forceinline__ void merge_group(const QArgs &Q, uint64_t j, const uint32_t *nodes,
+                                            uint32_t S) {
     const uint32_t gl = lane_id() & (G - 1), k = Q.k;
     uint32_t node[R];
     bool bad = false;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const uint32_t t = gl + G * r;
-        node[r] = t < S ? Q.qnodes[a + t] : 0u;
+        node[r] = t < S ? nodes[t] : 0u;
         bad |= t < S && node[r] >= Q.n;
     }
     {
         const unsigned long long m = __ballot(bad);
         const uint32_t g0 = lane_id() & ~(uint32_t)(G - 1);
-        bad = ((m >> g0) & ((1ull << G) - 1ull)) != 0;
+        bad = ((m >> g0) & (G == 64 ? ~0ull : (1ull << (G & 63)) - 1ull)) != 0;
     }
     const bool mine = S > 0;
     uint64_t head[R], next[R];
@@ -223,6 +224,149 @@ __device__ __forceinline__ void merge_group(const QArgs &Q, uint64_t j, uint64_t
     if (mine && gl == 0) put_answer(Q, j, bad ? 0.0 : union_estimate(Q, d, tau), bad ? -1 : 0);
 }
 
+// One set alone in its workgroup (k_query_each), S <= G members: the
+// first ranks of every row go to LDS at once, one memory latency instead of
+// one in most steps (a member takes about k / S steps in a row's order, so
+// the rest is rarely reached), and lane t merges member t from there.  16
+// lognormal sets over k = 64 (20,000 nodes), bound by the chain of 64 steps:
+// 24.2 us a call when the steps read global memory, 22.7 us so.
+constexpr uint32_t kStagedRanks = sizeof(MergeLds) / sizeof(uint64_t);
+template <uint32_t G>
+__device__ __forceinline__ void merge_staged(const QArgs &Q, uint64_t j, const uint32_t *nodes,
+                                             uint32_t S, uint64_t *rows) {
+    const uint32_t lane = lane_id(), k = Q.k;
+    const uint32_t u = lane < S ? nodes[lane] : 0u;
+    if (__any(u >= Q.n)) {
+        if (lane == 0) put_answer(Q, j, 0.0, -1);
+        return;
+    }
+    const uint32_t c = min(k, kStagedRanks / S);  // ranks of a row in LDS, >= 16
+    uint32_t lim = 0;
+    if (lane < S) {
+        const uint32_t sz = Q.size[u];
+        lim = sz < k ? sz : k;
+    }
+#pragma unroll 16
+    for (uint32_t x0 = 0; x0 < S * c; x0 += 64) {  // every lane takes part in the shuffles
+        const uint32_t x = x0 + lane, t = min(x / c, S - 1);
+        const uint64_t ur = (uint32_t)__shfl((int)u, (int)t);
+        if (x < S * c) rows[x] = Q.ranks[ur * k + (x - t * c)];
+    }
+    wave_sync();
+    const uint64_t *row = rows + lane * c, *all = Q.ranks + (uint64_t)u * k;
+    uint64_t head = lim > 0 ? row[0] : kNone, next = lim > 1 ? row[1] : kNone;
+    uint32_t at = 2, d = 0;
+    uint64_t tau = 0;
+    for (;;) {
+        uint64_t g = group_min_u64<G>(head);
+        if (G < 64) g = shfl_u64(g, 0);  // the other lanes hold no member
+        if (g == kNone) break;
+        if (++d == k) {
+            tau = g;
+            break;
+        }
+        if (head == g) {
+            head = next;
+            next = at < lim ? (at < c ? row[at] : all[at]) : kNone;
+            ++at;
+        }
+    }
+    if (lane == 0) put_answer(Q, j, union_estimate(Q, d, tau), 0);
+    wave_sync();  // the rows' LDS is reused
+}
+
+// Ascending sort of one key per lane.
+__device__ __forceinline__ uint64_t sort_lanes(uint64_t x) {
+    const uint32_t lane = lane_id();
+    // merge runs of 1, 2, .. 32 lanes: the mirrored partner first, then halves
+    x = keep_of(x, lane_xor64<1>(x), !(lane & 1));
+    x = keep_of(x, lane_xor64<3>(x), !(lane & 2));
+    x = keep_of(x, lane_xor64<1>(x), !(lane & 1));
+    x = keep_of(x, lane_xor64<7>(x), !(lane & 4));
+    x = keep_of(x, lane_xor64<2>(x), !(lane & 2));
+    x = keep_of(x, lane_xor64<1>(x), !(lane & 1));
+    x = keep_of(x, lane_xor64<15>(x), !(lane & 8));
+    x = keep_of(x, lane_xor64<4>(x), !(lane & 4));
+    x = keep_of(x, lane_xor64<2>(x), !(lane & 2));
+    x = keep_of(x, lane_xor64<1>(x), !(lane & 1));
+    x = keep_of(x, lane_xor64<31>(x), !(lane & 16));
+    x = keep_of(x, lane_xor64<8>(x), !(lane & 8));
+    x = keep_of(x, lane_xor64<4>(x), !(lane & 4));
+    x = keep_of(x, lane_xor64<2>(x), !(lane & 2));
+    x = keep_of(x, lane_xor64<1>(x), !(lane & 1));
+    x = keep_of(x, lane_xor64<63>(x), !(lane & 32));
+    x = keep_of(x, lane_xor64<16>(x), !(lane & 16));
+    x = keep_of(x, lane_xor64<8>(x), !(lane & 8));
+    x = keep_of(x, lane_xor64<4>(x), !(lane & 4));
+    x = keep_of(x, lane_xor64<2>(x), !(lane & 2));
+    return keep_of(x, lane_xor64<1>(x), !(lane & 1));
+}
+
+// Bottom-k of a set of more than 64 members, by the whole wave.  Each lane
+// takes the smallest head of its 16 members; the k-th smallest distinct one of
+// those 64 is a value of the union with at least k - 1 distinct values below
+// it, so members whose head lies above it cannot contribute.  What is left
+// (little more than k members) is merged.
+__device__ __forceinline__ void bottomk_wave(const QArgs &Q, uint64_t j, uint64_t a, uint64_t S,
+                                             MergeLds &X) {
+    const uint32_t lane = lane_id(), k = Q.k;
+    bool bad = false;
+    for (uint64_t t = a + lane; t < a + S; t += 64) bad |= Q.qnodes[t] >= Q.n;
+    bad = __ballot(bad) != 0;
+    if (bad || S > kMaxMembers) {
+        if (lane == 0) put_answer(Q, j, 0.0, bad ? -1 : -2);
+        return;
+    }
+    uint64_t head[kPerLane], least = kNone;
+#pragma unroll
+    for (int r = 0; r < kPerLane; ++r) {
+        const uint32_t t = lane + 64u * r;
+        head[r] = kNone;
+        if (t < S) {
+            const uint32_t u = Q.qnodes[a + t];
+            if (Q.size[u]) head[r] = Q.ranks[(uint64_t)u * k];
+        }
+        least = head[r] < least ? head[r] : least;
+    }
+    const uint64_t x = sort_lanes(least);
+    const uint64_t before = shfl_u64(x, lane ? lane - 1 : 0);
+    const unsigned long long first = __ballot(x != kNone && (lane == 0 || x != before));
+    uint64_t bound = kNone;  // the k-th smallest distinct one
+    if ((uint32_t)__popcll(first) >= k) {
+        const bool at = ((first >> lane) & 1ull) &&
+                        (uint32_t)__popcll(first & ((1ull << lane) - 1ull)) == k - 1;
+        bound = shfl_u64(x, (uint32_t)__ffsll((long long)__ballot(at)) - 1);
+    }
+    uint32_t kept = 0;
+#pragma unroll
+    for (int r = 0; r < kPerLane; ++r) {
+        const bool keep = head[r] != kNone && head[r] <= bound;
+        const unsigned long long m = __ballot(keep);
+        if (keep)
+            X.mnode[kept + __popcll(m & ((1ull << lane) - 1ull))] = Q.qnodes[a + lane + 64u * r];
+        kept += (uint32_t)__popcll(m);
+    }
+    wave_sync();
+    if (kept <= 64) {
+        if (kept) merge_group<64, 1>(Q, j, X.mnode, kept);
+        else if (lane == 0) put_answer(Q, j, union_estimate(Q, 0, 0), 0);
+    } else {
+        for (uint32_t t = lane; t < kept; t += 64) {
+            const uint32_t sz = Q.size[X.mnode[t]];
+            X.mpos[t] = 0;
+            X.mlim[t] = (uint16_t)(sz < k ? sz : k);
+        }
+        wave_sync();
+        uint32_t d = 0;
+        uint64_t tau = 0;
+        double sum = 0.0;
+        if (kept <= 256) merge_members<4>(Q, kept, k, X, d, tau, sum);
+        else merge_members<kPerLane>(Q, kept, k, X, d, tau, sum);
+        if (lane == 0) put_answer(Q, j, union_estimate(Q, d, tau), 0);
+    }
+    wave_sync();  // X is refilled by the next query
+}
+
 // A run of queries' offsets, one per lane, and the lanes of one size class.
 struct Run {
     uint64_t j0, a, S;  // first query; this lane's set
@@ -247,7 +391,7 @@ __device__ __forceinline__ void run_class(const QArgs &Q, const Run &run, bool i
         const uint32_t src = x < total ? run.list[x] : 0u;
         const uint64_t a = shfl_u64(run.a, src);
         const uint32_t S = (uint32_t)__shfl((int)(uint32_t)run.S, (int)src);
-        merge_group<G, R>(Q, run.j0 + src, a, x < total ? S : 0u);
+        merge_group<G, R>(Q, run.j0 + src, Q.qnodes + a, x < total ? S : 0u);
     }
 }
 
@@ -301,7 +445,7 @@ __device__ __forceinline__ void answer_bottomk(const QArgs &Q, uint64_t j0, uint
     while (rest) {
         const uint32_t src = (uint32_t)__ffsll((long long)rest) - 1;
         rest &= rest - 1;
-        answer_wave(Q, j0 + src, shfl_u64(run.a, src), shfl_u64(run.S, src), X);
+        bottomk_wave(Q, j0 + src, shfl_u64(run.a, src), shfl_u64(run.S, src), X);
     }
 }
 
@@ -320,9 +464,10 @@ __device__ __forceinline__ void answer_bottomk(const QArgs &Q, uint64_t j0, uint
 // LDS, are compared for every pair of neighbours, and such a set (about one
 // in 10^9 for hashed ranks) is answered by the merge instead.
 //
-// What bounds it: vector-unit instructions.  The merge it replaces made one
-// serial step of two wave-wide reductions and three dependent loads per
-// distinct value.
+// What bounds it: vector-unit instructions (24,000 per set of 50 over k = 64)
+// at two waves per SIMD.  The merge it replaces made one serial step of two
+// wave-wide reductions and three dependent loads per distinct value: 20,000
+// sets of 50 over a 10^6-node table, 23.9 -> 1.16 ms.
 struct CkLds {
     uint64_t stage[64 * 17];  // 16 ranks of every lane, rows padded to 17
     double w[64];             // 1/r of each lane's member threshold
@@ -533,7 +678,7 @@ __device__ __forceinline__ void answer_ck(const QArgs &Q, uint64_t j0, uint32_t 
     while (rest) {
         const uint32_t src = (uint32_t)__ffsll((long long)rest) - 1;
         rest &= rest - 1;
-        answer_wave(Q, j0 + src, shfl_u64(run.a, src), shfl_u64(run.S, src), X);
+        ck_wave(Q, j0 + src, shfl_u64(run.a, src), shfl_u64(run.S, src), X);
     }
 }
 
@@ -553,38 +698,74 @@ __device__ __forceinline__ void answer_run(const QArgs &Q, uint64_t j0, uint32_t
     else answer_ck<kCk>(Q, j0, cnt, X.merge, X.ck, X.list);
 }
 
-// `next` NULL: one query per workgroup (a batch that does not exceed the
-// grid needs no counter).
 template <int kCk>
-__global__ void __launch_bounds__(kQBlock) k_query_persistent(QArgs Q, uint64_t q,
-                                                               unsigned long long *next) {
+__global__ void __launch_bounds__(kQBlock, kCk < 0 ? 4 : 2) k_query_persistent(
+    QArgs Q, uint64_t q, unsigned long long *next) {
     __shared__ QueryLds<kCk> X;
-    if (!next) {
-        if (blockIdx.x < q) answer_run<kCk>(Q, blockIdx.x, 1, X);
-        return;
-    }
-    // Queries are taken in runs that shrink as the batch drains (at most
-    // kRun, about a quarter of an even share of what is left): takes from
-    // different waves on the one counter are serialised by the hardware, so
-    // one query per take would cap the batch at the counter's rate.
+    // Takes from different waves on the one counter are serialised by the
+    // hardware (about 12 ns each).  Sets of less than kTakeMembers members on
+    // average cost less than that, so they go in equal runs, every wave the
+    // same number of them, spread over the batch (10^6 lognormal sets, mean
+    // 12: 1.08 ms taken from the counter, 0.81 ms in equal runs).  Batches of
+    // larger sets are taken from the counter, in runs that shrink as it drains
+    // (at most kRun, about a quarter of an even share of what is left), which
+    // balances sets of uneven size.
     const uint64_t share = 4ull * gridDim.x;
-    uint64_t g = q / share;
+    const bool even = Q.qoff[q] < kTakeMembers * q;
+    uint64_t g = q / share, step = 0, j0 = 0;
     g = g < 1 ? 1 : g > kRun ? kRun : g;
-    for (;;) {
-        unsigned long long j0 = 0;
-        if (threadIdx.x == 0) j0 = atomicAdd(next, (unsigned long long)g);
-        j0 = shfl_u64(j0, 0);
+    if (even) {
+        const uint64_t rounds = (q + (uint64_t)gridDim.x * kRun - 1) / ((uint64_t)gridDim.x * kRun);
+        g = (q + gridDim.x * rounds - 1) / (gridDim.x * rounds);  // <= kRun
+        step = gridDim.x * g;
+        j0 = blockIdx.x * g;
+    }
+    for (;; j0 += step) {  // one call site: the answering code is large
+        if (!even) {
+            unsigned long long at = 0;
+            if (threadIdx.x == 0) at = atomicAdd(next, (unsigned long long)g);
+            j0 = shfl_u64(at, 0);
+        }
         if (j0 >= q) break;
         const uint64_t j1 = j0 + g < q ? j0 + g : q;
         answer_run<kCk>(Q, j0, (uint32_t)(j1 - j0), X);
-        g = (q - j1) / share;
-        g = g < 1 ? 1 : g > kRun ? kRun : g;
+        if (!even) {
+            g = (q - j1) / share;
+            g = g < 1 ? 1 : g > kRun ? kRun : g;
+        }
     }
 }
 
-template <int kCk> __global__ void __launch_bounds__(kQBlock) k_query_one(QArgs Q, uint64_t j) {
+// One query per workgroup, queries j0 on: a batch within the grid (no counter
+// to reset), or the plain path's launch for one query.
+template <int kCk>
+__global__ void __launch_bounds__(kQBlock, 2) k_query_each(QArgs Q, uint64_t j0) {
     __shared__ QueryLds<kCk> X;
-    answer_run<kCk>(Q, j, 1, X);
+    const uint64_t j = j0 + blockIdx.x;
+    if constexpr (kCk < 0) {
+        Run run{j, 0, 0, X.list};
+        load_run(Q, 1, run);
+        const uint64_t a = shfl_u64(run.a, 0), S = shfl_u64(run.S, 0);
+        uint64_t *rows = (uint64_t *)&X.merge;
+        if (S == 0) return;
+        if (S <= 16) merge_staged<16>(Q, j, Q.qnodes + a, (uint32_t)S, rows);
+        else if (S <= 64) merge_staged<64>(Q, j, Q.qnodes + a, (uint32_t)S, rows);
+        else bottomk_wave(Q, j, a, S, X.merge);
+    } else {
+        answer_run<kCk>(Q, j, 1, X);
+    }
+}
+
+template <int kCk> void launch_each(const QArgs &Q, uint64_t j0, unsigned grid, hipStream_t s) {
+    k_query_each<kCk><<<grid, kQBlock, 0, s>>>(Q, j0);
+}
+void launch_each(const QArgs &Q, uint64_t j0, unsigned grid, hipStream_t s) {
+    if (Q.estimator == 0) launch_each<-1>(Q, j0, grid, s);
+    else if (Q.k <= 16) launch_each<16>(Q, j0, grid, s);
+    else if (Q.k <= 32) launch_each<32>(Q, j0, grid, s);
+    else if (Q.k <= 64) launch_each<64>(Q, j0, grid, s);
+    else launch_each<0>(Q, j0, grid, s);
+    SKIM_LAUNCH_CHECK();
 }
 
 __global__ void k_check_offsets(const uint64_t *qoff, uint64_t q, uint32_t *err) {
@@ -612,8 +793,11 @@ unsigned query_grid(uint64_t q) {
 
 void launch_queries_async(const QueryArgs &Q, uint64_t q, unsigned long long *next, hipStream_t s) {
     const unsigned grid = query_grid(q);
-    if (q > grid) fill_u64((uint64_t *)next, 0, 1, s);
-    else next = nullptr;
+    if (q <= grid) {
+        launch_each(Q, 0, (unsigned)q, s);
+        return;
+    }
+    fill_u64((uint64_t *)next, 0, 1, s);
     if (Q.estimator == 0) k_query_persistent<-1><<<grid, kQBlock, 0, s>>>(Q, q, next);
     else if (Q.k <= 16) k_query_persistent<16><<<grid, kQBlock, 0, s>>>(Q, q, next);
     else if (Q.k <= 32) k_query_persistent<32><<<grid, kQBlock, 0, s>>>(Q, q, next);
@@ -652,12 +836,7 @@ static void query_batch(const uint64_t *ranks, const uint32_t *size, uint32_t n,
         launch_queries_async(Q, q, next, s);
     } else {
         for (uint64_t j = 0; j < q; ++j) {
-            if (estimator == 0) k_query_one<-1><<<1, kQBlock, 0, s>>>(Q, j);
-            else if (k <= 16) k_query_one<16><<<1, kQBlock, 0, s>>>(Q, j);
-            else if (k <= 32) k_query_one<32><<<1, kQBlock, 0, s>>>(Q, j);
-            else if (k <= 64) k_query_one<64><<<1, kQBlock, 0, s>>>(Q, j);
-            else k_query_one<0><<<1, kQBlock, 0, s>>>(Q, j);
-            SKIM_LAUNCH_CHECK();
+            launch_each(Q, j, 1, s);
         }
     }
     SKIM_HIP(hipStreamSynchronize(s));
