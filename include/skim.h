@@ -436,7 +436,7 @@ skim_status skim_greedy_records(const skim_greedy_state *state, uint32_t first, 
  *   tail              [bins + 1] out, device (double): tail[t] is an upper
  *                     bound on P[D_1 + ... + D_s >= t h]; tail[0] = 1.
  *                     With I = 0 the result is (1, 0, ..., 0).
- * Scratch: 12 * s * (bins + 1) bytes of device memory for the call.
+ * Scratch: 12 * s * (bins + 1) bytes and 4 MiB of device memory for the call.
  */
 skim_status skim_discrepancy_tail(uint32_t s, const uint64_t *tau, const uint32_t *second,
                                   const uint64_t *gain_pairs, uint32_t bins,
@@ -448,7 +448,7 @@ skim_status skim_discrepancy_tail(uint32_t s, const uint64_t *tau, const uint32_
  * serving loops, harnesses that forbid hipMalloc).  Same arguments and
  * result; it allocates nothing and only enqueues its work on `stream` (the
  * caller synchronises).  Its scratch is a file-scope device array of about
- * 12.3 MiB that each GPU the library runs on holds until the process ends:
+ * 16.3 MiB that each GPU the library runs on holds until the process ends:
  * s * (bins + 1) may be at most 2^20 (1,048,576), else SKIM_EUNSUPPORTED
  * with nothing enqueued.  Every call on one GPU shares that GPU's array, so
  * calls that overlap on one GPU (other streams or threads, before the

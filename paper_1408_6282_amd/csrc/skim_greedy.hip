@@ -978,10 +978,12 @@ constexpr uint32_t kTailMaxBins = 1u << 16;
 constexpr uint64_t kTailMaxCells = 1ull << 30;  // seeds * (bins + 1)
 constexpr int kTailBlock = 256;
 
+constexpr uint32_t kTailCounters = 1024;  // arrival counters, cleared at the start of a tail
 __global__ void __launch_bounds__(kTailBlock) k_tail_total(uint32_t s, const uint64_t *gain,
-                                                           uint64_t *total) {
+                                                           uint64_t *total, uint32_t *arrived) {
     __shared__ unsigned long long acc;
     if (threadIdx.x == 0) acc = 0;
+    for (uint32_t c = threadIdx.x; c < kTailCounters; c += kTailBlock) arrived[c] = 0;
     __syncthreads();
     unsigned long long t = 0;
     for (uint32_t r = threadIdx.x; r < s; r += kTailBlock) t += gain[r];
@@ -1034,96 +1036,199 @@ __global__ void __launch_bounds__(kTailBlock) k_tail_survival(
 // One level of the pairwise tree: out[p] = the capped sum of rows 2p and
 // 2p+1 of in (an odd last row is copied).  With a[i] = Sa[i] - Sa[i+1],
 //   Sc[j] = P[A + B >= j] = Sa[j+1] + sum_{i <= j} a[i] Sb[j-i],  Sa[bins+1] = 0.
-// A workgroup owns kTailOut consecutive outputs j0.. of one pair; each of its
-// kTailGroups waves takes the i tiles g, g + kTailGroups, ... of kTailI
-// values, and lane l of a wave keeps the partial sums of the kTailPer
-// consecutive outputs j0 + kTailPer l + c.  As i steps by one, the Sb values
-// those outputs need slide by one place, so a lane holds them in registers
-// and reads one new value per step.  A tile's a[i] and the Sb values it
-// meets, Sb[j0 - i0 - kTailI + u] for u = 0 .. kTailOut + kTailI - 1 (zero
-// outside 0 .. bins: below 0 this drops the terms with i > j), sit in the
-// wave's LDS with u interleaved by u mod kTailPer, so the lanes of a wave
-// read consecutive words.  The waves' partial sums are added in a fixed order
-// at the end, so the result does not depend on scheduling.
-constexpr int kTailGroups = 8, kTailPairBlock = 64 * kTailGroups;
-constexpr int kTailPer = 4, kTailOut = 64 * kTailPer, kTailI = 256;
-constexpr int kTailSpan = kTailOut + kTailI, kTailStride = kTailSpan / kTailPer;
+// The convolution on the fp64 matrix cores: with j = 16 c + r and
+// i = 16 b + t it is a sum over D = c - b of 16 x 16 x 16 products,
+//   out[r][c] = sum_D sum_t T_D[r][t] a[16 (c - D) + t],
+//   T_D[r][t] = Sb[16 D + r - t]  (zero outside 0 .. bins),
+// so a tile of 16 columns (256 outputs) takes four 16x16x4 products per D
+// = 0 .. its last column, all of them needed but for the triangles at both
+// ends.  A workgroup's four waves split the D range 8 steps at a time and
+// share the staged values; their sums are added in a fixed order.
+//
+// The last levels have few tiles and long D ranges (one pair: 17 tiles of up
+// to 272 steps at 4097 cells), a serial chain on a few CUs.  There a tile's D
+// range is cut into parts of `part` steps, one workgroup each; the parts' sums
+// go to scratch and the workgroup that finishes last adds them in order.  The
+// result does not depend on which one that is.
+//
+// 200 seeds, 4096 bins (3.34 GFLOP, 55 us at the 61 TFLOP/s that a large fp64
+// matrix product reaches here): vector units, 8 waves per 256 outputs, 0.58 ms;
+// this 0.18 ms (the first level 53 us, the last three 8 us each).
+constexpr int kTailTile = 256, kTailChunk = 32, kTailWaves = 4;
+constexpr int kTailPairBlock = 64 * kTailWaves;
+constexpr int kTailBlocks = kTailChunk + 15;       // 16-cell blocks of a that a chunk meets
+constexpr int kTailPad = 18;
+constexpr uint64_t kTailSplit = kTailCounters;     // fewer tiles than this: split their D ranges
+constexpr uint64_t kTailPartials = 2 * kTailSplit;  // at most, kTailTile values each
+typedef double v4d __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ int tail_pos(int u) { return (u % kTailPer) * kTailStride + u / kTailPer; }
+// Tiles of a row and, with `part` D steps per workgroup, the workgroups of a
+// pair (tile t takes 16 t + 16 steps).
+__host__ __device__ inline uint32_t tail_tiles(uint64_t W) {
+    return (uint32_t)((W + kTailTile - 1) / kTailTile);
+}
+__host__ __device__ inline uint32_t tail_parts(uint32_t tile, uint32_t part) {
+    return (16 * tile + 16 + part - 1) / part;
+}
 
 __global__ void __launch_bounds__(kTailPairBlock) k_tail_pair(const double *in, double *out,
-                                                              uint32_t rows, uint32_t bins) {
-    __shared__ double s_a[kTailGroups][kTailI];
-    __shared__ double s_b[kTailGroups][kTailSpan];
-    const uint64_t W = (uint64_t)bins + 1;
-    const uint64_t outs = ((uint64_t)rows + 1) / 2;
-    const uint64_t chunks = (W + kTailOut - 1) / kTailOut, nblk = outs * chunks;
-    const int g = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64;
-    for (uint64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-        const uint64_t p = blk / chunks;
-        const int64_t j0 = (int64_t)(blk - p * chunks) * kTailOut;
-        const int64_t j1 = j0 + kTailOut < (int64_t)W ? j0 + kTailOut : (int64_t)W;
-        const double *a = in + 2 * p * W;
-        double *o = out + p * W;
-        if (2 * p + 1 >= rows) {
-            for (int64_t j = j0 + threadIdx.x; j < j1; j += kTailPairBlock) o[j] = a[j];
+                                                              uint32_t rows, uint32_t bins,
+                                                              uint32_t part, uint64_t per_pair,
+                                                              double *partial, uint32_t *arrived) {
+    __shared__ double s_a[kTailBlocks * kTailPad];  // blocks of 16, padded: no bank conflicts
+    __shared__ double s_b[16 * kTailChunk + 16];
+    __shared__ double s_red[kTailWaves][kTailTile];
+    __shared__ uint32_t s_last;
+    const int64_t W = (int64_t)bins + 1;
+    const uint32_t T = tail_tiles((uint64_t)W);
+    const uint64_t pairs = rows / 2, items = pairs * per_pair + (rows % 2 ? T : 0);
+    const int tid = (int)threadIdx.x, wave = tid / 64, lane = tid % 64;
+    const int li = lane % 16, lk = lane / 16;
+    for (uint64_t item = blockIdx.x; item < items; item += gridDim.x) {
+        const uint64_t p = item / per_pair;
+        if (p >= pairs) {  // the odd last row
+            const int64_t j = (int64_t)(item - pairs * per_pair) * kTailTile + tid;
+            if (j < W) out[pairs * W + j] = in[2 * pairs * W + j];
             continue;
         }
-        const double *b = a + W;
-        double acc[kTailPer];
+        uint64_t rest = item - p * per_pair;
+        uint32_t tile = T - 1;  // the longest first
+        int more = -1;          // a second tile for this workgroup
+        if (part >= 16 * T) {   // whole tiles, a long one with a short one
+            more = (int)rest < (int)tile - (int)rest ? (int)rest : -1;
+            tile -= (uint32_t)rest;
+            rest = 0;
+        } else {
+            while (rest >= tail_parts(tile, part)) rest -= tail_parts(tile--, part);
+        }
+        const uint32_t nparts = tail_parts(tile, part);
+        for (;; tile = (uint32_t)more, more = -1) {
+        const int64_t c0 = 16 * (int64_t)tile;
+        const int64_t d0 = (int64_t)rest * part;
+        const int64_t d1 = d0 + part < c0 + 16 ? d0 + part : c0 + 16;
+        const double *a = in + 2 * p * W, *b = a + W;
+        v4d acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
+        // the next chunk's values are on their way while this one is multiplied
+        constexpr int kA = (16 * kTailBlocks + kTailPairBlock - 1) / kTailPairBlock;
+        constexpr int kB = (16 * kTailChunk + 15 + kTailPairBlock - 1) / kTailPairBlock;
+        double va[kA], vn[kA], vb[kB];
+        auto fetch = [&](int64_t D0) {
+            // block x of s_a is block c0 - D0 - 31 + x of a
+            const int64_t ia = 16 * (c0 - D0 - (kTailChunk - 1)), ib = 16 * D0 - 15;
 #pragma unroll
-        for (int c = 0; c < kTailPer; ++c) acc[c] = 0.0;
-        const int64_t tiles = (j1 + kTailI - 1) / kTailI;  // tiles with i0 < j1
-        for (int64_t round = 0; round * kTailGroups < tiles; ++round) {
-            const int64_t i0 = (round * kTailGroups + g) * kTailI;
-            const bool active = i0 < j1;
-            __syncthreads();  // the previous tiles are consumed
-            if (active) {
-                for (int t = lane; t < kTailI; t += 64) {
-                    const int64_t i = i0 + t;
-                    s_a[g][t] =
-                        i < (int64_t)W ? a[i] - (i + 1 < (int64_t)W ? a[i + 1] : 0.0) : 0.0;
-                }
-                const int64_t base = j0 - i0 - kTailI;
-                for (int u = lane; u < kTailSpan; u += 64) {
-                    const int64_t q = base + u;
-                    s_b[g][tail_pos(u)] = q >= 0 && q < (int64_t)W ? b[q] : 0.0;
-                }
+            for (int q = 0; q < kA; ++q) {
+                const int64_t i = ia + tid + q * kTailPairBlock;
+                va[q] = i >= 0 && i < W ? a[i] : 0.0;
+                vn[q] = i >= 0 && i + 1 < W ? a[i + 1] : 0.0;
+            }
+#pragma unroll
+            for (int q = 0; q < kB; ++q) {
+                const int64_t i = ib + tid + q * kTailPairBlock;
+                vb[q] = i >= 0 && i < W ? b[i] : 0.0;
+            }
+        };
+        fetch(d0);
+        for (int64_t D0 = d0; D0 < d1; D0 += kTailChunk) {
+            __syncthreads();  // the previous chunk is consumed
+#pragma unroll
+            for (int q = 0; q < kA; ++q) {
+                const int x = tid + q * kTailPairBlock;
+                if (x < 16 * kTailBlocks) s_a[(x / 16) * kTailPad + x % 16] = va[q] - vn[q];
+            }
+#pragma unroll
+            for (int q = 0; q < kB; ++q) {
+                const int x = tid + q * kTailPairBlock;
+                if (x < 16 * kTailChunk + 15) s_b[x] = vb[q];
             }
             __syncthreads();
-            if (active) {
-                // output j0 + kTailPer lane + c at step t needs u = kTailPer lane + c + kTailI - t
-                const double *sa = s_a[g];
-                const double *sb = s_b[g];
-                double w[kTailPer];
-#pragma unroll
-                for (int c = 0; c < kTailPer; ++c) w[c] = sb[tail_pos(kTailPer * lane + c + kTailI)];
-#pragma unroll 8
-                for (int t = 0; t < kTailI; ++t) {
-                    const double at = sa[t];
-#pragma unroll
-                    for (int c = 0; c < kTailPer; ++c) acc[c] += at * w[c];
-#pragma unroll
-                    for (int c = kTailPer - 1; c > 0; --c) w[c] = w[c - 1];
-                    w[0] = sb[tail_pos(kTailPer * lane + kTailI - 1 - t)];
-                }
+            if (D0 + kTailChunk < d1) fetch(D0 + kTailChunk);
+            const int steps = d1 - D0 < kTailChunk ? (int)(d1 - D0) : kTailChunk;
+#pragma unroll 2
+            for (int e = wave; e < steps; e += kTailWaves) {  // uniform over the wave
+                const double *sa = s_a + (li - e + kTailChunk - 1) * kTailPad + lk;
+                const double *sb = s_b + 16 * e + li - lk + 15;
+                acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(sb[0], sa[0], acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(sb[-4], sa[4], acc1, 0, 0, 0);
+                acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(sb[-8], sa[8], acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(sb[-12], sa[12], acc1, 0, 0, 0);
             }
         }
-        // fixed-order reduction over the waves, through the staging LDS
         __syncthreads();
-        double *red = &s_b[0][0];
 #pragma unroll
-        for (int c = 0; c < kTailPer; ++c) red[g * kTailOut + kTailPer * lane + c] = acc[c];
+        for (int q = 0; q < 4; ++q)  // row 4 q + lk, column li
+            s_red[wave][16 * li + 4 * q + lk] = acc0[q] + acc1[q];
         __syncthreads();
-        for (int jj = threadIdx.x; jj < kTailOut; jj += kTailPairBlock) {
-            const int64_t j = j0 + jj;
-            if (j < j1) {
-                double v = j + 1 < (int64_t)W ? a[j + 1] : 0.0;
-                for (int q = 0; q < kTailGroups; ++q) v += red[q * kTailOut + jj];
-                o[j] = v;
+        double v = 0.0;
+        for (int w = 0; w < kTailWaves; ++w) v += s_red[w][tid];
+        const int64_t j = 16 * c0 + tid;
+        if (nparts > 1) {
+            // item numbers of a tile's parts are consecutive
+            // (agent-scope stores and loads reach the memory all XCDs see, so
+            // no fence has to write back or invalidate a whole cache; the
+            // stores have arrived before the counter is touched)
+            st(partial + item * kTailTile + tid, v);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            if (tid == 0) {
+                uint32_t *cnt = arrived + p * T + tile;
+                const uint32_t before = atomicAdd(cnt, 1u);
+                s_last = before + 1 == nparts;
+                if (s_last) atomicExch(cnt, 0u);  // ready for the next level
             }
+            __syncthreads();
+            if (!s_last) break;  // uniform
+            const double *first = partial + (item - rest) * kTailTile;
+            v = 0.0;
+            for (uint32_t q = 0; q < nparts; ++q)
+                v += ld(first + (uint64_t)q * kTailTile + tid);
         }
-        __syncthreads();  // LDS is reused by the next block of the stride
+        if (j < W) out[p * W + j] = v + (j + 1 < W ? a[j + 1] : 0.0);
+        if (more < 0) break;
+        }
+    }
+}
+
+// Scratch of a tail: the gain total and the tiles' arrival counters (cleared
+// by k_tail_total), the parts' sums, and two buffers of survival functions.
+struct TailScratch {
+    uint64_t *total;
+    uint32_t *arrived;  // [kTailSplit]
+    double *partial;    // [kTailPartials * kTailTile]
+    double *bufA, *bufB;  // s W and ceil(s / 2) W values
+};
+
+// Survival functions of the s >= 1 records, then the tree; enqueued only.
+void tail_enqueue(uint32_t s, const uint64_t *tau, const uint32_t *second, const uint64_t *gain,
+                  uint32_t bins, double max_rel, const TailScratch &T, double *tail,
+                  hipStream_t hs) {
+    const uint64_t W = (uint64_t)bins + 1;
+    k_tail_total<<<1, kTailBlock, 0, hs>>>(s, gain, T.total, T.arrived);
+    SKIM_LAUNCH_CHECK();
+    double *in = s == 1 ? tail : T.bufA, *out = T.bufB;
+    k_tail_survival<<<grid_for((uint64_t)s * W, kTailBlock), kTailBlock, 0, hs>>>(
+        s, tau, second, gain, T.total, bins, max_rel, in);
+    SKIM_LAUNCH_CHECK();
+    const uint32_t tiles = tail_tiles(W);
+    for (uint32_t rows = s; rows > 1; rows = (rows + 1) / 2) {
+        const uint64_t pairs = rows / 2;
+        uint32_t part = 16 * tiles;
+        uint64_t per_pair = (tiles + 1) / 2;
+        if (pairs * tiles < kTailSplit) {
+            // about kTailSplit parts in all, none below one chunk of steps: a
+            // tile adds at most one more than its share, so there are at most
+            // kTailPartials of them
+            const uint64_t steps = pairs * 8 * tiles * (tiles + 1);
+            part = (uint32_t)std::max<uint64_t>(kTailChunk, (steps + kTailSplit - 1) / kTailSplit);
+            per_pair = 0;
+            for (uint32_t t = 0; t < tiles; ++t) per_pair += tail_parts(t, part);
+        }
+        const uint64_t items = pairs * per_pair + (rows % 2 ? tiles : 0);
+        if (rows == 2) out = tail;
+        k_tail_pair<<<(unsigned)std::min<uint64_t>(items, 1u << 20), kTailPairBlock, 0, hs>>>(
+            in, out, rows, bins, part, per_pair, T.partial, T.arrived);
+        SKIM_LAUNCH_CHECK();
+        std::swap(in, out);
     }
 }
 
@@ -1531,10 +1636,12 @@ namespace skim {
 namespace {
 
 // seeds * (bins + 1) at most; the words hold the gain total (one 256-byte
-// slot), s (bins + 1) survival values and ceil(s / 2) (bins + 1) values of
-// a tree level (at most half the cells plus half a row): about 12.3 MiB.
+// slot), the tiles' arrival counters, the parts' sums, s (bins + 1) survival
+// values and ceil(s / 2) (bins + 1) values of a tree level (at most half the
+// cells plus half a row): about 16.3 MiB.
 constexpr uint64_t kNoAllocCells = 1ull << 20;
-constexpr uint64_t kNoAllocWords = 32 + kNoAllocCells + kNoAllocCells / 2 + 32800;
+constexpr uint64_t kNoAllocHead = 32 + kTailSplit / 2 + kTailPartials * kTailTile;
+constexpr uint64_t kNoAllocWords = kNoAllocHead + kNoAllocCells + kNoAllocCells / 2 + 32800;
 
 }  // namespace
 }  // namespace skim
@@ -1590,24 +1697,13 @@ extern "C" skim_status skim_discrepancy_tail_noalloc(uint32_t s, const uint64_t 
         int dev = 0;
         SKIM_HIP(hipGetDevice(&dev));
         double *base = scratch_on_device(dev);
-        // layout: gain total (one 256-byte slot), survival functions, tree level
-        uint64_t *total = (uint64_t *)base;
-        double *bufA = base + 32;
-        double *bufB = bufA + (uint64_t)s * W;
-        k_tail_total<<<1, kTailBlock, 0, hs>>>(s, gain_pairs, total);
-        SKIM_LAUNCH_CHECK();
-        k_tail_survival<<<grid_for((uint64_t)s * W, kTailBlock), kTailBlock, 0, hs>>>(
-            s, tau, second, gain_pairs, total, bins, max_rel_error, bufA);
-        SKIM_LAUNCH_CHECK();
-        double *in = bufA, *out = bufB;
-        for (uint32_t rows = s; rows > 1; rows = (rows + 1) / 2) {
-            const uint64_t blocks = ((uint64_t)rows + 1) / 2 * ((W + kTailOut - 1) / kTailOut);
-            k_tail_pair<<<(unsigned)std::min<uint64_t>(blocks, 65536), kTailPairBlock, 0, hs>>>(
-                in, out, rows, bins);
-            SKIM_LAUNCH_CHECK();
-            std::swap(in, out);
-        }
-        SKIM_HIP(hipMemcpyAsync(tail, in, W * sizeof(double), hipMemcpyDeviceToDevice, hs));
+        TailScratch S;
+        S.total = (uint64_t *)base;
+        S.arrived = (uint32_t *)(base + 32);
+        S.partial = base + 32 + kTailSplit / 2;
+        S.bufA = base + kNoAllocHead;
+        S.bufB = S.bufA + (uint64_t)s * W;
+        tail_enqueue(s, tau, second, gain_pairs, bins, max_rel_error, S, tail, hs);
         return SKIM_OK;
     } catch (const Fail &f) {
         return f.st;
@@ -1639,23 +1735,13 @@ extern "C" skim_status skim_discrepancy_tail(uint32_t s, const uint64_t *tau,
             return SKIM_OK;
         }
         Arena T(hs);
-        uint64_t *total = T.alloc<uint64_t>(1);
-        double *bufA = T.alloc<double>((uint64_t)s * W);
-        double *bufB = T.alloc<double>(((uint64_t)s + 1) / 2 * W);
-        k_tail_total<<<1, kTailBlock, 0, hs>>>(s, gain_pairs, total);
-        SKIM_LAUNCH_CHECK();
-        k_tail_survival<<<grid_for((uint64_t)s * W, kTailBlock), kTailBlock, 0, hs>>>(
-            s, tau, second, gain_pairs, total, bins, max_rel_error, bufA);
-        SKIM_LAUNCH_CHECK();
-        double *in = bufA, *out = bufB;
-        for (uint32_t rows = s; rows > 1; rows = (rows + 1) / 2) {
-            const uint64_t blocks = ((uint64_t)rows + 1) / 2 * ((W + kTailOut - 1) / kTailOut);
-            k_tail_pair<<<(unsigned)std::min<uint64_t>(blocks, 65536), kTailPairBlock, 0, hs>>>(
-                in, out, rows, bins);
-            SKIM_LAUNCH_CHECK();
-            std::swap(in, out);
-        }
-        SKIM_HIP(hipMemcpyAsync(tail, in, W * sizeof(double), hipMemcpyDeviceToDevice, hs));
+        TailScratch S;
+        S.total = T.alloc<uint64_t>(1);
+        S.arrived = T.alloc<uint32_t>(kTailSplit);
+        S.partial = T.alloc<double>(kTailPartials * kTailTile);
+        S.bufA = T.alloc<double>((uint64_t)s * W);
+        S.bufB = T.alloc<double>(((uint64_t)s + 1) / 2 * W);
+        tail_enqueue(s, tau, second, gain_pairs, bins, max_rel_error, S, tail, hs);
         SKIM_HIP(hipStreamSynchronize(hs));
         return SKIM_OK;
     } catch (const Fail &f) {

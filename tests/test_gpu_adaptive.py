@@ -184,3 +184,18 @@ def test_tail_edge_cases():
         sk.skim_discrepancy_tail(big, big.to(torch.int32), big, 65536, 0.1,
                                  torch.empty(65537, dtype=torch.float64, device=dev()))
     assert ei.value.status == sk.SKIM_EUNSUPPORTED
+
+
+@pytest.mark.parametrize("s,bins", [(2, 15), (2, 16), (4, 254), (2, 4095), (7, 4111), (16, 4096),
+                                    (66, 4096), (130, 300), (2, 65535)])
+def test_tail_tiles_and_parts(s, bins):
+    """Rows that end inside a 16-cell block, at it, inside a 256-output tile;
+    levels with one workgroup per tile and with split D ranges; odd rows; the
+    same bits on every call, whichever part finishes last."""
+    rng = np.random.default_rng(s * 1013 + bins)
+    tau, second, gain = _synthetic(rng, s)
+    log(f"tail tiles s={s} bins={bins}")
+    got = gpu_tail(tau, second, gain, bins, 0.25)
+    _check(got, ad.discrepancy_tail(tau, second, gain, bins, 0.25), s, bins)
+    for _ in range(3):
+        assert np.array_equal(gpu_tail(tau, second, gain, bins, 0.25), got)
