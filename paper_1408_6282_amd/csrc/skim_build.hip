@@ -55,6 +55,7 @@
 // by the hardware, so shared counters sit on lines of their own and are
 // added to once per workgroup.
 #include "skim_internal.h"
+#include "skim_wave.h"
 
 #include <rocprim/device/device_radix_sort.hpp>
 
@@ -76,6 +77,7 @@ constexpr uint32_t kOvfFirst = 16u;  // the optimistic first window overflowed
 // with modest reach sets is still below where pruning starts; graphs where
 // it overflows restart with bucket 0 alone.
 constexpr uint32_t kFirstSpan = 5;
+constexpr uint64_t kOptimistic = 1u << 15;  // frontier from which it may be given up early
 constexpr int kBlock = 256;
 
 // Thrown inside the build when a buffer was too small; the windows restart
@@ -1163,6 +1165,318 @@ __global__ void k_tails_begin(Ctl *ctl, uint32_t L) {
     ctl->budget = 0;
 }
 
+// ------------------------------------------ dense windows: source bit sets
+// On graphs with a dense core most visits of an early window go to pairs that
+// many of its sources reach, and most of the attempts are repeats: R-MAT of
+// 2^18 nodes (l = 64, k = 32) made 69 M visits in its first four windows, 62 M
+// of them through the hash set, one atomic each in a table of up to 1 GiB.
+// While a window has few sources per instance, their set at a pair fits a few
+// 64-bit words instead: V[pair][w], bit s of instance i standing for the
+// instance's s-th source of the window.  The search then moves whole words
+// along live in-edges; a pair whose words grew since it was last expanded is
+// marked in a mask of dirty pairs (64 bits per node), and a level expands every
+// dirty pair, so sources that meet in a pair go on together.  V ends as the
+// set of accepted visits, which is all that the rest of the build uses of a
+// window: the pairs' counts and the records (in no particular order).  Pairs
+// that every claim would turn away (see claim) start with all bits set.
+//
+// What bounds it: one random line per live in-edge of a dirty pair (read, and
+// an atomic OR when it grows), and per window two passes over V and the pair
+// records.  That R-MAT build: 73 -> 11.7 ms (windows 0 to 3 with the redos of the
+// first: 47 -> 6 ms).
+constexpr uint32_t kDenseWords = 8;       // at most 512 sources per instance
+constexpr uint32_t kDenseNodes = 64;      // nodes per workgroup and round of a level
+constexpr uint32_t kDenseHeavy = 32;      // longer in-lists are cut into chunks of a wave's 64
+                                          // entries (a node's 64 lists of up to 128 held a
+                                          // workgroup for 50 us in nearly empty levels)
+constexpr int kDenseBatch = 4;            // levels launched without reading back
+constexpr uint32_t kDenseDeep = 48;       // a window of more levels: no dense window after it
+constexpr double kDenseVisits = 8.0;      // least visits per pair expected of a dense window
+
+struct DenseArgs {
+    uint64_t *prec;         // pair records (state, live-list word)
+    const uint32_t *lsrc;
+    const uint8_t *want;
+    uint32_t n, ell, k, win, nw;  // nw: words per pair
+    uint64_t *V;            // [n l][nw]
+    uint64_t *dirty[2];     // [n] by level parity
+    uint64_t *haslive;      // [n] instances in which the node has live in-edges
+    uint32_t *sources;      // [64][64 nw] pair id of each instance's sources
+    uint32_t *count;        // [64] lines of 128 bytes: sources numbered so far
+    uint64_t *heavy;        // (pair << 32 | chunk) of a level's long in-lists
+    uint64_t heavy_cap;
+    uint64_t *rec;
+    uint64_t rec_cap;
+    Ctl *ctl;
+};
+
+__device__ __forceinline__ bool dense_idle(uint64_t state, uint64_t live, bool want, uint32_t win,
+                                           uint32_t k) {
+    return prior_count(state, win) >= k || (!live && !want);
+}
+
+// Sources of every instance in [ws, we).
+__global__ void k_dense_count(const uint32_t *src, uint64_t ws, uint64_t we, uint32_t *count) {
+    __shared__ uint32_t c[64];
+    if (threadIdx.x < 64) c[threadIdx.x] = 0;
+    __syncthreads();
+    for (uint64_t t = ws + blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; t < we;
+         t += (uint64_t)gridDim.x * blockDim.x)
+        atomicAdd(&c[src[t] % kPairStride], 1u);
+    __syncthreads();
+    if (threadIdx.x < 64 && c[threadIdx.x]) atomicAdd(count + 32 * threadIdx.x, c[threadIdx.x]);
+}
+
+// One wave per node, lane i instance i.
+__global__ void __launch_bounds__(kBlock) k_dense_init(DenseArgs D) {
+    const uint32_t lane = lane_id();
+    const uint64_t waves = (uint64_t)gridDim.x * (kBlock / 64);
+    for (uint64_t v = blockIdx.x * (uint64_t)(kBlock / 64) + threadIdx.x / 64; v < D.n;
+         v += waves) {
+        uint64_t state = 0, live = 0;
+        const uint64_t q = v * kPairStride + lane;
+        if (lane < D.ell) {
+            state = D.prec[2 * q];
+            live = D.prec[2 * q + 1];
+            const uint64_t x =
+                dense_idle(state, live, D.want[v] != 0, D.win, D.k) ? ~0ull : 0ull;
+            uint64_t *row = D.V + (v * D.ell + lane) * D.nw;
+            for (uint32_t w = 0; w < D.nw; ++w) row[w] = x;
+        }
+        const unsigned long long h = __ballot(live != 0);
+        if (lane == 0) {
+            D.haslive[v] = h;
+            D.dirty[0][v] = D.dirty[1][v] = 0;
+        }
+    }
+}
+
+// Numbers the window's sources within their instances and visits their own
+// pairs (the count was cleared after k_dense_count).
+__global__ void k_dense_seed(DenseArgs D, const uint32_t *src, uint64_t ws, uint64_t we) {
+    for (uint64_t t = ws + blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; t < we;
+         t += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t p = src[t], i = p % kPairStride, v = p / kPairStride;
+        const uint32_t s = atomicAdd(D.count + 32 * i, 1u);  // < 64 nw (the host's count)
+        D.sources[i * 64 * D.nw + s] = p;
+        const uint64_t bit = 1ull << (s & 63);
+        uint64_t *word = D.V + ((uint64_t)v * D.ell + i) * D.nw + (s >> 6);
+        if (atomicOr((unsigned long long *)word, bit) & bit) continue;  // idle pair
+        if ((D.haslive[v] >> i) & 1ull)
+            atomicOr((unsigned long long *)&D.dirty[0][v], 1ull << i);
+    }
+}
+
+// The words m[0], m[stride], .. of an expanded pair reach pair (u, i).
+__device__ __forceinline__ void dense_visit(const DenseArgs &D, uint32_t u, uint32_t i,
+                                            const uint64_t *m, uint32_t stride, uint64_t *next) {
+    uint64_t *row = D.V + ((uint64_t)u * D.ell + i) * D.nw;
+    uint64_t grew = 0;
+    for (uint32_t w = 0; w < D.nw; ++w) {
+        const uint64_t x = m[w * stride];
+        // words only gain bits during a launch: a stale read only costs the OR
+        if (x & ~__hip_atomic_load(row + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+            grew |= x & ~atomicOr((unsigned long long *)(row + w), (unsigned long long)x);
+    }
+    if (!grew || !((D.haslive[u] >> i) & 1ull)) return;
+    const uint64_t bit = 1ull << i;
+    if (!(__hip_atomic_load(next + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit))
+        atomicOr((unsigned long long *)(next + u), (unsigned long long)bit);
+}
+
+// Level L: every dirty pair of a round's nodes, kBlock pairs at a time, their
+// in-lists laid end to end over the workgroup.  Reads and clears dirty[L % 2],
+// marks dirty[(L + 1) % 2]; the pairs expanded are added to size[L % 3].
+__global__ void __launch_bounds__(kBlock) k_dense_level(DenseArgs D, uint32_t L, uint32_t nodes) {
+    __shared__ uint64_t s_mask[kDenseNodes], s_m[kDenseWords * kBlock], s_list[kBlock];
+    __shared__ uint32_t s_pair[kDenseNodes + 1], s_ex[kBlock + 1], s_wsum[kBlock / 64];
+    __shared__ uint8_t s_inst[kBlock];
+    __shared__ uint64_t s_scratch[3 * (kBlock / 64)];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    uint64_t *cur = D.dirty[L & 1], *next = D.dirty[(L + 1) & 1];
+    if (blockIdx.x == 0 && tid == 0) {
+        D.ctl->size[16 * ((L + 1) % 3)] = 0;
+        D.ctl->hsize[16 * ((L + 1) % 2)] = 0;
+    }
+    uint32_t pairs = 0, scans = 0;
+    for (uint64_t v0 = (uint64_t)blockIdx.x * nodes; v0 < D.n; v0 += (uint64_t)gridDim.x * nodes) {
+        if (wave == 0) {  // nodes <= 64
+            uint64_t d = 0;
+            if (lane < nodes && v0 + lane < D.n) {
+                d = cur[v0 + lane];
+                if (d) cur[v0 + lane] = 0;
+            }
+            uint32_t incl = (uint32_t)__popcll(d);
+            for (uint32_t off = 1; off < 64; off <<= 1) {
+                const uint32_t y = __shfl_up(incl, off);
+                if (lane >= off) incl += y;
+            }
+            s_mask[lane] = d;
+            s_pair[lane + 1] = incl;
+            if (lane == 0) s_pair[0] = 0;
+        }
+        __syncthreads();
+        const uint32_t P = s_pair[kDenseNodes];
+        if (tid == 0) pairs += P;
+        for (uint32_t b0 = 0; b0 < P; b0 += kBlock) {  // uniform
+            uint32_t cnt = 0;
+            if (b0 + tid < P) {
+                const uint32_t j = b0 + tid;
+                uint32_t lo = 0, hi = kDenseNodes;  // s_pair[lo] <= j < s_pair[hi]
+                while (hi - lo > 1) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if (s_pair[mid] <= j) lo = mid;
+                    else hi = mid;
+                }
+                uint64_t d = s_mask[lo];
+                for (uint32_t r = j - s_pair[lo]; r > 0; --r) d &= d - 1;
+                const uint32_t i = (uint32_t)__ffsll((long long)d) - 1;
+                const uint64_t v = v0 + lo, live = D.prec[2 * (v * kPairStride + i) + 1];
+                cnt = (live & kLiveOne) ? 1u : live_count(live);
+                if (cnt > kDenseHeavy) {
+                    const uint32_t chunks = (cnt + 63) / 64;
+                    const uint64_t at =
+                        atomicAdd(&D.ctl->hsize[16 * (L % 2)], (unsigned long long)chunks);
+                    for (uint32_t c = 0; c < chunks; ++c)  // at + c < heavy_cap: see the host
+                        if (at + c < D.heavy_cap)
+                            D.heavy[at + c] = ((v * kPairStride + i) << 32) | c;
+                    cnt = 0;
+                }
+                s_list[tid] = live;
+                s_inst[tid] = (uint8_t)i;
+                const uint64_t *row = D.V + (v * D.ell + i) * D.nw;
+                for (uint32_t w = 0; w < D.nw; ++w) s_m[w * kBlock + tid] = row[w];
+            }
+            uint32_t incl = cnt;
+            for (uint32_t off = 1; off < 64; off <<= 1) {
+                const uint32_t y = __shfl_up(incl, off);
+                if (lane >= off) incl += y;
+            }
+            if (lane == 63u) s_wsum[wave] = incl;
+            __syncthreads();
+            uint32_t before = 0, H = 0;
+            for (uint32_t w = 0; w < kBlock / 64; ++w) {
+                before += w < wave ? s_wsum[w] : 0u;
+                H += s_wsum[w];
+            }
+            s_ex[tid] = before + incl - cnt;
+            if (tid == 0) s_ex[kBlock] = H;
+            __syncthreads();
+            for (uint32_t e = tid; e < H; e += kBlock) {
+                uint32_t lo = 0, hi = kBlock;  // s_ex[lo] <= e < s_ex[hi]
+                while (hi - lo > 1) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if (s_ex[mid] <= e) lo = mid;
+                    else hi = mid;
+                }
+                const uint64_t lv = s_list[lo];
+                const uint32_t u = (lv & kLiveOne) ? (uint32_t)lv
+                                                   : D.lsrc[(lv >> kLiveCountBits) + (e - s_ex[lo])];
+                dense_visit(D, u, s_inst[lo], s_m + lo, kBlock, next);
+                ++scans;
+            }
+            __syncthreads();  // the batch's LDS is reused
+        }
+        __syncthreads();  // s_mask and s_pair are refilled
+    }
+    block_add3(s_scratch, &D.ctl->size[16 * (L % 3)], pairs, &D.ctl->scans, scans, nullptr, 0);
+}
+
+// The long in-lists level L met, one chunk per wave.
+__global__ void __launch_bounds__(kBlock) k_dense_heavy(DenseArgs D, uint32_t L) {
+    __shared__ uint64_t s_m[kBlock / 64][kDenseWords];
+    const uint32_t lane = lane_id(), wave = threadIdx.x / 64;
+    const uint64_t total = D.ctl->hsize[16 * (L % 2)];
+    const uint64_t nh = total < D.heavy_cap ? total : D.heavy_cap;
+    uint64_t *next = D.dirty[(L + 1) & 1];
+    const uint64_t waves = (uint64_t)gridDim.x * (kBlock / 64);
+    for (uint64_t h = blockIdx.x * (uint64_t)(kBlock / 64) + wave; h < nh; h += waves) {
+        const uint64_t it = D.heavy[h];
+        const uint32_t q = (uint32_t)(it >> 32), v = q / kPairStride, i = q % kPairStride;
+        const uint64_t live = D.prec[2 * (uint64_t)q + 1];
+        const uint32_t e = (uint32_t)it * 64 + lane;
+        __builtin_amdgcn_wave_barrier();
+        if (lane < D.nw)
+            s_m[wave][lane] =
+                load_relaxed(D.V + ((uint64_t)v * D.ell + i) * D.nw + lane);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (e < live_count(live))
+            dense_visit(D, D.lsrc[(live >> kLiveCountBits) + e], i, s_m[wave], 1, next);
+    }
+}
+
+// After the search, one wave per node: the visits of its pairs, their counts
+// into the state words, and its records, as far as there is room.  kFirst
+// false: only the records again, in a larger buffer (a pair's count before the
+// window reads the same before and after its update).
+template <bool kFirst> __global__ void __launch_bounds__(kBlock) k_dense_finish(DenseArgs D) {
+    __shared__ uint64_t s_scratch[3 * (kBlock / 64)];
+    __shared__ uint32_t s_sum[kBlock / 64];
+    __shared__ unsigned long long s_base;
+    constexpr uint32_t kPer = 8;  // nodes per wave between reservations
+    const uint32_t lane = lane_id(), wave = threadIdx.x / 64;
+    uint32_t visits = 0, again = 0;
+    const uint64_t step = (uint64_t)gridDim.x * (kBlock / 64) * kPer;
+    for (uint64_t v0 = (uint64_t)blockIdx.x * (kBlock / 64) * kPer; v0 < D.n; v0 += step) {
+        uint32_t mine = 0, cs[kPer];  // records of this lane's pairs
+#pragma unroll
+        for (uint32_t r = 0; r < kPer; ++r) {
+            const uint64_t v = v0 + wave * kPer + r;
+            cs[r] = 0;
+            if (v >= D.n || lane >= D.ell) continue;
+            const uint64_t q = v * kPairStride + lane;
+            const uint64_t state = D.prec[2 * q], live = D.prec[2 * q + 1];
+            const bool want = D.want[v] != 0;
+            if (dense_idle(state, live, want, D.win, D.k)) continue;
+            const uint64_t *row = D.V + (v * D.ell + lane) * D.nw;
+            uint32_t c = 0;
+            for (uint32_t w = 0; w < D.nw; ++w) c += (uint32_t)__popcll(row[w]);
+            if (!c) continue;
+            if (kFirst)  // c <= 512: fits the arrival field
+                D.prec[2 * q] = ((uint64_t)D.win << 32) | ((uint64_t)c << 40) |
+                                ((uint64_t)prior_count(state, D.win) << 52);
+            visits += c;
+            again += c - 1;
+            if (want) {
+                cs[r] = c;
+                mine += c;
+            }
+        }
+        uint32_t incl = mine;
+        for (uint32_t off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(incl, off);
+            if (lane >= off) incl += y;
+        }
+        __syncthreads();  // the previous round's s_sum and s_base have been read
+        if (lane == 63u) s_sum[wave] = incl;
+        __syncthreads();
+        uint32_t before = 0, tot = 0;
+        for (uint32_t w = 0; w < kBlock / 64; ++w) {
+            before += w < wave ? s_sum[w] : 0u;
+            tot += s_sum[w];
+        }
+        if (threadIdx.x == 0)
+            s_base = tot ? atomicAdd(&D.ctl->records, (unsigned long long)tot) : 0;
+        __syncthreads();
+        uint64_t at = s_base + before + incl - mine;
+        for (uint32_t r = 0; r < kPer; ++r) {
+            if (!cs[r]) continue;
+            const uint64_t v = v0 + wave * kPer + r;
+            const uint64_t *row = D.V + (v * D.ell + lane) * D.nw;
+            for (uint32_t w = 0; w < D.nw; ++w)
+                for (uint64_t x = row[w]; x; x &= x - 1) {
+                    const uint32_t s = 64 * w + (uint32_t)__ffsll((long long)x) - 1;
+                    if (at < D.rec_cap)
+                        D.rec[at] = (v << 32) | D.sources[lane * 64 * D.nw + s];
+                    ++at;
+                }
+        }
+    }
+    if (kFirst)
+        block_add3(s_scratch, &D.ctl->visits, visits, &D.ctl->hinserts, again, nullptr, 0);
+}
+
 // Start of a window (or of its redo): clear the per-window fields and set
 // the running counters to their values at the window start.
 __global__ void k_ctl_begin(Ctl *ctl, unsigned long long visits, unsigned long long scans,
@@ -1393,6 +1707,7 @@ struct Capacity {
     uint64_t rec, front, hash;
     uint64_t hash_min;    // least hash-set size of a window (raised after an overflow)
     uint32_t first_span;  // buckets of window 0 (1 after an optimistic one overflowed)
+    bool dense;           // an optimistic first window overflowed its hash set
 };
 
 }  // namespace
@@ -1435,7 +1750,7 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
     // reallocated by windows that need more.
     uint64_t hset_size = std::min<uint64_t>(cap.hash, 1ull << 29);
     uint64_t *hset = A.alloc<uint64_t>(hset_size);
-    bool hset_clean = false;  // every slot kNone or a tagged key
+    uint64_t hset_clean = 0;  // slots [0, hset_clean): kNone or a tagged key
     const bool tagged = npairs <= (1ull << 28);  // pair ids leave room for a window tag
     uint64_t *snap = nullptr;  // pair records at the start of a guarded window
     uint64_t *sort_key = nullptr, *sort_live = nullptr, sort_cap = 0;  // sort_frontier
@@ -1448,7 +1763,7 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
     int pair_bits = 1;
     while (pair_bits < 32 && (1ull << pair_bits) < npairs) ++pair_bits;
     uint32_t levels_run = 0;
-    uint64_t windows_done = 0, prev_hash = 0, prev_nw = 0;
+    uint64_t windows_done = 0, prev_hash = 0, prev_nw = 0, want_visits = 0;
     const bool debug = std::getenv("SKIM_DEBUG") != nullptr;
     const bool debug2 = debug && std::atoi(std::getenv("SKIM_DEBUG")) > 1;
     const auto t_start = std::chrono::steady_clock::now();
@@ -1473,6 +1788,54 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
         capacity = nc;
     };
     Ctl h;
+    // Buffers of the dense windows, kept from one to the next.
+    DenseArgs D{};
+    uint64_t dense_words = 0;  // V's size in 64-bit words
+    uint32_t *dense_count = nullptr;
+    // Whether the window of sources [ws, we) can be a dense one: at most
+    // kDenseWords words per pair, and room for V (a sixth of the device's
+    // memory at most, and none if the device refuses).  Fills D.
+    auto dense_setup = [&](uint64_t ws, uint64_t we) -> bool {
+        if (we - ws > (uint64_t)ell * 64 * kDenseWords) return false;
+        if (!dense_count) dense_count = A.alloc<uint32_t>(64 * 32);
+        fill_u32(dense_count, 0, 64 * 32, s);
+        k_dense_count<<<grid_for(we - ws, kBlock, 256), kBlock, 0, s>>>(sources, ws, we,
+                                                                        dense_count);
+        SKIM_LAUNCH_CHECK();
+        uint32_t c[64 * 32], most = 0;
+        read_back(c, dense_count, sizeof c, s);
+        for (uint32_t i = 0; i < ell; ++i) most = std::max(most, c[32 * i]);
+        const uint32_t nw = (most + 63) / 64;
+        if (nw > kDenseWords || nw == 0) return false;
+        const uint64_t words = (uint64_t)n * ell * nw;
+        size_t fr = 0, tot = 0;
+        if (hipMemGetInfo(&fr, &tot) != hipSuccess || words * 8 > tot / 6) return false;
+        try {
+            if (!D.haslive) {
+                D.dirty[0] = A.alloc<uint64_t>(n);
+                D.dirty[1] = A.alloc<uint64_t>(n);
+                D.sources = A.alloc<uint32_t>(64ull * 64 * kDenseWords);
+                // a level meets every pair at most once: a list of c > 32 entries
+                // makes at most c / 64 + 1 < 3 c / 64 chunks
+                D.heavy_cap = live.maxlen > kDenseHeavy ? 3 * (live.nlive / 64) + 1 : 0;
+                if (D.heavy_cap) D.heavy = A.alloc<uint64_t>(D.heavy_cap);
+                D.haslive = A.alloc<uint64_t>(n);
+            }
+            if (words > dense_words) {
+                if (D.V) A.release(D.V);
+                D.V = nullptr;
+                dense_words = 0;
+                D.V = A.alloc<uint64_t>(words);
+                dense_words = words;
+            }
+        } catch (const Fail &) {
+            return false;
+        }
+        D.nw = nw;
+        return true;
+    };
+    bool dense_deep = false;   // a dense window took more than kDenseDeep levels
+    double expect = cap.dense ? kDenseVisits : 0.0;  // visits per pair expected of the next window
     // Window w covers buckets [bb, be): bucket 0 alone; then, unless that
     // was heavy, as many buckets as keep the arrivals per pair below k; then
     // sh.window_span buckets at a time, or one (twofold) after a window whose
@@ -1506,29 +1869,82 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
         // overflow there costs one redo of the window with more room instead
         // of a restart of all windows.  The first window restores the pair
         // records from scratch, the others from a copy taken here.
-        const bool guard = w == 0 || span_next == 1;
+        const bool dense = expect >= kDenseVisits && !dense_deep && !fwd && dense_setup(ws, we);
+        const bool guard = !dense && (w == 0 || span_next == 1);
         if (guard && w > 0) {
             if (!snap) snap = A.alloc<uint64_t>(2 * npairs);
             SKIM_HIP(hipMemcpyAsync(snap, prec, 2 * npairs * sizeof(uint64_t),
                                     hipMemcpyDeviceToDevice, s));
         }
         const Ctl base = h;  // counters at the window start
-        for (int redo = 0;; ++redo) {
+        if (dense) {
+            D.prec = prec;
+            D.lsrc = live.adj;
+            D.want = want;
+            D.n = n;
+            D.ell = ell;
+            D.k = k;
+            D.win = w;
+            D.count = dense_count;
+            D.ctl = ctl;
+            k_ctl_begin<<<1, 1, 0, s>>>(ctl, base.visits, base.scans, base.records);
+            fill_u32(dense_count, 0, 64 * 32, s);
+            k_dense_init<<<grid_for(n, kBlock / 64, 16384), kBlock, 0, s>>>(D);
+            SKIM_LAUNCH_CHECK();
+            {
+                LaunchTimer t("k_seed_window", s);
+                k_dense_seed<<<grid_for(nw, kBlock, 1024), kBlock, 0, s>>>(D, sources, ws, we);
+            }
+            SKIM_LAUNCH_CHECK();
+            const uint32_t per = std::max<uint32_t>(1, std::min<uint32_t>(kDenseNodes, n / 2048));
+            uint32_t L = 0;
+            do {
+                for (int j = 0; j < kDenseBatch; ++j, ++L) {
+                    LaunchTimer t("k_expand", s);
+                    k_dense_level<<<grid_for(n, per, 8192), kBlock, 0, s>>>(D, L, per);
+                    SKIM_LAUNCH_CHECK();
+                    if (D.heavy_cap) {
+                        k_dense_heavy<<<1024, kBlock, 0, s>>>(D, L);
+                        SKIM_LAUNCH_CHECK();
+                    }
+                }
+                read_back(&h, ctl, sizeof h, s);
+            } while (h.size[16 * ((L - 1) % 3)] != 0);  // the last level expanded pairs
+            levels_run = L;
+            dense_deep = L > kDenseDeep;
+            D.rec = rec;
+            D.rec_cap = rec_cap;
+            k_dense_finish<true><<<grid_for(n, kBlock / 8, 8192), kBlock, 0, s>>>(D);
+            SKIM_LAUNCH_CHECK();
+            read_back(&h, ctl, sizeof h, s);
+            if (h.records > rec_cap) {
+                grow_u64(rec, rec_cap, base.records, h.records);
+                D.rec = rec;
+                D.rec_cap = rec_cap;
+                fill_u64((uint64_t *)&ctl->records, base.records, 1, s);
+                k_dense_finish<false><<<grid_for(n, kBlock / 8, 8192), kBlock, 0, s>>>(D);
+                SKIM_LAUNCH_CHECK();
+            }
+        }
+        for (int redo = 0; !dense; ++redo) {
             uint32_t logcap = 0;
             while ((1ull << logcap) < hsize) ++logcap;
             if (hsize > hset_size) {
                 if (hset) A.release(hset);
                 hset = A.alloc<uint64_t>(hsize);
                 hset_size = hsize;
-                hset_clean = false;
+                hset_clean = 0;
             }
-            // tagged keys of earlier windows are free slots: clear only a
-            // set that never was (or a window being redone)
-            if (!tagged) {
+            // tagged keys of earlier windows are free slots: clear only the
+            // slots that never were (or all of a window's being redone)
+            if (!tagged || redo > 0) {
                 fill_u64(hset, kNone, hsize, s);
-            } else if (!hset_clean || redo > 0) {
-                fill_u64(hset, kNone, hset_size, s);
-                hset_clean = true;
+                hset_clean = std::max(hset_clean, hsize);
+            } else if (hset_clean < hsize) {
+                // small sets whole, large ones as far as they are used
+                const uint64_t to = std::min(hset_size, std::max<uint64_t>(hsize, 1ull << 22));
+                fill_u64(hset + hset_clean, kNone, to - hset_clean, s);
+                hset_clean = to;
             }
             k_ctl_begin<<<1, 1, 0, s>>>(ctl, base.visits, base.scans, base.records);
             SKIM_LAUNCH_CHECK();
@@ -1563,6 +1979,16 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
                 if (debug2)
                     std::fprintf(stderr, "skim window %u level %u: frontier %llu hashed %llu\n", w,
                                  L, (unsigned long long)f, h.hinserts);
+                // The optimistic first window is given up before it fills its
+                // hash set (a full set costs every insert all its probes: 15
+                // ms on R-MAT of 2^18 nodes): its frontier grew more than
+                // fourfold over the last level, and the same growth again
+                // would outrun the set.
+                if (w == 0 && span > 1 && f_prev && f > 4 * f_prev && f > kOptimistic &&
+                    (double)f * ((double)f / (double)f_prev) > 0.4 * (double)hsize) {
+                    overflow = kOvfHash;
+                    break;
+                }
                 // Room for the next level: the frontier and the records are grown
                 // to kGrow times the frontier, the hash set (rehashed) once it is
                 // 40% full.  A level that still overflows is redone with the
@@ -1587,7 +2013,7 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
                     SKIM_LAUNCH_CHECK();
                     A.release(hset);
                     hset = nt;  // cleared, then only this window's keys
-                    hset_size = hsize = ns;
+                    hset_size = hsize = hset_clean = ns;
                     logcap = nlog;
                     if (debug)
                         std::fprintf(stderr, "skim window %u: hash set grown to %llu\n", w,
@@ -1760,6 +2186,8 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
             const bool heavy =
                 per_pair > kHeavy * (merged ? std::max(1.0, span / 2.0) : 1.0);
             uint32_t next = heavy ? 1u : sh.window_span;
+            // until pruning takes hold, a pair's arrivals grow with the sources
+            expect = heavy || dense ? per_pair : 0.0;
             merged = false;
             if (w == 0 && span == 1 && !heavy) {
                 // Bucket 0 gave each visited pair per_pair arrivals; with no
@@ -1778,13 +2206,19 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
             }
             prev_visits = h.visits;
             span_next = next;
+            if (bb + span < W && nw)
+                expect *= (double)(wb[std::min(bb + span + next, W)] - wb[bb + span]) / (double)nw;
         }
         if (debug)
             std::fprintf(stderr, "skim window %u: sources %llu visits-so-far %llu hashed %llu "
                                  "table %llu levels %u records %llu at %.1f ms\n",
                          w, (unsigned long long)nw, h.visits, h.hinserts,
                          (unsigned long long)hsize, levels_run, h.records, elapsed_ms());
-        if (!last) {
+        // `want` may lag (a node then records more than it needs): windows
+        // with less than a visit per node fill few nodes and leave the pass
+        // over all pair records to a later one
+        if (!last && h.visits - want_visits >= n) {
+            want_visits = h.visits;
             fill_u64((uint64_t *)&ctl->full, 0, 1, s);
             k_want<<<grid_for((uint64_t)n * 8, kBlock, 8192), kBlock, 0, s>>>(prec, n, k, want,
                                                                               ctl);
@@ -1803,6 +2237,7 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
         A.release(flive[j]);
     }
     if (hset) A.release(hset);
+    if (D.V) A.release(D.V);
     if (pull_key) A.release(pull_key);
     if (fidx) {
         A.release(fidx);
@@ -1912,7 +2347,7 @@ static void build_sketches(const skim_graph *g, uint32_t ell, uint32_t k, uint64
     Capacity cap{std::max<uint64_t>(1ull << 20, 3 * (uint64_t)n * k),
                  std::max<uint64_t>(1ull << 20, 3 * biggest),
                  next_pow2(std::max<uint64_t>(1ull << 16, 8 * bucket_max)), 1ull << 16,
-                 shapes.first_span};
+                 shapes.first_span, false};
     uint32_t retry_flags = 0;
     int attempt = 0;
     for (;; ++attempt) {
@@ -1932,6 +2367,7 @@ static void build_sketches(const skim_graph *g, uint32_t ell, uint32_t k, uint64
             }
             if (r.flags & kOvfFirst) {
                 cap.first_span = 1;  // the wide first window was too much for this graph
+                cap.dense = (r.flags & kOvfHash) != 0;
             } else {
                 if (r.flags & kOvfRecords) cap.rec *= 2;
                 if (r.flags & kOvfSpill) cap.front *= 2;

@@ -81,6 +81,21 @@ template <int G> __device__ __forceinline__ uint64_t group_min_u64(uint64_t x) {
     return ((uint64_t)mh << 32) | ml;
 }
 
+// 64 x 64 bit transpose across the wave: bit j of lane i's result is bit i of
+// lane j's argument.
+template <int kStep> __device__ __forceinline__ uint64_t transpose_step(uint64_t x, uint64_t m) {
+    const uint64_t y = lane_xor64<kStep>(x);
+    return (__lane_id() & kStep) ? ((y >> kStep) & m) | (x & ~m) : (x & m) | ((y & m) << kStep);
+}
+__device__ __forceinline__ uint64_t wave_transpose(uint64_t x) {
+    x = transpose_step<32>(x, 0x00000000FFFFFFFFull);
+    x = transpose_step<16>(x, 0x0000FFFF0000FFFFull);
+    x = transpose_step<8>(x, 0x00FF00FF00FF00FFull);
+    x = transpose_step<4>(x, 0x0F0F0F0F0F0F0F0Full);
+    x = transpose_step<2>(x, 0x3333333333333333ull);
+    return transpose_step<1>(x, 0x5555555555555555ull);
+}
+
 // One compare-exchange step of a sorting network between lanes: the lane
 // keeps the smaller (low) or the larger of its own value and its partner's.
 __device__ __forceinline__ uint64_t keep_of(uint64_t own, uint64_t other, bool low) {

@@ -220,3 +220,31 @@ def test_chung_lu_1m_full_parity(chung_lu_1m, shape):
         sk.skim_set_build_params(None)
     log(f"gpu work {work}")
     check_digests(golden("chung_lu_1m"), g, R, S, E)
+
+
+@pytest.mark.parametrize("n,deg,denom,ell,k,hub", [
+    (300, 6, 1, 64, 256, False),     # one word to eight, every pair reaches every source
+    (2000, 8, 2, 64, 32, True),      # a hub: in-lists cut into chunks, two and more
+    (2000, 8, 2, 7, 64, False),      # few instances
+    (9001, 8, 2, 1, 64, False),      # one instance
+    (20000, 6, 2, 33, 16, True),     # several nodes per workgroup and round
+])
+def test_dense_windows(oracle_lib, n, deg, denom, ell, k, hub):
+    """Graphs whose optimistic first window overflows: the windows after it
+    keep their sources as bit sets per pair."""
+    rng = np.random.default_rng(n + k)
+    e = rng.integers(0, n, size=(deg * n, 2))
+    if hub:
+        e = np.concatenate([e, np.stack([np.arange(1, n), np.zeros(n - 1, dtype=np.int64)], 1)])
+    e = np.unique(e, axis=0)
+    e = e[e[:, 0] != e[:, 1]]
+    g = from_edges(n, e[:, 0], e[:, 1], 0xFFFFFFFF // denom)
+    log(f"dense windows n={n} m={g.m} ell={ell} k={k} hub={hub}")
+    R, S, E, work, _ = gpu_build(g, ell, k, 5)
+    assert work["restart_flags"] & 16, "the first window was meant to overflow"
+    wr, ws, _ = oracle_lib.build_alg2(g, 5, ell, k)
+    assert np.array_equal(S, ws)
+    assert np.array_equal(R, wr)
+    assert np.array_equal(E, oracle_lib.estimates(wr, ws, k, ell))
+    R2, _, _, _, _ = gpu_build(g, ell, k, 5)
+    assert np.array_equal(R, R2)
