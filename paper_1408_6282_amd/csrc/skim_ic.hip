@@ -3,28 +3,30 @@
 // permutation ranks") in the limit of infinitely many instances.
 //
 // Positions t = 1 .. k n come in k chunks of n; each chunk holds every node
-// once, in the order of a SplitMix64 hash (a rocPRIM segmented radix sort per
-// chunk).  Every position has an instance of its own, so the sketch of u is
-// the k smallest positions t whose node v_t u reaches in instance t, and the
-// influence estimate is n (k - 1) / (T - 1) with T the k-th smallest.  Nothing
-// prunes a search here (an instance has one source), so:
-//  * one thread per position runs the complete reverse search from v_t over
-//    the in-edges whose coin in instance t is live (coins on the fly from a
-//    per-edge SplitMix64 stream), deduplicating with a visited bitmap of its
-//    own and clearing only the bits it set; a search that grows beyond
-//    kIcLight nodes is handed to a workgroup (the heavy searches of hubs
-//    would otherwise serialise in one thread);
-//  * a first pass counts the nodes each search reaches, a scan gives every
-//    position its record range, and a second pass writes the records
-//    (node << 32 | t) there, so no record needs an atomic;
+// once, in the order of a SplitMix64 hash (one rocPRIM radix sort of all
+// chunks, the chunk leading the key).  Every position has an instance of its
+// own, so the sketch of u is the k smallest positions t whose node v_t u reaches
+// in instance t, and the influence estimate is n (k - 1) / (T - 1) with T the
+// k-th smallest.  Nothing prunes a search here (an instance has one source),
+// so:
+//  * a wave runs the complete reverse searches of 12 positions together, over
+//    the in-edges whose coin in the position's instance is live (coins on the
+//    fly from a per-edge SplitMix64 stream), its queue and its visited set in
+//    LDS (k_ic_wave); a wave whose searches outgrow them hands its positions on
+//    to a wave each, and a search that outgrows that to a workgroup
+//    (k_ic_heavy);
+//  * a search's nodes are recorded (node, t), but a node that already
+//    has k records from earlier chunks needs no more: the chunks go in phases
+//    of fourfold length, and each node keeps the phase in which it had k;
 //  * the records are radix-sorted; every node holds at least k of them (it
 //    reaches itself in every chunk) and keeps its first k.
 #include "skim_internal.h"
+#include "skim_wave.h"
 
 #include <rocprim/device/device_radix_sort.hpp>
-#include <rocprim/device/device_segmented_radix_sort.hpp>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace skim {
 
@@ -32,53 +34,89 @@ namespace {
 
 constexpr uint64_t kIcChunk = 1ull << 63;                  // counters of the chunk hashes
 constexpr uint64_t kIcEdge = (1ull << 63) | (1ull << 62);  // counters of the per-edge streams
-constexpr int kIcBlock = 256;
-constexpr uint64_t kIcStateBudget = 8ull << 30;            // bytes of per-thread search state
-constexpr uint32_t kIcLight = 1024;   // a thread's search hands over beyond this many nodes
 constexpr int kIcHeavyBlock = 1024;   // one workgroup per handed-over search
 constexpr uint64_t kIcHeavyBudget = 2ull << 30;            // bytes of per-workgroup state
 constexpr uint64_t kIcRecordCap = 1ull << 28;  // records of the single pass (2 GiB)
+// A wave's searches: positions at a time, queue entries (all of them stay until
+// the searches end) and visited-set slots.  Measured on the 20,000-node graph
+// (k = 64), whole build: 12 positions 2.54 ms, 16 (512 entries) 2.79, 24 (768,
+// 2048 slots) 3.14, 8 (320, 512) 2.76.
+constexpr uint32_t kIcWave = 12, kIcQueue = 384, kIcSlots = 1024;
+constexpr uint32_t kIcStage = 128;    // records staged per wave (256: fewer waves fit, 3.10 ms not 2.79)
+constexpr uint32_t kIcAhead = 4;      // rounds of 64 in-edges loaded at once
+constexpr uint32_t kIcOne = 1024;     // queue entries of a wave with one position
+constexpr uint32_t kIcNodeBits = 26;  // node ids (64 n < 2^32)
+constexpr uint32_t kIcOpen = 0xFFu;   // phase of a node with less than k records
 
-// Coin of edge (u -> w) in the instance of position t (>= 1): the high
-// (t - 1 even) or low (t - 1 odd) half of output floor((t - 1) / 2) of the
-// stream seeded with SM(seed, kIcEdge + u n + w).
-__device__ __forceinline__ bool ic_live(uint64_t seed, uint32_t n, uint32_t u, uint32_t w,
-                                        uint32_t t, uint32_t thr) {
-    const uint64_t edge_seed = sm_at(seed, kIcEdge + (uint64_t)u * n + w);
-    const uint64_t h = sm_at(edge_seed, (t - 1) / 2);
-    const uint32_t coin = ((t - 1) & 1u) == 0 ? (uint32_t)(h >> 32) : (uint32_t)h;
-    return coin <= thr;
+// An in-edge (u -> w): its source, its threshold and the seed of its coin
+// stream, SM(seed, kIcEdge + u n + w).
+struct alignas(16) IcEdge {
+    uint64_t stream;
+    uint32_t src, thr;
+};
+
+// Its coin in the instance of position t (>= 1): the high (t - 1 even) or low
+// (t - 1 odd) half of output floor((t - 1) / 2) of that stream.  `step` is
+// ic_step(t), the stream position times the SplitMix64 increment.
+__device__ __forceinline__ uint64_t ic_step(uint32_t t) {
+    return ((uint64_t)((t - 1) / 2) + 1) * kGolden;
+}
+__device__ __forceinline__ bool ic_live(const IcEdge &e, uint64_t step, uint32_t t) {
+    const uint64_t h = sm_mix(e.stream + step);
+    return (((t - 1) & 1u) == 0 ? (uint32_t)(h >> 32) : (uint32_t)h) <= e.thr;
 }
 
-__global__ void k_ic_indeg(const uint32_t *col, uint64_t m, uint32_t *indeg) {
+// In-edges grouped by head: the edges radix-sorted by head (key head << 32 |
+// source, value the threshold), then their coin streams, and the heads' offsets
+// from the places where the head changes.  (Counting and placing by an atomic
+// per edge took 175 us on 320,000 edges, most of it queueing on the hubs.)
+__global__ void k_ic_keys(const uint32_t *esrc, const uint32_t *col, uint64_t m, uint64_t *key) {
     for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e < m;
          e += (uint64_t)gridDim.x * blockDim.x)
-        atomicAdd(indeg + col[e], 1u);
+        key[e] = (uint64_t)col[e] << 32 | esrc[e];
 }
-
-// In-edges grouped by head: source and threshold (order within a head is
-// immaterial: a search's reached set does not depend on it).
-__global__ void k_ic_rfill(const uint32_t *esrc, const uint32_t *col, const uint32_t *thr,
-                           uint64_t m, const uint64_t *rptr, uint32_t *cursor, uint32_t *rsrc,
-                           uint32_t *rthr) {
-    for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e < m;
-         e += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t w = col[e];
-        const uint64_t at = rptr[w] + atomicAdd(cursor + w, 1u);
-        rsrc[at] = esrc[e];
-        rthr[at] = thr[e];
+__global__ void k_ic_rfill(const uint64_t *key, const uint32_t *thr, uint64_t m, uint32_t n,
+                           uint64_t seed, uint64_t *rptr, IcEdge *redge) {
+    for (uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; t < m;
+         t += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t w = (uint32_t)(key[t] >> 32), u = (uint32_t)key[t];
+        redge[t] = {sm_at(seed, kIcEdge + (uint64_t)u * n + w), u, thr[t]};
+        // rptr of this head and of the heads without in-edges before it
+        for (uint32_t x = t ? (uint32_t)(key[t - 1] >> 32) + 1 : 0; x <= w; ++x) rptr[x] = t;
+        if (t + 1 == m)
+            for (uint32_t x = w + 1; x <= n; ++x) rptr[x] = m;
     }
 }
 
-__global__ void k_ic_hash(uint32_t n, uint32_t k, uint64_t seed, uint64_t *keys, uint32_t *vals,
-                          uint32_t *offs) {
+// Keys of the structured permutation: the chunk in the leading bits, then the
+// leading bits of h_c(v); one sort orders every chunk.
+__global__ void k_ic_hash(uint32_t n, uint32_t k, uint32_t chunk_bits, uint64_t seed,
+                          uint64_t *keys, uint32_t *vals) {
     const uint64_t total = (uint64_t)n * k;
     for (uint64_t x = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; x < total;
          x += (uint64_t)gridDim.x * blockDim.x) {
-        keys[x] = sm_at(seed, kIcChunk + x);  // x = c n + v
-        vals[x] = (uint32_t)(x % n);
-        if (x % n == 0) offs[x / n] = (uint32_t)x;
-        if (x == 0) offs[k] = (uint32_t)total;
+        keys[x] = (x / n) << (64 - chunk_bits) | sm_at(seed, kIcChunk + x) >> chunk_bits;
+        vals[x] = (uint32_t)(x % n);  // x = c n + v
+    }
+}
+
+// The hash's last chunk_bits bits are not in the keys: runs of equal keys (about
+// n^2 k / 2^(65 - chunk_bits) pairs) are put in order of the whole hash by the
+// thread at their start.
+__global__ void k_ic_ties(const uint64_t *keys, uint32_t *vals, uint32_t n, uint64_t total,
+                          uint64_t seed) {
+    for (uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; t + 1 < total;
+         t += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t key = keys[t];
+        if (keys[t + 1] != key || (t > 0 && keys[t - 1] == key)) continue;
+        const uint64_t base = kIcChunk + t / n * n;  // the run lies within a chunk
+        for (uint64_t i = t + 1; i < total && keys[i] == key; ++i) {
+            const uint32_t v = vals[i];
+            uint64_t j = i;
+            for (; j > t && sm_at(seed, base + vals[j - 1]) > sm_at(seed, base + v); --j)
+                vals[j] = vals[j - 1];
+            vals[j] = v;
+        }
     }
 }
 
@@ -86,16 +124,19 @@ struct IcArgs {
     uint32_t n, k;
     uint64_t seed;
     const uint64_t *rptr;
-    const uint32_t *rsrc, *rthr;
+    const IcEdge *redge;
     const uint32_t *node_at;  // [k n] node at position t = index + 1
     uint32_t *counts;         // [k n] pass 0 out
     const uint64_t *offsets;  // [k n + 1] pass 1 in
     uint64_t *records;        // pass 1 out (pass 2: appended, up to rcap)
     unsigned long long *rcount;  // pass 2: records appended
     uint64_t rcap;
+    uint32_t tbits;           // a record is node << tbits | t
     uint32_t *ovf;            // pass 2: the records outgrew rcap
-    uint32_t *bitmaps;        // [threads][(n + 31) / 32]
-    uint32_t *queues;         // [threads][kIcLight]
+    uint32_t *had;            // [n] pass 2: records of a node, counted up to k
+    uint8_t *full;            // [n] pass 2: phase in which it had k (kIcOpen: none yet)
+    uint32_t *more;           // positions handed to a wave each
+    unsigned long long *nmore;
     uint32_t *heavy;          // positions handed to the workgroup search
     unsigned long long *nheavy;
     uint32_t *hbitmaps;       // [workgroups][(n + 31) / 32]
@@ -109,154 +150,195 @@ template <class T> __device__ __forceinline__ void ic_st(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Inclusive prefix sum over the wave's lanes, and the lane whose range holds
-// flat position j of the lanes' items laid end to end (binary lifting).
-__device__ __forceinline__ uint32_t ic_wave_incl(uint32_t v, uint32_t lane) {
-#pragma unroll
-    for (uint32_t off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(v, off);
-        if (lane >= off) v += y;
-    }
-    return v;
-}
-__device__ __forceinline__ uint32_t ic_wave_owner(uint32_t incl, uint32_t j) {
-    uint32_t r = 0;
-#pragma unroll
-    for (uint32_t step = 32; step > 0; step >>= 1) {
-        const uint32_t v = (uint32_t)__shfl((int)incl, (int)(r + step - 1));
-        if (v <= j) r += step;
-    }
-    return r & 63u;
+// LDS accesses of one wave, in program order for the compiler too.
+__device__ __forceinline__ void ic_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One search per position, one position per thread.  The 64 searches of a
-// wave advance together: at each step every lane takes the next node of its
-// own queue, and the wave lays those nodes' in-edges end to end and tests
-// them 64 at a time, so a lane whose node is a hub (thousands of in-edges,
-// each a coin) does not hold the other 63.  A node that passes its coin and
-// is new to its search (an atomic OR on that search's bitmap) is appended
-// to its queue at its rank among that search's new nodes of the round.  A
-// search that would reach more than kIcLight nodes stops, clears what it
-// marked and hands the position to the workgroup search (first pass:
-// appended to the heavy list; second pass: skipped, its count being above
-// kIcLight).  Pass 2 is the single pass used when the records fit a buffer
-// sized up front: the heavy list as in pass 0, and every other search's
-// records appended at a place reserved once per wave.
-template <int kPass>
-__global__ void __launch_bounds__(kIcBlock) k_ic_search(IcArgs A) {
-    const uint64_t tid = blockIdx.x * (uint64_t)kIcBlock + threadIdx.x;
-    const uint64_t threads = (uint64_t)gridDim.x * kIcBlock;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t wave0 = tid - lane;  // thread id of the wave's lane 0
-    const uint32_t words = (A.n + 31) / 32;
-    uint32_t *bm = A.bitmaps + tid * words;
-    uint32_t *Q = A.queues + tid * kIcLight;
-    const uint64_t total = (uint64_t)A.n * A.k;
-    for (uint64_t x0 = 0; x0 < total; x0 += threads) {
-        const uint64_t x = x0 + tid;
-        const bool mine = x < total && !(kPass == 1 && A.counts[x] > kIcLight);
-        const uint32_t t = (uint32_t)(x + 1);
-        bool heavy = false;
-        uint32_t cnt = 0, head = 0;
-        if (mine) {
-            const uint32_t v = A.node_at[x];
-            Q[0] = v;
-            atomicOr(bm + (v >> 5), 1u << (v & 31));
-            cnt = 1;
+// Phase of position index x: chunk 0 is phase 0, chunks 4^(p-1) .. 4^p - 1 are
+// phase p (of twofold length the phases left the chip half empty at their ends
+// more often than the fewer records paid for).
+__device__ __forceinline__ uint32_t ic_phase(uint64_t x, uint32_t n) {
+    const uint32_t c = (uint32_t)(x / n);
+    return c ? (33u - (uint32_t)__clz((int)c)) / 2 : 0u;
+}
+
+// One wave, the searches of up to kB positions at once: positions x0 + first ..
+// of an index range, or of a list.  All visited (search, node) entries stand in
+// one queue in LDS, in the order found; a step takes the next 64 entries,
+// whichever searches they belong to, lays their nodes' in-edges end to end and
+// tests 64 at a time, so neither a search of a thousand nodes nor a hub's
+// thousands of in-edges hold the other lanes.  An entry new to the wave's
+// visited set (an LDS hash set of entries, at most half full) is appended.
+//
+// What bounds it: dependent LDS and L2 accesses per step, and the coins (213 M
+// of them on the graph below).  With a thread per position, taking one node per
+// step, and visited bitmaps in global memory, a wave took as many steps as its
+// largest search had nodes and two device atomics per visited node: 3.3 ms on
+// the 20,000-node weighted-cascade graph (k = 64, 1.28 M searches of 12 nodes on
+// average, 200 at most); this 1.5 ms in
+// all phases.
+//
+// kPass 0 counts each search's nodes, 1 writes its records at its offset, 2
+// (the single pass, when the records fit a buffer sized up front) appends the
+// records that can still matter.  A wave whose queue overflows hands its
+// positions on: to `more` (a wave each), or with one position to `heavy`.
+template <int kPass, uint32_t kB, uint32_t kCap, uint32_t kHash>
+__global__ void __launch_bounds__(64) k_ic_wave(IcArgs A, uint64_t x0, uint64_t x1,
+                                                const uint32_t *list) {
+    __shared__ uint32_t F[kCap];   // search << kIcNodeBits | node
+    __shared__ uint32_t H[kHash];  // entries, or all ones
+    __shared__ uint64_t s_off[64], s_step[kB], s_stage[kPass == 2 ? kIcStage : 1];
+    __shared__ uint32_t s_t[kB], s_cnt[kB];
+    __shared__ uint8_t s_rank[64], s_mark[64 * kIcAhead];
+    constexpr uint32_t kMask = (1u << kIcNodeBits) - 1;
+    const uint32_t lane = threadIdx.x;
+    const unsigned long long lower = (1ull << lane) - 1ull;
+    uint32_t staged = 0;  // uniform
+    auto flush = [&]() {
+        ic_sync();
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(A.rcount, (unsigned long long)staged);
+        base = ((unsigned long long)(uint32_t)__shfl((int)(uint32_t)(base >> 32), 0) << 32) |
+               (uint32_t)__shfl((int)(uint32_t)base, 0);
+        if (base + staged <= A.rcap) {
+            for (uint32_t j = lane; j < staged; j += 64) A.records[base + j] = s_stage[j];
+        } else if (lane == 0) {
+            atomicOr(A.ovf, 1u);
         }
-        for (;;) {
-            const bool act = mine && !heavy && head < cnt;
-            if (!__any(act)) break;  // uniform over the wave
-            uint32_t y = 0, d = 0;
+        staged = 0;
+        ic_sync();
+    };
+    for (uint64_t b = x0 + (uint64_t)blockIdx.x * kB; b < x1; b += (uint64_t)gridDim.x * kB) {
+        const uint32_t m = x1 - b < kB ? (uint32_t)(x1 - b) : kB;
+        ic_sync();
+        for (uint32_t j = lane; j < kHash; j += 64) H[j] = 0xFFFFFFFFu;
+        if (lane < m) {
+            const uint32_t x = list ? list[b + lane] : (uint32_t)(b + lane);
+            s_t[lane] = x + 1;
+            s_step[lane] = ic_step(x + 1);
+            s_cnt[lane] = 0;
+            F[lane] = lane << kIcNodeBits | A.node_at[x];
+        }
+        ic_sync();
+        // true if `e` is new to the visited set
+        auto insert = [&](uint32_t e) {
+            uint32_t h = (e * 0x9E3779B1u) >> 16;
+            for (;;) {
+                h &= kHash - 1;
+                const uint32_t old = atomicCAS(&H[h], 0xFFFFFFFFu, e);
+                if (old == 0xFFFFFFFFu) return true;
+                if (old == e) return false;
+                ++h;
+            }
+        };
+        if (lane < m) insert(F[lane]);
+        uint32_t head = 0, tail = m;
+        bool over = false;
+        while (head < tail && !over) {  // uniform
+            const uint32_t T = min(tail - head, 64u);
+            uint32_t d = 0, r = 0;
             uint64_t e0 = 0;
-            if (act) {
-                y = Q[head++];
+            if (lane < T) {
+                const uint32_t f = F[head + lane], y = f & kMask;
+                r = f >> kIcNodeBits;
                 e0 = A.rptr[y];
                 d = (uint32_t)(A.rptr[y + 1] - e0);
             }
-            const uint32_t incl = ic_wave_incl(d, lane);
-            const uint32_t tot = (uint32_t)__shfl((int)incl, 63);
-            const uint32_t mine_first = incl - d;  // this lane's items: [mine_first, incl)
-            for (uint32_t base = 0; base < tot; base += 64) {
-                const uint32_t j = base + lane, r = ic_wave_owner(incl, j);
-                const uint32_t first = (uint32_t)__shfl((int)incl, (int)r) -
-                                       (uint32_t)__shfl((int)d, (int)r);
-                const uint32_t ry = (uint32_t)__shfl((int)y, (int)r);
-                const uint32_t rt = (uint32_t)__shfl((int)t, (int)r);
-                const uint32_t elo = (uint32_t)__shfl((int)(uint32_t)e0, (int)r);
-                const uint32_t ehi = (uint32_t)__shfl((int)(uint32_t)(e0 >> 32), (int)r);
-                const uint32_t rcnt = (uint32_t)__shfl((int)cnt, (int)r);
-                uint32_t u = 0;
-                bool add = false;
-                if (j < tot) {
-                    const uint64_t e = (((uint64_t)ehi << 32) | elo) + (j - first);
-                    u = A.rsrc[e];
-                    if (ic_live(A.seed, A.n, u, ry, rt, A.rthr[e])) {
-                        const uint32_t bit = 1u << (u & 31);
-                        uint32_t *rbm = A.bitmaps + (wave0 + r) * words + (u >> 5);
-                        add = (atomicOr(rbm, bit) & bit) == 0;
+            head += T;
+            const uint32_t incl = wave_scan_sum(d), first = incl - d;
+            const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            s_off[lane] = e0 - first;  // in-edge of flat position j: s_off + j
+            s_rank[lane] = (uint8_t)r;
+            uint32_t carry = 0;  // owner (lane + 1) of the round's first positions
+            for (uint32_t base = 0; base < tot && !over; base += 64 * kIcAhead) {
+                // owners: lanes mark their first position, the last mark at or
+                // before a position owns it
+#pragma unroll
+                for (uint32_t w = 0; w < kIcAhead; ++w) s_mark[64 * w + lane] = 0;
+                ic_sync();
+                if (d && first >= base && first - base < 64 * kIcAhead)
+                    s_mark[first - base] = (uint8_t)(lane + 1);
+                ic_sync();
+                // the round's edges, all loads in flight before the first coin
+                IcEdge e[kIcAhead];
+                uint32_t rr[kIcAhead];
+#pragma unroll
+                for (uint32_t w = 0; w < kIcAhead; ++w) {
+                    if (base + 64 * w >= tot) break;  // uniform
+                    uint32_t o = wave_scan_max(s_mark[64 * w + lane]);
+                    o = o ? o : carry;
+                    carry = (uint32_t)__builtin_amdgcn_readlane((int)o, 63);
+                    const uint32_t j = base + 64 * w + lane;
+                    if (j < tot) {
+                        rr[w] = s_rank[o - 1];
+                        e[w] = A.redge[s_off[o - 1] + j];
                     }
                 }
-                // rank among the same search's new nodes of this round (its
-                // positions are consecutive lanes, from lane first - base on)
-                const unsigned long long m = __ballot(add);
-                const uint32_t lo = first > base ? first - base : 0u;
-                const unsigned long long below =
-                    m & ((1ull << lane) - 1ull) & ~((1ull << lo) - 1ull);
-                if (add) {
-                    const uint32_t idx = rcnt + (uint32_t)__popcll(below);
-                    if (idx < kIcLight) {
-                        A.queues[(wave0 + r) * kIcLight + idx] = u;
-                    } else {  // the search overflows: unmark, it goes to a workgroup
-                        atomicAnd(A.bitmaps + (wave0 + r) * words + (u >> 5),
-                                  ~(1u << (u & 31)));
+#pragma unroll
+                for (uint32_t w = 0; w < kIcAhead; ++w) {
+                    if (base + 64 * w >= tot || over) break;  // uniform
+                    bool add = false;
+                    uint32_t f = 0;
+                    if (base + 64 * w + lane < tot && ic_live(e[w], s_step[rr[w]], s_t[rr[w]])) {
+                        f = rr[w] << kIcNodeBits | e[w].src;
+                        add = insert(f);
                     }
-                }
-                // this lane's search counts its own new nodes of the round
-                if (mine_first < base + 64 && incl > base) {
-                    const uint32_t a = mine_first > base ? mine_first - base : 0u;
-                    const uint32_t b = incl < base + 64 ? incl - base : 64u;
-                    const unsigned long long range =
-                        (b >= 64 ? ~0ull : ((1ull << b) - 1ull)) & ~((1ull << a) - 1ull);
-                    cnt += (uint32_t)__popcll(m & range);
-                }
-            }
-            if (cnt > kIcLight) heavy = true;
-        }
-        if (mine) {
-            const uint32_t kept = cnt < kIcLight ? cnt : kIcLight;
-            if (kPass == 0) {
-                A.counts[x] = heavy ? 0u : cnt;
-            } else if (kPass == 2) {
-                A.counts[x] = 0u;  // a heavy search's count comes from the workgroup pass
-            } else if (!heavy) {
-                uint64_t *out = A.records + A.offsets[x];
-                for (uint32_t j = 0; j < kept; ++j) out[j] = ((uint64_t)Q[j] << 32) | t;
-            }
-            for (uint32_t j = 0; j < kept; ++j) atomicAnd(bm + (Q[j] >> 5), 0u);
-        }
-        if (kPass == 2) {  // every lane of the wave takes part
-            const uint32_t nrec = mine && !heavy ? (cnt < kIcLight ? cnt : kIcLight) : 0u;
-            const uint32_t incl = ic_wave_incl(nrec, lane);
-            const uint32_t wtot = (uint32_t)__shfl((int)incl, 63);
-            unsigned long long base = 0;
-            if (lane == 0 && wtot) base = atomicAdd(A.rcount, (unsigned long long)wtot);
-            base = ((unsigned long long)(uint32_t)__shfl((int)(uint32_t)(base >> 32), 0) << 32) |
-                   (uint32_t)__shfl((int)(uint32_t)base, 0);
-            if (nrec) {
-                if (base + wtot <= A.rcap) {
-                    uint64_t *out = A.records + base + (incl - nrec);
-                    for (uint32_t j = 0; j < nrec; ++j) out[j] = ((uint64_t)Q[j] << 32) | t;
-                } else {
-                    atomicOr(A.ovf, 1u);
+                    const unsigned long long am = __ballot(add);
+                    const uint32_t c = (uint32_t)__popcll(am);
+                    if (tail + c > kCap) {  // the set holds at most kCap + 64 entries
+                        over = true;
+                        break;
+                    }
+                    if (add) F[tail + (uint32_t)__popcll(am & lower)] = f;
+                    tail += c;
                 }
             }
+            ic_sync();
         }
-        if (kPass != 1) {  // every lane of the wave takes part in the reservation
-            const uint64_t slot = wave_reserve(A.nheavy, heavy);
-            if (heavy) A.heavy[slot] = (uint32_t)x;
+        if (over) {
+            uint32_t *out = kB == 1 ? A.heavy : A.more;
+            unsigned long long *cnt = kB == 1 ? A.nheavy : A.nmore;
+            unsigned long long at = 0;
+            if (lane == 0) at = atomicAdd(cnt, (unsigned long long)m);
+            at = (uint32_t)__shfl((int)(uint32_t)at, 0);  // fewer than 2^32 positions
+            if (lane < m) out[at + lane] = s_t[lane] - 1;
+            continue;
+        }
+        for (uint32_t j0 = 0; j0 < tail; j0 += 64) {
+            const uint32_t j = j0 + lane;
+            const uint32_t f = j < tail ? F[j] : 0u, u = f & kMask, r = f >> kIcNodeBits;
+            const uint32_t t = j < tail ? s_t[r] : 1u;
+            if constexpr (kPass == 2) {
+                bool rec = false;
+                if (j < tail) {
+                    const uint32_t ph = ic_phase(t - 1, A.n);
+                    rec = ic_ld(A.full + u) >= ph;
+                    // counted until it is known to have k: while the phases
+                    // are run in order, those are of phases up to this one
+                    // (positions handed on come after the last phase, and do
+                    // not count)
+                    if (rec && !list && ic_ld(A.had + u) < A.k && atomicAdd(A.had + u, 1u) + 1 == A.k)
+                        ic_st(A.full + u, (uint8_t)ph);
+                }
+                const unsigned long long rm = __ballot(rec);
+                if (staged + 64 > kIcStage) flush();
+                if (rec)
+                    s_stage[staged + (uint32_t)__popcll(rm & lower)] = ((uint64_t)u << A.tbits) | t;
+                staged += (uint32_t)__popcll(rm);
+            } else if (j < tail) {
+                const uint32_t at = atomicAdd(&s_cnt[r], 1u);
+                if (kPass == 1) A.records[A.offsets[t - 1] + at] = ((uint64_t)u << A.tbits) | t;
+            }
+        }
+        if (kPass == 0) {
+            ic_sync();
+            if (lane < m) A.counts[s_t[lane] - 1] = s_cnt[lane];
         }
     }
+    if (kPass == 2 && staged) flush();
 }
 
 // One workgroup per handed-over position: the breadth-first search takes up
@@ -273,6 +355,7 @@ __global__ void __launch_bounds__(kIcHeavyBlock) k_ic_heavy(IcArgs A, uint64_t n
     for (uint64_t h = blockIdx.x; h < nheavy; h += gridDim.x) {
         const uint64_t x = A.heavy[h];
         const uint32_t t = (uint32_t)(x + 1);
+        const uint64_t step = ic_step(t);
         if (tid == 0) {
             const uint32_t v = A.node_at[x];
             atomicOr(bm + (v >> 5), 1u << (v & 31));
@@ -289,10 +372,9 @@ __global__ void __launch_bounds__(kIcHeavyBlock) k_ic_heavy(IcArgs A, uint64_t n
             if (tid < chunk) {
                 const uint32_t y = ic_ld(Q + head + tid);
                 for (uint64_t e = A.rptr[y]; e < A.rptr[y + 1]; ++e) {
-                    const uint32_t u = A.rsrc[e];
-                    const uint32_t bit = 1u << (u & 31);
-                    bool add = (ic_ld(bm + (u >> 5)) & bit) == 0 &&
-                               ic_live(A.seed, A.n, u, y, t, A.rthr[e]);
+                    const IcEdge edge = A.redge[e];
+                    const uint32_t u = edge.src, bit = 1u << (u & 31);
+                    bool add = (ic_ld(bm + (u >> 5)) & bit) == 0 && ic_live(edge, step, t);
                     if (add) add = (atomicOr(bm + (u >> 5), bit) & bit) == 0;
                     const uint64_t slot = wave_reserve(&s_tail, add);
                     if (add) ic_st(Q + slot, u);
@@ -307,7 +389,7 @@ __global__ void __launch_bounds__(kIcHeavyBlock) k_ic_heavy(IcArgs A, uint64_t n
         } else {
             uint64_t *out = A.records + A.offsets[x];
             for (uint64_t j = tid; j < cnt; j += kIcHeavyBlock)
-                out[j] = ((uint64_t)ic_ld(Q + j) << 32) | t;
+                out[j] = ((uint64_t)ic_ld(Q + j) << A.tbits) | t;
         }
         for (uint64_t j = tid; j < cnt; j += kIcHeavyBlock) ic_st(bm + (ic_ld(Q + j) >> 5), 0u);
         __syncthreads();  // the bitmap is clean before the next position
@@ -315,22 +397,26 @@ __global__ void __launch_bounds__(kIcHeavyBlock) k_ic_heavy(IcArgs A, uint64_t n
 }
 
 // start[u] = index of u's first record (every node has records).
-__global__ void k_ic_starts(const uint64_t *rec, uint64_t R, uint64_t *start) {
+__global__ void k_ic_starts(const uint64_t *rec, uint64_t R, uint32_t tbits, uint64_t *start) {
     for (uint64_t j = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; j < R;
          j += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t node = (uint32_t)(rec[j] >> 32);
-        if (j == 0 || (uint32_t)(rec[j - 1] >> 32) != node) start[node] = j;
+        const uint32_t node = (uint32_t)(rec[j] >> tbits);
+        if (j == 0 || (uint32_t)(rec[j - 1] >> tbits) != node) start[node] = j;
     }
 }
 
-__global__ void k_ic_select(const uint64_t *rec, const uint64_t *start, uint32_t n, uint32_t k,
-                            uint32_t *pos, double *est) {
-    for (uint64_t u = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; u < n;
-         u += (uint64_t)gridDim.x * blockDim.x) {
+// One wave per node.
+__global__ void __launch_bounds__(256) k_ic_select(const uint64_t *rec, const uint64_t *start,
+                                                   uint32_t n, uint32_t k, uint32_t tbits,
+                                                   uint32_t *pos, double *est) {
+    const uint64_t mask = (1ull << tbits) - 1;
+    const uint64_t waves = (uint64_t)gridDim.x * 4;
+    for (uint64_t u = blockIdx.x * 4ull + threadIdx.x / 64; u < n; u += waves) {
         const uint64_t s = start[u];
-        for (uint32_t j = 0; j < k; ++j) pos[u * k + j] = (uint32_t)rec[s + j];
-        if (est) {
-            const uint32_t T = (uint32_t)rec[s + k - 1];
+        for (uint32_t j = threadIdx.x & 63u; j < k; j += 64)
+            pos[u * k + j] = (uint32_t)(rec[s + j] & mask);
+        if (est && (threadIdx.x & 63u) == 0) {
+            const uint32_t T = (uint32_t)(rec[s + k - 1] & mask);
             est[u] = ((double)n * (double)(k - 1)) / (double)(T - 1);
         }
     }
@@ -507,21 +593,27 @@ extern "C" skim_status skim_build_ic_sketches(const skim_graph *g, uint32_t k, u
         uint32_t *esrc = T.alloc<uint32_t>(m ? m : 1);
         validate_graph(g, esrc, T);
         // reverse graph with thresholds
-        uint32_t *indeg = T.alloc<uint32_t>(n);
-        fill_u32(indeg, 0, n, hs);
-        if (m) {
-            k_ic_indeg<<<grid_for(m, 256, 16384), 256, 0, hs>>>(g->col, m, indeg);
-            SKIM_LAUNCH_CHECK();
-        }
+        int node_bits = 1;
+        while (node_bits < 32 && (1ull << node_bits) < n) ++node_bits;
         uint64_t *rptr = T.alloc<uint64_t>((uint64_t)n + 1);
-        exclusive_scan_u32(indeg, rptr, n, T);
-        uint32_t *rsrc = T.alloc<uint32_t>(m ? m : 1);
-        uint32_t *rthr = T.alloc<uint32_t>(m ? m : 1);
-        fill_u32(indeg, 0, n, hs);  // reused as per-head cursors
+        IcEdge *redge = T.alloc<IcEdge>(m ? m : 1);
         if (m) {
-            k_ic_rfill<<<grid_for(m, 256, 16384), 256, 0, hs>>>(esrc, g->col, g->thr, m, rptr,
-                                                               indeg, rsrc, rthr);
+            uint64_t *key = T.alloc<uint64_t>(m), *skey = T.alloc<uint64_t>(m);
+            uint32_t *sthr = T.alloc<uint32_t>(m);
+            k_ic_keys<<<grid_for(m, 256, 16384), 256, 0, hs>>>(esrc, g->col, m, key);
             SKIM_LAUNCH_CHECK();
+            size_t tb = 0;
+            SKIM_HIP(rocprim::radix_sort_pairs(nullptr, tb, key, skey, (const uint32_t *)g->thr,
+                                               sthr, (size_t)m, 32, 32 + node_bits, hs));
+            void *tmp = T.get(tb ? tb : 1);
+            SKIM_HIP(rocprim::radix_sort_pairs(tmp, tb, key, skey, (const uint32_t *)g->thr, sthr,
+                                               (size_t)m, 32, 32 + node_bits, hs));
+            k_ic_rfill<<<grid_for(m, 256, 16384), 256, 0, hs>>>(skey, sthr, m, n, seed, rptr,
+                                                               redge);
+            SKIM_LAUNCH_CHECK();
+            for (void *p : {(void *)key, (void *)skey, (void *)sthr, tmp}) T.release(p);
+        } else {
+            fill_u64(rptr, 0, (uint64_t)n + 1, hs);
         }
         // the structured permutation: chunk c orders the nodes by their hash
         const uint64_t total = (uint64_t)n * k;
@@ -529,48 +621,44 @@ extern "C" skim_status skim_build_ic_sketches(const skim_graph *g, uint32_t k, u
         uint64_t *hkeys2 = T.alloc<uint64_t>(total);
         uint32_t *hvals = T.alloc<uint32_t>(total);
         uint32_t *node_at = T.alloc<uint32_t>(total);
-        uint32_t *offs = T.alloc<uint32_t>((uint64_t)k + 1);
-        k_ic_hash<<<grid_for(total, 256, 16384), 256, 0, hs>>>(n, k, seed, hkeys, hvals, offs);
+        uint32_t chunk_bits = 1;
+        while ((1u << chunk_bits) < k) ++chunk_bits;
+        k_ic_hash<<<grid_for(total, 256, 16384), 256, 0, hs>>>(n, k, chunk_bits, seed, hkeys,
+                                                              hvals);
         SKIM_LAUNCH_CHECK();
         size_t tmp_bytes = 0;
-        SKIM_HIP(rocprim::segmented_radix_sort_pairs(nullptr, tmp_bytes, hkeys, hkeys2, hvals,
-                                                     node_at, (unsigned)total, k, offs, offs + 1,
-                                                     0, 64, hs));
+        SKIM_HIP(rocprim::radix_sort_pairs(nullptr, tmp_bytes, hkeys, hkeys2, hvals, node_at,
+                                           (size_t)total, 0u, 64u, hs));
         void *tmp = T.get(tmp_bytes);
-        SKIM_HIP(rocprim::segmented_radix_sort_pairs(tmp, tmp_bytes, hkeys, hkeys2, hvals,
-                                                     node_at, (unsigned)total, k, offs, offs + 1,
-                                                     0, 64, hs));
+        SKIM_HIP(rocprim::radix_sort_pairs(tmp, tmp_bytes, hkeys, hkeys2, hvals, node_at,
+                                           (size_t)total, 0u, 64u, hs));
+        k_ic_ties<<<grid_for(total, 256, 16384), 256, 0, hs>>>(hkeys2, node_at, n, total, seed);
+        SKIM_LAUNCH_CHECK();
         T.release(tmp);
         T.release(hkeys);
         T.release(hkeys2);
         T.release(hvals);
-        // per-thread search state within the budget
         const uint32_t words = (n + 31) / 32;
-        const uint64_t per_thread = ((uint64_t)words + kIcLight) * sizeof(uint32_t);
-        uint64_t threads = std::max<uint64_t>(kIcBlock, kIcStateBudget / per_thread);
-        threads = std::min<uint64_t>(threads, (total + kIcBlock - 1) / kIcBlock * kIcBlock);
-        threads = std::min<uint64_t>(threads, 1ull << 19);  // enough to fill the chip
-        threads = threads / kIcBlock * kIcBlock;
         IcArgs A{};
         A.n = n;
         A.k = k;
         A.seed = seed;
         A.rptr = rptr;
-        A.rsrc = rsrc;
-        A.rthr = rthr;
+        A.redge = redge;
         A.node_at = node_at;
-        A.bitmaps = T.alloc<uint32_t>(threads * words);
-        A.queues = T.alloc<uint32_t>(threads * kIcLight);
-        fill_u32(A.bitmaps, 0, threads * words, hs);
+        A.tbits = 1;
+        while ((total >> A.tbits) != 0) ++A.tbits;  // t <= k n < 2^32
         A.counts = T.alloc<uint32_t>(total);
+        A.had = T.alloc<uint32_t>(n);
+        A.full = T.alloc<uint8_t>((uint64_t)n + 4);
+        A.more = T.alloc<uint32_t>(total);
         A.heavy = T.alloc<uint32_t>(total);
+        A.nmore = T.alloc<unsigned long long>(1);
         A.nheavy = T.alloc<unsigned long long>(1);
-        fill_u64((uint64_t *)A.nheavy, 0, 1, hs);
-        const unsigned grid = (unsigned)(threads / kIcBlock);
-        // One pass when the light searches' records fit a buffer sized up
-        // front (32 per position, at most kIcRecordCap): they are appended
-        // as the searches end.  Otherwise, or for the handed-over searches,
-        // a counting pass, a scan and a writing pass.
+        // One pass when the records fit a buffer sized up front (32 per
+        // position, at most kIcRecordCap): they are appended as the searches
+        // end.  Otherwise, or for the workgroup searches, a counting pass, a
+        // scan and a writing pass.
         uint64_t rcap = std::min<uint64_t>(std::max<uint64_t>(total * 32, 1u << 20), kIcRecordCap);
         if (take_fault(kFaultIcRecords)) rcap = 1;  // tests of the counting path
         uint64_t *recbuf = T.alloc<uint64_t>(rcap);
@@ -580,24 +668,48 @@ extern "C" skim_status skim_build_ic_sketches(const skim_graph *g, uint32_t k, u
         A.ovf = T.alloc<uint32_t>(1);
         fill_u64((uint64_t *)A.rcount, 0, 1, hs);
         fill_u32(A.ovf, 0, 1, hs);
-        {
+        fill_u32(A.counts, 0, total, hs);  // a workgroup search's count comes from its own pass
+        fill_u32(A.had, 0, n, hs);
+        fill_u32((uint32_t *)A.full, kIcOpen * 0x01010101u, (n + 3) / 4, hs);
+        // two batches of positions per wave, one where that leaves waves idle
+        // (equal shares of all of them: waves idle at the ends of the phases;
+        // four 2.76 ms, eight 3.35 ms)
+        constexpr unsigned kGrid = 1u << 20;
+        auto grid_of = [&](uint64_t batches) {
+            return grid_for(batches, batches > 8192 ? 2 : 1, kGrid);
+        };
+        // every position, then the ones a wave handed on; leaves nheavy
+        uint64_t nheavy = 0;
+        auto searches = [&](auto pass) {
+            constexpr int kPass = decltype(pass)::value;
+            fill_u64((uint64_t *)A.nmore, 0, 1, hs);
+            fill_u64((uint64_t *)A.nheavy, 0, 1, hs);
             LaunchTimer t("k_ic_search", hs);
-            k_ic_search<2><<<grid, kIcBlock, 0, hs>>>(A);
-            SKIM_LAUNCH_CHECK();
-        }
+            for (uint64_t c0 = 0, c1 = 1; c0 < k; c0 = c1, c1 = 4 * c1) {
+                if (kPass != 2) c1 = k;  // phases only matter to the appending pass
+                const uint64_t x0 = c0 * n, x1 = std::min<uint64_t>(c1, k) * n;
+                k_ic_wave<kPass, kIcWave, kIcQueue, kIcSlots>
+                    <<<grid_of((x1 - x0 + kIcWave - 1) / kIcWave), 64, 0, hs>>>(A, x0, x1, nullptr);
+                SKIM_LAUNCH_CHECK();
+            }
+            uint64_t nmore = 0;
+            read_back(&nmore, A.nmore, sizeof nmore, hs);
+            if (nmore) {
+                k_ic_wave<kPass, 1, kIcOne, 2 * kIcOne>
+                    <<<grid_of(nmore), 64, 0, hs>>>(A, 0, nmore, A.more);
+                SKIM_LAUNCH_CHECK();
+                read_back(&nheavy, A.nheavy, sizeof nheavy, hs);
+            }
+        };
+        searches(std::integral_constant<int, 2>{});
         uint32_t ovf = 0;
         uint64_t rlight = 0;
         read_back(&ovf, A.ovf, sizeof ovf, hs);
         read_back(&rlight, A.rcount, sizeof rlight, hs);
         if (ovf) {  // back to counting first
             rlight = 0;
-            fill_u64((uint64_t *)A.nheavy, 0, 1, hs);
-            LaunchTimer t("k_ic_search", hs);
-            k_ic_search<0><<<grid, kIcBlock, 0, hs>>>(A);
-            SKIM_LAUNCH_CHECK();
+            searches(std::integral_constant<int, 0>{});
         }
-        uint64_t nheavy = 0;
-        read_back(&nheavy, A.nheavy, sizeof nheavy, hs);
         unsigned hgrid = 1;
         if (nheavy) {
             const uint64_t per_block = ((uint64_t)words + n) * sizeof(uint32_t);
@@ -612,12 +724,14 @@ extern "C" skim_status skim_build_ic_sketches(const skim_graph *g, uint32_t k, u
             SKIM_LAUNCH_CHECK();
         }
         // offsets of what is still to be written: every search after a
-        // counting pass, the handed-over ones after the single pass
-        uint64_t *offsets = T.alloc<uint64_t>(total + 1);
-        exclusive_scan_u32(A.counts, offsets, total, T);
+        // counting pass, the workgroup searches after the single pass
         uint64_t rrest = 0;
-        read_back(&rrest, offsets + total, sizeof rrest, hs);
-        A.offsets = offsets;
+        if (ovf || nheavy) {
+            uint64_t *offsets = T.alloc<uint64_t>(total + 1);
+            exclusive_scan_u32(A.counts, offsets, total, T);
+            read_back(&rrest, offsets + total, sizeof rrest, hs);
+            A.offsets = offsets;
+        }
         const uint64_t R = rlight + rrest;
         uint64_t *records = recbuf;
         if (R > rcap) {  // room for the rest after the appended records
@@ -628,30 +742,22 @@ extern "C" skim_status skim_build_ic_sketches(const skim_graph *g, uint32_t k, u
             T.release(recbuf);
         }
         A.records = records + rlight;
-        if (ovf) {
-            LaunchTimer t("k_ic_search", hs);
-            k_ic_search<1><<<grid, kIcBlock, 0, hs>>>(A);
-            SKIM_LAUNCH_CHECK();
-        }
+        if (ovf) searches(std::integral_constant<int, 1>{});
         if (nheavy) {
             LaunchTimer t("k_ic_heavy", hs);
             k_ic_heavy<1><<<hgrid, kIcHeavyBlock, 0, hs>>>(A, nheavy);
             SKIM_LAUNCH_CHECK();
         }
         A.records = records;
-        T.release(A.bitmaps);
-        T.release(A.queues);
         if (nheavy) {
             T.release(A.hbitmaps);
             T.release(A.hqueues);
         }
         // records by (node, position); every node keeps its first k
         uint64_t *sorted = T.alloc<uint64_t>(R);
-        // the keys' high bits above the node id are zero: large sorts skip
-        // them (small ones take the whole key)
-        int node_bits = 1;
-        while (node_bits < 32 && (1ull << node_bits) < n) ++node_bits;
-        const unsigned end_bit = R > (1ull << 21) ? 32u + (unsigned)node_bits : 64u;
+        // the keys' bits above the node id are zero: large sorts skip them
+        // (small ones take the whole key)
+        const unsigned end_bit = R > (1ull << 20) ? A.tbits + (unsigned)node_bits : 64u;
         tmp_bytes = 0;
         SKIM_HIP(rocprim::radix_sort_keys(nullptr, tmp_bytes, A.records, sorted, (size_t)R, 0u,
                                           end_bit, hs));
@@ -659,9 +765,10 @@ extern "C" skim_status skim_build_ic_sketches(const skim_graph *g, uint32_t k, u
         SKIM_HIP(rocprim::radix_sort_keys(tmp, tmp_bytes, A.records, sorted, (size_t)R, 0u, end_bit,
                                           hs));
         uint64_t *start = T.alloc<uint64_t>(n);
-        k_ic_starts<<<grid_for(R, 256, 16384), 256, 0, hs>>>(sorted, R, start);
+        k_ic_starts<<<grid_for(R, 256, 16384), 256, 0, hs>>>(sorted, R, A.tbits, start);
         SKIM_LAUNCH_CHECK();
-        k_ic_select<<<grid_for(n, 256, 4096), 256, 0, hs>>>(sorted, start, n, k, positions, est);
+        k_ic_select<<<grid_for(n, 4, 16384), 256, 0, hs>>>(sorted, start, n, k, A.tbits, positions,
+                                                           est);
         SKIM_LAUNCH_CHECK();
         SKIM_HIP(hipStreamSynchronize(hs));
         return SKIM_OK;

@@ -81,6 +81,31 @@ template <int G> __device__ __forceinline__ uint64_t group_min_u64(uint64_t x) {
     return ((uint64_t)mh << 32) | ml;
 }
 
+// Inclusive prefix sum and prefix maximum over the wave's lanes (rows of 16 by
+// shifts, then the row ends broadcast to the rows after them; lanes without a
+// source add 0).
+template <int kCtrl, int kRows> __device__ __forceinline__ uint32_t dpp_or_zero(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, kRows, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_scan_sum(uint32_t x) {
+    x += dpp_or_zero<0x111, 0xF>(x);  // row_shr 1, 2, 4, 8
+    x += dpp_or_zero<0x112, 0xF>(x);
+    x += dpp_or_zero<0x114, 0xF>(x);
+    x += dpp_or_zero<0x118, 0xF>(x);
+    x += dpp_or_zero<0x142, 0xA>(x);  // row_bcast 15 into rows 1 and 3
+    x += dpp_or_zero<0x143, 0xC>(x);  // row_bcast 31 into rows 2 and 3
+    return x;
+}
+__device__ __forceinline__ uint32_t wave_scan_max(uint32_t x) {
+    x = max(x, dpp_or_zero<0x111, 0xF>(x));
+    x = max(x, dpp_or_zero<0x112, 0xF>(x));
+    x = max(x, dpp_or_zero<0x114, 0xF>(x));
+    x = max(x, dpp_or_zero<0x118, 0xF>(x));
+    x = max(x, dpp_or_zero<0x142, 0xA>(x));
+    x = max(x, dpp_or_zero<0x143, 0xC>(x));
+    return x;
+}
+
 // 64 x 64 bit transpose across the wave: bit j of lane i's result is bit i of
 // lane j's argument.
 template <int kStep> __device__ __forceinline__ uint64_t transpose_step(uint64_t x, uint64_t m) {

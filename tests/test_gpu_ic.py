@@ -177,3 +177,29 @@ def test_counting_path(oracle_lib):
             _check(oracle_lib, g, k, seed)
     finally:
         sk.skim_debug_inject(sk.SKIM_FAULT_IC_RECORDS, 0)
+
+
+@pytest.mark.parametrize("n,deg,denom,k", [
+    (1, 0, 1, 2),          # one node, no edges
+    (15, 2, 4, 3),         # less than a wave's positions in a chunk
+    (500, 8, 6, 65),       # searches of a few hundred: most waves hand on
+    (900, 8, 6, 40),       # some of them near the queue of a wave of their own
+    (1700, 8, 5, 9),       # below and above it
+    (4000, 6, 8, 64),      # small searches: every chunk phase prunes records
+])
+def test_waves_hand_on(oracle_lib, n, deg, denom, k):
+    """Searches around the limits of a wave's queue, with the records of full
+    nodes left out from phase to phase; and the same by the counting path."""
+    import paper_1408_6282_amd as sk
+    rng = np.random.default_rng(n * 7 + k)
+    e = np.unique(rng.integers(0, n, size=(deg * n, 2)), axis=0)
+    e = e[e[:, 0] != e[:, 1]] if len(e) else e.reshape(0, 2)
+    g = from_edges(n, e[:, 0], e[:, 1], 0xFFFFFFFF // denom)
+    wpos, west, _ = oracle_lib.ic_sketches(g, k, 21)
+    for counting in (0, 1):
+        sk.skim_debug_inject(sk.SKIM_FAULT_IC_RECORDS, counting)
+        try:
+            pos, est = gpu_ic(g, k, 21)
+        finally:
+            sk.skim_debug_inject(sk.SKIM_FAULT_IC_RECORDS, 0)
+        assert np.array_equal(pos, wpos) and np.array_equal(est, west), counting
