@@ -40,12 +40,14 @@
 // seed's discrepancy with eq. (chernoff) on a grid of discrepancy values and
 // convolves the per-seed distributions pairwise in a tree of launches.
 #include "skim_internal.h"
+#include "skim_wave.h"
 
 #include <mutex>
 
 #include <rocprim/device/device_radix_sort.hpp>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <memory>
 #include <utility>
@@ -58,7 +60,7 @@ constexpr int kSkimBlock = 1024;
 constexpr uint32_t kSkimLdsNodes = 20480;  // graphs up to this size keep size[] in LDS
 constexpr uint32_t kSkimPairListNodes = 1u << 17;  // from this size, in-lists as pair words
 constexpr uint32_t kSkimLdsWords = kSkimLdsNodes / 2;
-constexpr uint32_t kFlagPool = 1u;
+constexpr uint32_t kFlagPool = 1u, kFlagAhead = 2u;
 // Items whose search, index entry or out-list is at most this long are
 // walked by their own thread; a batch or level with a longer one spreads
 // its work over the block by flat position.
@@ -83,6 +85,8 @@ constexpr uint32_t kHeavyItems = 1u << 16;
 // Entries of the nodes that fill within a batch, kept to find the filling
 // prefix directly (more: binary search over prefixes).
 constexpr uint32_t kSkimCand = 1024;
+// Entries of a batch that fit in LDS.
+constexpr uint32_t kSkimStage = 8192;
 // The first kSkimLdsFront entries of a residual level in the workgroup live
 // in LDS (the rest in the queue area): small levels never go through global
 // memory between one level and the next.
@@ -102,7 +106,10 @@ struct SkCtl {
     // its own; level L reads rsize[L % 3], appends to rsize[(L + 1) % 3]).
     uint32_t pend, px, rcur, pad;
     unsigned long long rgain;
-    unsigned long long pad2[10];
+    // The window of searches ahead: positions [a_lo, a_lo + min(a_w, a_fail)),
+    // pool entries taken, searches left to the wave and workgroup kernels.
+    unsigned long long a_lo, a_w, a_fail, a_used, nlong, ngiant;
+    unsigned long long pad2[4];
     unsigned long long rsize[3 * 16];
     unsigned long long hsize[3 * 16];  // pairs level L deferred: hsize[16 (L % 3)]
 };
@@ -119,16 +126,21 @@ struct SkArgs {
     const uint64_t *fptr;
     const uint32_t *fadj;
     const uint32_t *order;  // pair ids by increasing rank
+    uint64_t ordered;       // of them, in place so far
     uint32_t *covered;      // [64 n] 0/1
-    uint32_t *size;         // [2 ceil(n / 4)] packed 16-bit counters
+    uint32_t *size;         // [size_words(n)] packed 16-bit counters
     uint32_t *sel;          // [n] 0/1
     uint64_t *idx;          // [64 n] first pool entry << 32 | entries, 0 = no entry
     uint32_t *pool;
     uint64_t pool_cap;
-    uint32_t *bcnt;         // [2 ceil(n / 4)] per-batch increment counters, packed
-    uint32_t *queues;       // [kSkimBlock * n]
+    uint32_t *front;        // [2 * 64 n] residual levels
+    uint64_t *ahead;        // [kAheadMax] searches of the window
+    uint32_t *apool;        // [apool_cap] their nodes
+    uint64_t apool_cap;
+    uint32_t *along;        // [2 kAheadMax] searches left to the wave kernel, to the workgroup kernel
+    uint32_t *gqueue;       // [kAheadGiants * n]
     uint64_t *heavy;        // [3][2 kHeavyItems] grid residual, deferred (pair, count), first out-edge
-    uint32_t *vis;          // [kSkimBlock * vis_words] per-thread visited bitmaps, kept zero
+    uint32_t *vis;          // [kAheadGiants * vis_words] visited bitmaps, kept zero
     uint32_t vis_words;     // ceil(n / 32)
     SkCtl *ctl;
     uint64_t seed;
@@ -136,20 +148,10 @@ struct SkArgs {
     uint32_t *rec_second;   // [n] per selected seed: second largest sketch
 };
 
-// A thread's reverse search marks the nodes it has queued in its own bitmap
-// (test and set: one load and at most one store per scanned edge, instead of
-// a scan of the queue) and clears the words it touched when it is done.
-__device__ __forceinline__ bool mark_new(uint32_t *V, uint32_t w) {
-    const uint32_t bit = 1u << (w & 31u), word = V[w >> 5];
-    if (word & bit) return false;
-    V[w >> 5] = word | bit;
-    return true;
-}
-
-// size[] and the batch counters are 16-bit halves of 32-bit words (sizes
-// never exceed k <= 256, batch counts never exceed one batch of 1024 pairs),
-// so twice as many nodes fit in LDS.  Adds and subtracts never carry across
-// halves.
+// size[] is 16-bit halves of 32-bit words (sizes stay at most 65535, see the
+// scan), so twice as many nodes fit in LDS.  Adds and subtracts never carry
+// across halves.  Whole 16-byte groups, zero beyond n.
+__host__ __device__ inline uint32_t size_words(uint32_t n) { return (n + 7) / 8 * 4; }
 __device__ __forceinline__ uint32_t half_shift(uint32_t v) { return (v & 1u) << 4; }
 
 // State shared between the block's threads goes through agent-scope atomic
@@ -170,8 +172,8 @@ __device__ __forceinline__ void cadd(uint32_t *c, uint32_t v, uint32_t d) {
 __device__ __forceinline__ void csub(uint32_t *c, uint32_t v, uint32_t d) {
     atomicSub(c + (v >> 1), d << half_shift(v));
 }
-__device__ __forceinline__ void czero(uint32_t *c, uint32_t v) {
-    atomicAnd(c + (v >> 1), ~(0xFFFFu << half_shift(v)));
+__device__ __forceinline__ uint32_t cadd_old(uint32_t *c, uint32_t v, uint32_t d) {
+    return (atomicAdd(c + (v >> 1), d << half_shift(v)) >> half_shift(v)) & 0xFFFFu;
 }
 
 // Exclusive prefix sum of v over the block (NT threads, called by all of
@@ -256,8 +258,10 @@ struct ResidStage {
 };
 
 struct ScanShared {
-    uint64_t cand[kSkimCand];  // (pair position << 32) | node, nodes that fill
-    uint32_t ncand, tmin;
+    uint64_t cand[kSkimCand];    // (pair position << 32) | node, nodes that fill
+    uint32_t seen[kSkimCand];
+    uint32_t entry[kSkimStage];  // the batch's searches, laid end to end
+    uint32_t ncand;
 };
 
 // One chunk of a residual level: frontier entries [base, base + NT) of
@@ -408,38 +412,301 @@ __device__ __forceinline__ void resid_chunk(const SkArgs &A, uint32_t *SZ, const
     __syncthreads();  // the chunk's LDS arrays are reused
 }
 
+// ------------------------------------------------------- searches ahead
+// The reverse searches of the next pairs in rank order (the window: positions
+// [a_lo, a_lo + a_w)), on the whole grid, before k_skim scans them.  A search
+// does not depend on the seeds chosen meanwhile: an uncovered pair reaches no
+// covered one, so it stays as it is until its pair is covered, and k_skim
+// passes over covered pairs.  (Searched by k_skim's own threads as they were
+// scanned, the 100 batches of 50 seeds on 10^6 nodes took 8 ms of one
+// workgroup's time, a long chain of dependent loads in one lane each, and a
+// seed that committed 75 pairs searched 1024.)
+//
+// Search r of the window is ahead[r] = first entry in apool << 32 | entries
+// (0 entries: covered).  Three kernels: a lane per search up to kAheadShort
+// nodes, then a wave per search up to kAheadWave nodes (queue and visited set
+// in LDS), then a workgroup per search.  A search that no longer fits in the
+// pool ends the window before its position.
+constexpr uint32_t kAheadShort = 16;
+constexpr uint32_t kAheadWave = 1024, kAheadHash = 4096;
+constexpr uint32_t kAheadFirst = 1024, kAheadMax = 1u << 16;  // positions of a window
+constexpr uint64_t kAheadEntries = 1ull << 20;  // entries a window is sized for
+constexpr uint32_t kAheadPoolNodes = 512;       // the pool holds this many searches of n nodes
+constexpr int kAheadBlock = 256, kAheadGiantBlock = 1024;
+constexpr uint32_t kAheadGiants = 128;  // workgroups with a queue and a bitmap of their own
+
+// The live in-list of pair q: node `one` (count 1, not stored), or a range.
+struct InList {
+    uint64_t begin;
+    uint32_t count, one;
+    bool stored;
+};
+__device__ __forceinline__ InList in_list(const SkArgs &A, uint32_t q) {
+    if (!A.rlive) {
+        const uint64_t e0 = A.rptr[q];
+        return {e0, (uint32_t)(A.rptr[q + 1] - e0), 0u, true};
+    }
+    const uint64_t lw = A.rlive[q];
+    if (lw & kLiveOne) return {0, 1u, (uint32_t)lw, false};
+    return {lw >> kLiveCountBits, (uint32_t)(lw & ((1u << kLiveCountBits) - 1)), 0u, true};
+}
+__device__ __forceinline__ uint32_t in_node(const SkArgs &A, const InList &L, uint32_t j) {
+    if (!L.stored) return L.one;
+    return A.rlive ? A.rsrc[L.begin + j] : A.radj[L.begin + j];
+}
+__device__ __forceinline__ void ahead_fail(const SkArgs &A, uint32_t r) {
+    A.ahead[r] = 0;
+    atomicMin(&A.ctl->a_fail, (unsigned long long)r);
+}
+
+__global__ void __launch_bounds__(kAheadBlock) k_ahead_short(SkArgs A) {
+    __shared__ uint32_t s_q[kAheadShort][kAheadBlock];
+    const uint32_t tid = threadIdx.x;
+    const uint64_t lo = A.ctl->a_lo;
+    const uint32_t w = (uint32_t)min(A.ctl->a_w, (unsigned long long)(A.ordered - lo));
+    for (uint32_t r0 = blockIdx.x * kAheadBlock; r0 < w; r0 += gridDim.x * kAheadBlock) {
+        const uint32_t r = r0 + tid;
+        uint32_t cnt = 0;
+        bool more = false;
+        if (r < w) {
+            const uint32_t p = A.order[lo + r];
+            if (!A.covered[p]) {
+                const uint32_t i = p % kPairStride;
+                s_q[0][tid] = p / kPairStride;
+                cnt = 1;
+                for (uint32_t head = 0; head < cnt && !more; ++head) {
+                    const InList L = in_list(A, s_q[head][tid] * kPairStride + i);
+                    for (uint32_t j = 0; j < L.count && !more; ++j) {
+                        const uint32_t v = in_node(A, L, j);
+                        bool seen = false;
+                        for (uint32_t c = 0; c < cnt; ++c) seen |= s_q[c][tid] == v;
+                        if (seen) continue;
+                        if (cnt == kAheadShort) more = true;
+                        else s_q[cnt++][tid] = v;
+                    }
+                }
+            }
+        }
+        // a pair alone needs no pool entries
+        const uint32_t take = more || cnt < 2 ? 0u : cnt;
+        const uint32_t incl = wave_scan_sum(take);
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        unsigned long long base = 0;
+        if (total && (tid & 63u) == 0) base = atomicAdd(&A.ctl->a_used, (unsigned long long)total);
+        base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base);
+        base += incl - take;
+        if (r < w && !more) {
+            if (base + take > A.apool_cap) {
+                if (take) ahead_fail(A, r);
+                else A.ahead[r] = cnt;
+            } else {
+                A.ahead[r] = (base << 32) | cnt;
+                for (uint32_t j = 0; j < take; ++j) A.apool[base + j] = s_q[j][tid];
+            }
+        }
+        const uint64_t slot = wave_reserve(&A.ctl->nlong, more);
+        if (more) A.along[slot] = r;
+    }
+}
+
+constexpr uint32_t kAheadWaves = 4, kAheadWaveGrid = 1024;
+__global__ void __launch_bounds__(64 * kAheadWaves) k_ahead_wave(SkArgs A) {
+    __shared__ uint32_t s_hash[kAheadWaves][kAheadHash / 2], s_q[kAheadWaves][kAheadWave];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    uint32_t *H = s_hash[wave], *Q = s_q[wave];
+    constexpr uint32_t kSlots = kAheadHash / 2;
+    const uint32_t nlong = (uint32_t)A.ctl->nlong;
+    const uint64_t lo = A.ctl->a_lo;
+    for (uint32_t x = blockIdx.x * kAheadWaves + wave; x < nlong; x += gridDim.x * kAheadWaves) {
+        const uint32_t r = A.along[x], p = A.order[lo + r], i = p % kPairStride;
+        for (uint32_t s = lane; s < kSlots; s += 64) H[s] = 0xFFFFFFFFu;
+        __builtin_amdgcn_wave_barrier();
+        // true when v was not in the set yet (at most kAheadWave + 64 nodes in
+        // kSlots places)
+        auto insert = [&](uint32_t v) {
+            for (uint32_t s = (v * 0x9E3779B1u) >> 21;; s = (s + 1) & (kSlots - 1)) {
+                const uint32_t was = atomicCAS(&H[s], 0xFFFFFFFFu, v);
+                if (was == v) return false;
+                if (was == 0xFFFFFFFFu) return true;
+            }
+        };
+        static_assert(kSlots == 2048, "the hash takes 11 bits");
+        if (lane == 0) {
+            Q[0] = p / kPairStride;
+            insert(Q[0]);
+        }
+        __builtin_amdgcn_wave_barrier();
+        uint32_t cnt = 1;
+        bool more = false;
+        for (uint32_t head = 0; head < cnt && !more;) {
+            const uint32_t take = min(64u, cnt - head);
+            InList L = {0, 0, 0, true};
+            if (lane < take) L = in_list(A, Q[head + lane] * kPairStride + i);
+            head += take;
+            // the lists end to end, 64 entries at a time
+            const uint64_t big = __ballot(L.count >= (1u << 24));
+            const uint32_t incl = wave_scan_sum(L.count);
+            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            if (big) {  // (a prefix sum of longer lists could wrap)
+                more = true;
+                break;
+            }
+            for (uint32_t b = 0; b < total; b += 64) {
+                const uint32_t j = b + lane, o = wave_owner(incl, j);
+                InList M;
+                M.count = 0;
+                M.begin = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(L.begin >> 32), (int)o) << 32) |
+                          (uint32_t)__shfl((int)(uint32_t)L.begin, (int)o);
+                M.one = (uint32_t)__shfl((int)L.one, (int)o);
+                M.stored = __shfl((int)L.stored, (int)o) != 0;
+                const uint32_t first = (uint32_t)__shfl((int)(incl - L.count), (int)o);
+                bool add = false;
+                uint32_t v = 0;
+                if (j < total) {
+                    v = in_node(A, M, j - first);
+                    add = insert(v);
+                }
+                const uint64_t m = __ballot(add);
+                const uint32_t pos = cnt + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+                if (add && pos < kAheadWave) Q[pos] = v;
+                cnt += (uint32_t)__popcll(m);
+                if (cnt > kAheadWave) {
+                    more = true;
+                    break;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (more) {
+            if (lane == 0) A.along[kAheadMax + atomicAdd(&A.ctl->ngiant, 1ull)] = r;
+            continue;
+        }
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(&A.ctl->a_used, (unsigned long long)cnt);
+        base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32) |
+               (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base);
+        if (base + cnt > A.apool_cap) {
+            if (lane == 0) ahead_fail(A, r);
+            continue;
+        }
+        for (uint32_t j = lane; j < cnt; j += 64) A.apool[base + j] = Q[j];
+        if (lane == 0) A.ahead[r] = (base << 32) | cnt;
+    }
+}
+
+// Each workgroup searches in a queue and a visited bitmap of its own (kept
+// zero), kAheadGiantBlock queue entries at a time, every wave over its 64
+// entries' lists laid end to end.
+__global__ void __launch_bounds__(kAheadGiantBlock) k_ahead_giant(SkArgs A) {
+    __shared__ uint32_t s_tail;
+    __shared__ unsigned long long s_base;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t ngiant = (uint32_t)A.ctl->ngiant;
+    const uint64_t lo = A.ctl->a_lo;
+    uint32_t *Q = A.gqueue + (uint64_t)blockIdx.x * A.n;
+    uint32_t *V = A.vis + (uint64_t)blockIdx.x * A.vis_words;
+    for (uint32_t x = blockIdx.x; x < ngiant; x += gridDim.x) {
+        const uint32_t r = A.along[kAheadMax + x], p = A.order[lo + r], i = p % kPairStride;
+        if (tid == 0) {
+            const uint32_t v = p / kPairStride;
+            st(Q, v);
+            atomicOr(V + (v >> 5), 1u << (v & 31u));
+            s_tail = 1;
+        }
+        __syncthreads();
+        for (uint32_t head = 0;;) {
+            const uint32_t tail = s_tail;
+            __syncthreads();
+            if (head >= tail) break;  // uniform
+            const uint32_t take = min((uint32_t)kAheadGiantBlock, tail - head);
+            InList L = {0, 0, 0, true};
+            if (tid < take) L = in_list(A, ld(Q + head + tid) * kPairStride + i);
+            head += take;
+            uint32_t at = 0;  // entries of this lane's list laid out so far
+            while (__any(at < L.count)) {
+                // at most 2^16 of each list at a time: their sum does not wrap
+                const uint32_t part = min(L.count - at, 1u << 16);
+                const uint32_t incl = wave_scan_sum(part);
+                const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+                for (uint32_t b = 0; b < total; b += 64) {
+                    const uint32_t j = b + lane, o = wave_owner(incl, j);
+                    InList M;
+                    M.count = 0;
+                    const uint64_t from = L.begin + at;
+                    M.begin = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(from >> 32), (int)o) << 32) |
+                              (uint32_t)__shfl((int)(uint32_t)from, (int)o);
+                    M.one = (uint32_t)__shfl((int)L.one, (int)o);
+                    M.stored = __shfl((int)L.stored, (int)o) != 0;
+                    const uint32_t first = (uint32_t)__shfl((int)(incl - part), (int)o);
+                    bool add = false;
+                    uint32_t v = 0;
+                    if (j < total) {
+                        v = in_node(A, M, j - first);
+                        const uint32_t bit = 1u << (v & 31u);
+                        add = !(ld(V + (v >> 5)) & bit) && !(atomicOr(V + (v >> 5), bit) & bit);
+                    }
+                    const uint64_t m = __ballot(add);
+                    if (m) {
+                        uint32_t pos = 0;
+                        if (lane == (uint32_t)__ffsll((long long)m) - 1u)
+                            pos = atomicAdd(&s_tail, (uint32_t)__popcll(m));
+                        pos = (uint32_t)__shfl((int)pos, __ffsll((long long)m) - 1) +
+                              (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+                        if (add) st(Q + pos, v);  // each node once: at most n
+                    }
+                }
+                at += part;
+            }
+            __syncthreads();
+        }
+        const uint32_t cnt = s_tail;
+        if (tid == 0) s_base = atomicAdd(&A.ctl->a_used, (unsigned long long)cnt);
+        __syncthreads();
+        const unsigned long long base = s_base;
+        const bool fits = base + cnt <= A.apool_cap;
+        for (uint32_t j = tid; j < cnt; j += kAheadGiantBlock) {
+            const uint32_t v = ld(Q + j);
+            st(V + (v >> 5), 0u);
+            if (fits) A.apool[base + j] = v;
+        }
+        if (tid == 0) {
+            if (fits) A.ahead[r] = (base << 32) | cnt;
+            else ahead_fail(A, r);
+        }
+        __syncthreads();  // the queue, the bitmap and s_tail are reused
+    }
+}
+
+// The selection loop.  kLds: size[] is in LDS (graphs of at most
+// kSkimLdsNodes nodes: every search adds to it, and device atomics from
+// different waves on one cache line are serialised).
+template <bool kLds>
 __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, uint64_t handoff,
                                                      uint32_t *seeds, uint64_t *gains,
                                                      double *gain_d, uint64_t *rec_tau,
                                                      uint32_t *rec_second) {
     __shared__ unsigned long long s_cursor, s_pool, s_gain, s_best, s_tau, s_fcnt[2];
-    __shared__ int s_x, s_filler;
-    __shared__ uint32_t s_found, s_stop, s_fill_cnt, s_second, s_xmin, s_resume, s_rcur;
-    // size[] and the batch counters live in LDS when the graph is small
-    // enough: every pair's search adds to them, and device atomics from
-    // different waves on one cache line are serialised.
-    __shared__ __align__(8) uint32_t s_size[kSkimLdsWords];
-    __shared__ __align__(8) uint32_t s_bcnt[kSkimLdsWords];
+    __shared__ int s_x;
+    __shared__ uint32_t s_stop, s_second, s_xmin, s_resume, s_rcur;
+    __shared__ unsigned long long s_fill0, s_fill1;
+    __shared__ __align__(16) uint32_t s_size[kLds ? kSkimLdsWords : 4];
     __shared__ FlatShared<kSkimBlock> X;
     __shared__ ScanShared C;
     __shared__ uint32_t s_front[2][kSkimLdsFront];
     const uint32_t tid = threadIdx.x;
     const uint32_t n = A.n, k = A.k;
-    const bool in_lds = n <= kSkimLdsNodes;
-    uint32_t *SZ = in_lds ? s_size : A.size;
-    uint32_t *BC = in_lds ? s_bcnt : A.bcnt;
-    if (in_lds)
-        for (uint32_t w = tid; w < kSkimLdsWords; w += kSkimBlock) {
-            s_size[w] = w < (n + 1) / 2 ? ld(A.size + w) : 0u;
-            s_bcnt[w] = 0;
-        }
-    uint32_t *Q = A.queues + (uint64_t)tid * n;
-    uint32_t *V = A.vis + (uint64_t)tid * A.vis_words;
+    uint32_t *SZ = kLds ? s_size : A.size;
+    const uint32_t swords = size_words(n);
+    if constexpr (kLds)
+        for (uint32_t w = tid; w < swords; w += kSkimBlock) s_size[w] = ld(A.size + w);
+    const uint64_t a_lo = A.ctl->a_lo;
+    const uint64_t a_hi = min((unsigned long long)A.ordered,
+                              a_lo + min(A.ctl->a_w, A.ctl->a_fail));
     if (tid == 0) {
         s_cursor = A.ctl->cursor;
         s_pool = A.ctl->pool_used;
         s_stop = 0;
-        s_found = 0;
         C.ncand = 0;
         // a residual search the grid handed back (its frontier got small):
         // the launch starts by finishing that seed
@@ -453,194 +720,183 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
         }
     }
     __syncthreads();
-    // entry t of the batch's searches, laid end to end in thread order
-    auto entry = [&](uint64_t t) {
+    // Entry t of the batch's searches, laid end to end in thread order:
+    // staged in LDS when there is room for all of them.
+    bool staged = true;
+    auto far_entry = [&](uint64_t t) {
         const uint32_t r = run_of<kSkimBlock>(X.ex, t);
-        return ld(A.queues + (uint64_t)r * n + (t - X.ex[r]));
+        const uint32_t j = (uint32_t)(t - X.ex[r]);
+        return j ? A.apool[(uint64_t)X.o[r] + j] : X.q[r];
     };
+    auto entry = [&](uint64_t t) { return staged ? C.entry[t] : far_entry(t); };
     uint32_t done = 0;
     for (uint32_t it = 0; it < goal; ++it) {
         const bool resumed = it == 0 && s_resume;  // uniform
         if (!resumed) {
         if (tid == 0) {
             s_x = -1;
-            s_filler = -1;
+            s_fill0 = s_fill1 = 0;
         }
         __syncthreads();
         // ------------------------------------------------ scan pairs by rank
         while (s_x < 0 && s_cursor < A.nsrc) {
             const uint64_t cursor = s_cursor;
-            const uint64_t left = A.nsrc - cursor;
-            const uint32_t B = left < (uint64_t)kSkimBlock ? (uint32_t)left : (uint32_t)kSkimBlock;
-            uint32_t cnt = 0, p = 0;
-            if (tid < B) {
-                p = A.order[cursor + tid];
-                if (!ld(A.covered + p)) {
-                    const uint32_t i = p % kPairStride;
-                    Q[0] = p / kPairStride;
-                    mark_new(V, Q[0]);
-                    cnt = 1;
-                    for (uint32_t head = 0; head < cnt; ++head) {
-                        const uint32_t q = Q[head] * kPairStride + i;
-                        if (!A.rlive) {
-                            for (uint64_t e = A.rptr[q]; e < A.rptr[q + 1]; ++e) {
-                                const uint32_t w = A.radj[e];
-                                if (mark_new(V, w)) Q[cnt++] = w;
-                            }
-                            continue;
-                        }
-                        const uint64_t lw = A.rlive[q];
-                        if (lw & kLiveOne) {
-                            const uint32_t w = (uint32_t)lw;
-                            if (mark_new(V, w)) Q[cnt++] = w;
-                        } else {
-                            const uint64_t e0 = lw >> kLiveCountBits;
-                            const uint64_t e1 = e0 + (lw & ((1u << kLiveCountBits) - 1));
-                            for (uint64_t e = e0; e < e1; ++e) {
-                                const uint32_t w = A.rsrc[e];
-                                if (mark_new(V, w)) Q[cnt++] = w;
-                            }
-                        }
-                    }
-                    for (uint32_t j = 0; j < cnt; ++j) V[Q[j] >> 5] = 0u;  // back to zero
-                }
-            }
-            {
-                uint64_t tot;
-                const uint64_t ex = block_excl_scan<kSkimBlock>(cnt, X.wsum, tot);
-                X.ex[tid] = ex;
-                if (tid == 0) X.ex[kSkimBlock] = tot;
-            }
-            const bool heavy = __syncthreads_or(cnt > kSkimSerial) != 0;
-            // Does some node reach k within the first T pairs?  Sizes are
-            // below k at the start of a batch and grow by one per pair.  The
-            // whole batch is tried first; if some node fills, the entries of
-            // every such node are kept, and the first filling prefix is the
-            // smallest position at which one of them receives its
-            // (k - size)-th entry (a search holds a node at most once).  With
-            // too many such entries, the prefix is found by binary search.
-            bool filled = false;
-            uint32_t lo = 0, hi = B, T = B;
-            for (;;) {
-                const uint64_t end = X.ex[T];
-                bool cand = false;
-                auto keep = [&](uint32_t r, uint32_t v) {
-                    if (T != B) return;
-                    const uint32_t slot = atomicAdd(&C.ncand, 1u);
-                    if (slot < kSkimCand) C.cand[slot] = ((uint64_t)r << 32) | v;
-                };
-                if (heavy) {
-                    for (uint64_t t = tid; t < end; t += kSkimBlock) cadd(BC, entry(t), 1u);
-                    __syncthreads();
-                    for (uint64_t t = tid; t < end; t += kSkimBlock) {
-                        const uint32_t v = entry(t);
-                        if (cget(SZ, v) + cget(BC, v) >= k) {
-                            cand = true;
-                            keep(run_of<kSkimBlock>(X.ex, t), v);
-                        }
-                    }
-                } else {
-                    if (tid < T)
-                        for (uint32_t j = 0; j < cnt; ++j) cadd(BC, Q[j], 1u);
-                    __syncthreads();
-                    if (tid < T)
-                        for (uint32_t j = 0; j < cnt; ++j)
-                            if (cget(SZ, Q[j]) + cget(BC, Q[j]) >= k) {
-                                cand = true;
-                                keep(tid, Q[j]);
-                            }
-                }
-                if (__any(cand) && (tid & 63u) == 0) atomicOr(&s_found, 1u);
-                __syncthreads();
-                const bool f = s_found != 0;
-                if (heavy) {
-                    for (uint64_t t = tid; t < end; t += kSkimBlock) czero(BC, entry(t));
-                } else if (tid < T) {
-                    for (uint32_t j = 0; j < cnt; ++j) czero(BC, Q[j]);
-                }
-                __syncthreads();
-                if (tid == 0) s_found = 0;
-                __syncthreads();
-                if (T == B) {
-                    filled = f;
-                    if (!f) break;
-                    const uint32_t nc = C.ncand;
-                    if (nc <= kSkimCand) {
-                        if (tid == 0) C.tmin = 0xFFFFFFFFu;
-                        __syncthreads();
-                        for (uint32_t c = tid; c < nc; c += kSkimBlock) {
-                            const uint64_t e = C.cand[c];
-                            const uint32_t r = (uint32_t)(e >> 32), v = (uint32_t)e;
-                            uint32_t before = 0;  // entries of v at earlier positions
-                            for (uint32_t c2 = 0; c2 < nc; ++c2) {
-                                const uint64_t e2 = C.cand[c2];
-                                before += (uint32_t)e2 == v && (uint32_t)(e2 >> 32) < r;
-                            }
-                            if (before + 1 == k - cget(SZ, v)) atomicMin(&C.tmin, r);
-                        }
-                        __syncthreads();
-                        hi = C.tmin + 1;
-                        break;
-                    }
-                } else if (f) {
-                    hi = T;
-                } else {
-                    lo = T;
-                }
-                if (hi - lo <= 1) break;
-                T = lo + (hi - lo) / 2;
-            }
-            T = hi;  // B when nothing fills; else the first filling prefix
-            // does the committed prefix fit in the index pool?
-            const uint64_t need = X.ex[T], pbase = s_pool;
-            if (pbase + need > A.pool_cap) {
+            if (cursor >= a_hi) {  // the window is used up: the host has the next one searched
                 if (tid == 0) {
-                    A.ctl->flags |= kFlagPool;
-                    A.ctl->need = pbase + need;
                     s_stop = 1;
+                    const uint64_t w = A.ctl->a_w, used = A.ctl->a_used;
+                    // four times as long, if that is about kAheadEntries
+                    // entries; a window that outgrew the pool, a quarter
+                    uint64_t next = min(4 * w, w * kAheadEntries / (used ? used : 1));
+                    next = min(max(next, (uint64_t)kAheadFirst), (uint64_t)kAheadMax);
+                    if (A.ctl->a_fail < w) next = (w + 3) / 4;
+                    A.ctl->a_lo = cursor;
+                    A.ctl->a_w = next;
+                    A.ctl->a_fail = ~0ull;
+                    A.ctl->a_used = A.ctl->nlong = A.ctl->ngiant = 0;
+                    A.ctl->flags |= kFlagAhead;
                 }
                 __syncthreads();
                 break;
             }
-            // commit pairs [0, T): index entries in pair order, sizes
-            if (heavy) {
-                for (uint64_t t = tid; t < need; t += kSkimBlock) {
-                    const uint32_t v = entry(t);
-                    st(A.pool + pbase + t, v);
-                    cadd(SZ, v, 1u);
-                }
-            } else if (tid < T) {
-                for (uint32_t j = 0; j < cnt; ++j) {
-                    st(A.pool + pbase + X.ex[tid] + j, Q[j]);
-                    cadd(SZ, Q[j], 1u);
+            // sizes are below k here and grow by at most one per pair: they
+            // stay in 16 bits with all of a batch added
+            const uint32_t B = (uint32_t)min(a_hi - cursor,
+                                             (uint64_t)min((uint32_t)kSkimBlock, 65536u - k));
+            uint32_t cnt = 0, p = 0, first = 0;
+            if (tid < B) {
+                p = A.order[cursor + tid];
+                const uint64_t a = A.ahead[cursor - a_lo + tid];
+                if (!ld(A.covered + p)) {
+                    cnt = (uint32_t)a;
+                    first = (uint32_t)(a >> 32);
                 }
             }
-            if (tid < T && cnt) {
-                st(A.idx + p, ((pbase + X.ex[tid]) << 32) | cnt);
+            uint64_t tot;
+            const uint64_t ex = block_excl_scan<kSkimBlock>(cnt, X.wsum, tot);
+            X.ex[tid] = ex;
+            X.q[tid] = p / kPairStride;
+            X.o[tid] = first;
+            if (tid == 0) {
+                X.ex[kSkimBlock] = tot;
+                s_xmin = 0xFFFFFFFFu;
             }
-            if (tid == 0) s_xmin = 0xFFFFFFFFu;
+            staged = tot <= kSkimStage;
+            if (staged) {
+                if (__syncthreads_or(cnt > kSkimSerial)) {
+                    for (uint64_t t = tid; t < tot; t += kSkimBlock) C.entry[t] = far_entry(t);
+                } else if (cnt) {
+                    C.entry[ex] = p / kPairStride;
+                    for (uint32_t j = 1; j < cnt; ++j)
+                        C.entry[ex + j] = A.apool[(uint64_t)first + j];
+                }
+            }
             __syncthreads();
+            // All of the batch is added to the sizes.  If some node reaches k
+            // the entries of all that did are kept, and the first filling
+            // prefix is the smallest position at which one of them receives
+            // its k-th (a search holds a node at most once); with too many
+            // such entries it is found by binary search over prefixes.  The
+            // pairs after that prefix are then taken back.
+            bool f = false;
+            for (uint64_t t = tid; t < tot; t += kSkimBlock)
+                f |= cadd_old(SZ, entry(t), 1u) + 1 >= k;
+            const bool filled = __syncthreads_or(f) != 0;
+            uint32_t T = B;
+            if (filled) {
+                for (uint64_t t = tid; t < tot; t += kSkimBlock) {
+                    const uint32_t v = entry(t);
+                    if (cget(SZ, v) < k) continue;
+                    const uint32_t slot = atomicAdd(&C.ncand, 1u);
+                    if (slot < kSkimCand) {
+                        C.cand[slot] = ((uint64_t)run_of<kSkimBlock>(X.ex, t) << 32) | v;
+                        C.seen[slot] = 0;
+                    }
+                }
+                __syncthreads();
+                // moves the sizes from prefix `from` of the batch to prefix `to`
+                auto move = [&](uint32_t from, uint32_t to) {
+                    for (uint64_t t = X.ex[min(from, to)] + tid; t < X.ex[max(from, to)];
+                         t += kSkimBlock) {
+                        if (from < to) cadd(SZ, entry(t), 1u);
+                        else csub(SZ, entry(t), 1u);
+                    }
+                    __syncthreads();
+                };
+                const uint32_t nc = C.ncand;
+                uint32_t at = B;
+                if (nc <= kSkimCand) {
+                    // per candidate: entries of its node in the batch (high
+                    // half) and those at earlier positions, the other
+                    // candidates dealt over the block's threads
+                    const uint32_t parts = kSkimBlock / nc, c = tid % nc, part = tid / nc;
+                    if (part < parts) {
+                        const uint64_t e = C.cand[c];
+                        uint32_t seen = 0;
+                        for (uint32_t c2 = part; c2 < nc; c2 += parts) {
+                            const uint64_t e2 = C.cand[c2];
+                            if ((uint32_t)e2 == (uint32_t)e) seen += e2 < e ? 0x10001u : 0x10000u;
+                        }
+                        if (seen) atomicAdd(&C.seen[c], seen);
+                    }
+                    __syncthreads();
+                    for (uint32_t c = tid; c < nc; c += kSkimBlock) {
+                        const uint64_t e = C.cand[c];
+                        const uint32_t seen = C.seen[c];
+                        if (cget(SZ, (uint32_t)e) - (seen >> 16) + (seen & 0xFFFFu) + 1 == k)
+                            atomicMin(&s_xmin, (uint32_t)(e >> 32));
+                    }
+                    __syncthreads();
+                    T = s_xmin + 1;
+                } else {
+                    uint32_t none = 0;  // prefixes none and T: nothing fills, something does
+                    while (T - none > 1) {
+                        const uint32_t mid = none + (T - none) / 2;
+                        move(at, mid);
+                        at = mid;
+                        bool g = false;
+                        for (uint64_t t = tid; t < X.ex[mid]; t += kSkimBlock)
+                            g |= cget(SZ, entry(t)) >= k;
+                        if (__syncthreads_or(g)) T = mid;
+                        else none = mid;
+                    }
+                }
+                move(at, T);
+                if (tid == 0) s_xmin = 0xFFFFFFFFu;
+            }
+            // does the committed prefix fit in the index pool?
+            const uint64_t need = X.ex[T], pbase = s_pool;
+            if (pbase + need > A.pool_cap) {
+                for (uint64_t t = tid; t < need; t += kSkimBlock) csub(SZ, entry(t), 1u);
+                if (tid == 0) {
+                    A.ctl->flags |= kFlagPool;
+                    A.ctl->need = pbase + need;
+                    s_stop = 1;
+                    C.ncand = 0;
+                }
+                __syncthreads();
+                break;
+            }
+            // commit pairs [0, T): index entries in pair order
+            for (uint64_t t = tid; t < need; t += kSkimBlock) st(A.pool + pbase + t, entry(t));
+            if (tid < T && cnt) st(A.idx + p, ((pbase + ex) << 32) | cnt);
             if (filled) {
                 // the nodes that just reached k are in pair T - 1's search;
                 // the seed is the smallest of them
-                if (heavy) {
-                    for (uint64_t t = X.ex[T - 1] + tid; t < need; t += kSkimBlock) {
-                        const uint32_t v = entry(t);
-                        if (cget(SZ, v) >= k) atomicMin(&s_xmin, v);
-                    }
-                } else if (tid == T - 1) {
-                    for (uint32_t j = 0; j < cnt; ++j)
-                        if (cget(SZ, Q[j]) >= k) atomicMin(&s_xmin, Q[j]);
-                }
-                if (tid == T - 1) {
-                    s_filler = (int)tid;
-                    s_fill_cnt = cnt;
-                    s_tau = pair_rank(A.seed, p);
-                }
                 __syncthreads();
-                if (tid == 0) s_x = s_xmin == 0xFFFFFFFFu ? -1 : (int)s_xmin;
+                for (uint64_t t = X.ex[T - 1] + tid; t < need; t += kSkimBlock) {
+                    const uint32_t v = entry(t);
+                    if (cget(SZ, v) >= k) atomicMin(&s_xmin, v);
+                }
+                if (tid == T - 1) s_tau = pair_rank(A.seed, p);
+                __syncthreads();
             }
             if (tid == 0) {
+                if (filled) {
+                    s_x = s_xmin == 0xFFFFFFFFu ? -1 : (int)s_xmin;
+                    s_fill0 = X.ex[T - 1];
+                    s_fill1 = need;
+                }
                 s_cursor = cursor + T;
                 s_pool = pbase + need;
                 C.ncand = 0;
@@ -671,67 +927,71 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
         }
         const uint32_t xs = (uint32_t)s_x;  // the seed
         // ------------------------------------ records for the error estimate
-        // The filling pair's search is still in its thread's queue; the batch
-        // counters are all zero here and mark it while the sizes are scanned.
-        const uint32_t *Qf = s_filler >= 0 ? A.queues + (uint64_t)s_filler * n : nullptr;
-        const uint32_t fcnt = s_filler >= 0 ? s_fill_cnt : 0u;
-        for (uint32_t j = tid; j < fcnt; j += kSkimBlock) cadd(BC, ld(Qf + j), 1u);
-        if (tid == 0) s_second = 0;
+        // The filling pair's search is still the batch's; its nodes' sizes
+        // are one less, and the seed's is 0, while the sizes are scanned.
+        // Selected nodes need no test: every pair a seed reaches is covered,
+        // so its size is 0 from then on and no later search reaches it.
+        const uint64_t fill0 = s_fill0, fill1 = s_fill1;
+        for (uint64_t t = fill0 + tid; t < fill1; t += kSkimBlock) {
+            const uint32_t v = entry(t);
+            if (v != xs) csub(SZ, v, 1u);
+        }
+        uint32_t xsize = 0;
+        if (tid == 0) {
+            s_second = 0;
+            xsize = cget(SZ, xs);
+            csub(SZ, xs, xsize);
+        }
+        // (the atomics above have reached the L2 before the barrier; the
+        // fence after it drops this CU's cached copies of the sizes)
+        __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
+        if constexpr (!kLds) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         {
-            // Selected nodes need no test: every pair a seed reaches is
-            // covered, so its size is 0 from then on and no later search
-            // reaches it.  Four nodes per 64-bit load (the arrays are padded
-            // to whole pairs of words).
-            uint32_t best2 = 0;
-            const uint64_t *SZ2 = reinterpret_cast<const uint64_t *>(SZ);
-            const uint64_t *BC2 = reinterpret_cast<const uint64_t *>(BC);
-            // four words per thread in flight at once (a loop of single
-            // loads waits for each: 0.1 ms per seed on 10^6 nodes)
-            const uint32_t nw = (n + 3) / 4;
-            for (uint32_t w0 = tid; w0 < nw; w0 += 4 * kSkimBlock) {
-                uint64_t a[4], b[4];
+            // eight sizes per load, eight loads in flight: one workgroup reads
+            // the 2 MB of 10^6 nodes
+            typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+            us2 best2 = {0, 0};
+            auto upto = [&](uint32_t w) {
+                best2 = __builtin_elementwise_max(best2, __builtin_bit_cast(us2, w));
+            };
+            const uint4 *SZ4 = reinterpret_cast<const uint4 *>(SZ);
+            const uint32_t nw = swords / 4;
+            for (uint32_t w0 = tid; w0 < nw; w0 += 8 * kSkimBlock) {
+                uint4 a[8];
 #pragma unroll
-                for (uint32_t u = 0; u < 4; ++u) {
-                    const uint32_t w2 = w0 + u * kSkimBlock;
-                    a[u] = w2 < nw ? ld(SZ2 + w2) : 0ull;
-                    b[u] = w2 < nw ? ld(BC2 + w2) : 0ull;
+                for (uint32_t u = 0; u < 8; ++u) {
+                    const uint32_t w = w0 + u * kSkimBlock;
+                    a[u] = w < nw ? SZ4[w] : uint4{0, 0, 0, 0};
                 }
 #pragma unroll
-                for (uint32_t u = 0; u < 4; ++u) {
-#pragma unroll
-                    for (uint32_t h = 0; h < 4; ++h) {
-                        const uint32_t v = 4 * (w0 + u * kSkimBlock) + h;
-                        const uint32_t sz = (uint32_t)((a[u] >> (16 * h)) & 0xFFFFu) -
-                                            (uint32_t)((b[u] >> (16 * h)) & 0xFFFFu);
-                        if (v < n && v != xs && sz > best2) best2 = sz;
-                    }
-                }
+                for (uint32_t u = 0; u < 8; ++u) upto(a[u].x), upto(a[u].y), upto(a[u].z), upto(a[u].w);
             }
             // one LDS atomic per wave: lanes on one address are serialised
-            for (int off = 32; off > 0; off >>= 1) {
-                const uint32_t o = (uint32_t)__shfl_xor((int)best2, off);
-                best2 = o > best2 ? o : best2;
-            }
-            if ((tid & 63) == 0 && best2) atomicMax(&s_second, best2);
+            uint32_t b = max((uint32_t)best2.x, (uint32_t)best2.y);
+            b = 0xFFFFFFFFu - group_min_u32<64>(0xFFFFFFFFu - b);
+            if ((tid & 63) == 0 && b) atomicMax(&s_second, b);
         }
         __syncthreads();
-        for (uint32_t j = tid; j < fcnt; j += kSkimBlock) czero(BC, ld(Qf + j));
+        for (uint64_t t = fill0 + tid; t < fill1; t += kSkimBlock) {
+            const uint32_t v = entry(t);
+            if (v != xs) cadd(SZ, v, 1u);
+        }
         if (tid == 0) {
-            rec_tau[it] = s_filler >= 0 ? (uint64_t)s_tau : ~0ull;
+            cadd(SZ, xs, xsize);
+            rec_tau[it] = fill1 ? (uint64_t)s_tau : ~0ull;
             rec_second[it] = s_second;
         }
         }  // !resumed
         const uint32_t x = (uint32_t)s_x;
         // ------------------------------------------------- residual problem
         // Level-synchronous over all instances at once: a frontier of pairs
-        // (64 v + i) in two halves of the queue area (free here: the scan's
-        // searches are done and the filler's queue has been read).  A pair is
+        // (64 v + i) in two halves of the queue area.  A pair is
         // claimed by the CAS that covers it; its index entry is erased then.
         // A level with more than `handoff` pairs (0: none) and the rest of
         // the search go to the whole grid (k_resid_level); the host then
         // completes the seed.
-        uint32_t *F[2] = {A.queues, A.queues + (uint64_t)A.n * kPairStride};
+        uint32_t *F[2] = {A.front, A.front + (uint64_t)A.n * kPairStride};
         if (!resumed) {
         if (tid == 0) {
             s_gain = 0;
@@ -804,9 +1064,9 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
         ++done;
         __syncthreads();
     }
-    if (in_lds) {
+    if constexpr (kLds) {
         __syncthreads();
-        for (uint32_t w = tid; w < (n + 1) / 2; w += kSkimBlock) st(A.size + w, s_size[w]);
+        for (uint32_t w = tid; w < swords; w += kSkimBlock) st(A.size + w, s_size[w]);
     }
     if (tid == 0) {
         A.ctl->cursor = s_cursor;
@@ -843,8 +1103,8 @@ __global__ void __launch_bounds__(kResidBlock) k_resid_level(SkArgs A, uint32_t 
     if (fc == 0 && nh == 0) return;  // uniform
     const uint32_t cur = (r0 + L) & 1u;
     const uint64_t half = (uint64_t)A.n * kPairStride;
-    const uint32_t *Fin = A.queues + cur * half;
-    uint32_t *Fout = A.queues + (cur ^ 1u) * half;
+    const uint32_t *Fin = A.front + cur * half;
+    uint32_t *Fout = A.front + (cur ^ 1u) * half;
     unsigned long long *next = &A.ctl->rsize[16 * ((L + 1) % 3)];
     const uint64_t *hin = A.heavy + 2 * (uint64_t)kHeavyItems * ((L + 2) % 3);
     for (uint32_t h0 = 0; h0 < nh; h0 += kResidBlock) {
@@ -934,6 +1194,59 @@ __global__ void k_pair_keys(uint32_t n, uint32_t ell, uint64_t seed, uint64_t *k
         const uint32_t p = (uint32_t)(t / ell) * kPairStride + (uint32_t)(t % ell);
         keys[t] = pair_rank(seed, p);
         vals[t] = p;
+    }
+}
+
+// A run uses the lowest ranks only (50 seeds on 10^6 nodes: 74 thousand of 64
+// million), so past kOrderWhole pairs the order is made in steps, kOrderFirst
+// pairs first and four times as many in each later step: the pairs with ranks
+// in [r0, r1] are counted, collected in any order and sorted, which continues
+// the order exactly (ranks are distinct: they are one SplitMix64 sequence).
+// Ranks are uniform, so a step is about as long as aimed at.  10^6 nodes,
+// l = 64: all ranks 2.8 ms, the first step 0.3 ms.
+constexpr uint64_t kOrderFirst = 1ull << 18, kOrderWhole = 1ull << 20;
+constexpr int kOrderBlock = 256;
+constexpr uint32_t kOrderGrid = 2048;
+__global__ void __launch_bounds__(kOrderBlock) k_rank_count(uint32_t n, uint32_t ell, uint64_t seed,
+                                                            uint64_t r0, uint64_t r1,
+                                                            uint32_t *counts,
+                                                            unsigned long long *total) {
+    __shared__ uint32_t s_count;
+    if (threadIdx.x == 0) s_count = 0;
+    __syncthreads();
+    uint32_t c = 0;
+    for (uint64_t p = blockIdx.x * (uint64_t)kOrderBlock + threadIdx.x; p < (uint64_t)n * kPairStride;
+         p += (uint64_t)gridDim.x * kOrderBlock) {
+        const uint64_t r = pair_rank(seed, (uint32_t)p);
+        c += p % kPairStride < ell && r >= r0 && r <= r1;
+    }
+    atomicAdd(&s_count, c);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        counts[blockIdx.x] = s_count;
+        atomicAdd(total, (unsigned long long)s_count);
+    }
+}
+__global__ void __launch_bounds__(kOrderBlock) k_rank_take(uint32_t n, uint32_t ell, uint64_t seed,
+                                                           uint64_t r0, uint64_t r1,
+                                                           const uint32_t *counts,
+                                                           unsigned long long *taken,
+                                                           uint64_t *keys, uint32_t *vals) {
+    __shared__ unsigned long long s_base;
+    __shared__ uint32_t s_at;
+    if (threadIdx.x == 0) {
+        s_base = atomicAdd(taken, (unsigned long long)counts[blockIdx.x]);
+        s_at = 0;
+    }
+    __syncthreads();
+    for (uint64_t p = blockIdx.x * (uint64_t)kOrderBlock + threadIdx.x; p < (uint64_t)n * kPairStride;
+         p += (uint64_t)gridDim.x * kOrderBlock) {
+        const uint64_t r = pair_rank(seed, (uint32_t)p);
+        if (p % kPairStride < ell && r >= r0 && r <= r1) {
+            const uint64_t slot = s_base + atomicAdd(&s_at, 1u);
+            keys[slot] = r;
+            vals[slot] = (uint32_t)p;
+        }
     }
 }
 
@@ -1245,10 +1558,86 @@ struct skim_greedy_state {
     const uint32_t *col = nullptr;
     const uint32_t *thr = nullptr;
     uint32_t selected = 0;
+    uint64_t rank_next = 0;   // the order holds every pair of a rank below this one
+    uint32_t *order = nullptr;
+    uint64_t order_step = 0;  // pairs the next step aims at
+    bool ahead_due = true;    // the window has not been searched yet
+    uint64_t cursor = 0;      // pairs used, as the last launch left it
     skim::SkArgs args{};
 };
 
 namespace skim {
+
+// The control block of a run that has used `cursor` pairs; the next window
+// has not been searched.
+void greedy_set_ctl(skim_greedy_state *st, uint64_t cursor, uint64_t pool_used, hipStream_t s) {
+    SkCtl c{};
+    c.cursor = c.a_lo = cursor;
+    c.pool_used = pool_used;
+    c.a_w = kAheadFirst;
+    c.a_fail = ~0ull;
+    st->ahead_due = true;
+    st->cursor = cursor;
+    SKIM_HIP(hipMemcpyAsync(st->args.ctl, &c, sizeof c, hipMemcpyHostToDevice, s));
+    SKIM_HIP(hipStreamSynchronize(s));
+}
+
+// The next step of the pairs' order by rank.
+void greedy_extend_order(skim_greedy_state *st, hipStream_t s) {
+    SkArgs &A = st->args;
+    const uint64_t left = A.nsrc - A.ordered;
+    const bool whole = A.nsrc <= kOrderWhole;
+    Arena T(s);
+    uint64_t count = A.nsrc;
+    uint64_t *keys;
+    uint32_t *vals;
+    if (whole) {
+        keys = T.alloc<uint64_t>(count);
+        vals = T.alloc<uint32_t>(count);
+        k_pair_keys<<<grid_for(count, 256, 8192), 256, 0, s>>>(A.n, A.ell, A.seed, keys, vals);
+        SKIM_LAUNCH_CHECK();
+    } else {
+        // the last step (the one that would leave less than it takes) ends
+        // at the highest rank
+        const double width = std::ldexp((double)st->order_step / (double)A.nsrc, 64);
+        const bool last = left <= 2 * st->order_step ||
+                          (double)st->rank_next + width >= std::ldexp(1.0, 64) * (1 - 1e-9);
+        const uint64_t r0 = st->rank_next, r1 = last ? ~0ull : r0 + (uint64_t)width;
+        uint32_t *counts = T.alloc<uint32_t>(kOrderGrid);
+        unsigned long long *totals = T.alloc<unsigned long long>(2);
+        fill_u64((uint64_t *)totals, 0, 2, s);
+        k_rank_count<<<kOrderGrid, kOrderBlock, 0, s>>>(A.n, A.ell, A.seed, r0, r1, counts, totals);
+        SKIM_LAUNCH_CHECK();
+        read_back(&count, totals, sizeof count, s);
+        keys = T.alloc<uint64_t>(count ? count : 1);
+        vals = T.alloc<uint32_t>(count ? count : 1);
+        k_rank_take<<<kOrderGrid, kOrderBlock, 0, s>>>(A.n, A.ell, A.seed, r0, r1, counts,
+                                                       totals + 1, keys, vals);
+        SKIM_LAUNCH_CHECK();
+        st->rank_next = r1 + 1;
+        st->order_step *= 4;
+    }
+    if (count) {
+        uint64_t *keys2 = T.alloc<uint64_t>(count);
+        uint32_t *out = st->order + A.ordered;
+        size_t tmp_bytes = 0;
+        // large sorts on the high halves (then k_rank_ties); small ones go to
+        // another rocPRIM algorithm, which on the high halves alone did not
+        // order the pairs of a 1000-node graph, and are cheap: the whole rank
+        const unsigned begin_bit = count > kHalfSortPairs ? 32u : 0u;
+        SKIM_HIP(rocprim::radix_sort_pairs(nullptr, tmp_bytes, keys, keys2, vals, out, (size_t)count,
+                                           begin_bit, 64u, s));
+        void *tmp = T.get(tmp_bytes);
+        SKIM_HIP(rocprim::radix_sort_pairs(tmp, tmp_bytes, keys, keys2, vals, out, (size_t)count,
+                                           begin_bit, 64u, s));
+        if (begin_bit) {
+            k_rank_ties<<<grid_for(count, 256, 8192), 256, 0, s>>>(keys2, out, count);
+            SKIM_LAUNCH_CHECK();
+        }
+    }
+    SKIM_HIP(hipStreamSynchronize(s));
+    A.ordered += count;
+}
 
 skim_greedy_state *greedy_create(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t seed,
                                         hipStream_t s) {
@@ -1285,48 +1674,33 @@ skim_greedy_state *greedy_create(const skim_graph *g, uint32_t ell, uint32_t k, 
         }
         st->args.fptr = fwd.ptr;
         st->args.fadj = fwd.adj;
-        // pairs by increasing rank
-        const uint64_t nsrc = (uint64_t)n * ell;
-        uint64_t *keys = T.alloc<uint64_t>(nsrc);
-        uint64_t *keys2 = T.alloc<uint64_t>(nsrc);
-        uint32_t *vals = T.alloc<uint32_t>(nsrc);
-        uint32_t *order = M.alloc<uint32_t>(nsrc);
-        k_pair_keys<<<grid_for(nsrc, 256, 8192), 256, 0, s>>>(n, ell, seed, keys, vals);
-        SKIM_LAUNCH_CHECK();
-        size_t tmp_bytes = 0;
-        // large sorts on the high halves (then k_rank_ties); small ones go to
-        // another rocPRIM algorithm, which on the high halves alone did not
-        // order the pairs of a 1000-node graph, and are cheap: the whole rank
-        const unsigned begin_bit = nsrc > kHalfSortPairs ? 32u : 0u;
-        SKIM_HIP(rocprim::radix_sort_pairs(nullptr, tmp_bytes, keys, keys2, vals, order, (size_t)nsrc,
-                                           begin_bit, 64u, s));
-        void *tmp = T.get(tmp_bytes);
-        SKIM_HIP(rocprim::radix_sort_pairs(tmp, tmp_bytes, keys, keys2, vals, order, (size_t)nsrc,
-                                           begin_bit, 64u, s));
-        if (begin_bit) {
-            k_rank_ties<<<grid_for(nsrc, 256, 8192), 256, 0, s>>>(keys2, order, nsrc);
-            SKIM_LAUNCH_CHECK();
-        }
         SKIM_HIP(hipStreamSynchronize(s));
-        st->args.order = order;
-        st->args.nsrc = nsrc;
     }
+    const uint64_t nsrc = (uint64_t)n * ell;
+    st->order = M.alloc<uint32_t>(nsrc);
+    st->order_step = kOrderFirst;
+    st->args.order = st->order;
+    st->args.nsrc = nsrc;
     const uint64_t npairs = (uint64_t)n * kPairStride;
     SkArgs &A = st->args;
     A.n = n;
     A.ell = ell;
     A.k = k;
     A.covered = M.alloc<uint32_t>(npairs);
-    const uint64_t cwords = 2 * (((uint64_t)n + 3) / 4);  // whole 64-bit words
+    const uint64_t cwords = size_words(n);
     A.size = M.alloc<uint32_t>(cwords);
     A.sel = M.alloc<uint32_t>(n);
     A.idx = M.alloc<uint64_t>(npairs);
     A.heavy = M.alloc<uint64_t>(3 * 2 * (uint64_t)kHeavyItems);
-    A.bcnt = M.alloc<uint32_t>(cwords);
-    A.queues = M.alloc<uint32_t>((uint64_t)kSkimBlock * n);
+    A.front = M.alloc<uint32_t>(2 * npairs);
+    A.ahead = M.alloc<uint64_t>(kAheadMax);
+    A.apool_cap = std::max<uint64_t>(1ull << 16, (uint64_t)kAheadPoolNodes * n);
+    A.apool = M.alloc<uint32_t>(A.apool_cap);
+    A.along = M.alloc<uint32_t>(2 * kAheadMax);
+    A.gqueue = M.alloc<uint32_t>((uint64_t)kAheadGiants * n);
     A.vis_words = (n + 31) / 32;
-    A.vis = M.alloc<uint32_t>((uint64_t)kSkimBlock * A.vis_words);
-    fill_u32(A.vis, 0, (uint64_t)kSkimBlock * A.vis_words, s);
+    A.vis = M.alloc<uint32_t>((uint64_t)kAheadGiants * A.vis_words);
+    fill_u32(A.vis, 0, (uint64_t)kAheadGiants * A.vis_words, s);
     A.pool_cap = std::max<uint64_t>(1ull << 16, 2 * A.nsrc);
     A.pool = M.alloc<uint32_t>(A.pool_cap);
     A.ctl = M.alloc<SkCtl>(1);
@@ -1337,8 +1711,7 @@ skim_greedy_state *greedy_create(const skim_graph *g, uint32_t ell, uint32_t k, 
     fill_u32(A.size, 0, cwords, s);
     fill_u32(A.sel, 0, n, s);
     fill_u64(A.idx, 0, npairs, s);
-    fill_u32(A.bcnt, 0, cwords, s);
-    fill_u64((uint64_t *)A.ctl, 0, sizeof(SkCtl) / 8, s);
+    greedy_set_ctl(st.get(), 0, 0, s);
     st->n = n;
     st->ell = ell;
     st->k = k;
@@ -1357,12 +1730,24 @@ void greedy_run(skim_greedy_state *st, uint32_t s_goal, uint32_t *seeds, uint64_
     uint32_t done = 0;
     int growths = 0;
     while (done < s_goal) {
-        k_skim<<<1, kSkimBlock, 0, s>>>(A, s_goal - done, kSkimHandoff, seeds + done,
-                                        gains + done, gain_d ? gain_d + done : nullptr,
-                                        A.rec_tau + st->selected, A.rec_second + st->selected);
+        if (st->ahead_due) {
+            while (A.ordered < A.nsrc && A.ordered <= st->cursor) greedy_extend_order(st, s);
+            k_ahead_short<<<kAheadMax / kAheadBlock, kAheadBlock, 0, s>>>(A);
+            SKIM_LAUNCH_CHECK();
+            k_ahead_wave<<<kAheadWaveGrid, 64 * kAheadWaves, 0, s>>>(A);
+            SKIM_LAUNCH_CHECK();
+            k_ahead_giant<<<kAheadGiants, kAheadGiantBlock, 0, s>>>(A);
+            SKIM_LAUNCH_CHECK();
+            st->ahead_due = false;
+        }
+        auto skim = A.n <= kSkimLdsNodes ? k_skim<true> : k_skim<false>;
+        skim<<<1, kSkimBlock, 0, s>>>(A, s_goal - done, kSkimHandoff, seeds + done, gains + done,
+                                      gain_d ? gain_d + done : nullptr, A.rec_tau + st->selected,
+                                      A.rec_second + st->selected);
         SKIM_LAUNCH_CHECK();
         SkCtl c;
         read_back(&c, A.ctl, sizeof c, s);
+        st->cursor = c.cursor;
         done += c.done;
         st->selected += c.done;
         if (c.flags & kFlagPool) {
@@ -1375,6 +1760,9 @@ void greedy_run(skim_greedy_state *st, uint32_t s_goal, uint32_t *seeds, uint64_
             st->mem->release(A.pool);
             A.pool = np;
             A.pool_cap = cap;
+            fill_u32(&A.ctl->flags, 0, 1, s);
+        } else if (c.flags & kFlagAhead) {
+            st->ahead_due = true;
             fill_u32(&A.ctl->flags, 0, 1, s);
         } else if (c.pend) {
             // the seed's residual search continues on the whole grid, levels
@@ -1587,11 +1975,7 @@ extern "C" skim_status skim_greedy_state_load(const skim_graph *g, uint32_t ell,
         for (const auto &pt : parts)
             if (pt.len)
                 SKIM_HIP(hipMemcpyAsync(pt.dst, b + pt.off, pt.len, hipMemcpyHostToDevice, hs));
-        skim::SkCtl c{};
-        c.cursor = h.cursor;
-        c.pool_used = h.pool_used;
-        SKIM_HIP(hipMemcpyAsync(A.ctl, &c, sizeof c, hipMemcpyHostToDevice, hs));
-        SKIM_HIP(hipStreamSynchronize(hs));
+        skim::greedy_set_ctl(st, h.cursor, h.pool_used, hs);
         st->selected = (uint32_t)h.selected;
         *state = st;
         return SKIM_OK;

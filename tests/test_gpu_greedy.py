@@ -224,3 +224,20 @@ def test_saved_state_refused_for_other_runs():
         assert b.selected == 5
     finally:
         b.free()
+
+
+@pytest.mark.parametrize("n,m,denom,ell,k,s", [
+    (1200, 3600, 2, 16, 8, 20),       # searches past 16 nodes; bits of the pairs in LDS at its limit
+    (1201, 3600, 2, 16, 8, 20),       # ... and past it
+    (3000, 12000, 1, 8, 8, 6),        # searches past 1024 nodes; the window outgrows the pool
+    (20000, 20000, 10, 64, 60, 5),    # nearly all ranks, in several steps
+    (140000, 280000, 1, 2, 4, 3),     # in-lists as pair words, searches of 10^5 nodes
+])
+def test_searches_ahead(oracle_lib, n, m, denom, ell, k, s):
+    from workloads.graphs import Graph, er_graph
+    rp, col = er_graph(n, m, n)
+    g = Graph(n, rp, col, np.full(col.size, 0xFFFFFFFF // denom, dtype=np.uint32))
+    log(f"skim searches ahead n={n} ell={ell} k={k}")
+    seeds, gains, _, _ = gpu_greedy(g, ell, k, 5, [s - 1, 1])
+    ws, wg, _ = oracle_lib.skim(g, 5, ell, k, s)
+    assert np.array_equal(seeds, ws) and np.array_equal(gains, wg)
