@@ -1,23 +1,23 @@
 // skim_greedy.hip -- SKIM greedy seed selection (Section 4, Algorithm 1).
 //
 // State on the device: live reverse and forward lists of every pair, the
-// pairs sorted by rank, covered[pair], size[node], and the inverted index
+// pairs sorted by rank, a few bits per pair, size[node], and the inverted index
 // (for every processed pair, the nodes its reverse search reached).
 //
 // One persistent workgroup runs the selection loop (the loop is sequential
-// per seed); residual searches that grow large continue on the whole grid:
-//  * scan: the next B pairs in rank order each run their complete reverse
-//    search in parallel (one thread per pair; an uncovered pair never reaches
-//    a covered one, so the searches are independent of each other's
-//    increments).  If some node's size reaches k with all B pairs, the first
-//    prefix length T at which one does is the smallest position at which a
-//    filling node receives its (k - size)-th entry, found from the entries
-//    of the filling nodes alone (binary search over prefixes when there are
-//    too many); pairs [0, T) are committed (size increments, index entries),
-//    the rest are re-scanned later.  The nodes that reached k all sit in
-//    pair T-1's search; the smallest id among them is the seed.  Batches
-//    with a long search spread the per-entry work over the block by flat
-//    position instead of per thread.
+// per seed); the searches it scans are made ahead on the whole grid, and
+// residual searches that grow large continue there:
+//  * rank order: made in steps as the loop gets there, the lowest ranks first.
+//  * scan: the reverse searches of the next pairs in rank order (an uncovered
+//    pair never reaches a covered one, so a search is independent of the
+//    others and of the seeds chosen since it was made) are added to the sizes
+//    a batch at a time.  If some node's size reaches k, the first prefix at
+//    which one does is the smallest position at which a filling node receives
+//    its k-th entry, found from the entries of the filling nodes alone (binary
+//    search over prefixes when there are too many); the pairs after it are
+//    taken back and scanned again later, the others are committed (index
+//    entries).  The nodes that reached k all sit in the last committed pair's
+//    search; the smallest id among them is the seed.
 //  * exhaustion: with every rank processed, the unselected node with the
 //    largest size (smallest id on ties) is the seed.
 //  * records: before the residual update, the rank tau of the pair that filled
@@ -25,16 +25,13 @@
 //    the other unselected nodes, one less for nodes in that pair's search)
 //    are stored per seed for the adaptive error estimate (Section 4).
 //  * residual: a level-synchronous forward search from the seed over all
-//    instances at once (each level's frontier of pairs shared by the block)
-//    over live out-edges, not entering covered pairs; every newly covered
-//    pair counts towards the seed's gain and decrements the size of every
-//    node in its index entry, which is then erased.  A level of more than
-//    kSkimHandoff pairs, or a seed with more than kSkimHandoffEdges live
-//    out-edges, ends the workgroup's launch; the host runs the rest of that
-//    search level by level on the whole grid (k_resid_level; pairs of long
-//    out-lists are expanded edge-balanced by the next level's launch) and then
-//    relaunches the loop; a search whose next level there is small again is
-//    handed back, and the relaunched loop resumes it at that level.
+//    instances at once over live out-edges, not entering covered pairs; every
+//    newly covered pair counts towards the seed's gain and decrements the size
+//    of every node in its index entry, which is then erased.  A level of more
+//    than kSkimHandoff pairs, or a seed with more than kSkimHandoffEdges live
+//    out-edges, ends the workgroup's launch; the rest of that search runs level
+//    by level on the whole grid (k_resid_level); a search whose next level
+//    there is small again is handed back, and the relaunched loop resumes it.
 //
 // The adaptive error estimate itself (skim_discrepancy_tail) bounds each
 // seed's discrepancy with eq. (chernoff) on a grid of discrepancy values and
@@ -60,14 +57,19 @@ constexpr int kSkimBlock = 1024;
 constexpr uint32_t kSkimLdsNodes = 20480;  // graphs up to this size keep size[] in LDS
 constexpr uint32_t kSkimPairListNodes = 1u << 17;  // from this size, in-lists as pair words
 constexpr uint32_t kSkimLdsWords = kSkimLdsNodes / 2;
+// ... and up to this size, in the same LDS words, the bits of their pairs (34
+// bytes per node in all).
+constexpr uint32_t kSkimStateNodes = 1200;
+static_assert(kSkimStateNodes % 8 == 0 && kSkimStateNodes / 2 + 8 * kSkimStateNodes <= kSkimLdsWords, "");
 constexpr uint32_t kFlagPool = 1u, kFlagAhead = 2u;
-// Items whose search, index entry or out-list is at most this long are
-// walked by their own thread; a batch or level with a longer one spreads
-// its work over the block by flat position.
+// Searches of at most this many nodes are staged by their own thread; a batch
+// with a longer one is staged by flat position.
 constexpr uint32_t kSkimSerial = 32;
-// ... and a wave whose items all have at most this many walks them lane by
-// lane; with a longer one the wave lays them end to end.
-constexpr uint32_t kSkimFlat = 4;
+// A pair with more live out-edges than this is expanded apart from the other
+// pairs of its level, its edges spread over the whole block or grid: a wave
+// with a few such pairs is the last of a level (10^6 nodes, 50 seeds, with
+// lists above 32, 64, 128 and 256: 20.0, 20.0, 20.6 and 21.4 ms).
+constexpr uint64_t kLongEdges = 64;
 // A residual level with more pairs than this continues on the whole grid.
 constexpr uint64_t kSkimHandoff = 4096;
 // ... and so does a seed whose own live out-edges are more than this.
@@ -75,18 +77,23 @@ constexpr uint64_t kSkimHandoffEdges = 65536;
 // A search on the grid whose next level has at most this many pairs goes
 // back to the workgroup (a level there costs less than two launches).
 constexpr uint64_t kSkimHandBack = 2048;
-// On the grid, pairs with more live out-edges than this are deferred to the
-// next level's launch, which spreads their edges over every workgroup before
-// it takes its own frontier (their heads join the level after it: the
-// covered set does not depend on the order of the expansions).  At most
-// kHeavyItems per level; more are expanded where they are.
-constexpr uint64_t kSplitEdges = 1024;
-constexpr uint32_t kHeavyItems = 1u << 16;
+// Long pairs of a level: in the workgroup at most kBlockItems, on the grid at
+// most kHeavyItems; more are expanded with the others.
+constexpr uint32_t kBlockItems = 64, kHeavyItems = 1u << 16;
+// Levels of a round on the grid: after one, a search that has ended or become
+// small goes back to k_skim.  A multiple of 6: the level counters (three) and
+// the frontier buffers (two) are again where they were.
+constexpr int kRoundLevels = 6;
+// Rounds enqueued before the host reads the control block.
+constexpr int kRounds = 8;
 // Entries of the nodes that fill within a batch, kept to find the filling
 // prefix directly (more: binary search over prefixes).
 constexpr uint32_t kSkimCand = 1024;
 // Entries of a batch that fit in LDS.
 constexpr uint32_t kSkimStage = 8192;
+// Positions of the window whose pairs and searches are in LDS.
+constexpr uint32_t kSkimAt = 2 * kSkimBlock;
+
 // The first kSkimLdsFront entries of a residual level in the workgroup live
 // in LDS (the rest in the queue area): small levels never go through global
 // memory between one level and the next.
@@ -98,7 +105,7 @@ struct SkCtl {
     unsigned long long cursor;     // next position in the rank order
     unsigned long long pool_used;  // index entries in use
     unsigned long long need;       // pool entries a failed batch needed
-    uint32_t done;                 // seeds completed by the last launch
+    uint32_t done;                 // seeds completed in this call
     uint32_t flags;
     // A residual search handed to the whole grid (its frontier outgrew the
     // workgroup): the seed, the frontier buffer of its current level, the
@@ -110,8 +117,8 @@ struct SkCtl {
     // pool entries taken, searches left to the wave and workgroup kernels.
     unsigned long long a_lo, a_w, a_fail, a_used, nlong, ngiant;
     unsigned long long pad2[4];
-    unsigned long long rsize[3 * 16];
-    unsigned long long hsize[3 * 16];  // pairs level L deferred: hsize[16 (L % 3)]
+    unsigned long long rsize[3 * 16];  // pairs of the level (low half); newly covered (high half)
+    unsigned long long hsize[3 * 16];  // long pairs of the level
 };
 
 struct SkArgs {
@@ -127,10 +134,10 @@ struct SkArgs {
     const uint32_t *fadj;
     const uint32_t *order;  // pair ids by increasing rank
     uint64_t ordered;       // of them, in place so far
-    uint32_t *covered;      // [64 n] 0/1
+    uint64_t *state;        // [4 n] bits of 16 pairs, see kCovered
     uint32_t *size;         // [size_words(n)] packed 16-bit counters
     uint32_t *sel;          // [n] 0/1
-    uint64_t *idx;          // [64 n] first pool entry << 32 | entries, 0 = no entry
+    uint64_t *idx;          // [64 n] first pool entry << 32 | entries, of committed pairs
     uint32_t *pool;
     uint64_t pool_cap;
     uint32_t *front;        // [2 * 64 n] residual levels
@@ -139,7 +146,7 @@ struct SkArgs {
     uint64_t apool_cap;
     uint32_t *along;        // [2 kAheadMax] searches left to the wave kernel, to the workgroup kernel
     uint32_t *gqueue;       // [kAheadGiants * n]
-    uint64_t *heavy;        // [3][2 kHeavyItems] grid residual, deferred (pair, count), first out-edge
+    uint32_t *heavy;        // [2][kHeavyItems] long pairs of a grid level
     uint32_t *vis;          // [kAheadGiants * vis_words] visited bitmaps, kept zero
     uint32_t vis_words;     // ceil(n / 32)
     SkCtl *ctl;
@@ -154,26 +161,55 @@ struct SkArgs {
 __host__ __device__ inline uint32_t size_words(uint32_t n) { return (n + 7) / 8 * 4; }
 __device__ __forceinline__ uint32_t half_shift(uint32_t v) { return (v & 1u) << 4; }
 
-// State shared between the block's threads goes through agent-scope atomic
-// loads and stores, so no thread reads a stale cached copy of it.
-template <class T> __device__ __forceinline__ T ld(const T *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Relaxed atomic accesses at scope kScope: kGroup where one workgroup alone
+// reads and writes the data of a launch (k_skim: they are served by the CU's
+// cache and its XCD's L2), kAgent where workgroups on several XCDs share it
+// (atomics then go to the memory side, several times as long).
+constexpr int kGroup = __HIP_MEMORY_SCOPE_WORKGROUP, kAgent = __HIP_MEMORY_SCOPE_AGENT;
+template <int kScope, class T> __device__ __forceinline__ T ld(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, kScope);
 }
-template <class T> __device__ __forceinline__ void st(T *p, T v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+template <int kScope, class T> __device__ __forceinline__ void st(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, kScope);
+}
+template <int kScope> __device__ __forceinline__ uint32_t or_old(uint32_t *p, uint32_t v) {
+    return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, kScope);
 }
 
-__device__ __forceinline__ uint32_t cget(const uint32_t *c, uint32_t v) {
-    return (ld(c + (v >> 1)) >> half_shift(v)) & 0xFFFFu;
+// The bits of 16 pairs in a word: covered (a seed reached it), committed (it
+// has an index entry), and of its live out-list, whether it is not empty and
+// whether it is long (more than kLongEdges).  The atomic that covers a pair
+// returns all four: a pair with neither out-edges nor an entry goes no
+// further, a long list goes to the level's own list of them at once.  (A word
+// per pair and an index word read for each covered pair were 768 MB of random
+// lines on 10^6 nodes; these words are 32 MB.)
+constexpr uint64_t kCovered = 1, kCommitted = 1ull << 16, kHasEdges = 1ull << 32, kLong = 1ull << 48;
+constexpr uint64_t kPairBits = kCovered | kCommitted | kHasEdges | kLong;
+template <int kScope>
+__device__ __forceinline__ bool is_covered(const uint64_t *state, uint32_t p) {
+    return (ld<kScope>(reinterpret_cast<const uint32_t *>(state + (p >> 4))) >> (p & 15u)) & 1u;
 }
-__device__ __forceinline__ void cadd(uint32_t *c, uint32_t v, uint32_t d) {
-    atomicAdd(c + (v >> 1), d << half_shift(v));
+// Sets the covered bit and gives the bits as they were.
+template <int kScope> __device__ __forceinline__ uint64_t cover(uint64_t *state, uint32_t p) {
+    return (__hip_atomic_fetch_or(state + (p >> 4), kCovered << (p & 15u), __ATOMIC_RELAXED, kScope) >>
+            (p & 15u)) & kPairBits;
 }
-__device__ __forceinline__ void csub(uint32_t *c, uint32_t v, uint32_t d) {
-    atomicSub(c + (v >> 1), d << half_shift(v));
+template <int kScope> __device__ __forceinline__ void commit(uint64_t *state, uint32_t p) {
+    __hip_atomic_fetch_or(state + (p >> 4), kCommitted << (p & 15u), __ATOMIC_RELAXED, kScope);
 }
-__device__ __forceinline__ uint32_t cadd_old(uint32_t *c, uint32_t v, uint32_t d) {
-    return (atomicAdd(c + (v >> 1), d << half_shift(v)) >> half_shift(v)) & 0xFFFFu;
+// Frontier entries are a pair and whether it has an index entry.
+constexpr uint32_t kHasEntry = 1u << 31;
+
+template <int kScope> __device__ __forceinline__ uint32_t cget(const uint32_t *c, uint32_t v) {
+    return (ld<kScope>(c + (v >> 1)) >> half_shift(v)) & 0xFFFFu;
+}
+template <int kScope>
+__device__ __forceinline__ uint32_t cadd(uint32_t *c, uint32_t v, uint32_t d) {  // the count as it was
+    return (__hip_atomic_fetch_add(c + (v >> 1), d << half_shift(v), __ATOMIC_RELAXED, kScope) >>
+            half_shift(v)) & 0xFFFFu;
+}
+template <int kScope> __device__ __forceinline__ void csub(uint32_t *c, uint32_t v, uint32_t d) {
+    __hip_atomic_fetch_sub(c + (v >> 1), d << half_shift(v), __ATOMIC_RELAXED, kScope);
 }
 
 // Exclusive prefix sum of v over the block (NT threads, called by all of
@@ -200,11 +236,35 @@ __device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t *wsum, 
     return before + x - v;
 }
 
+// The same for 32-bit values (wave totals below 2^31); `any` is whether flag is
+// set in some thread.
+template <uint32_t NT>
+__device__ __forceinline__ uint64_t block_excl_scan32(uint32_t v, bool flag, uint32_t *wsum,
+                                                      uint64_t &total, bool &any) {
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t x = wave_scan_sum(v);
+    const bool mine = __any(flag);
+    if (lane == 63u) wsum[wave] = x | (mine ? 1u << 31 : 0u);
+    __syncthreads();
+    uint64_t before = 0, tot = 0;
+    uint32_t flags = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < NT / 64; ++w) {
+        const uint32_t word = wsum[w], s = word & ~(1u << 31);
+        flags |= word;
+        before += w < wave ? s : 0;
+        tot += s;
+    }
+    total = tot;
+    any = flags >> 31;
+    return before + x - v;
+}
+
 // The run that holds flat position t: the largest r with ex[r] <= t, for
 // exclusive prefix sums ex[0..NT] (runs of length zero are never returned
 // for t below the total).
-template <uint32_t NT>
-__device__ __forceinline__ uint32_t run_of(const uint64_t *ex, uint64_t t) {
+template <uint32_t NT, class T>
+__device__ __forceinline__ uint32_t run_of(const T *ex, T t) {
     uint32_t lo = 0, hi = NT;  // ex[lo] <= t < ex[hi]
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
@@ -236,180 +296,125 @@ __device__ __forceinline__ uint32_t wave_owner(uint32_t incl, uint32_t j) {
     return r & 63u;
 }
 
-// Work that depends on the length of a search or of an adjacency list is
-// spread over the whole block by flat position (prefix sums over the
-// block's items, then a binary search per position), so one long item
-// does not hold up a level.
-template <uint32_t NT> struct FlatShared {
-    uint64_t ex[NT + 1];   // scan: queue lengths; residual: out-edges
-    uint64_t ex2[NT + 1];  // residual: index entries
-    uint64_t f0[NT];       // residual: first out-edge
-    uint32_t q[NT];        // residual: the pair
-    uint32_t o[NT];        // residual: first index entry
-    uint64_t wsum[NT / 64];
+// Long pairs of a grid level, their out-edges laid end to end.
+struct FlatShared {
+    uint64_t ex[kResidBlock + 1], f0[kResidBlock];
+    uint32_t q[kResidBlock];
+    uint64_t wsum[kResidBlock / 64];
 };
 
 // Appends of a grid-wide residual level, staged in LDS and reserved in
 // global memory once per chunk (one counter serves the whole grid).
 struct ResidStage {
     uint32_t buf[8 * kResidBlock];
-    uint32_t n;
+    uint32_t n, gain;
     unsigned long long base;
 };
 
 struct ScanShared {
-    uint64_t cand[kSkimCand];    // (pair position << 32) | node, nodes that fill
+    uint64_t ex[kSkimBlock + 1];  // the batch's searches, laid end to end
+    uint32_t entry[kSkimStage];
+    uint32_t q[kSkimBlock], o[kSkimBlock];  // root and first pool entry of a search
+    uint64_t cand[kSkimCand];     // (flat position << 32) | node, nodes that fill
     uint32_t seen[kSkimCand];
-    uint32_t entry[kSkimStage];  // the batch's searches, laid end to end
-    uint32_t ncand;
 };
 
-// One chunk of a residual level: frontier entries [base, base + NT) of
-// Fin (fc entries).  Each newly covered pair's index entry is erased (its
-// nodes lose one from their sizes), and its live out-edges cover the pairs
-// they reach in the same instance, appended to Fout (counted in *next).
-// Called by all NT threads of the block.
-// Precheck: read a pair's covered flag before the CAS (fewer atomics when
-// many targets are covered already; one more step of latency).
-template <uint32_t NT, bool Precheck>
-__device__ __forceinline__ void resid_chunk(const SkArgs &A, uint32_t *SZ, const uint32_t *Fin,
-                                            uint32_t *Fout, uint64_t fc, uint64_t base,
-                                            FlatShared<NT> &X, unsigned long long *next,
-                                            ResidStage *stage, unsigned long long *hcount,
-                                            uint64_t *hbuf, const uint32_t *lfin = nullptr,
-                                            uint32_t *lfout = nullptr) {
-    const uint32_t tid = threadIdx.x;
-    // one wave's newly covered pairs: to the stage (when there is one) or
-    // straight to Fout
-    auto push = [&](bool add, uint32_t qw) {
-        if (!stage) {
-            const uint64_t slot = wave_reserve(next, add);
-            if (add) {
-                if (lfout && slot < kSkimLdsFront) lfout[slot] = qw;
-                else st(Fout + slot, qw);
-            }
-            return;
-        }
-        const unsigned long long m = __ballot(add);
-        if (!m) return;
-        const int leader = __ffsll((long long)m) - 1;
-        const uint32_t lane = lane_id();
-        uint32_t pos0 = 0;
-        if ((int)lane == leader) pos0 = atomicAdd(&stage->n, (uint32_t)__popcll(m));
-        const uint32_t pos = (uint32_t)__shfl((int)pos0, leader) +
-                             (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-        if (!add) return;
-        if (pos < 8 * kResidBlock) stage->buf[pos] = qw;
-        else Fout[atomicAdd(next, 1ull)] = qw;  // stage full
-    };
-    auto flush = [&]() {
-        if (!stage) return;
-        __syncthreads();
-        const uint32_t ns = stage->n < 8 * kResidBlock ? stage->n : 8 * kResidBlock;
-        if (tid == 0 && ns) stage->base = atomicAdd(next, (unsigned long long)ns);
-        __syncthreads();
-        const unsigned long long b = stage->base;
-        for (uint32_t j = tid; j < ns; j += NT) Fout[b + j] = stage->buf[j];
-        __syncthreads();
-        if (tid == 0) stage->n = 0;  // before the next chunk's first barrier
-    };
-    const uint64_t e = base + tid;
-    uint32_t q = 0, o = 0, c = 0;
-    uint64_t f0 = 0, deg = 0;
-    if (e < fc) {
-        q = lfin && e < kSkimLdsFront ? lfin[e] : Fin[e];
-        const uint64_t ix = ld(A.idx + q);
-        c = (uint32_t)ix;
-        if (c) {
-            o = (uint32_t)(ix >> 32);
-            st(A.idx + q, (uint64_t)0);
-        }
-        f0 = A.fptr[q];
-        deg = A.fptr[q + 1] - f0;
-        if (hcount && deg > kSplitEdges) {  // deferred to the next level's launch
-            const unsigned long long slot = atomicAdd(hcount, 1ull);
-            if (slot < kHeavyItems) {
-                hbuf[2 * slot] = ((uint64_t)q << 32) | (uint32_t)deg;
-                hbuf[2 * slot + 1] = f0;
-                deg = 0;
-            }
-        }
-    }
-    const bool light = __syncthreads_or(c > kSkimSerial || deg > kSkimSerial) == 0;
-    if (light) {
-        // each wave lays its 64 items' index entries, then their out-edges,
-        // end to end and takes them 64 at a time
-        const uint32_t lane = tid & 63u;
-        if (!__any(c > kSkimFlat)) {  // short everywhere: each lane its own
-            for (uint32_t j = 0; j < c; ++j) csub(SZ, ld(A.pool + o + j), 1u);
-        } else {
-            const uint32_t incl = wave_incl(c), total = (uint32_t)__shfl((int)incl, 63);
-            for (uint32_t base = 0; base < total; base += 64) {
-                const uint32_t j = base + lane, r = wave_owner(incl, j);
-                const uint32_t first = (uint32_t)__shfl((int)incl, (int)r) -
-                                       (uint32_t)__shfl((int)c, (int)r);
-                const uint32_t ro = (uint32_t)__shfl((int)o, (int)r);
-                if (j < total) csub(SZ, ld(A.pool + ro + (j - first)), 1u);
-            }
-        }
-        const uint32_t d = (uint32_t)deg;  // <= kSkimSerial here
-        if (!__any(d > kSkimFlat)) {  // short everywhere: each lane its own
-            for (uint64_t x2 = f0; x2 < f0 + d; ++x2) {
-                const uint32_t qw = A.fadj[x2] * kPairStride + q % kPairStride;
-                const bool add = (!Precheck || !ld(A.covered + qw)) &&
-                                 atomicCAS(A.covered + qw, 0u, 1u) == 0u;
-                push(add, qw);
-            }
-            flush();
-            return;
-        }
-        const uint32_t incl = wave_incl(d), total = (uint32_t)__shfl((int)incl, 63);
-        for (uint32_t base = 0; base < total; base += 64) {
-            const uint32_t j = base + lane, r = wave_owner(incl, j);
-            const uint32_t first = (uint32_t)__shfl((int)incl, (int)r) -
-                                   (uint32_t)__shfl((int)d, (int)r);
-            const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)f0, (int)r);
-            const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(f0 >> 32), (int)r);
-            const uint32_t rq = (uint32_t)__shfl((int)q, (int)r);
-            bool add = false;
-            uint32_t qw = 0;
-            if (j < total) {
-                qw = A.fadj[(((uint64_t)hi << 32) | lo) + (j - first)] * kPairStride +
-                     rq % kPairStride;
-                add = (!Precheck || !ld(A.covered + qw)) &&
-                      atomicCAS(A.covered + qw, 0u, 1u) == 0u;
-            }
-            push(add, qw);
-        }
-        flush();
+// Erases the index entries (words ix) of a wave's covered pairs q that have
+// one: their nodes lose one from their sizes.  Called by all lanes.
+template <int kScope>
+__device__ __forceinline__ void erase_entry(const SkArgs &A, uint32_t *SZ, uint32_t q, uint64_t ix) {
+    const uint32_t lane = lane_id();
+    const bool has = q & kHasEntry;
+    if (!__any(has)) return;
+    // the search's first node is the pair's own
+    if (has) csub<kScope>(SZ, (q & ~kHasEntry) / kPairStride, 1u);
+    const uint32_t c = has ? (uint32_t)ix - 1u : 0u, o = (uint32_t)(ix >> 32) + 1u;
+    if (__any(c >= (1u << 24))) {  // (a prefix sum of longer entries could wrap)
+        for (uint32_t j = 0; j < c; ++j) csub<kScope>(SZ, ld<kScope>(A.pool + o + j), 1u);
         return;
     }
-    uint64_t ctot, dtot;
-    const uint64_t cex = block_excl_scan<NT>(c, X.wsum, ctot);
-    const uint64_t dex = block_excl_scan<NT>(deg, X.wsum, dtot);
-    X.ex2[tid] = cex;
-    X.ex[tid] = dex;
-    X.q[tid] = q;
-    X.o[tid] = o;
-    X.f0[tid] = f0;
-    if (tid == 0) {
-        X.ex2[NT] = ctot;
-        X.ex[NT] = dtot;
+    const uint32_t incl = wave_scan_sum(c);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    for (uint32_t b = 0; b < total; b += 64) {
+        const uint32_t j = b + lane, w = wave_owner(incl, j);
+        const uint32_t first = (uint32_t)__shfl((int)(incl - c), (int)w);
+        const uint32_t wo = (uint32_t)__shfl((int)o, (int)w);
+        if (j < total) csub<kScope>(SZ, ld<kScope>(A.pool + wo + (j - first)), 1u);
     }
-    __syncthreads();
-    for (uint64_t t = tid; t < ctot; t += NT) {
-        const uint32_t r = run_of<NT>(X.ex2, t);
-        csub(SZ, ld(A.pool + X.o[r] + (t - X.ex2[r])), 1u);
+}
+
+// One wave's share of a residual level: frontier entries base + 0 .. 64 R - 1
+// of fc, R per lane so that R accesses per lane are in flight at each step of
+// the chain (out-list, out-edge, cover).  The out-edges are laid end to end,
+// kResidEdges per lane at a time, and the bits of the pairs they reach, as
+// they were, go to `push`.  Index entries of
+// the frontier's pairs are erased.
+constexpr int kResidEdges = 4;
+template <int R> struct ResidWave {
+    uint64_t f0[64 * R];
+    uint32_t ex[64 * R + 1], q[64 * R];
+};
+template <int kScope, int R, class Fin, class Push>
+__device__ __forceinline__ void resid_wave(const SkArgs &A, uint32_t *SZ, uint64_t *ST, uint64_t base,
+                                           uint64_t fc, ResidWave<R> &W, Fin fin,
+                                           Push push) {
+    const uint32_t lane = lane_id();
+    uint32_t q[R];
+    uint64_t f0[R], deg[R], ix[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) q[r] = base + 64 * r + lane < fc ? fin(base + 64 * r + lane) : 0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        f0[r] = deg[r] = 0;
+        if (base + 64 * r + lane < fc) {
+            const uint32_t p = q[r] & ~kHasEntry;
+            f0[r] = A.fptr[p];
+            deg[r] = A.fptr[p + 1] - f0[r];
+        }
     }
-    for (uint64_t t = tid; t < dtot; t += NT) {
-        const uint32_t r = run_of<NT>(X.ex, t);
-        const uint32_t qw = A.fadj[X.f0[r] + (t - X.ex[r])] * kPairStride + X.q[r] % kPairStride;
-        const bool add =
-            (!Precheck || !ld(A.covered + qw)) && atomicCAS(A.covered + qw, 0u, 1u) == 0u;
-        push(add, qw);
+#pragma unroll
+    for (int r = 0; r < R; ++r) ix[r] = q[r] & kHasEntry ? A.idx[q[r] & ~kHasEntry] : 0ull;
+    for (;;) {
+        // at most 2^22 edges of a pair at a time: their sum does not wrap
+        uint32_t total = 0, part[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            part[r] = (uint32_t)min(deg[r], (uint64_t)(1u << 22));
+            const uint32_t incl = wave_scan_sum(part[r]);
+            W.ex[64 * r + lane] = total + incl - part[r];
+            W.f0[64 * r + lane] = f0[r];
+            W.q[64 * r + lane] = q[r] % kPairStride;
+            total += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        }
+        if (total == 0) break;
+        if (lane == 0) W.ex[64 * R] = total;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (uint32_t b = 0; b < total; b += 64 * kResidEdges) {
+            uint32_t qw[kResidEdges];
+            bool add[kResidEdges];
+#pragma unroll
+            for (int u = 0; u < kResidEdges; ++u) {
+                const uint32_t t = b + 64 * u + lane;
+                add[u] = t < total;
+                qw[u] = 0;
+                if (add[u]) {
+                    const uint32_t r = run_of<64 * R>(W.ex, t);
+                    qw[u] = A.fadj[W.f0[r] + (t - W.ex[r])] * kPairStride + W.q[r];
+                }
+            }
+            uint64_t was[kResidEdges];
+#pragma unroll
+            for (int u = 0; u < kResidEdges; ++u) was[u] = add[u] ? cover<kScope>(ST, qw[u]) : kCovered;
+            push(was, qw);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            f0[r] += part[r];
+            deg[r] -= part[r];
+        }
     }
-    flush();
-    __syncthreads();  // the chunk's LDS arrays are reused
+#pragma unroll
+    for (int r = 0; r < R; ++r) erase_entry<kScope>(A, SZ, q[r], ix[r]);
 }
 
 // ------------------------------------------------------- searches ahead
@@ -470,7 +475,7 @@ __global__ void __launch_bounds__(kAheadBlock) k_ahead_short(SkArgs A) {
         bool more = false;
         if (r < w) {
             const uint32_t p = A.order[lo + r];
-            if (!A.covered[p]) {
+            if (!is_covered<kAgent>(A.state, p)) {
                 const uint32_t i = p % kPairStride;
                 s_q[0][tid] = p / kPairStride;
                 cnt = 1;
@@ -610,8 +615,8 @@ __global__ void __launch_bounds__(kAheadGiantBlock) k_ahead_giant(SkArgs A) {
         const uint32_t r = A.along[kAheadMax + x], p = A.order[lo + r], i = p % kPairStride;
         if (tid == 0) {
             const uint32_t v = p / kPairStride;
-            st(Q, v);
-            atomicOr(V + (v >> 5), 1u << (v & 31u));
+            st<kGroup>(Q, v);
+            or_old<kGroup>(V + (v >> 5), 1u << (v & 31u));
             s_tail = 1;
         }
         __syncthreads();
@@ -621,7 +626,7 @@ __global__ void __launch_bounds__(kAheadGiantBlock) k_ahead_giant(SkArgs A) {
             if (head >= tail) break;  // uniform
             const uint32_t take = min((uint32_t)kAheadGiantBlock, tail - head);
             InList L = {0, 0, 0, true};
-            if (tid < take) L = in_list(A, ld(Q + head + tid) * kPairStride + i);
+            if (tid < take) L = in_list(A, ld<kGroup>(Q + head + tid) * kPairStride + i);
             head += take;
             uint32_t at = 0;  // entries of this lane's list laid out so far
             while (__any(at < L.count)) {
@@ -644,7 +649,7 @@ __global__ void __launch_bounds__(kAheadGiantBlock) k_ahead_giant(SkArgs A) {
                     if (j < total) {
                         v = in_node(A, M, j - first);
                         const uint32_t bit = 1u << (v & 31u);
-                        add = !(ld(V + (v >> 5)) & bit) && !(atomicOr(V + (v >> 5), bit) & bit);
+                        add = !(ld<kGroup>(V + (v >> 5)) & bit) && !(or_old<kGroup>(V + (v >> 5), bit) & bit);
                     }
                     const uint64_t m = __ballot(add);
                     if (m) {
@@ -653,7 +658,7 @@ __global__ void __launch_bounds__(kAheadGiantBlock) k_ahead_giant(SkArgs A) {
                             pos = atomicAdd(&s_tail, (uint32_t)__popcll(m));
                         pos = (uint32_t)__shfl((int)pos, __ffsll((long long)m) - 1) +
                               (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-                        if (add) st(Q + pos, v);  // each node once: at most n
+                        if (add) st<kGroup>(Q + pos, v);  // each node once: at most n
                     }
                 }
                 at += part;
@@ -666,8 +671,8 @@ __global__ void __launch_bounds__(kAheadGiantBlock) k_ahead_giant(SkArgs A) {
         const unsigned long long base = s_base;
         const bool fits = base + cnt <= A.apool_cap;
         for (uint32_t j = tid; j < cnt; j += kAheadGiantBlock) {
-            const uint32_t v = ld(Q + j);
-            st(V + (v >> 5), 0u);
+            const uint32_t v = ld<kGroup>(Q + j);
+            st<kGroup>(V + (v >> 5), 0u);
             if (fits) A.apool[base + j] = v;
         }
         if (tid == 0) {
@@ -680,26 +685,48 @@ __global__ void __launch_bounds__(kAheadGiantBlock) k_ahead_giant(SkArgs A) {
 
 // The selection loop.  kLds: size[] is in LDS (graphs of at most
 // kSkimLdsNodes nodes: every search adds to it, and device atomics from
-// different waves on one cache line are serialised).
-template <bool kLds>
-__global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, uint64_t handoff,
+// different waves on one cache line are serialised).  kLdsState: so are the
+// pairs' bits (at most kSkimStateNodes nodes), one access to the L2 less, of
+// 0.5 us, per batch and per residual level (1000 nodes, 200 seeds: 3.5 to 3.1 ms).
+//
+// What bounds it: the chain of accesses and barriers, about 3 us per batch,
+// 3 us per seed's first filling prefix and 2 us per residual level.  1000
+// nodes, l = k = 64, 200 seeds: 6.0 ms with a search per thread in each batch
+// and six barriers per level, 2.6 ms now; 10^6 nodes, 50 seeds: 20 and 5 ms.
+template <bool kLds, bool kLdsState>
+__global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, bool begin, uint64_t handoff,
                                                      uint32_t *seeds, uint64_t *gains,
                                                      double *gain_d, uint64_t *rec_tau,
                                                      uint32_t *rec_second) {
-    __shared__ unsigned long long s_cursor, s_pool, s_gain, s_best, s_tau, s_fcnt[2];
+    __shared__ unsigned long long s_cursor, s_pool, s_gain, s_best, s_tau;
     __shared__ int s_x;
-    __shared__ uint32_t s_stop, s_second, s_xmin, s_resume, s_rcur;
+    __shared__ uint32_t s_stop, s_second, s_xmin, s_ncand, s_resume, s_rcur, s_T, s_found;
     __shared__ unsigned long long s_fill0, s_fill1;
+    __shared__ uint32_t s_fcnt[3], s_hcnt[3], s_wsum[kSkimBlock / 64];
     __shared__ __align__(16) uint32_t s_size[kLds ? kSkimLdsWords : 4];
-    __shared__ FlatShared<kSkimBlock> X;
-    __shared__ ScanShared C;
+    __shared__ union {
+        ScanShared scan;                     // while pairs are scanned
+        ResidWave<4> wave[kSkimBlock / 64];  // in the residual search
+    } s_u;
+    ScanShared &C = s_u.scan;
+    __shared__ uint64_t s_ahead[kSkimAt];
+    __shared__ uint32_t s_pair[kSkimAt];
     __shared__ uint32_t s_front[2][kSkimLdsFront];
+    __shared__ uint32_t s_long[2][kBlockItems];
     const uint32_t tid = threadIdx.x;
     const uint32_t n = A.n, k = A.k;
+    // launches are enqueued ahead: nothing to do while a search is on the
+    // grid, a request waits for the host or the call's seeds are complete
+    const uint32_t it0 = begin ? 0u : A.ctl->done;
+    if (A.ctl->pend == 1 || A.ctl->flags || it0 >= goal) return;
     uint32_t *SZ = kLds ? s_size : A.size;
     const uint32_t swords = size_words(n);
+    uint64_t *ST = kLdsState ? reinterpret_cast<uint64_t *>(s_size + size_words(kSkimStateNodes))
+                             : A.state;
+    if constexpr (kLdsState)
+        for (uint32_t w = tid; w < 4 * n; w += kSkimBlock) ST[w] = ld<kGroup>(A.state + w);
     if constexpr (kLds)
-        for (uint32_t w = tid; w < swords; w += kSkimBlock) s_size[w] = ld(A.size + w);
+        for (uint32_t w = tid; w < swords; w += kSkimBlock) s_size[w] = ld<kGroup>(A.size + w);
     const uint64_t a_lo = A.ctl->a_lo;
     const uint64_t a_hi = min((unsigned long long)A.ordered,
                               a_lo + min(A.ctl->a_w, A.ctl->a_fail));
@@ -707,7 +734,7 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
         s_cursor = A.ctl->cursor;
         s_pool = A.ctl->pool_used;
         s_stop = 0;
-        C.ncand = 0;
+        s_ncand = s_found = 0;
         // a residual search the grid handed back (its frontier got small):
         // the launch starts by finishing that seed
         s_resume = A.ctl->pend == 2;
@@ -715,8 +742,8 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
             A.ctl->pend = 0;
             s_x = (int)A.ctl->px;
             s_rcur = A.ctl->rcur;
-            s_gain = A.ctl->rgain;
-            s_fcnt[s_rcur] = A.ctl->rsize[0];
+            s_gain = A.ctl->rgain + (A.ctl->rsize[0] >> 32);
+            s_fcnt[0] = (uint32_t)A.ctl->rsize[0];
         }
     }
     __syncthreads();
@@ -724,14 +751,17 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
     // staged in LDS when there is room for all of them.
     bool staged = true;
     auto far_entry = [&](uint64_t t) {
-        const uint32_t r = run_of<kSkimBlock>(X.ex, t);
-        const uint32_t j = (uint32_t)(t - X.ex[r]);
-        return j ? A.apool[(uint64_t)X.o[r] + j] : X.q[r];
+        const uint32_t r = run_of<kSkimBlock>(C.ex, t);
+        const uint32_t j = (uint32_t)(t - C.ex[r]);
+        return j ? A.apool[(uint64_t)C.o[r] + j] : C.q[r];
     };
     auto entry = [&](uint64_t t) { return staged ? C.entry[t] : far_entry(t); };
-    uint32_t done = 0;
-    for (uint32_t it = 0; it < goal; ++it) {
-        const bool resumed = it == 0 && s_resume;  // uniform
+    uint64_t at0 = 0, at1 = 0;  // positions in s_pair and s_ahead
+    uint32_t tag = 0;            // of the batch, in s_found if some node reaches k
+    uint32_t batch = kSkimBlock, taken = 0;  // pairs of a batch; taken since the last seed
+    uint32_t it = it0;
+    for (; it < goal; ++it) {
+        const bool resumed = it == it0 && s_resume;  // uniform
         if (!resumed) {
         if (tid == 0) {
             s_x = -1;
@@ -759,35 +789,50 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
                 __syncthreads();
                 break;
             }
-            // sizes are below k here and grow by at most one per pair: they
+            // The batch: what a seed took before, four times, so that most
+            // batches of a run of filling ones fill and few pairs are added
+            // in vain.
+            // Sizes are below k here and grow by at most one per pair: they
             // stay in 16 bits with all of a batch added
-            const uint32_t B = (uint32_t)min(a_hi - cursor,
-                                             (uint64_t)min((uint32_t)kSkimBlock, 65536u - k));
-            uint32_t cnt = 0, p = 0, first = 0;
-            if (tid < B) {
-                p = A.order[cursor + tid];
-                const uint64_t a = A.ahead[cursor - a_lo + tid];
-                if (!ld(A.covered + p)) {
-                    cnt = (uint32_t)a;
-                    first = (uint32_t)(a >> 32);
+            const uint32_t B = (uint32_t)min(a_hi - cursor, (uint64_t)min(batch, 65536u - k));
+            if (cursor < at0 || cursor + B > at1) {  // uniform
+                at0 = cursor;
+                at1 = min(a_hi, cursor + kSkimAt);
+                for (uint32_t j = tid; j < at1 - at0; j += kSkimBlock) {
+                    s_pair[j] = A.order[cursor + j];
+                    s_ahead[j] = A.ahead[cursor - a_lo + j];
                 }
+                __syncthreads();
+            }
+            uint32_t cnt = 0, p = 0, first = 0, next = 0;
+            if (tid < B) {
+                p = s_pair[cursor - at0 + tid];
+                const uint64_t a = s_ahead[cursor - at0 + tid];
+                first = (uint32_t)(a >> 32);
+                // (the second node is on its way with the pair's bits)
+                if ((uint32_t)a > 1) next = A.apool[(uint64_t)first + 1];
+                if (!is_covered<kGroup>(ST, p)) cnt = (uint32_t)a;
             }
             uint64_t tot;
-            const uint64_t ex = block_excl_scan<kSkimBlock>(cnt, X.wsum, tot);
-            X.ex[tid] = ex;
-            X.q[tid] = p / kPairStride;
-            X.o[tid] = first;
+            bool longer;
+            const uint64_t ex =
+                block_excl_scan32<kSkimBlock>(cnt, cnt > kSkimSerial, s_wsum, tot, longer);
+            C.ex[tid] = ex;
+            C.q[tid] = p / kPairStride;
+            C.o[tid] = first;
             if (tid == 0) {
-                X.ex[kSkimBlock] = tot;
+                C.ex[kSkimBlock] = tot;
                 s_xmin = 0xFFFFFFFFu;
             }
             staged = tot <= kSkimStage;
             if (staged) {
-                if (__syncthreads_or(cnt > kSkimSerial)) {
+                if (longer) {
+                    __syncthreads();  // C.ex and the roots are in place
                     for (uint64_t t = tid; t < tot; t += kSkimBlock) C.entry[t] = far_entry(t);
                 } else if (cnt) {
                     C.entry[ex] = p / kPairStride;
-                    for (uint32_t j = 1; j < cnt; ++j)
+                    if (cnt > 1) C.entry[ex + 1] = next;
+                    for (uint32_t j = 2; j < cnt; ++j)
                         C.entry[ex + j] = A.apool[(uint64_t)first + j];
                 }
             }
@@ -800,35 +845,58 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
             // pairs after that prefix are then taken back.
             bool f = false;
             for (uint64_t t = tid; t < tot; t += kSkimBlock)
-                f |= cadd_old(SZ, entry(t), 1u) + 1 >= k;
-            const bool filled = __syncthreads_or(f) != 0;
+                f |= cadd<kGroup>(SZ, entry(t), 1u) + 1 >= k;
+            ++tag;
+            if (__any(f) && (tid & 63u) == 0) s_found = tag;
+            __syncthreads();
+            const bool filled = s_found == tag;
             uint32_t T = B;
             if (filled) {
-                for (uint64_t t = tid; t < tot; t += kSkimBlock) {
-                    const uint32_t v = entry(t);
-                    if (cget(SZ, v) < k) continue;
-                    const uint32_t slot = atomicAdd(&C.ncand, 1u);
-                    if (slot < kSkimCand) {
-                        C.cand[slot] = ((uint64_t)run_of<kSkimBlock>(X.ex, t) << 32) | v;
+                for (uint64_t t0 = 0; t0 < tot; t0 += kSkimBlock) {
+                    const uint64_t t = t0 + tid;
+                    const uint32_t v = t < tot ? entry(t) : 0u;
+                    const bool fills = t < tot && cget<kGroup>(SZ, v) >= k;
+                    const uint64_t m = __ballot(fills);
+                    if (!m) continue;
+                    uint32_t slot = 0;
+                    if ((tid & 63u) == 0) slot = atomicAdd(&s_ncand, (uint32_t)__popcll(m));
+                    slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot) +
+                           (uint32_t)__popcll(m & ((1ull << (tid & 63u)) - 1ull));
+                    if (fills && slot < kSkimCand) {
+                        C.cand[slot] = (t << 32) | v;  // (t below 1024 n <= 2^32)
                         C.seen[slot] = 0;
                     }
                 }
                 __syncthreads();
                 // moves the sizes from prefix `from` of the batch to prefix `to`
                 auto move = [&](uint32_t from, uint32_t to) {
-                    for (uint64_t t = X.ex[min(from, to)] + tid; t < X.ex[max(from, to)];
+                    for (uint64_t t = C.ex[min(from, to)] + tid; t < C.ex[max(from, to)];
                          t += kSkimBlock) {
-                        if (from < to) cadd(SZ, entry(t), 1u);
-                        else csub(SZ, entry(t), 1u);
+                        if (from < to) cadd<kGroup>(SZ, entry(t), 1u);
+                        else csub<kGroup>(SZ, entry(t), 1u);
                     }
                     __syncthreads();
                 };
-                const uint32_t nc = C.ncand;
+                const uint32_t nc = s_ncand;
                 uint32_t at = B;
-                if (nc <= kSkimCand) {
-                    // per candidate: entries of its node in the batch (high
-                    // half) and those at earlier positions, the other
-                    // candidates dealt over the block's threads
+                if (nc <= 64) {
+                    // every wave by itself, a candidate per lane: entries of
+                    // its node in the batch and those at earlier positions
+                    const uint32_t lane = tid & 63u;
+                    const uint64_t e = lane < nc ? C.cand[lane] : ~0ull;
+                    const uint32_t v = (uint32_t)e, pos = (uint32_t)(e >> 32);
+                    uint32_t same = 0, before = 0;
+                    for (uint32_t c2 = 0; c2 < nc; ++c2) {
+                        const uint32_t v2 = (uint32_t)__builtin_amdgcn_readlane((int)v, (int)c2);
+                        const uint32_t p2 = (uint32_t)__builtin_amdgcn_readlane((int)pos, (int)c2);
+                        same += v2 == v;
+                        before += v2 == v && p2 < pos;
+                    }
+                    const bool kth = lane < nc && cget<kGroup>(SZ, v) - same + before + 1 == k;
+                    T = group_min_u32<64>(kth ? pos : 0xFFFFFFFFu);
+                } else if (nc <= kSkimCand) {
+                    // the same with the pairs of candidates dealt over the
+                    // block's threads (both counts in one word)
                     const uint32_t parts = kSkimBlock / nc, c = tid % nc, part = tid / nc;
                     if (part < parts) {
                         const uint64_t e = C.cand[c];
@@ -843,11 +911,11 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
                     for (uint32_t c = tid; c < nc; c += kSkimBlock) {
                         const uint64_t e = C.cand[c];
                         const uint32_t seen = C.seen[c];
-                        if (cget(SZ, (uint32_t)e) - (seen >> 16) + (seen & 0xFFFFu) + 1 == k)
+                        if (cget<kGroup>(SZ, (uint32_t)e) - (seen >> 16) + (seen & 0xFFFFu) + 1 == k)
                             atomicMin(&s_xmin, (uint32_t)(e >> 32));
                     }
                     __syncthreads();
-                    T = s_xmin + 1;
+                    T = s_xmin;
                 } else {
                     uint32_t none = 0;  // prefixes none and T: nothing fills, something does
                     while (T - none > 1) {
@@ -855,51 +923,65 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
                         move(at, mid);
                         at = mid;
                         bool g = false;
-                        for (uint64_t t = tid; t < X.ex[mid]; t += kSkimBlock)
-                            g |= cget(SZ, entry(t)) >= k;
-                        if (__syncthreads_or(g)) T = mid;
+                        for (uint64_t t = tid; t < C.ex[mid]; t += kSkimBlock)
+                            g |= cget<kGroup>(SZ, entry(t)) >= k;
+                        ++tag;
+                        if (__any(g) && (tid & 63u) == 0) s_found = tag;
+                        __syncthreads();
+                        if (s_found == tag) T = mid;
                         else none = mid;
                     }
+                }
+                if (nc <= kSkimCand) {  // T is a flat position: its pair's prefix
+                    if (T - (uint32_t)ex < cnt) s_T = tid + 1;
+                    __syncthreads();
+                    T = s_T;
                 }
                 move(at, T);
                 if (tid == 0) s_xmin = 0xFFFFFFFFu;
             }
             // does the committed prefix fit in the index pool?
-            const uint64_t need = X.ex[T], pbase = s_pool;
+            const uint64_t need = C.ex[T], pbase = s_pool;
             if (pbase + need > A.pool_cap) {
-                for (uint64_t t = tid; t < need; t += kSkimBlock) csub(SZ, entry(t), 1u);
+                for (uint64_t t = tid; t < need; t += kSkimBlock) csub<kGroup>(SZ, entry(t), 1u);
                 if (tid == 0) {
                     A.ctl->flags |= kFlagPool;
                     A.ctl->need = pbase + need;
                     s_stop = 1;
-                    C.ncand = 0;
+                    s_ncand = 0;
                 }
                 __syncthreads();
                 break;
             }
             // commit pairs [0, T): index entries in pair order
-            for (uint64_t t = tid; t < need; t += kSkimBlock) st(A.pool + pbase + t, entry(t));
-            if (tid < T && cnt) st(A.idx + p, ((pbase + ex) << 32) | cnt);
+            for (uint64_t t = tid; t < need; t += kSkimBlock) st<kGroup>(A.pool + pbase + t, entry(t));
+            if (tid < T && cnt) {
+                st<kGroup>(A.idx + p, ((pbase + ex) << 32) | cnt);
+                commit<kGroup>(ST, p);
+            }
             if (filled) {
                 // the nodes that just reached k are in pair T - 1's search;
                 // the seed is the smallest of them
                 __syncthreads();
-                for (uint64_t t = X.ex[T - 1] + tid; t < need; t += kSkimBlock) {
+                for (uint64_t t = C.ex[T - 1] + tid; t < need; t += kSkimBlock) {
                     const uint32_t v = entry(t);
-                    if (cget(SZ, v) >= k) atomicMin(&s_xmin, v);
+                    if (cget<kGroup>(SZ, v) >= k) atomicMin(&s_xmin, v);
                 }
                 if (tid == T - 1) s_tau = pair_rank(A.seed, p);
                 __syncthreads();
             }
+            taken += T;
+            batch = filled ? min((uint32_t)kSkimBlock, max(64u, 4 * taken)) : (uint32_t)kSkimBlock;
+            if (filled) taken = 0;
             if (tid == 0) {
                 if (filled) {
                     s_x = s_xmin == 0xFFFFFFFFu ? -1 : (int)s_xmin;
-                    s_fill0 = X.ex[T - 1];
+                    s_fill0 = C.ex[T - 1];
                     s_fill1 = need;
                 }
                 s_cursor = cursor + T;
                 s_pool = pbase + need;
-                C.ncand = 0;
+                s_ncand = 0;
             }
             __syncthreads();
         }
@@ -910,9 +992,9 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
             __syncthreads();
             unsigned long long best = 0;
             for (uint32_t v = tid; v < n; v += kSkimBlock)
-                if (!ld(A.sel + v)) {
+                if (!ld<kGroup>(A.sel + v)) {
                     const unsigned long long key =
-                        ((unsigned long long)cget(SZ, v) << 32) | (0xFFFFFFFFu - v);
+                        ((unsigned long long)cget<kGroup>(SZ, v) << 32) | (0xFFFFFFFFu - v);
                     best = key > best ? key : best;
                 }
             atomicMax(&s_best, best);
@@ -934,19 +1016,15 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
         const uint64_t fill0 = s_fill0, fill1 = s_fill1;
         for (uint64_t t = fill0 + tid; t < fill1; t += kSkimBlock) {
             const uint32_t v = entry(t);
-            if (v != xs) csub(SZ, v, 1u);
+            if (v != xs) csub<kGroup>(SZ, v, 1u);
         }
         uint32_t xsize = 0;
         if (tid == 0) {
             s_second = 0;
-            xsize = cget(SZ, xs);
-            csub(SZ, xs, xsize);
+            xsize = cget<kGroup>(SZ, xs);
+            csub<kGroup>(SZ, xs, xsize);
         }
-        // (the atomics above have reached the L2 before the barrier; the
-        // fence after it drops this CU's cached copies of the sizes)
-        __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        if constexpr (!kLds) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         {
             // eight sizes per load, eight loads in flight: one workgroup reads
             // the 2 MB of 10^6 nodes
@@ -975,10 +1053,10 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
         __syncthreads();
         for (uint64_t t = fill0 + tid; t < fill1; t += kSkimBlock) {
             const uint32_t v = entry(t);
-            if (v != xs) cadd(SZ, v, 1u);
+            if (v != xs) cadd<kGroup>(SZ, v, 1u);
         }
         if (tid == 0) {
-            cadd(SZ, xs, xsize);
+            cadd<kGroup>(SZ, xs, xsize);
             rec_tau[it] = fill1 ? (uint64_t)s_tau : ~0ull;
             rec_second[it] = s_second;
         }
@@ -986,51 +1064,58 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
         const uint32_t x = (uint32_t)s_x;
         // ------------------------------------------------- residual problem
         // Level-synchronous over all instances at once: a frontier of pairs
-        // (64 v + i) in two halves of the queue area.  A pair is
-        // claimed by the CAS that covers it; its index entry is erased then.
+        // (64 v + i) in two halves of the queue area.  A pair is claimed by
+        // the atomic that covers it.  One barrier a level: level L reads
+        // counter L % 3, appends to (L + 1) % 3 and clears (L + 2) % 3.
+        // Pairs of long out-lists are expanded by the whole block.  (10^6 nodes, levels of 1 to 4 thousand
+        // pairs: 1024 pairs at a time with six barriers each 30 us a level.)
         // A level with more than `handoff` pairs (0: none) and the rest of
         // the search go to the whole grid (k_resid_level); the host then
         // completes the seed.
         uint32_t *F[2] = {A.front, A.front + (uint64_t)A.n * kPairStride};
-        if (!resumed) {
+        const uint32_t par0 = resumed ? s_rcur : 0u;  // buffer of local level 0
         if (tid == 0) {
-            s_gain = 0;
-            s_fcnt[0] = 0;
+            s_fcnt[1] = s_fcnt[2] = 0;
+            s_hcnt[1] = s_hcnt[2] = 0;
+            if (resumed) s_hcnt[0] = 0;
         }
-        __syncthreads();
-        {
-            bool add = false;
-            uint32_t px = 0;
-            if (tid < A.ell) {
-                px = x * kPairStride + tid;
-                add = atomicCAS(A.covered + px, 0u, 1u) == 0u;
-            }
+        if (!resumed) {
             if (tid < 64) {  // the first wave holds every instance (l <= 64)
-                const uint64_t slot = wave_reserve(&s_fcnt[0], add);
-                if (add) s_front[0][slot] = px;
+                const uint32_t px = x * kPairStride + tid;
+                const uint64_t was = tid < A.ell ? cover<kGroup>(ST, px) : kCovered;
+                const bool fresh = !(was & kCovered);
+                const bool any = fresh && (was & (kHasEdges | kCommitted));
+                const bool big = any && (was & kLong), add = any && !big;
+                const uint64_t m = __ballot(add), mb = __ballot(big), below = (1ull << tid) - 1ull;
+                const uint32_t e = px | (was & kCommitted ? kHasEntry : 0u);
+                if (add) s_front[0][__popcll(m & below)] = e;
+                if (big) s_long[0][__popcll(mb & below)] = e;  // l <= kBlockItems
+                const uint64_t g = __ballot(fresh);
+                if (tid == 0) {
+                    s_fcnt[0] = (uint32_t)__popcll(m);
+                    s_hcnt[0] = (uint32_t)__popcll(mb);
+                    s_gain = (unsigned long long)__popcll(g);
+                }
             }
-        }
         } else {
             // the grid left the pending level in the queue area
-            const uint64_t fc = s_fcnt[s_rcur];
-            for (uint32_t e = tid; e < fc && e < kSkimLdsFront; e += kSkimBlock)
-                s_front[s_rcur][e] = F[s_rcur][e];
+            for (uint32_t e = tid; e < s_fcnt[0] && e < kSkimLdsFront; e += kSkimBlock)
+                s_front[par0][e] = F[par0][e];
         }
         bool handed = false;
         const uint64_t seed_edges = A.fptr[(uint64_t)x * kPairStride + kPairStride] -
                                     A.fptr[(uint64_t)x * kPairStride];
-        // a resumed search continues at its pending level (not level 0)
-        for (uint32_t cur = resumed ? s_rcur : 0u, level = resumed ? 1u : 0u;;
-             cur ^= 1u, ++level) {
+        for (uint32_t L = 0;; ++L) {
             __syncthreads();
-            // (the counter reset below is of the next level's counter, read
-            // by nobody in this level)
-            const uint64_t fc = s_fcnt[cur];
-            if (fc == 0) break;
-            if (handoff && (fc > handoff || (level == 0 && seed_edges > kSkimHandoffEdges))) {
+            const uint32_t cur = (par0 + L) & 1u, c0 = L % 3, c1 = (L + 1) % 3, c2 = (L + 2) % 3;
+            const uint32_t fc = s_fcnt[c0], nh = min(s_hcnt[c0], kBlockItems);
+            if (fc == 0 && nh == 0) break;
+            if (handoff &&
+                (fc > handoff || (L == 0 && !resumed && seed_edges > kSkimHandoffEdges))) {
                 // the grid reads the level from the queue area
+                if (tid < nh) st<kGroup>(A.heavy + (uint64_t)kHeavyItems * cur + tid, s_long[cur][tid]);
                 for (uint32_t e = tid; e < fc && e < kSkimLdsFront; e += kSkimBlock)
-                    st(F[cur] + e, s_front[cur][e]);
+                    st<kGroup>(F[cur] + e, s_front[cur][e]);
                 if (tid == 0) {
                     A.ctl->pend = 1;
                     A.ctl->px = x;
@@ -1038,152 +1123,289 @@ __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, ui
                     A.ctl->rsize[0] = fc;
                     A.ctl->rsize[16] = 0;
                     A.ctl->rsize[32] = 0;
-                    A.ctl->hsize[0] = A.ctl->hsize[16] = A.ctl->hsize[32] = 0;
+                    A.ctl->hsize[0] = nh;
+                    A.ctl->hsize[16] = A.ctl->hsize[32] = 0;
                     A.ctl->rgain = s_gain;
                 }
                 handed = true;
                 break;
             }
             if (tid == 0) {
-                s_fcnt[cur ^ 1u] = 0;
-                s_gain += fc;
+                s_fcnt[c2] = s_hcnt[c2] = 0;
             }
-            for (uint64_t base = 0; base < fc; base += kSkimBlock)
-                resid_chunk<kSkimBlock, false>(A, SZ, F[cur], F[cur ^ 1u], fc, base, X,
-                                               &s_fcnt[cur ^ 1u], nullptr, nullptr, nullptr,
-                                               s_front[cur], s_front[cur ^ 1u]);
+            auto fin = [&](uint64_t e) { return e < kSkimLdsFront ? s_front[cur][e] : ld<kGroup>(F[cur] + e); };
+            auto push = [&](const uint64_t (&was)[kResidEdges], const uint32_t (&qw)[kResidEdges]) {
+                uint64_t m[kResidEdges];
+                uint32_t all = 0, fresh = 0, pos = 0;
+                bool add[kResidEdges];
+#pragma unroll
+                for (int u = 0; u < kResidEdges; ++u) {
+                    add[u] = !(was[u] & kCovered) && (was[u] & (kHasEdges | kCommitted));
+                    fresh += (uint32_t)__popcll(__ballot(!(was[u] & kCovered)));
+                    if (add[u] && (was[u] & kLong)) {
+                        const uint32_t slot = atomicAdd(&s_hcnt[c1], 1u);
+                        if (slot < kBlockItems) {
+                            s_long[cur ^ 1u][slot] = qw[u] | (was[u] & kCommitted ? kHasEntry : 0u);
+                            add[u] = false;
+                        }
+                    }
+                    m[u] = __ballot(add[u]);
+                    all += (uint32_t)__popcll(m[u]);
+                }
+                if (!fresh) return;
+                if (lane_id() == 0) {
+                    atomicAdd(&s_gain, (unsigned long long)fresh);
+                    pos = atomicAdd(&s_fcnt[c1], all);
+                }
+                pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos);
+#pragma unroll
+                for (int u = 0; u < kResidEdges; ++u) {
+                    const uint32_t j = pos + (uint32_t)__popcll(m[u] & ((1ull << lane_id()) - 1ull));
+                    pos += (uint32_t)__popcll(m[u]);
+                    if (add[u]) {
+                        const uint32_t e = qw[u] | (was[u] & kCommitted ? kHasEntry : 0u);
+                        if (j < kSkimLdsFront) s_front[cur ^ 1u][j] = e;
+                        else st<kGroup>(F[cur ^ 1u] + j, e);
+                    }
+                }
+            };
+            const uint32_t wave = tid >> 6;
+            if (fc <= kSkimBlock) {
+                ResidWave<1> &W = reinterpret_cast<ResidWave<1> &>(s_u.wave[wave]);
+                if (64 * wave < fc)
+                    resid_wave<kGroup, 1>(A, SZ, ST, 64 * wave, fc, W, fin, push);
+            } else {
+                for (uint32_t base = 256 * wave; base < fc; base += 4 * kSkimBlock)
+                    resid_wave<kGroup, 4>(A, SZ, ST, base, fc, s_u.wave[wave], fin, push);
+            }
+            for (uint32_t h = 0; h < nh; ++h) {
+                const uint32_t q = s_long[cur][h], pq = q & ~kHasEntry;
+                const uint64_t f0 = A.fptr[pq], deg = A.fptr[pq + 1] - f0;
+                for (uint64_t b = 0; b < deg; b += kResidEdges * kSkimBlock) {
+                    uint32_t qw[kResidEdges];
+                    uint64_t was[kResidEdges];
+#pragma unroll
+                    for (int u = 0; u < kResidEdges; ++u) {
+                        const uint64_t t = b + u * kSkimBlock + tid;
+                        qw[u] = t < deg ? A.fadj[f0 + t] * kPairStride + pq % kPairStride : 0xFFFFFFFFu;
+                    }
+#pragma unroll
+                    for (int u = 0; u < kResidEdges; ++u)
+                        was[u] = qw[u] != 0xFFFFFFFFu ? cover<kGroup>(ST, qw[u]) : kCovered;
+                    push(was, qw);
+                }
+                if (tid < 64) {
+                    const bool mine = tid == 0 && (q & kHasEntry);
+                    erase_entry<kGroup>(A, SZ, mine ? q : 0u, mine ? A.idx[pq] : 0ull);
+                }
+            }
         }
         if (handed) break;  // uniform
         __syncthreads();
         if (tid == 0) {
-            st(A.sel + x, 1u);
+            st<kGroup>(A.sel + x, 1u);
             seeds[it] = x;
             gains[it] = s_gain;
             if (gain_d) gain_d[it] = (double)s_gain / (double)A.ell;
         }
-        ++done;
         __syncthreads();
     }
     if constexpr (kLds) {
         __syncthreads();
-        for (uint32_t w = tid; w < swords; w += kSkimBlock) st(A.size + w, s_size[w]);
+        for (uint32_t w = tid; w < swords; w += kSkimBlock) st<kGroup>(A.size + w, s_size[w]);
+        if constexpr (kLdsState)
+            for (uint32_t w = tid; w < 4 * n; w += kSkimBlock) st<kGroup>(A.state + w, ST[w]);
     }
     if (tid == 0) {
         A.ctl->cursor = s_cursor;
         A.ctl->pool_used = s_pool;
-        A.ctl->done = done;
+        A.ctl->done = it;
     }
 }
 
-// Level L of a residual search handed over by k_skim, on the whole grid:
-// frontier buffer (r0 + L) & 1 of the queue area, sizes in global memory.
-// First the pairs level L - 1 deferred (long out-lists), their edges laid end
-// to end and split evenly over every workgroup, kResidBlock pairs at a time;
-// then the level's own frontier.  Both append to level L + 1.  A launch with
-// nothing to do returns at once, so the host launches levels in batches and
-// reads the sizes back after each batch.
-__global__ void __launch_bounds__(kResidBlock) k_resid_level(SkArgs A, uint32_t L, uint32_t r0) {
-    __shared__ FlatShared<kResidBlock> X;
+// Level L of a round of a residual search handed over by k_skim, on the whole
+// grid: frontier buffer (rcur + L) & 1 of the queue area, sizes in global
+// memory.  First the level's long pairs, their edges laid end to end and split
+// evenly over every workgroup, kResidBlock pairs at a time; then the others.
+// Both append to level L + 1.  A launch with nothing to do returns at once.
+//
+// What bounds it: small levels (most of them) the chain of accesses, 7 us;
+// large ones the wave with the most edges.
+__global__ void __launch_bounds__(kResidBlock) k_resid_level(SkArgs A, uint32_t L) {
+    __shared__ FlatShared X;
+    __shared__ ResidWave<4> W[kResidBlock / 64];
     __shared__ ResidStage S;
-    __shared__ unsigned long long s_fc, s_nh;
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x, lane = lane_id();
+    // (none of these words is written while a level reads it)
+    const uint32_t pend = A.ctl->pend, cur = (A.ctl->rcur + L) & 1u;
+    const uint64_t rs = A.ctl->rsize[16 * (L % 3)], hs = A.ctl->hsize[16 * (L % 3)];
+    if (pend != 1) return;
     if (tid == 0) {
-        S.n = 0;
-        s_fc = ld(&A.ctl->rsize[16 * (L % 3)]);
-        s_nh = ld(&A.ctl->hsize[16 * ((L + 2) % 3)]);  // deferred by level L - 1
+        S.n = S.gain = 0;
         if (blockIdx.x == 0) {
             A.ctl->rsize[16 * ((L + 2) % 3)] = 0;  // level L + 1 appends there
-            A.ctl->hsize[16 * ((L + 1) % 3)] = 0;  // and defers there
-            A.ctl->rgain += s_fc;
+            A.ctl->hsize[16 * ((L + 2) % 3)] = 0;
+            A.ctl->rgain += rs >> 32;
         }
     }
-    __syncthreads();
-    const uint64_t fc = s_fc;
-    const uint32_t nh = s_nh < kHeavyItems ? (uint32_t)s_nh : kHeavyItems;
+    const uint64_t fc = rs & 0xFFFFFFFFu;
+    const uint32_t nh = hs < kHeavyItems ? (uint32_t)hs : kHeavyItems;
     if (fc == 0 && nh == 0) return;  // uniform
-    const uint32_t cur = (r0 + L) & 1u;
+    __syncthreads();
     const uint64_t half = (uint64_t)A.n * kPairStride;
     const uint32_t *Fin = A.front + cur * half;
     uint32_t *Fout = A.front + (cur ^ 1u) * half;
     unsigned long long *next = &A.ctl->rsize[16 * ((L + 1) % 3)];
-    const uint64_t *hin = A.heavy + 2 * (uint64_t)kHeavyItems * ((L + 2) % 3);
-    for (uint32_t h0 = 0; h0 < nh; h0 += kResidBlock) {
+    unsigned long long *hnext = &A.ctl->hsize[16 * ((L + 1) % 3)];
+    const uint32_t *hin = A.heavy + (uint64_t)kHeavyItems * cur;
+    uint32_t *hout = A.heavy + (uint64_t)kHeavyItems * (cur ^ 1u);
+    auto fin = [&](uint64_t e) { return Fin[e]; };
+    auto push = [&](const uint64_t (&was)[kResidEdges], const uint32_t (&qw)[kResidEdges]) {
+        uint64_t m[kResidEdges];
+        uint32_t all = 0, fresh = 0, pos = 0;
+        bool add[kResidEdges];
+#pragma unroll
+        for (int u = 0; u < kResidEdges; ++u) {
+            add[u] = !(was[u] & kCovered) && (was[u] & (kHasEdges | kCommitted));
+            fresh += (uint32_t)__popcll(__ballot(!(was[u] & kCovered)));
+            if (add[u] && (was[u] & kLong)) {
+                const unsigned long long slot = atomicAdd(hnext, 1ull);
+                if (slot < kHeavyItems) {
+                    hout[slot] = qw[u] | (was[u] & kCommitted ? kHasEntry : 0u);
+                    add[u] = false;
+                }
+            }
+            m[u] = __ballot(add[u]);
+            all += (uint32_t)__popcll(m[u]);
+        }
+        if (!fresh) return;
+        if (lane == 0) {
+            atomicAdd(&S.gain, fresh);
+            pos = atomicAdd(&S.n, all);
+        }
+        pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos);
+#pragma unroll
+        for (int u = 0; u < kResidEdges; ++u) {
+            const uint32_t j = pos + (uint32_t)__popcll(m[u] & ((1ull << lane) - 1ull));
+            pos += (uint32_t)__popcll(m[u]);
+            if (add[u]) {
+                const uint32_t e = qw[u] | (was[u] & kCommitted ? kHasEntry : 0u);
+                if (j < 8 * kResidBlock) S.buf[j] = e;
+                else Fout[(uint32_t)atomicAdd(next, 1ull)] = e;  // stage full
+            }
+        }
+    };
+    // the stage to level L + 1 (called by all threads, after a barrier)
+    auto flush = [&]() {
+        const uint32_t ns = min(S.n, 8u * kResidBlock);
+        if (tid == 0 && S.gain)
+            S.base = atomicAdd(next, ((unsigned long long)S.gain << 32) | ns) & 0xFFFFFFFFu;
+        __syncthreads();
+        const unsigned long long b = S.base;
+        for (uint32_t j = tid; j < ns; j += kResidBlock) Fout[b + j] = S.buf[j];
+        __syncthreads();
+        if (tid == 0) S.n = S.gain = 0;
+        __syncthreads();
+    };
+    // Where the lower half of the workgroups is enough for the others, the
+    // upper half takes the long pairs: two chains side by side.
+    const uint32_t lb0 = fc <= (uint64_t)gridDim.x / 2 * kResidBlock ? gridDim.x / 2 : 0u;
+    const uint32_t lb = blockIdx.x - lb0, lbs = gridDim.x - lb0;
+    for (uint32_t h0 = 0; h0 < nh && blockIdx.x >= lb0; h0 += kResidBlock) {
         uint64_t deg = 0, f0 = 0;
         uint32_t q = 0;
         if (h0 + tid < nh) {
-            const uint64_t w = hin[2 * (h0 + tid)];
-            q = (uint32_t)(w >> 32);
-            deg = (uint32_t)w;
-            f0 = hin[2 * (h0 + tid) + 1];
+            q = hin[h0 + tid];
+            f0 = A.fptr[q & ~kHasEntry];
+            deg = A.fptr[(q & ~kHasEntry) + 1] - f0;
         }
         uint64_t tot;
         const uint64_t e = block_excl_scan<kResidBlock>(deg, X.wsum, tot);
         X.ex[tid] = e;
-        X.q[tid] = q;
+        X.q[tid] = q % kPairStride;
         X.f0[tid] = f0;
         if (tid == 0) X.ex[kResidBlock] = tot;
         __syncthreads();
-        const uint64_t a = tot * blockIdx.x / gridDim.x, b = tot * (blockIdx.x + 1) / gridDim.x;
-        for (uint64_t base = a; base < b; base += kResidBlock) {
-            const uint64_t t = base + tid;
-            bool add = false;
-            uint32_t qw = 0;
-            if (t < b) {
-                const uint32_t r = run_of<kResidBlock>(X.ex, t);
-                qw = A.fadj[X.f0[r] + (t - X.ex[r])] * kPairStride + X.q[r] % kPairStride;
-                add = !ld(A.covered + qw) && atomicCAS(A.covered + qw, 0u, 1u) == 0u;
-            }
-            const unsigned long long m = __ballot(add);
-            if (m) {
-                const int leader = __ffsll((long long)m) - 1;
-                const uint32_t lane = lane_id();
-                uint32_t pos0 = 0;
-                if ((int)lane == leader) pos0 = atomicAdd(&S.n, (uint32_t)__popcll(m));
-                const uint32_t pos = (uint32_t)__shfl((int)pos0, leader) +
-                                     (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-                if (add) {
-                    if (pos < 8 * kResidBlock) S.buf[pos] = qw;
-                    else Fout[atomicAdd(next, 1ull)] = qw;
+        // one workgroup erases the index entries
+        if (lb == (h0 / kResidBlock) % lbs)
+            erase_entry<kAgent>(A, A.size, q, q & kHasEntry ? A.idx[q & ~kHasEntry] : 0ull);
+        const uint64_t a = tot * lb / lbs, b = tot * (lb + 1) / lbs;
+        for (uint64_t base = a; base < b; base += kResidEdges * kResidBlock) {
+            uint32_t qw[kResidEdges];
+            bool in[kResidEdges];
+            uint64_t was[kResidEdges];
+#pragma unroll
+            for (int u = 0; u < kResidEdges; ++u) {
+                const uint64_t t = base + u * kResidBlock + tid;
+                in[u] = t < b;
+                qw[u] = 0;
+                if (in[u]) {
+                    const uint32_t r = run_of<kResidBlock>(X.ex, t);
+                    qw[u] = A.fadj[X.f0[r] + (t - X.ex[r])] * kPairStride + X.q[r];
                 }
             }
+#pragma unroll
+            for (int u = 0; u < kResidEdges; ++u)
+                was[u] = in[u] ? cover<kAgent>(A.state, qw[u]) : kCovered;
+            push(was, qw);
             __syncthreads();
-            const uint32_t ns = S.n < 8 * kResidBlock ? S.n : 8 * kResidBlock;
+            const bool full = S.n > 4 * kResidBlock;
             __syncthreads();  // every thread has read S.n: the test below is uniform
-            if (ns > 7 * kResidBlock || base + kResidBlock >= b) {
-                if (tid == 0 && ns) S.base = atomicAdd(next, (unsigned long long)ns);
-                __syncthreads();
-                for (uint32_t j = tid; j < ns; j += kResidBlock) Fout[S.base + j] = S.buf[j];
-                __syncthreads();
-                if (tid == 0) S.n = 0;
-                __syncthreads();
-            }
+            if (full) flush();
         }
         __syncthreads();  // X is reused
     }
-    uint64_t *hout = A.heavy + 2 * (uint64_t)kHeavyItems * (L % 3);
-    for (uint64_t base = (uint64_t)blockIdx.x * kResidBlock; base < fc;
-         base += (uint64_t)gridDim.x * kResidBlock)
-        resid_chunk<kResidBlock, true>(A, A.size, Fin, Fout, fc, base, X, next, &S,
-                                       &A.ctl->hsize[16 * (L % 3)], hout);
+    // four pairs per lane where there is one for every lane of the grid
+    const bool many = fc > (uint64_t)kResidGrid * kResidBlock;
+    const uint64_t chunk = many ? 4 * kResidBlock : kResidBlock;
+    for (uint64_t base = blockIdx.x * chunk; base < fc; base += gridDim.x * chunk) {
+        const uint32_t wave = tid >> 6;
+        if (many)
+            resid_wave<kAgent, 4>(A, A.size, A.state, base + 256 * wave, fc, W[wave], fin, push);
+        else
+            resid_wave<kAgent, 1>(A, A.size, A.state, base + 64 * wave, fc,
+                                  reinterpret_cast<ResidWave<1> &>(W[wave]), fin, push);
+        __syncthreads();
+        const bool full = S.n > 4 * kResidBlock;
+        __syncthreads();
+        if (full) flush();
+    }
+    __syncthreads();
+    flush();
 }
 
-// The handed-over search's next level (L) is small: k_skim finishes it.
-__global__ void k_resid_handback(SkArgs A, uint32_t L, uint32_t r0) {
-    A.ctl->rsize[0] = A.ctl->rsize[16 * (L % 3)];
-    A.ctl->rcur = (r0 + L) & 1u;
-    A.ctl->pend = 2;
+// The end of a round: a search that has ended completes its seed, one that has
+// become small goes back to k_skim, any other goes on in the next round.
+__global__ void k_resid_end(SkArgs A, uint32_t *seeds, uint64_t *gains, double *gain_d) {
+    SkCtl *c = A.ctl;
+    if (c->pend != 1) return;
+    const uint32_t f = (uint32_t)c->rsize[0];
+    if (c->hsize[0] == 0 && f == 0) {
+        const uint32_t x = c->px, it = c->done;
+        const unsigned long long g = c->rgain + (c->rsize[0] >> 32);
+        A.sel[x] = 1u;
+        seeds[it] = x;
+        gains[it] = g;
+        if (gain_d) gain_d[it] = (double)g / (double)A.ell;
+        c->pend = 0;
+        c->done = it + 1;
+    } else if (c->hsize[0] == 0 && f <= kSkimHandBack) {
+        c->pend = 2;
+    }
 }
 
-// The handed-over seed is complete: outputs, and the node leaves the
-// candidates.
-__global__ void k_resid_finish(SkArgs A, uint32_t *seeds, uint64_t *gains, double *gain_d) {
-    const uint32_t x = A.ctl->px;
-    const unsigned long long g = A.ctl->rgain;
-    A.sel[x] = 1u;
-    seeds[0] = x;
-    gains[0] = g;
-    if (gain_d) gain_d[0] = (double)g / (double)A.ell;
-    A.ctl->pend = 0;
+// State words of a new run: every pair's out-list bits.
+__global__ void k_state_init(uint32_t n, const uint64_t *fptr, uint64_t *state) {
+    const uint64_t npairs = (uint64_t)n * kPairStride;
+    for (uint64_t p = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; p < npairs;
+         p += (uint64_t)gridDim.x * blockDim.x) {  // whole waves: 64 pairs are a node's
+        const uint64_t deg = fptr[p + 1] - fptr[p];
+        const uint64_t some = __ballot(deg > 0), more = __ballot(deg > kLongEdges);
+        const uint32_t part = (uint32_t)(p % 64);
+        if (part < 4)
+            state[p / 64 * 4 + part] = ((some >> (16 * part)) & 0xFFFFu) << 32 |
+                                       ((more >> (16 * part)) & 0xFFFFu) << 48;
+    }
 }
 
 __global__ void k_pair_keys(uint32_t n, uint32_t ell, uint64_t seed, uint64_t *keys,
@@ -1479,7 +1701,7 @@ __global__ void __launch_bounds__(kTailPairBlock) k_tail_pair(const double *in, 
             // (agent-scope stores and loads reach the memory all XCDs see, so
             // no fence has to write back or invalidate a whole cache; the
             // stores have arrived before the counter is touched)
-            st(partial + item * kTailTile + tid, v);
+            st<kAgent>(partial + item * kTailTile + tid, v);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
@@ -1494,7 +1716,7 @@ __global__ void __launch_bounds__(kTailPairBlock) k_tail_pair(const double *in, 
             const double *first = partial + (item - rest) * kTailTile;
             v = 0.0;
             for (uint32_t q = 0; q < nparts; ++q)
-                v += ld(first + (uint64_t)q * kTailTile + tid);
+                v += ld<kAgent>(first + (uint64_t)q * kTailTile + tid);
         }
         if (j < W) out[p * W + j] = v + (j + 1 < W ? a[j + 1] : 0.0);
         if (more < 0) break;
@@ -1686,12 +1908,12 @@ skim_greedy_state *greedy_create(const skim_graph *g, uint32_t ell, uint32_t k, 
     A.n = n;
     A.ell = ell;
     A.k = k;
-    A.covered = M.alloc<uint32_t>(npairs);
+    A.state = M.alloc<uint64_t>(npairs / 16);
     const uint64_t cwords = size_words(n);
     A.size = M.alloc<uint32_t>(cwords);
     A.sel = M.alloc<uint32_t>(n);
     A.idx = M.alloc<uint64_t>(npairs);
-    A.heavy = M.alloc<uint64_t>(3 * 2 * (uint64_t)kHeavyItems);
+    A.heavy = M.alloc<uint32_t>(2 * (uint64_t)kHeavyItems);
     A.front = M.alloc<uint32_t>(2 * npairs);
     A.ahead = M.alloc<uint64_t>(kAheadMax);
     A.apool_cap = std::max<uint64_t>(1ull << 16, (uint64_t)kAheadPoolNodes * n);
@@ -1707,10 +1929,10 @@ skim_greedy_state *greedy_create(const skim_graph *g, uint32_t ell, uint32_t k, 
     A.seed = seed;
     A.rec_tau = M.alloc<uint64_t>(n);
     A.rec_second = M.alloc<uint32_t>(n);
-    fill_u32(A.covered, 0, npairs, s);
+    k_state_init<<<grid_for(npairs, 256, 8192), 256, 0, s>>>(n, A.fptr, A.state);
+    SKIM_LAUNCH_CHECK();
     fill_u32(A.size, 0, cwords, s);
     fill_u32(A.sel, 0, n, s);
-    fill_u64(A.idx, 0, npairs, s);
     greedy_set_ctl(st.get(), 0, 0, s);
     st->n = n;
     st->ell = ell;
@@ -1727,8 +1949,19 @@ skim_greedy_state *greedy_create(const skim_graph *g, uint32_t ell, uint32_t k, 
 void greedy_run(skim_greedy_state *st, uint32_t s_goal, uint32_t *seeds, uint64_t *gains,
                        double *gain_d, hipStream_t s) {
     SkArgs &A = st->args;
+    const uint32_t before = st->selected;
     uint32_t done = 0;
-    int growths = 0;
+    int growths = 0, rounds = 0;
+    bool begin = true;
+    auto skim = [&] {
+        auto kernel = A.n <= kSkimStateNodes ? k_skim<true, true>
+                      : A.n <= kSkimLdsNodes ? k_skim<true, false>
+                                             : k_skim<false, false>;
+        kernel<<<1, kSkimBlock, 0, s>>>(A, s_goal, begin, kSkimHandoff, seeds, gains, gain_d,
+                                        A.rec_tau + before, A.rec_second + before);
+        SKIM_LAUNCH_CHECK();
+        begin = false;
+    };
     while (done < s_goal) {
         if (st->ahead_due) {
             while (A.ordered < A.nsrc && A.ordered <= st->cursor) greedy_extend_order(st, s);
@@ -1740,16 +1973,27 @@ void greedy_run(skim_greedy_state *st, uint32_t s_goal, uint32_t *seeds, uint64_
             SKIM_LAUNCH_CHECK();
             st->ahead_due = false;
         }
-        auto skim = A.n <= kSkimLdsNodes ? k_skim<true> : k_skim<false>;
-        skim<<<1, kSkimBlock, 0, s>>>(A, s_goal - done, kSkimHandoff, seeds + done, gains + done,
-                                      gain_d ? gain_d + done : nullptr, A.rec_tau + st->selected,
-                                      A.rec_second + st->selected);
-        SKIM_LAUNCH_CHECK();
+        if (rounds == 0) skim();
+        // once a search has gone to the grid, rounds of levels and the loop's
+        // next launch are enqueued together: each finds out on the device
+        // what there is to do (reading the control block between them left
+        // the device idle 25 us each time)
+        for (int r = 0; r < rounds; ++r) {
+            for (uint32_t L = 0; L < kRoundLevels; ++L) {
+                k_resid_level<<<kResidGrid, kResidBlock, 0, s>>>(A, L);
+                SKIM_LAUNCH_CHECK();
+            }
+            k_resid_end<<<1, 1, 0, s>>>(A, seeds, gains, gain_d);
+            SKIM_LAUNCH_CHECK();
+            skim();
+        }
         SkCtl c;
         read_back(&c, A.ctl, sizeof c, s);
+        const bool moved = c.done > done || c.cursor > st->cursor;
         st->cursor = c.cursor;
-        done += c.done;
-        st->selected += c.done;
+        done = c.done;
+        st->selected = before + done;
+        rounds = 0;
         if (c.flags & kFlagPool) {
             SKIM_REQUIRE(++growths < 40, "SKIM index pool did not converge");
             // grow the inverted-index pool, keep its contents, continue
@@ -1765,37 +2009,8 @@ void greedy_run(skim_greedy_state *st, uint32_t s_goal, uint32_t *seeds, uint64_
             st->ahead_due = true;
             fill_u32(&A.ctl->flags, 0, 1, s);
         } else if (c.pend) {
-            // the seed's residual search continues on the whole grid, levels
-            // in batches (an empty level's launch does nothing); every level
-            // covers at least one new pair
-            const uint64_t max_levels = (uint64_t)A.n * kPairStride + 1;
-            const uint32_t r0 = c.rcur;
-            uint32_t L = 0;
-            bool back = false;
-            for (;;) {
-                for (int j = 0; j < 8; ++j, ++L) {
-                    k_resid_level<<<kResidGrid, kResidBlock, 0, s>>>(A, L, r0);
-                    SKIM_LAUNCH_CHECK();
-                }
-                read_back(&c, A.ctl, sizeof c, s);
-                // level L's frontier, and the pairs level L - 1 deferred
-                const uint64_t f = c.rsize[16 * (L % 3)], h = c.hsize[16 * ((L + 2) % 3)];
-                if (f == 0 && h == 0) break;
-                if (h == 0 && f <= kSkimHandBack) {  // k_skim resumes the search at level L
-                    k_resid_handback<<<1, 1, 0, s>>>(A, L, r0);
-                    SKIM_LAUNCH_CHECK();
-                    back = true;
-                    break;
-                }
-                SKIM_REQUIRE(L < max_levels, "SKIM residual search did not end");
-            }
-            if (back) continue;
-            k_resid_finish<<<1, 1, 0, s>>>(A, seeds + done, gains + done,
-                                           gain_d ? gain_d + done : nullptr);
-            SKIM_LAUNCH_CHECK();
-            ++done;
-            ++st->selected;
-        } else if (done < s_goal) {
+            rounds = kRounds;
+        } else if (done < s_goal && !moved) {
             set_error("SKIM stopped early");
             throw Fail{SKIM_EDEVICE};
         }
@@ -1845,6 +2060,31 @@ extern "C" uint32_t skim_greedy_state_selected(const skim_greedy_state *state) {
 // offset rounded up to 8 bytes.
 namespace skim {
 namespace {
+
+// A saved state holds a word per pair, 1 if it is covered, and the index word
+// of every committed pair that is not covered, 0 for the others.
+// Made kImagePairs pairs at a time (a multiple of 64).
+constexpr uint64_t kImagePairs = 1ull << 22;
+__global__ void k_state_unpack(SkArgs A, uint64_t p0, uint64_t count, uint32_t *covered,
+                               uint64_t *idx) {
+    for (uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; t < count;
+         t += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t p = p0 + t;
+        const uint64_t w = A.state[p / 16] >> (p % 16);
+        covered[t] = w & kCovered ? 1u : 0u;
+        idx[t] = (w & (kCovered | kCommitted)) == kCommitted ? A.idx[p] : 0ull;
+    }
+}
+__global__ void k_state_pack(SkArgs A, uint64_t p0, uint64_t count, const uint32_t *covered) {
+    for (uint64_t w = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; w < count / 16;
+         w += (uint64_t)gridDim.x * blockDim.x) {
+        uint64_t bits = 0;
+        for (uint32_t j = 0; j < 16; ++j)
+            bits |= (covered[16 * w + j] ? kCovered << j : 0u) |
+                    (A.idx[p0 + 16 * w + j] ? kCommitted << j : 0u);
+        A.state[p0 / 16 + w] |= bits;
+    }
+}
 
 constexpr char kImageMagic[8] = {'S', 'K', 'I', 'M', 'G', 'R', 'D', '1'};
 
@@ -1907,14 +2147,24 @@ extern "C" skim_status skim_greedy_state_save(const skim_greedy_state *state, vo
         std::memcpy(b, &h, sizeof h);
         const uint64_t npairs = (uint64_t)state->n * skim::kPairStride;
         const uint64_t cwords = 2 * (((uint64_t)state->n + 3) / 4);
+        skim::Arena T(hs);
+        const uint64_t chunk = std::min(npairs, skim::kImagePairs);
+        uint32_t *covered = T.alloc<uint32_t>(chunk);
+        uint64_t *idx = T.alloc<uint64_t>(chunk);
+        for (uint64_t p0 = 0; p0 < npairs; p0 += chunk) {
+            const uint64_t c1 = std::min(chunk, npairs - p0);
+            skim::k_state_unpack<<<skim::grid_for(c1, 256, 8192), 256, 0, hs>>>(A, p0, c1, covered,
+                                                                              idx);
+            SKIM_LAUNCH_CHECK();
+            SKIM_HIP(hipMemcpyAsync(b + L.covered + 4 * p0, covered, 4 * c1, hipMemcpyDeviceToHost, hs));
+            SKIM_HIP(hipMemcpyAsync(b + L.idx + 8 * p0, idx, 8 * c1, hipMemcpyDeviceToHost, hs));
+        }
         const struct {
             uint64_t off;
             const void *src;
             uint64_t len;
-        } parts[] = {{L.covered, A.covered, npairs * 4},
-                     {L.size, A.size, cwords * 4},
+        } parts[] = {{L.size, A.size, cwords * 4},
                      {L.sel, A.sel, (uint64_t)state->n * 4},
-                     {L.idx, A.idx, npairs * 8},
                      {L.pool, A.pool, c.pool_used * 4},
                      {L.tau, A.rec_tau, (uint64_t)state->selected * 8},
                      {L.second, A.rec_second, (uint64_t)state->selected * 4}};
@@ -1965,8 +2215,7 @@ extern "C" skim_status skim_greedy_state_load(const skim_graph *g, uint32_t ell,
         const struct {
             void *dst;
             uint64_t off, len;
-        } parts[] = {{A.covered, L.covered, npairs * 4},
-                     {A.size, L.size, cwords * 4},
+        } parts[] = {{A.size, L.size, cwords * 4},
                      {A.sel, L.sel, (uint64_t)h.n * 4},
                      {A.idx, L.idx, npairs * 8},
                      {A.pool, L.pool, h.pool_used * 4},
@@ -1975,6 +2224,15 @@ extern "C" skim_status skim_greedy_state_load(const skim_graph *g, uint32_t ell,
         for (const auto &pt : parts)
             if (pt.len)
                 SKIM_HIP(hipMemcpyAsync(pt.dst, b + pt.off, pt.len, hipMemcpyHostToDevice, hs));
+        skim::Arena T(hs);
+        const uint64_t chunk = std::min(npairs, skim::kImagePairs);
+        uint32_t *covered = T.alloc<uint32_t>(chunk);
+        for (uint64_t p0 = 0; p0 < npairs; p0 += chunk) {
+            const uint64_t c1 = std::min(chunk, npairs - p0);
+            SKIM_HIP(hipMemcpyAsync(covered, b + L.covered + 4 * p0, 4 * c1, hipMemcpyHostToDevice, hs));
+            skim::k_state_pack<<<skim::grid_for(c1 / 16, 256, 8192), 256, 0, hs>>>(A, p0, c1, covered);
+            SKIM_LAUNCH_CHECK();
+        }
         skim::greedy_set_ctl(st, h.cursor, h.pool_used, hs);
         st->selected = (uint32_t)h.selected;
         *state = st;

@@ -226,6 +226,16 @@ def test_saved_state_refused_for_other_runs():
         b.free()
 
 
+def _cycle_with_hubs(n, hubs, fan, rng):
+    # a cycle, and node 0 <= h < hubs with out-edges to `fan` other nodes
+    src, dst = [np.arange(n)], [(np.arange(n) + 1) % n]
+    for h in range(hubs):
+        others = np.setdiff1d(np.arange(n), [h, (h + 1) % n])
+        src.append(np.full(fan, h))
+        dst.append(rng.choice(others, fan, replace=False))
+    return np.concatenate(src), np.concatenate(dst)
+
+
 @pytest.mark.parametrize("n,m,denom,ell,k,s", [
     (1200, 3600, 2, 16, 8, 20),       # searches past 16 nodes; bits of the pairs in LDS at its limit
     (1201, 3600, 2, 16, 8, 20),       # ... and past it
@@ -240,4 +250,20 @@ def test_searches_ahead(oracle_lib, n, m, denom, ell, k, s):
     log(f"skim searches ahead n={n} ell={ell} k={k}")
     seeds, gains, _, _ = gpu_greedy(g, ell, k, 5, [s - 1, 1])
     ws, wg, _ = oracle_lib.skim(g, 5, ell, k, s)
+    assert np.array_equal(seeds, ws) and np.array_equal(gains, wg)
+
+
+@pytest.mark.parametrize("n,hubs,fan,ell,k,s", [
+    (1000, 3, 64, 64, 16, 4),      # out-lists at the limit of a wave's share
+    (1000, 3, 65, 64, 16, 4),      # ... past it, more than 64 of them in a level
+    (30000, 40, 900, 64, 8, 4),    # on the grid
+    (1200, 0, 0, 64, 65500, 2),    # sizes near 16 bits: batches of 36 pairs
+])
+def test_long_lists_and_counter_limits(oracle_lib, n, hubs, fan, ell, k, s):
+    src, dst = _cycle_with_hubs(n, hubs, fan, np.random.default_rng(n + fan))
+    thr = np.full(src.size, 0xFFFFFFFF if k > 1000 else 0xE0000000, dtype=np.uint32)
+    g = from_edges(n, src, dst, thr)
+    log(f"skim long lists n={n} hubs={hubs} fan={fan} k={k}")
+    seeds, gains, _, _ = gpu_greedy(g, ell, k, 11, [s])
+    ws, wg, _ = oracle_lib.skim(g, 11, ell, k, s)
     assert np.array_equal(seeds, ws) and np.array_equal(gains, wg)
