@@ -108,7 +108,7 @@ struct alignas(128) Ctl {
     uint32_t flags;                   // overflow bits
     uint32_t level;                   // level reached by the tail kernel
     char pad5[120];
-    unsigned long long budget;        // visits reserved by the workgroup tails (k_tails)
+    unsigned long long budget;        // visits reserved by the tails (k_tails)
     char pad6[120];
     unsigned long long hsize[2 * 16];  // long-list entries of level L: hsize[16 (L % 2)]
 };
@@ -964,195 +964,158 @@ __global__ void k_pair_init(const uint64_t *live, uint64_t npairs, uint64_t *pre
 
 constexpr uint64_t kTailRecords = 1ull << 20;  // record room the host adds before the tails
 
-// ------------------------------------- tails in many independent workgroups
-// The last levels of a window, once its frontier is small, in many
-// workgroups that never wait for each other: the frontier is split between
-// them and each runs its own level-synchronous search over its part, its
-// frontier in LDS, until that part dies out.  A window's result does not
-// depend on the order of its visits (pruning reads only counts from before
-// the window, and every (pair, source) visit is claimed exactly once, on
-// the device), so workgroups at different levels stay exact.  A workgroup
-// hands its frontier back to global memory (appended to the next level's
-// array, which the host then continues level by level) when its next level
-// could outgrow its LDS frontier or the visits reserved by all tails could
-// outgrow the room for records or hash-set inserts that the host gave.
-// There is no inter-workgroup barrier: every workgroup leaves its loop on
-// its own.
-constexpr uint32_t kTailsCap = 512;    // frontier entries per workgroup (LDS)
+// ---------------------------------------- tails in many independent waves
+// The last levels of a window, once its frontier is small, in many waves
+// that never wait for each other: the frontier is split between them and each
+// runs its own search over its part, a stack in LDS, until that part dies
+// out.  A window's result does not depend on the order of its visits (pruning
+// reads only counts from before the window, and every (pair, source) visit is
+// claimed exactly once, on the device), so waves at different levels stay
+// exact.  A wave hands its stack back to global memory (appended to the next
+// level's array, which the host then continues level by level) when it could
+// outgrow its LDS or the visits reserved by all tails could outgrow the room
+// for records or hash-set inserts that the host gave.  There is no barrier
+// between waves: every wave leaves its loop on its own.
+//
+// What bounds it: the longest chain of visits, three dependent accesses each
+// (live source, pair, claim), so nothing else is on the chain: records are
+// reserved when the stage fills, visits 64 at a time past a wave's share of
+// the room, and no step has a barrier.  20,000 nodes, weighted cascade: 265 us
+// a window with a workgroup's level-synchronous search (eight barriers and a
+// reservation of visits and of records per level), 116 us so.
+constexpr uint32_t kTailsCap = 192;    // stack entries per wave (LDS)
 constexpr int kTailsBlock = 256;
+constexpr int kTailsWaves = kTailsBlock / 64;
 constexpr uint32_t kTailsGrid = 1024;  // workgroups that fit on the device at once (4 per CU)
 constexpr uint32_t kTailsPer = 16;     // entries per workgroup at the start, or more
+constexpr uint32_t kTailsStart = 64;   // and at most per wave
 constexpr uint64_t kTailsMax = (uint64_t)kTailsGrid * 192;  // frontiers handed to the tails
+constexpr uint32_t kTailsStage = 128;  // records staged per wave
+constexpr uint32_t kTailsCredit = 64;  // visits reserved at a time
 
-struct TailsShared {
-    uint64_t key[2][kTailsCap];
-    uint64_t live[2][kTailsCap];
-    uint32_t n[2];
-    StageR R;
-    uint32_t ex[kTailsCap + 1];  // the level's live edges laid end to end: entry starts
-    uint32_t wsum[kTailsBlock / 64];
-    uint32_t hashed;
-    uint32_t spilled;
-    unsigned long long work;
-    uint32_t dump;
-    unsigned long long rbase;
+struct TailsWave {
+    uint64_t key[kTailsCap];
+    uint64_t live[kTailsCap];
+    uint64_t rec[kTailsStage];
+    uint32_t mark[64];
 };
 
-__device__ __forceinline__ void tails_visit(const WinArgs &A, TailsShared &T, uint32_t nxt,
-                                            uint32_t w, uint32_t i, uint32_t src,
-                                            uint32_t &scans, uint32_t &hashed, uint32_t &visits) {
-    const uint32_t q = w * kPairStride + i;
-    ++scans;
-    const bool want = wants_record(A, w);
-    uint64_t live;
-    if (claim(A, q, src, want, hashed, live) == 1) {
-        ++visits;
-        if (live) {  // room: the level's visits were bounded by kTailsCap before it ran
-            const uint32_t pos = stage_slots(&T.n[nxt]);
-            T.key[nxt][pos] = ((uint64_t)q << 32) | src;
-            T.live[nxt][pos] = live;
-        }
-        if (want) {
-            const uint32_t pos = stage_slots(&T.R.n);
-            if (pos < kStageR) {
-                T.R.buf[pos] = ((uint64_t)w << 32) | src;
-            } else {  // stage full: straight to global memory
-                atomicAdd(&T.spilled, 1u);
-                const uint64_t g = wave_reserve(&A.ctl->records, true);
-                if (g < A.rec_cap) A.rec[g] = ((uint64_t)w << 32) | src;
-                else atomicOr(&A.ctl->flags, kOvfRecords);
-            }
-        }
-    }
-}
-
 // The frontier of level L (nin entries at fkey/flive[L & 1]) split over the
-// grid; entries handed back go to level L + 1's arrays, counted in
+// grid's waves; entries handed back go to level L + 1's arrays, counted in
 // ctl->size[(L + 1) % 3] (zero at launch).  room: visits all tails may
 // reserve in total (bounded by the free records and hash-set room).
 __global__ void __launch_bounds__(kTailsBlock) k_tails(WinArgs A, uint32_t L, uint64_t nin,
                                                        unsigned long long room) {
-    __shared__ TailsShared T;
-    const uint32_t tid = threadIdx.x;
-    const uint64_t a = nin * blockIdx.x / gridDim.x, b = nin * (blockIdx.x + 1) / gridDim.x;
-    const uint32_t n0 = (uint32_t)(b - a);  // <= kTailsCap (the host sizes the grid)
-    if (tid == 0) {
-        T.n[0] = n0;
-        T.R.n = 0;
+    __shared__ TailsWave s_wave[kTailsWaves];
+    __shared__ uint64_t s_sums[3 * kTailsWaves];
+    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
+    TailsWave &T = s_wave[wave];
+    const uint64_t waves = (uint64_t)gridDim.x * kTailsWaves;
+    const uint64_t me = blockIdx.x + (uint64_t)gridDim.x * wave;
+    const uint64_t a = nin * me / waves, b = nin * (me + 1) / waves;
+    uint32_t n = (uint32_t)(b - a);  // <= kTailsStart (the host sizes the grid)
+    for (uint32_t t = lane; t < n; t += 64) {
+        T.key[t] = A.fkey[L & 1][a + t];
+        T.live[t] = A.flive[L & 1][a + t];
     }
-    for (uint32_t t = tid; t < n0; t += blockDim.x) {
-        T.key[0][t] = A.fkey[L & 1][a + t];
-        T.live[0][t] = A.flive[L & 1][a + t];
-    }
-    uint32_t scans = 0, visits = 0, cur = 0;
-    uint64_t *okey = A.fkey[(L + 1) & 1], *olive = A.flive[(L + 1) & 1];
-    unsigned long long *ocount = &A.ctl->size[16 * ((L + 1) % 3)];
-    for (;;) {
-        if (tid == 0) {
-            T.n[cur ^ 1] = 0;
-            T.hashed = 0;
-            T.spilled = 0;
-            T.work = 0;
-            T.dump = 0;
+    uint32_t scans = 0, visits = 0, hashed = 0;
+    uint32_t nrec = 0;  // staged records
+    // half of the room is dealt out in equal shares, the rest as waves ask
+    const unsigned long long share = room / 2 / waves, rest = room - share * waves;
+    uint32_t credit = (uint32_t)min(share, 1ull << 30);
+    auto flush = [&]() {
+        unsigned long long base = 0;
+        if (lane == 0) base = atomicAdd(&A.ctl->records, (unsigned long long)nrec);
+        base = shfl_u64(base, 0);
+        if (lane == 0 && base + nrec > A.rec_cap) atomicOr(&A.ctl->flags, kOvfRecords);
+        for (uint32_t j = lane; j < nrec; j += 64)
+            if (base + j < A.rec_cap) A.rec[base + j] = T.rec[j];
+        nrec = 0;
+    };
+    while (n) {
+        // the entries at the top of the stack, their live edges end to end:
+        // up to 64 edges, and no more than the stack has room for
+        const uint32_t take = min(n, 64u);
+        uint64_t key = 0, live = 0;
+        uint32_t c = 0;
+        if (lane < take) {
+            key = T.key[n - 1 - lane];
+            live = T.live[n - 1 - lane];
+            c = (live & kLiveOne) ? 1u : min(live_count(live), 64u);
         }
-        __syncthreads();
-        const uint32_t nc = T.n[cur];
-        if (nc == 0) break;  // uniform: read after the barrier
-        {   // the level's live in-edges bound its visits, records and inserts
-            unsigned long long wk = 0;
-            for (uint32_t t = tid; t < nc; t += blockDim.x) {
-                const uint64_t live = T.live[cur][t];
-                wk += (live & kLiveOne) ? 1u : live_count(live);
+        const uint32_t incl = wave_scan_sum(c);
+        const uint32_t E = min(min((uint32_t)__builtin_amdgcn_readlane((int)incl, 63), 64u),
+                               kTailsCap - n);
+        bool dump = E == 0;
+        if (credit < E) {
+            unsigned long long old = 0;
+            uint32_t fl = 0;
+            if (lane == 0) {
+                fl = __hip_atomic_load(&A.ctl->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                old = atomicAdd(&A.ctl->budget, (unsigned long long)kTailsCredit);
             }
-            if (wk) atomicAdd(&T.work, wk);
+            // (a reservation past the room stays: it only makes later waves stop sooner)
+            dump |= shfl_u64(old, 0) + kTailsCredit > rest || __shfl((int)fl, 0) != 0;
+            credit += kTailsCredit;
         }
-        __syncthreads();
-        if (tid == 0) {
-            const unsigned long long W = T.work;
-            const uint32_t fl =
-                __hip_atomic_load(&A.ctl->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (fl || W > kTailsCap) {
-                T.dump = 1;
-            } else if (atomicAdd(&A.ctl->budget, W) + W > room) {
-                T.dump = 1;  // the reservation stays: it only makes later tails stop sooner
-            }
-        }
-        __syncthreads();
-        if (T.dump) {  // hand the level's entries back to global memory
-            if (tid == 0) T.rbase = atomicAdd(ocount, (unsigned long long)nc);
-            __syncthreads();
-            const unsigned long long base = T.rbase;
-            if (tid == 0 && base + nc > A.front_cap) atomicOr(&A.ctl->flags, kOvfSpill);
-            for (uint32_t t = tid; t < nc; t += blockDim.x) {
+        if (dump) {  // hand the stack back to global memory
+            unsigned long long base = 0;
+            if (lane == 0) base = atomicAdd(&A.ctl->size[16 * ((L + 1) % 3)], (unsigned long long)n);
+            base = shfl_u64(base, 0);
+            if (lane == 0 && base + n > A.front_cap) atomicOr(&A.ctl->flags, kOvfSpill);
+            for (uint32_t t = lane; t < n; t += 64)
                 if (base + t < A.front_cap) {
-                    okey[base + t] = T.key[cur][t];
-                    olive[base + t] = T.live[cur][t];
+                    A.fkey[(L + 1) & 1][base + t] = T.key[t];
+                    A.flive[(L + 1) & 1][base + t] = T.live[t];
                 }
-            }
             break;
         }
-        const uint32_t nxt = cur ^ 1;
-        uint32_t hashed = 0;
-        {   // the level's live edges (at most kTailsCap) laid end to end and
-            // taken kTailsBlock at a time: thread t owns entries 2t and 2t + 1
-            uint32_t c[2] = {0, 0};
-            for (uint32_t h = 0; h < 2; ++h) {
-                const uint32_t e = 2 * tid + h;
-                if (e < nc) {
-                    const uint64_t lv = T.live[cur][e];
-                    c[h] = (lv & kLiveOne) ? 1u : live_count(lv);
-                }
-            }
-            const uint32_t lane = lane_id(), wave = tid >> 6;
-            uint32_t incl = c[0] + c[1];
-            for (uint32_t off = 1; off < 64; off <<= 1) {
-                const uint32_t y = __shfl_up(incl, off);
-                if (lane >= off) incl += y;
-            }
-            if (lane == 63u) T.wsum[wave] = incl;
-            __syncthreads();
-            uint32_t before = 0, W = 0;
-            for (uint32_t w = 0; w < kTailsBlock / 64; ++w) {
-                before += w < wave ? T.wsum[w] : 0u;
-                W += T.wsum[w];
-            }
-            const uint32_t start = before + incl - c[0] - c[1];
-            T.ex[2 * tid] = start;
-            T.ex[2 * tid + 1] = start + c[0];
-            if (tid == 0) T.ex[kTailsCap] = W;
-            __syncthreads();
-            for (uint32_t p = tid; p < W; p += kTailsBlock) {
-                uint32_t lo = 0, hi = kTailsCap;  // ex[lo] <= p < ex[hi]
-                while (hi - lo > 1) {
-                    const uint32_t mid = (lo + hi) >> 1;
-                    if (T.ex[mid] <= p) lo = mid;
-                    else hi = mid;
-                }
-                const uint64_t it = T.key[cur][lo], lv = T.live[cur][lo];
-                const uint32_t w = (lv & kLiveOne) ? (uint32_t)lv
-                                                   : A.lsrc[(lv >> kLiveCountBits) + (p - T.ex[lo])];
-                tails_visit(A, T, nxt, w, (uint32_t)(it >> 32) % kPairStride, (uint32_t)it, scans,
-                            hashed, visits);
+        credit -= E;
+        // the entry of edge `lane`: entries mark their first edge, the last
+        // mark at or before an edge is its entry's
+        const uint32_t first = incl - c;
+        T.mark[lane] = 0;
+        if (c && first < 64) T.mark[first] = lane;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const uint32_t o = wave_scan_max(T.mark[lane]);
+        const uint64_t ek = shfl_u64(key, o), el = shfl_u64(live, o);
+        const uint32_t at = lane - (uint32_t)__shfl((int)first, (int)o);
+        // entries used up leave the stack; the one cut short keeps its rest
+        const uint32_t used = (uint32_t)__popcll(__ballot(lane < take && incl <= E &&
+                                                          ((live & kLiveOne) || live_count(live) == c)));
+        const bool cut = lane == used && lane < take && first < E;
+        if (cut)
+            T.live[n - 1 - lane] = live + ((uint64_t)(E - first < c ? E - first : c) << kLiveCountBits) -
+                                   (E - first < c ? E - first : c);
+        n -= used;
+        bool push = false, keep = false;
+        uint64_t nlive = 0, nkey = 0;
+        uint32_t w = 0;
+        if (lane < E) {
+            w = (el & kLiveOne) ? (uint32_t)el : A.lsrc[(el >> kLiveCountBits) + at];
+            const uint32_t q = w * kPairStride + (uint32_t)(ek >> 32) % kPairStride;
+            ++scans;
+            const bool want = wants_record(A, w);
+            if (claim(A, q, (uint32_t)ek, want, hashed, nlive) == 1) {
+                ++visits;
+                push = nlive != 0;
+                keep = want;
+                nkey = ((uint64_t)q << 32) | (uint32_t)ek;
             }
         }
-        if (hashed) atomicAdd(&T.hashed, hashed);
-        __syncthreads();
-        // the level's staged records to global memory, one reservation
-        const uint32_t mr = T.R.n < kStageR ? T.R.n : kStageR;
-        if (tid == 0) {
-            T.rbase = mr ? atomicAdd(&A.ctl->records, (unsigned long long)mr) : 0;
-            if (mr && T.rbase + mr > A.rec_cap) atomicOr(&A.ctl->flags, kOvfRecords);
-            if (T.hashed) atomicAdd(&A.ctl->hinserts, (unsigned long long)T.hashed);
+        const uint64_t mp = __ballot(push), mr = __ballot(keep), below = (1ull << lane) - 1ull;
+        if (push) {
+            const uint32_t pos = n + (uint32_t)__popcll(mp & below);
+            T.key[pos] = nkey;
+            T.live[pos] = nlive;
         }
-        __syncthreads();
-        const unsigned long long rb = T.rbase;
-        for (uint32_t j = tid; j < mr; j += blockDim.x)
-            if (rb + j < A.rec_cap) A.rec[rb + j] = T.R.buf[j];
-        __syncthreads();
-        if (tid == 0) T.R.n = 0;
-        cur = nxt;
+        n += (uint32_t)__popcll(mp);
+        if (keep) T.rec[nrec + (uint32_t)__popcll(mr & below)] = ((uint64_t)w << 32) | (uint32_t)ek;
+        nrec += (uint32_t)__popcll(mr);
+        if (nrec > kTailsStage - 64) flush();
     }
-    block_add3((uint64_t *)T.R.buf, &A.ctl->scans, scans, &A.ctl->visits, visits, nullptr, 0);
+    if (nrec) flush();
+    block_add3(s_sums, &A.ctl->scans, scans, &A.ctl->visits, visits, &A.ctl->hinserts, hashed);
 }
 
 // Before the tails at level L: the counter of the entries they hand back
@@ -1963,7 +1926,7 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
             SKIM_LAUNCH_CHECK();
             uint32_t L = 0;
             uint32_t overflow = 0;
-            uint64_t f_prev = 0;
+            uint64_t f_prev = 0, f_tails = 0;  // frontier before the last level, before the tails
             bool tails_ok = true;  // false right after the tails handed entries back
             for (;;) {
                 read_back(&h, ctl, sizeof h, s);
@@ -1982,10 +1945,11 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
                 // The optimistic first window is given up before it fills its
                 // hash set (a full set costs every insert all its probes: 15
                 // ms on R-MAT of 2^18 nodes): its frontier grew more than
-                // fourfold over the last level, and the same growth again
-                // would outrun the set.
-                if (w == 0 && span > 1 && f_prev && f > 4 * f_prev && f > kOptimistic &&
-                    (double)f * ((double)f / (double)f_prev) > 0.4 * (double)hsize) {
+                // fourfold over the last level (or the tails' few), and the
+                // same growth again would outrun the set.
+                const uint64_t f_ref = f_prev ? f_prev : f_tails;
+                if (w == 0 && span > 1 && f_ref && f > 4 * f_ref && f > kOptimistic &&
+                    (double)f * ((double)f / (double)f_ref) > 0.4 * (double)hsize) {
                     overflow = kOvfHash;
                     break;
                 }
@@ -2055,21 +2019,25 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
                     continue;
                 }
                 if (f <= kTailsMax && tails_ok) {
-                    // the rest of the window in independent workgroups (about
+                    // the rest of the window in independent waves (about
                     // kTailsPer entries each, as many as fit on the device at
                     // once), with room for the records of many levels; what
                     // they hand back continues here as level L + 1
                     const uint32_t G = (uint32_t)std::min<uint64_t>(
                         kTailsGrid, std::max<uint64_t>(1, (f + kTailsPer - 1) / kTailsPer));
-                    const uint64_t per = (f + G - 1) / G;
-                    if (per <= kTailsCap) {
+                    const uint64_t waves = (uint64_t)G * kTailsWaves;
+                    if ((f + waves - 1) / waves <= kTailsStart) {
                         grow_u64(rec, rec_cap, h.records,
                                  h.records + std::max<uint64_t>(kTailRecords, 4 * f));
                         {
-                            uint64_t c[2] = {front_cap, front_cap};
-                            grow_u64(fkey[(L + 1) & 1], c[0], 0, f);
-                            grow_u64(flive[(L + 1) & 1], c[1], 0, f);
-                            front_cap = std::min(front_cap, std::min(c[0], c[1]));
+                            // room for every wave's stack
+                            uint64_t c[4] = {front_cap, front_cap, front_cap, front_cap};
+                            const uint64_t need = waves * kTailsCap;
+                            grow_u64(fkey[L & 1], c[0], f, need);
+                            grow_u64(flive[L & 1], c[1], f, need);
+                            grow_u64(fkey[(L + 1) & 1], c[2], 0, need);
+                            grow_u64(flive[(L + 1) & 1], c[3], 0, need);
+                            front_cap = std::min(std::min(c[0], c[1]), std::min(c[2], c[3]));
                         }
                         const uint64_t hroom = 2 * hsize / 5 > h.hinserts
                                                    ? 2 * hsize / 5 - h.hinserts : 0;
@@ -2083,6 +2051,7 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
                         ++L;
                         tails_ok = false;  // at least one level by k_expand before the next
                         f_prev = 0;
+                        f_tails = f;
                         continue;
                     }
                 }

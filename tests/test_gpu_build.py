@@ -248,3 +248,23 @@ def test_dense_windows(oracle_lib, n, deg, denom, ell, k, hub):
     assert np.array_equal(E, oracle_lib.estimates(wr, ws, k, ell))
     R2, _, _, _, _ = gpu_build(g, ell, k, 5)
     assert np.array_equal(R, R2)
+
+
+@pytest.mark.parametrize("n,fan,denom,ell,k", [
+    (400, 64, 1, 4, 8),      # in-lists of one step of a wave
+    (400, 65, 1, 4, 8),      # ... and cut after it
+    (3000, 400, 1, 64, 64),  # cut several times, more entries than a stack holds
+    (3000, 130, 3, 16, 16),
+])
+def test_tails_lists_and_stacks(oracle_lib, n, fan, denom, ell, k):
+    """Small frontiers that meet long in-lists: a cycle whose every 50th node
+    has `fan` in-edges."""
+    rng = np.random.default_rng(fan)
+    e = [np.stack([np.arange(n), (np.arange(n) + 1) % n], 1)]
+    for v in range(0, n, 50):
+        e.append(np.stack([rng.choice(n, fan, replace=False), np.full(fan, v)], 1))
+    e = np.unique(np.concatenate(e), axis=0)
+    e = e[e[:, 0] != e[:, 1]]
+    g = from_edges(n, e[:, 0], e[:, 1], 0xFFFFFFFF // denom)
+    log(f"tails n={n} fan={fan} ell={ell} k={k}")
+    _check(oracle_lib, g, ell, k, 9)
