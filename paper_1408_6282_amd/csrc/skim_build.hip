@@ -57,7 +57,7 @@
 #include "skim_internal.h"
 #include "skim_wave.h"
 
-#include <rocprim/device/device_radix_sort.hpp>
+#include "skim_sort.h"
 
 #include <algorithm>
 #include <chrono>
@@ -2221,10 +2221,10 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
         int nb = 1;
         while (nb < 32 && (1ull << nb) < n) ++nb;
         size_t tmp_bytes = 0;
-        SKIM_HIP(rocprim::radix_sort_keys(nullptr, tmp_bytes, rec, seg, (size_t)nrec, 32, 32 + nb, s));
+        SKIM_HIP(rocprim::radix_sort_keys<FewBits>(nullptr, tmp_bytes, rec, seg, (size_t)nrec, 32, 32 + nb, s));
         void *tmp = A.get(tmp_bytes ? tmp_bytes : 1);
         LaunchTimer t("sort_records", s);
-        SKIM_HIP(rocprim::radix_sort_keys(tmp, tmp_bytes, rec, seg, (size_t)nrec, 32, 32 + nb, s));
+        SKIM_HIP(rocprim::radix_sort_keys<FewBits>(tmp, tmp_bytes, rec, seg, (size_t)nrec, 32, 32 + nb, s));
     }
     if (nrec) {
         k_bounds<<<grid_for(nrec, kBlock, 65536), kBlock, 0, s>>>(seg, nrec, gstart, gend);

@@ -23,7 +23,7 @@
 #include "skim_internal.h"
 #include "skim_wave.h"
 
-#include <rocprim/device/device_radix_sort.hpp>
+#include "skim_sort.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -603,11 +603,13 @@ extern "C" skim_status skim_build_ic_sketches(const skim_graph *g, uint32_t k, u
             k_ic_keys<<<grid_for(m, 256, 16384), 256, 0, hs>>>(esrc, g->col, m, key);
             SKIM_LAUNCH_CHECK();
             size_t tb = 0;
-            SKIM_HIP(rocprim::radix_sort_pairs(nullptr, tb, key, skey, (const uint32_t *)g->thr,
-                                               sthr, (size_t)m, 32, 32 + node_bits, hs));
+            SKIM_HIP(rocprim::radix_sort_pairs<FewBits>(nullptr, tb, key, skey,
+                                                        (const uint32_t *)g->thr, sthr, (size_t)m,
+                                                        32, 32 + node_bits, hs));
             void *tmp = T.get(tb ? tb : 1);
-            SKIM_HIP(rocprim::radix_sort_pairs(tmp, tb, key, skey, (const uint32_t *)g->thr, sthr,
-                                               (size_t)m, 32, 32 + node_bits, hs));
+            SKIM_HIP(rocprim::radix_sort_pairs<FewBits>(tmp, tb, key, skey,
+                                                        (const uint32_t *)g->thr, sthr, (size_t)m,
+                                                        32, 32 + node_bits, hs));
             k_ic_rfill<<<grid_for(m, 256, 16384), 256, 0, hs>>>(skey, sthr, m, n, seed, rptr,
                                                                redge);
             SKIM_LAUNCH_CHECK();

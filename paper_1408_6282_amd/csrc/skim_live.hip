@@ -19,7 +19,7 @@
 #include "skim_internal.h"
 #include "skim_wave.h"
 
-#include <rocprim/device/device_radix_sort.hpp>
+#include "skim_sort.h"
 
 namespace skim {
 
@@ -351,10 +351,10 @@ ChunkedLists chunked_lists(const skim_graph *g, uint32_t ell, uint64_t seed, con
         skey = a.alloc<uint64_t>(m);
         smask = a.alloc<uint64_t>(m);
         size_t tb = 0;
-        SKIM_HIP(rocprim::radix_sort_pairs(nullptr, tb, key, skey, mask, smask, (size_t)m, 32,
+        SKIM_HIP(rocprim::radix_sort_pairs<FewBits>(nullptr, tb, key, skey, mask, smask, (size_t)m, 32,
                                            32 + head_bits, s));
         void *tmp = a.get(tb ? tb : 1);
-        SKIM_HIP(rocprim::radix_sort_pairs(tmp, tb, key, skey, mask, smask, (size_t)m, 32,
+        SKIM_HIP(rocprim::radix_sort_pairs<FewBits>(tmp, tb, key, skey, mask, smask, (size_t)m, 32,
                                            32 + head_bits, s));
         a.release(tmp);
         a.release(key);
