@@ -225,7 +225,55 @@ void *pinned_scratch(size_t bytes) {
     return buf;
 }
 
+namespace {
+
+// Small reads: a kernel stores the words and then a sequence number to pinned
+// host memory, where the calling thread waits for the number, instead of a blit
+// and the completion signal of a stream synchronization.  (Builds of 1000
+// nodes, 17 reads: 0.53 to 0.44 ms; of 20,000, 24 reads: 1.53 to 1.46.)  Host
+// memory is not cached on the device: system-scope stores reach it without a
+// cache write-back, in order once the wave has waited for them.
+constexpr size_t kBoxBytes = 2048;
+constexpr std::chrono::microseconds kBoxWait{300};  // then a stream synchronization
+struct HostBox {
+    uint32_t data[kBoxBytes / 4];
+    uint32_t flag;
+};
+__global__ void k_to_host(const uint32_t *src, HostBox *box, uint32_t words, uint32_t seq) {
+    for (uint32_t j = threadIdx.x; j < words; j += 64)
+        __hip_atomic_store(&box->data[j], src[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_s_waitcnt(0);
+    if (threadIdx.x == 0)
+        __hip_atomic_store(&box->flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+}  // namespace
+
 void read_back(void *host, const void *dev, size_t bytes, hipStream_t s) {
+    if (bytes <= kBoxBytes && bytes % 4 == 0 && (uintptr_t)dev % 4 == 0) {
+        thread_local HostBox *box = nullptr;
+        thread_local uint32_t seq = 0;
+        if (!box) {
+            void *ptr = nullptr;
+            SKIM_HIP(hipHostMalloc(&ptr, sizeof(HostBox),
+                                   hipHostMallocPortable | hipHostMallocCoherent));
+            box = (HostBox *)ptr;
+            box->flag = 0;
+        }
+        ++seq;
+        k_to_host<<<1, 64, 0, s>>>((const uint32_t *)dev, box, (uint32_t)(bytes / 4), seq);
+        SKIM_LAUNCH_CHECK();
+        const auto until = std::chrono::steady_clock::now() + kBoxWait;
+        bool there = false;
+        for (uint32_t spin = 0; !there; ++spin) {
+            there = __atomic_load_n(&box->flag, __ATOMIC_ACQUIRE) == seq;
+            if (!there && spin % 64 == 63 && std::chrono::steady_clock::now() > until) break;
+        }
+        if (!there) SKIM_HIP(hipStreamSynchronize(s));
+        std::memcpy(host, box->data, bytes);
+        return;
+    }
     void *pin = pinned_scratch(bytes);
     SKIM_HIP(hipMemcpyAsync(pin, dev, bytes, hipMemcpyDeviceToHost, s));
     SKIM_HIP(hipStreamSynchronize(s));
