@@ -1504,38 +1504,106 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Bitonic sort of 64 R keys held in registers by one wave: key r of lane l
-// is element r * 64 + l.  Strides below 64 pair lanes (shuffles), larger
-// strides pair the registers of one lane.  Ascending on return.
-template <int R>
-__device__ __forceinline__ void wave_bitonic(uint64_t (&x)[R], uint32_t lane) {
+// A step of a bitonic sort of 64 R 32-bit keys held in registers by one wave
+// (key r of lane l is element r * 64 + l), on the vector unit alone: a lane
+// move and one med3 (with 0 the smaller of the two, with all ones the larger).
+template <int R, uint32_t kSize, uint32_t kStride>
+__device__ __forceinline__ void bitonic_step32(uint32_t (&x)[R], uint32_t lane) {
+    if constexpr (kStride >= 64) {
+        constexpr int rs = kStride / 64;
 #pragma unroll
-    for (uint32_t size = 2; size <= 64u * R; size <<= 1) {
-#pragma unroll
-        for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-            if (stride >= 64) {
-                const uint32_t rs = stride / 64;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    if ((r & rs) == 0) {
-                        const bool up = ((r * 64u + lane) & size) == 0;
-                        const uint64_t a = x[r], b = x[r | rs];
-                        const bool swap = (a > b) == up;
-                        x[r] = swap ? b : a;
-                        x[r | rs] = swap ? a : b;
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const uint64_t o = shfl_xor_u64(x[r], (int)stride);
-                    const bool up = ((r * 64u + lane) & size) == 0;
-                    const bool low = (lane & stride) == 0;
-                    x[r] = (low == up) ? (x[r] < o ? x[r] : o) : (x[r] < o ? o : x[r]);
-                }
+        for (int r = 0; r < R; ++r)
+            if ((r & rs) == 0) {
+                const uint32_t a = x[r], b = x[r | rs];
+                const bool up = ((r * 64u) & kSize) == 0;  // kSize > kStride >= 64
+                x[r] = up ? min(a, b) : max(a, b);
+                x[r | rs] = up ? max(a, b) : min(a, b);
             }
+    } else {
+        // all ones where the lane's bits of stride and size differ
+        constexpr int kS = __builtin_ctz(kStride), kZ = __builtin_ctz(kSize);
+        uint32_t lim = (uint32_t)((int32_t)(lane << (31 - kS)) >> 31);
+        if constexpr (kSize < 64) lim ^= (uint32_t)((int32_t)(lane << (31 - kZ)) >> 31);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t o = lane_xor<(int)kStride>(x[r]);
+            const uint32_t l = kSize >= 64 && ((r * 64u) & kSize) ? ~lim : lim;
+            x[r] = max(min(x[r], o), min(max(x[r], o), l));  // the middle of the three
         }
     }
+    if constexpr (kStride > 1) bitonic_step32<R, kSize, kStride / 2>(x, lane);
+    else if constexpr (kSize < 64u * R) bitonic_step32<R, 2 * kSize, kSize>(x, lane);
+}
+
+// A wave's ascending bitonic sort in LDS, in rolled loops: where few waves
+// sort, the time is that of fetching the code (512 ranks unrolled in
+// registers are 12 KB, 50 us cold).
+__device__ void lds_bitonic(uint64_t *buf, uint32_t count, uint32_t lane) {
+    for (uint32_t size = 2; size <= count; size <<= 1)
+        for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
+            for (uint32_t e = lane; e < count / 2; e += 64) {
+                const uint32_t i = (e / stride) * 2 * stride + e % stride;
+                const uint64_t a = buf[i], b = buf[i + stride];
+                if ((a > b) == ((i & size) == 0)) {
+                    buf[i] = b;
+                    buf[i + stride] = a;
+                }
+            }
+            wave_lds_sync();
+        }
+}
+
+// Sorts the wave's 64 R ranks, ascending (element r * 64 + lane; kNone last),
+// through buf[64 R]: by their leading bits, as many as fit in 31 beside the
+// element's place (all ones for kNone), then the ranks by place.  Should two
+// ranks share those bits (128 hashed ranks, 24 bits: 5 in 10^4 sorts) the
+// whole ranks are sorted in LDS.  64-bit keys and LDS permutes, 512 ranks: 20
+// us; this 4.
+template <int R>
+__device__ __forceinline__ void wave_sort(uint64_t (&x)[R], uint64_t *buf, uint32_t lane) {
+    constexpr int kPlace = R == 1 ? 6 : R == 2 ? 7 : R == 4 ? 8 : 9;  // bits of a place
+    uint32_t top = 0, low = 0;  // high and low halves
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (x[r] != kNone) {
+            top = max(top, (uint32_t)(x[r] >> 32));
+            low = max(low, (uint32_t)x[r]);
+        }
+    top = ~group_min_u32<64>(~top);
+    low = ~group_min_u32<64>(~low);
+    const int bits = top ? 64 - __clz((int)top) : 32 - __clz((int)low);
+    const int shift = bits > 31 - kPlace ? bits - (31 - kPlace) : 0;
+    uint32_t y[R];
+    // (the steps' lane masks are made where they are used: kept over a loop
+    // over nodes they would hold 60 registers)
+    uint32_t here = lane;
+    asm volatile("" : "+v"(here));
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t j = r * 64u + lane;
+        y[r] = x[r] != kNone ? (uint32_t)(x[r] >> shift) << kPlace | j : 0xFFFFFFFFu;
+        buf[j] = x[r];
+    }
+    bitonic_step32<R, 2, 1>(y, here);
+    bool tie = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        uint32_t next = (uint32_t)__shfl_down((int)y[r], 1);
+        const uint32_t over = (uint32_t)__builtin_amdgcn_readfirstlane((int)y[r + 1 < R ? r + 1 : r]);
+        if (lane == 63) next = r + 1 < R ? over : 0xFFFFFFFFu;
+        tie |= next != 0xFFFFFFFFu && y[r] >> kPlace == next >> kPlace;
+    }
+    wave_lds_sync();
+    if (__any(tie)) {
+        lds_bitonic(buf, 64u * R, lane);
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[r] = buf[r * 64 + lane];
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            x[r] = y[r] != 0xFFFFFFFFu ? buf[y[r] & ((1u << kPlace) - 1)] : kNone;
+    }
+    wave_lds_sync();  // buf may be written again
 }
 
 // The k smallest of the S <= 64 R ranks of segment `a` (records sorted by
@@ -1543,14 +1611,14 @@ __device__ __forceinline__ void wave_bitonic(uint64_t (&x)[R], uint32_t lane) {
 template <int R>
 __device__ __forceinline__ void select_regs(const uint64_t *seg, uint64_t a, uint64_t S,
                                             uint32_t k, uint64_t seed, const uint64_t *table,
-                                            uint64_t *row, uint32_t lane) {
+                                            uint64_t *row, uint64_t *buf, uint32_t lane) {
     uint64_t x[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const uint64_t j = r * 64u + lane;
         x[r] = j < S ? rank_of(seed, table, (uint32_t)seg[a + j]) : kNone;
     }
-    wave_bitonic<R>(x, lane);
+    wave_sort<R>(x, buf, lane);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const uint32_t j = r * 64u + lane;
@@ -1559,48 +1627,66 @@ __device__ __forceinline__ void select_regs(const uint64_t *seg, uint64_t a, uin
     for (uint32_t j = 64u * R + lane; j < k; j += 64) row[j] = kNone;  // k above 64 R
 }
 
-// One wave per node: keep the k smallest ranks of the node's records
-// seg[start[v], end[v]).  Up to 512 records are sorted in registers; a
-// longer segment goes through LDS in chunks of 256, keeping the 256
-// smallest so far (k <= 256).
-__global__ void __launch_bounds__(256) k_select(const uint64_t *start, const uint64_t *end,
-                                                const uint64_t *seg, uint32_t n, uint32_t k,
-                                                uint64_t seed, const uint64_t *table,
-                                                uint64_t *ranks, uint32_t *size) {
-    __shared__ uint64_t lbuf[4][512];
+// The nodes of more than kSelectSmall records, a workgroup each (a wave alone
+// was 70 us in the hubs of 20,000 nodes): every wave keeps the 256 smallest
+// (k <= 256) of its quarter, and the quarters are merged.  A workgroup looks
+// through `chunk` (at most 64) nodes at a time, far apart: hubs are often
+// neighbours.
+constexpr uint32_t kSelectSmall = 512;
+__device__ __forceinline__ void select_long(uint64_t (*lbuf)[kSelectSmall], uint32_t block,
+                                            uint32_t blocks, const uint64_t *start,
+                                            const uint64_t *end, const uint64_t *seg, uint32_t n,
+                                            uint32_t k, uint64_t seed, const uint64_t *table,
+                                            uint64_t *ranks, uint32_t chunk) {
     const uint32_t lane = lane_id(), wave = threadIdx.x / 64;
     uint64_t *buf = lbuf[wave];
-    const uint64_t waves = (uint64_t)gridDim.x * 4;
-    for (uint64_t v = blockIdx.x * 4ull + wave; v < n; v += waves) {
-        const uint64_t a = start[v], b = end[v];
-        const uint64_t S = b - a;
-        uint64_t *row = ranks + v * k;
-        if (S <= 64) select_regs<1>(seg, a, S, k, seed, table, row, lane);
-        else if (S <= 128) select_regs<2>(seg, a, S, k, seed, table, row, lane);
-        else if (S <= 256) select_regs<4>(seg, a, S, k, seed, table, row, lane);
-        else if (S <= 512) select_regs<8>(seg, a, S, k, seed, table, row, lane);
-        else {
+    for (uint64_t v0 = block; v0 < n; v0 += (uint64_t)blocks * chunk) {
+        uint64_t va = 0, vb = 0;
+        const uint64_t v = v0 + (uint64_t)blocks * lane;
+        if (lane < chunk && v < n) {
+            va = start[v];
+            vb = end[v];
+        }
+        for (uint64_t m = __ballot(vb - va > kSelectSmall); m; m &= m - 1) {  // alike in all waves
+            const uint32_t o = (uint32_t)__ffsll((long long)m) - 1u;
+            const uint64_t a = shfl_u64(va, o), b = shfl_u64(vb, o);
             // buf[0, 256): the 256 smallest so far, ascending; buf[256, 256 + nc):
             // candidates since, the ranks below the k-th smallest so far (no
             // other can be among the k smallest).  The candidates are merged
-            // in by one sort of the 512 slots once they may outgrow their room.
+            // in by one sort of the 512 slots when the next 256 records, four
+            // loads in flight, would outgrow their room.
             for (uint32_t j = lane; j < 512; j += 64) buf[j] = kNone;
             wave_lds_sync();
             uint64_t tau = kNone;
             uint32_t nc = 0;
-            for (uint64_t c = a; c < b; c += 64) {
-                const uint64_t x =
-                    c + lane < b ? rank_of(seed, table, (uint32_t)seg[c + lane]) : kNone;
-                const bool cand = x < tau;
-                const unsigned long long m = __ballot(cand);
-                if (cand) buf[256 + nc + __popcll(m & ((1ull << lane) - 1ull))] = x;
-                nc += (uint32_t)__popcll(m);
-                if (nc > 192 || (c + 64 >= b && nc > 0)) {
+            // phase 0: the wave's quarter; 1 and 2: pairs of waves, then of
+            // pairs.  One call site of the sort: few waves run this, and its
+            // code comes from memory.
+            uint64_t c = a + 256 * wave;
+            for (uint32_t phase = 0; phase < 3;) {
+                uint64_t x[4] = {kNone, kNone, kNone, kNone};
+                bool sort;
+                if (phase == 0) {
+                    uint32_t cnt = 0;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const uint64_t t = c + 64 * r + lane;
+                        if (t < b) x[r] = rank_of(seed, table, (uint32_t)seg[t]);
+                        cnt += (uint32_t)__popcll(__ballot(x[r] < tau));
+                    }
+                    sort = nc + cnt > 256 || (c >= b && nc);
+                } else {
+                    __syncthreads();
+                    sort = wave % (2 * phase) == 0;
+                    if (sort)
+                        for (uint32_t j = lane; j < 256; j += 64) buf[256 + j] = lbuf[wave + phase][j];
+                }
+                if (sort) {  // the 512 slots in order, the upper 256 given up
                     wave_lds_sync();
                     uint64_t y[8];
 #pragma unroll
                     for (int r = 0; r < 8; ++r) y[r] = buf[r * 64 + lane];
-                    wave_bitonic<8>(y, lane);
+                    wave_sort<8>(y, buf, lane);
 #pragma unroll
                     for (int r = 0; r < 4; ++r) buf[r * 64 + lane] = y[r];
 #pragma unroll
@@ -1609,11 +1695,63 @@ __global__ void __launch_bounds__(256) k_select(const uint64_t *start, const uin
                     tau = buf[k - 1];
                     nc = 0;
                 }
+                if (phase || c >= b) {
+                    ++phase;
+                    continue;
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool cand = x[r] < tau;
+                    const unsigned long long mc = __ballot(cand);
+                    if (cand) buf[256 + nc + __popcll(mc & ((1ull << lane) - 1ull))] = x[r];
+                    nc += (uint32_t)__popcll(mc);
+                }
+                c += 1024;
             }
-            for (uint32_t j = lane; j < k; j += 64) row[j] = buf[j];
-            wave_lds_sync();  // buf is refilled for the wave's next node
+            if (wave == 0)
+                for (uint32_t j = lane; j < k; j += 64) ranks[(v0 + (uint64_t)blocks * o) * k + j] = buf[j];
+            __syncthreads();  // the buffers are refilled for the next node
         }
-        if (lane == 0) size[v] = (uint32_t)(S < k ? S : k);
+    }
+}
+
+// Keep the k smallest ranks of each node's records seg[start[v], end[v]): the
+// first `longs` workgroups those of the nodes of more than kSelectSmall, the
+// others a wave per node, sorted in registers.  What bounds it: the wait for
+// the records and the ranks' hashes.  A wave reads the bounds of `chunk` (at
+// most 64) nodes at once.  10^6 nodes, k = 64: 1.50 ms at 2 waves per SIMD
+// with 64-bit sorts by LDS permutes (192 registers), 0.69 ms so.
+__global__ void __launch_bounds__(256, 5) k_select(const uint64_t *start, const uint64_t *end,
+                                                   const uint64_t *seg, uint32_t n, uint32_t k,
+                                                   uint64_t seed, const uint64_t *table,
+                                                   uint64_t *ranks, uint32_t *size, uint32_t chunk,
+                                                   uint32_t longs) {
+    __shared__ uint64_t lbuf[4][kSelectSmall];
+    if (blockIdx.x < longs) {
+        select_long(lbuf, blockIdx.x, longs, start, end, seg, n, k, seed, table, ranks,
+                    min(8 * chunk, 64u));
+        return;
+    }
+    const uint32_t lane = lane_id(), wave = threadIdx.x / 64;
+    uint64_t *buf = lbuf[wave];
+    const uint64_t waves = (uint64_t)(gridDim.x - longs) * 4;
+    for (uint64_t v0 = ((blockIdx.x - longs) * 4ull + wave) * chunk; v0 < n; v0 += waves * chunk) {
+        uint64_t va = 0, vb = 0;
+        const bool valid = lane < chunk && v0 + lane < n;
+        if (valid) {
+            va = start[v0 + lane];
+            vb = end[v0 + lane];
+            size[v0 + lane] = (uint32_t)(vb - va < k ? vb - va : k);
+        }
+        for (uint64_t m = __ballot(valid && vb - va <= kSelectSmall); m; m &= m - 1) {
+            const uint32_t o = (uint32_t)__ffsll((long long)m) - 1u;
+            const uint64_t a = shfl_u64(va, o), S = shfl_u64(vb, o) - a;
+            uint64_t *row = ranks + (v0 + o) * k;
+            if (S <= 64) select_regs<1>(seg, a, S, k, seed, table, row, buf, lane);
+            else if (S <= 128) select_regs<2>(seg, a, S, k, seed, table, row, buf, lane);
+            else if (S <= 256) select_regs<4>(seg, a, S, k, seed, table, row, buf, lane);
+            else select_regs<8>(seg, a, S, k, seed, table, row, buf, lane);
+        }
     }
 }
 
@@ -2232,8 +2370,10 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
     }
     {
         LaunchTimer t("k_select", s);
-        k_select<<<grid_for(n, 4, 65536), 256, 0, s>>>(gstart, gend, seg, n, k, seed, rs.table,
-                                                      ranks_out, size_out);
+        const uint32_t chunk = std::min(std::max(1u, n / 16384), 64u);
+        const unsigned longs = grid_for((n + chunk - 1) / chunk, 8, 4096);
+        k_select<<<longs + grid_for((n + chunk - 1) / chunk, 4, 65536), 256, 0, s>>>(
+            gstart, gend, seg, n, k, seed, rs.table, ranks_out, size_out, chunk, longs);
     }
     SKIM_LAUNCH_CHECK();
     if (work) {

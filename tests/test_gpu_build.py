@@ -268,3 +268,18 @@ def test_tails_lists_and_stacks(oracle_lib, n, fan, denom, ell, k):
     g = from_edges(n, e[:, 0], e[:, 1], 0xFFFFFFFF // denom)
     log(f"tails n={n} fan={fan} ell={ell} k={k}")
     _check(oracle_lib, g, ell, k, 9)
+
+
+@pytest.mark.parametrize("ell,k", [(4, 256), (64, 16), (16, 64)])
+def test_select_segment_sizes(oracle_lib, ell, k):
+    """Nodes of every record count about the sizes where the selection changes
+    its sort (64, 128, 256, 512 records), and of a few thousand."""
+    rng = np.random.default_rng(ell)
+    n = 1600
+    fans = [14, 15, 16, 17, 30, 31, 32, 33, 62, 63, 64, 65, 126, 127, 128, 129, 200, 255, 256, 257,
+            400, 511, 512, 513, 700, 1500]
+    e = np.concatenate([np.stack([rng.choice(np.arange(len(fans), n), f, replace=False),
+                                  np.full(f, v)], 1) for v, f in enumerate(fans)])
+    g = from_edges(n, e[:, 0], e[:, 1], 0xFFFFFFFF)
+    log(f"segment sizes ell={ell} k={k}")
+    _check(oracle_lib, g, ell, k, 21)
