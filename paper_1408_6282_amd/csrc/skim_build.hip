@@ -1446,6 +1446,7 @@ __global__ void k_ctl_begin(Ctl *ctl, unsigned long long visits, unsigned long l
                             unsigned long long records) {
     ctl->size[16 * (0)] = ctl->size[16 * (1)] = ctl->size[16 * (2)] = 0;
     ctl->hsize[0] = ctl->hsize[16] = 0;
+    ctl->budget = 0;
     ctl->hinserts = 0;
     ctl->flags = 0;
     ctl->visits = visits;
@@ -2180,8 +2181,10 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
                         const uint64_t hroom = 2 * hsize / 5 > h.hinserts
                                                    ? 2 * hsize / 5 - h.hinserts : 0;
                         const uint64_t room = std::min<uint64_t>(rec_cap - h.records, hroom);
-                        k_tails_begin<<<1, 1, 0, s>>>(ctl, L);
-                        SKIM_LAUNCH_CHECK();
+                        if (L > 0) {  // (k_ctl_begin left these counters zero)
+                            k_tails_begin<<<1, 1, 0, s>>>(ctl, L);
+                            SKIM_LAUNCH_CHECK();
+                        }
                         const WinArgs WA = args();
                         LaunchTimer t("k_tails", s);
                         k_tails<<<G, kTailsBlock, 0, s>>>(WA, L, f, room);
@@ -2351,9 +2354,8 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
         A.release(fend);
     }
     uint64_t *seg = A.alloc<uint64_t>(nrec ? nrec : 1);
-    uint64_t *gstart = A.alloc<uint64_t>(n), *gend = A.alloc<uint64_t>(n);
-    fill_u64(gstart, 0, n, s);
-    fill_u64(gend, 0, n, s);
+    uint64_t *gstart = A.alloc<uint64_t>(2 * (uint64_t)n), *gend = gstart + n;
+    fill_u64(gstart, 0, 2 * (uint64_t)n, s);
     if (nrec) {
         // stable radix sort of the records on their node bits
         int nb = 1;

@@ -361,9 +361,8 @@ ChunkedLists chunked_lists(const skim_graph *g, uint32_t ell, uint64_t seed, con
         a.release(mask);
     }
     // runs and their chunks
-    uint64_t *beg = a.alloc<uint64_t>(n), *end = a.alloc<uint64_t>(n);
-    fill_u64(beg, 0, n, s);
-    fill_u64(end, 0, n, s);
+    uint64_t *beg = a.alloc<uint64_t>(2 * (uint64_t)n), *end = beg + n;
+    fill_u64(beg, 0, 2 * (uint64_t)n, s);
     k_in_runs<<<grid_for(m, 256, 65536), 256, 0, s>>>(skey, m, beg, end);
     SKIM_LAUNCH_CHECK();
     uint32_t *nch = a.alloc<uint32_t>(n);
@@ -380,8 +379,8 @@ ChunkedLists chunked_lists(const skim_graph *g, uint32_t ell, uint64_t seed, con
     const ChunkArgs C{skey, smask, beg, end, choff, chnode, nchunks, ell};
     // 1. counts per chunk and per pair
     uint32_t *ccnt = a.alloc<uint32_t>(nchunks * kPairStride);
-    uint32_t *pcnt = a.alloc<uint32_t>(npairs);
-    fill_u32(pcnt, 0, npairs, s);
+    uint32_t *pcnt = a.alloc<uint32_t>(npairs + 2), *flags = pcnt + npairs;
+    fill_u32(pcnt, 0, npairs + 2, s);
     const unsigned cgrid = grid_for(nchunks, 4, 65536);  // four waves (chunks) per block
     {
         LaunchTimer t("k_pair_count", s);
@@ -390,8 +389,6 @@ ChunkedLists chunked_lists(const skim_graph *g, uint32_t ell, uint64_t seed, con
     SKIM_LAUNCH_CHECK();
     // 2. room per node, scan over the nodes
     uint32_t *room = a.alloc<uint32_t>(n);
-    uint32_t *flags = a.alloc<uint32_t>(2);
-    fill_u32(flags, 0, 2, s);
     k_pair_room<<<grid_for(n, 4, 65536), 256, 0, s>>>(pcnt, n, csr, room, flags);
     SKIM_LAUNCH_CHECK();
     uint64_t *node_off = a.alloc<uint64_t>((uint64_t)n + 1);
@@ -418,7 +415,7 @@ ChunkedLists chunked_lists(const skim_graph *g, uint32_t ell, uint64_t seed, con
     }
     SKIM_LAUNCH_CHECK();
     if (csr) fill_u64(L.live + npairs, tot, 1, s);
-    for (void *p : {(void *)node_off, (void *)beg, (void *)end, (void *)skey, (void *)smask,
+    for (void *p : {(void *)node_off, (void *)beg, (void *)skey, (void *)smask,
                     (void *)choff, (void *)chnode, (void *)ccnt, (void *)pcnt})
         a.release(p);
     return L;

@@ -283,3 +283,13 @@ def test_select_segment_sizes(oracle_lib, ell, k):
     g = from_edges(n, e[:, 0], e[:, 1], 0xFFFFFFFF)
     log(f"segment sizes ell={ell} k={k}")
     _check(oracle_lib, g, ell, k, 21)
+
+
+@pytest.mark.parametrize("n", [1, 2, 4095, 4096, 4097, 32767, 32769])
+def test_scan_sizes(oracle_lib, n):
+    """Node counts at the edges of the single-workgroup prefix sum's rounds and
+    of its range."""
+    src = np.arange(0, n - 1, 3)
+    g = from_edges(n, src, src + 1, 0xFFFFFFFF)
+    log(f"scan sizes n={n}")
+    _check(oracle_lib, g, 2, 4, 3)
