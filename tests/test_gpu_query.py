@@ -218,3 +218,22 @@ def test_set_sizes_at_class_edges(oracle_lib, k, low_bits):
             want, _ = oracle_lib.perm_union_query(P, S, 1 << 17, k, ell, off,
                                                   np.minimum(nodes, n - 1), estimator)
             assert np.array_equal(est.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("k,q", [(16, 64), (16, 65), (33, 1024), (33, 1025), (64, 1024), (64, 1025),
+                                 (64, 2000)])
+def test_batch_sizes_at_kernel_edges(oracle_lib, k, q):
+    """Bottom-k batches at the sizes where the kernel for few queries gives way
+    to a wave per query, within the grid of the persistent one."""
+    from gpu_util import to_dev_u32, to_dev_u64
+    n, ell = 300, 16
+    rng = np.random.default_rng(k + q)
+    R, S = _pool_tables(rng, n, k, 0)
+    sets = [rng.integers(0, n, size=int(s)).tolist()
+            for s in rng.choice([0, 1, 2, 7, 8, 9, 16, 17, 64, 65, 300], size=q)]
+    off, nodes = _sets(sets)
+    log(f"batch sizes k={k} q={q}")
+    want, wst = oracle_lib.union_query(R, S, k, ell, off, nodes)
+    got, status = gpu_query(to_dev_u64(R.reshape(-1)), to_dev_u32(S), n, k, ell, off, nodes, 0)
+    assert np.array_equal(status, wst)
+    assert np.array_equal(got, want)
