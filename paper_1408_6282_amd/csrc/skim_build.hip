@@ -35,21 +35,23 @@
 //     searches of a window advance together, level by level: one
 //     whole-grid launch per level (frontiers in batches of levels launched
 //     without reading their sizes back); once the frontier is small it is
-//     split over many workgroups that each run the remaining levels of their
-//     part in LDS, without waiting for each other (the window's result does
-//     not depend on the order of its visits).  Visits are
+//     split over many waves that each search on in their part with a stack
+//     in LDS, without waiting for each other (the window's result does not
+//     depend on the order of its visits).  Visits are
 //     deduplicated per source exactly: the first visitor of a pair in the
 //     window claims the pair's state word; later visitors go through a
 //     hash set keyed by (pair, source).  The same word counts the pair's
 //     arrivals (up to k, all pruning needs).  A visit that could neither
 //     expand nor record (no live in-edge, node no longer recording) is
-//     skipped.
+//     skipped.  On graphs whose first window overflows, windows of few
+//     sources per instance keep each pair's sources as bit sets instead and
+//     move whole words along live in-edges (dense windows, below).
 //  4. Records.  A visit of node v is recorded while v held fewer than k
 //     ranks at the window start; windows go up in rank, so the k smallest
 //     records of v are its sketch.
 //  5. Merge.  Records are sorted by node (radix sort on the node bits) and
-//     each node keeps its k smallest ranks in LDS (bitonic sort), written
-//     ascending.
+//     each node keeps its k smallest ranks (sorted by leading bits in
+//     registers), written ascending.
 //
 // Device atomics from different waves on one 128-byte line are serialised
 // by the hardware, so shared counters sit on lines of their own and are
@@ -1931,6 +1933,7 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
                 dense_words = words;
             }
         } catch (const Fail &) {
+            clear_error();  // not this call's error: the window goes without
             return false;
         }
         D.nw = nw;
