@@ -1925,12 +1925,23 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
                 if (D.heavy_cap) D.heavy = A.alloc<uint64_t>(D.heavy_cap);
                 D.haslive = A.alloc<uint64_t>(n);
             }
-            if (words > dense_words) {
+            // V is taken at the largest size a window may need: grown from
+            // window to window it left its smaller blocks behind (on R-MAT of
+            // 2^24 nodes, 17 GB of pair records, the blocks of a build then
+            // outgrew the cache and each build spent 2.6 s of 2.9 allocating)
+            const uint64_t most_words =
+                std::min<uint64_t>(kDenseWords, tot / 6 / 8 / ((uint64_t)n * ell));
+            for (uint64_t want_words : {(uint64_t)n * ell * most_words, words}) {
+                if (words <= dense_words) break;
                 if (D.V) A.release(D.V);
                 D.V = nullptr;
                 dense_words = 0;
-                D.V = A.alloc<uint64_t>(words);
-                dense_words = words;
+                try {
+                    D.V = A.alloc<uint64_t>(want_words);
+                    dense_words = want_words;
+                } catch (const Fail &) {
+                    if (want_words == words) throw;
+                }
             }
         } catch (const Fail &) {
             clear_error();  // not this call's error: the window goes without
@@ -2030,6 +2041,11 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
                 k_dense_finish<false><<<grid_for(n, kBlock / 8, 8192), kBlock, 0, s>>>(D);
                 SKIM_LAUNCH_CHECK();
             }
+        }
+        if (!dense && D.V) {  // room for the hash set
+            A.release(D.V);
+            D.V = nullptr;
+            dense_words = 0;
         }
         for (int redo = 0; !dense; ++redo) {
             uint32_t logcap = 0;

@@ -66,11 +66,14 @@ int current_device() {
     return dev;
 }
 
-// Free cached blocks of `dev` (largest first) until at most `keep` bytes stay.
+// Free cached blocks of `dev` until at most `keep` bytes stay: the smallest
+// that is enough, else the largest (taking a block of tens of GB again costs
+// the next call most of a second).
 void trim_cache(int dev, size_t keep) {
     DeviceCache &C = g_cache[dev];
     while (C.cached > keep && !C.free.empty()) {
-        auto it = std::prev(C.free.end());
+        auto it = C.free.lower_bound(C.cached - keep);
+        if (it == C.free.end()) --it;
         C.cached -= it->first;
         (void)hipFree(it->second);
         C.free.erase(it);
@@ -166,12 +169,23 @@ void *Arena::get(size_t bytes) {
         static const bool trace = std::getenv("SKIM_TRACE_ALLOC") != nullptr;
         const auto t0 = std::chrono::steady_clock::now();
         hipError_t e = hipMalloc(&p, cls);
-        if (e != hipSuccess || !p) {  // give the cache back to the device and try once more
+        if (e != hipSuccess || !p) {
+            // give the cache and this arena's spare blocks back to the device
+            // and try once more
             (void)hipGetLastError();
             {
                 std::lock_guard<std::mutex> lk(g_cache_mu);
                 trim_cache(dev_, 0);
             }
+            bool any = false;
+            for (auto &b : spare_) any |= b.p != nullptr;
+            if (any) quiesce(dev_, s_, false);  // the stream may still use them
+            for (auto &b : spare_)
+                if (b.p) {
+                    (void)hipFree(b.p);
+                    b.p = nullptr;
+                }
+            (void)hipGetLastError();
             p = nullptr;
             e = hipMalloc(&p, cls);
         }
