@@ -105,7 +105,7 @@ struct SkCtl {
     unsigned long long cursor;     // next position in the rank order
     unsigned long long pool_used;  // index entries in use
     unsigned long long need;       // pool entries a failed batch needed
-    uint32_t done;                 // seeds completed in this call
+    uint32_t done;                 // seeds completed in this call (cleared with flags)
     uint32_t flags;
     // A residual search handed to the whole grid (its frontier outgrew the
     // workgroup): the seed, the frontier buffer of its current level, the
@@ -1785,6 +1785,7 @@ struct skim_greedy_state {
     uint64_t order_step = 0;  // pairs the next step aims at
     bool ahead_due = true;    // the window has not been searched yet
     uint64_t cursor = 0;      // pairs used, as the last launch left it
+    bool running = false;     // a call is under way, or ended in an error
     skim::SkArgs args{};
 };
 
@@ -1953,6 +1954,9 @@ void greedy_run(skim_greedy_state *st, uint32_t s_goal, uint32_t *seeds, uint64_
     uint32_t done = 0;
     int growths = 0, rounds = 0;
     bool begin = true;
+    // a call that failed (memory) left its count and its request behind
+    if (st->running) fill_u32(&A.ctl->done, 0, 2, s);
+    st->running = true;
     auto skim = [&] {
         auto kernel = A.n <= kSkimStateNodes ? k_skim<true, true>
                       : A.n <= kSkimLdsNodes ? k_skim<true, false>
@@ -2015,6 +2019,7 @@ void greedy_run(skim_greedy_state *st, uint32_t s_goal, uint32_t *seeds, uint64_
             throw Fail{SKIM_EDEVICE};
         }
     }
+    st->running = false;
 }
 
 }  // namespace skim

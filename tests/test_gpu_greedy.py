@@ -267,3 +267,32 @@ def test_long_lists_and_counter_limits(oracle_lib, n, hubs, fan, ell, k, s):
     seeds, gains, _, _ = gpu_greedy(g, ell, k, 11, [s])
     ws, wg, _ = oracle_lib.skim(g, 11, ell, k, s)
     assert np.array_equal(seeds, ws) and np.array_equal(gains, wg)
+
+
+def test_run_continues_after_a_failed_allocation(oracle_lib):
+    # the rank order's scratch is refused once: the call fails, the state stays
+    # good and the next calls give the oracle's sequence
+    import torch
+    import paper_1408_6282_amd as sk
+    cfg = make_config("served-skim")
+    g = make_graph(cfg)
+    G = sk.DeviceGraph.from_host(g, "cuda:0")
+    state = sk.GreedyState()
+    a = torch.empty(12, dtype=torch.int32, device="cuda:0")
+    b = torch.empty(12, dtype=torch.int64, device="cuda:0")
+    try:
+        sk.skim_greedy(G, cfg["ell"], cfg["k"], cfg["seed"], 0, a, b, state=state)
+        sk.skim_debug_inject(sk.SKIM_FAULT_ALLOC, 1)
+        with pytest.raises(sk.SkimError) as ei:
+            sk.skim_greedy(G, cfg["ell"], cfg["k"], cfg["seed"], 5, a, b, state=state)
+        assert ei.value.status == sk.SKIM_ENOMEM
+        sk.skim_debug_inject(sk.SKIM_FAULT_ALLOC, 0)
+        sk.skim_greedy(G, cfg["ell"], cfg["k"], cfg["seed"], 5, a[:5], b[:5], state=state)
+        sk.skim_greedy(G, cfg["ell"], cfg["k"], cfg["seed"], 7, a[5:], b[5:], state=state)
+        torch.cuda.synchronize()
+    finally:
+        sk.skim_debug_inject(sk.SKIM_FAULT_ALLOC, 0)
+        state.free()
+    ws, wg, _ = oracle_lib.skim(g, cfg["seed"], cfg["ell"], cfg["k"], 12)
+    assert np.array_equal(a.cpu().numpy().view(np.uint32), ws)
+    assert np.array_equal(b.cpu().numpy().view(np.uint64), wg)
