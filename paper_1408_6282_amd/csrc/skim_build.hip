@@ -2110,7 +2110,8 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
                 // every node (R-MAT, 4096 nodes, l = 64: 2.4 ms carried on,
                 // 3.2 ms given up; 16384 nodes, l = 7: 5.1 and 2.5 ms).
                 const uint64_t f_ref = f_prev ? f_prev : n > kOptimisticNodes ? f_tails : 0;
-                if (w == 0 && span > 1 && f_ref && f > 4 * f_ref && f > kOptimistic &&
+                if (w == 0 && span > 1 && f_ref && f > 4 * f_ref &&
+                    f > (f_prev ? kOptimistic : kOptimistic / 2) &&
                     (double)f * ((double)f / (double)f_ref) > 0.4 * (double)hsize) {
                     overflow = kOvfHash;
                     break;
