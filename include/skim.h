@@ -85,12 +85,14 @@ const char *skim_last_error(void);
  * with status -5 and its slot is freed); SKIM_FAULT_IC_RECORDS: the next
  * `count` skim_build_ic_sketches calls give their single record-appending
  * pass room for one record, so that they take the counting path (same
- * results).  count = 0 disarms.  Process-wide.  SKIM_EINVAL for an unknown
+ * results); SKIM_FAULT_ALLOC_NTH: of the device allocations from now on, the
+ * count-th fails, once.  count = 0 disarms.  Process-wide.  SKIM_EINVAL for an unknown
  * kind.
  */
 #define SKIM_FAULT_ALLOC 1u
 #define SKIM_FAULT_SERVE 2u
 #define SKIM_FAULT_IC_RECORDS 3u
+#define SKIM_FAULT_ALLOC_NTH 4u
 skim_status skim_debug_inject(uint32_t what, uint32_t count);
 
 /*
@@ -269,7 +271,10 @@ void skim_query_plan_free(skim_query_plan *plan);
  *     selects the next s seeds (g, l, k, seed must be those of the run;
  *     the graph buffers must stay valid while the state lives).  Resuming
  *     in steps gives exactly the one-shot sequence.  s may not exceed the
- *     number of unselected nodes.
+ *     number of unselected nodes.  A resuming call that fails with
+ *     SKIM_ENOMEM leaves a good state: the seeds it had selected by then (the
+ *     rise of skim_greedy_state_selected) are in its outputs, and the next
+ *     call goes on after them.
  */
 typedef struct skim_greedy_state skim_greedy_state;
 

@@ -127,18 +127,24 @@ Arena::~Arena() {
     if (C.cached > C.limit) trim_cache(dev_, C.limit);
 }
 
-std::atomic<uint32_t> g_fault[4];
+std::atomic<uint32_t> g_fault[5];
 
-bool take_fault(FaultKind what) {
+// Counts down by one; the count as it was.
+static uint32_t count_fault(FaultKind what) {
     std::atomic<uint32_t> &c = g_fault[what];
     uint32_t v = c.load();
     while (v && !c.compare_exchange_weak(v, v - 1)) {
     }
-    return v != 0;
+    return v;
+}
+bool take_fault(FaultKind what) { return count_fault(what) != 0; }
+bool alloc_fault() {
+    const bool nth = count_fault(kFaultAllocNth) == 1;
+    return take_fault(kFaultAlloc) || nth;
 }
 
 void *Arena::get(size_t bytes) {
-    if (take_fault(kFaultAlloc)) {
+    if (alloc_fault()) {
         set_error("device allocation of %zu bytes failed: injected failure", bytes);
         throw Fail{SKIM_ENOMEM};
     }
@@ -641,7 +647,8 @@ extern "C" uint32_t skim_abi_version(void) { return SKIM_ABI_VERSION; }
 
 extern "C" skim_status skim_debug_inject(uint32_t what, uint32_t count) {
     skim::clear_error();
-    if (what != SKIM_FAULT_ALLOC && what != SKIM_FAULT_SERVE && what != SKIM_FAULT_IC_RECORDS) {
+    if (what != SKIM_FAULT_ALLOC && what != SKIM_FAULT_SERVE && what != SKIM_FAULT_IC_RECORDS &&
+        what != SKIM_FAULT_ALLOC_NTH) {
         skim::set_error("unknown fault kind %u", what);
         return SKIM_EINVAL;
     }

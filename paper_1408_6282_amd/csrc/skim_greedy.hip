@@ -1805,13 +1805,16 @@ void greedy_set_ctl(skim_greedy_state *st, uint64_t cursor, uint64_t pool_used, 
     SKIM_HIP(hipStreamSynchronize(s));
 }
 
-// The next step of the pairs' order by rank.
+// The next step of the pairs' order by rank.  An allocation may fail anywhere
+// in it and the state goes on being used: what the order holds, the rank it
+// goes on from and the next step's length change together, once the step's
+// pairs are in place.
 void greedy_extend_order(skim_greedy_state *st, hipStream_t s) {
     SkArgs &A = st->args;
     const uint64_t left = A.nsrc - A.ordered;
     const bool whole = A.nsrc <= kOrderWhole;
     Arena T(s);
-    uint64_t count = A.nsrc;
+    uint64_t count = A.nsrc, rank_next = st->rank_next, order_step = st->order_step;
     uint64_t *keys;
     uint32_t *vals;
     if (whole) {
@@ -1832,13 +1835,18 @@ void greedy_extend_order(skim_greedy_state *st, hipStream_t s) {
         k_rank_count<<<kOrderGrid, kOrderBlock, 0, s>>>(A.n, A.ell, A.seed, r0, r1, counts, totals);
         SKIM_LAUNCH_CHECK();
         read_back(&count, totals, sizeof count, s);
+        if (count > left || (last && count != left)) {  // `order` has room for all ranks, once
+            set_error("%llu pairs in a step of the rank order, %llu left",
+                      (unsigned long long)count, (unsigned long long)left);
+            throw Fail{SKIM_EDEVICE};
+        }
         keys = T.alloc<uint64_t>(count ? count : 1);
         vals = T.alloc<uint32_t>(count ? count : 1);
         k_rank_take<<<kOrderGrid, kOrderBlock, 0, s>>>(A.n, A.ell, A.seed, r0, r1, counts,
                                                        totals + 1, keys, vals);
         SKIM_LAUNCH_CHECK();
-        st->rank_next = r1 + 1;
-        st->order_step *= 4;
+        rank_next = r1 + 1;
+        order_step *= 4;
     }
     if (count) {
         uint64_t *keys2 = T.alloc<uint64_t>(count);
@@ -1860,6 +1868,8 @@ void greedy_extend_order(skim_greedy_state *st, hipStream_t s) {
     }
     SKIM_HIP(hipStreamSynchronize(s));
     A.ordered += count;
+    st->rank_next = rank_next;
+    st->order_step = order_step;
 }
 
 skim_greedy_state *greedy_create(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t seed,

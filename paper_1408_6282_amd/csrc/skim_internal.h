@@ -118,9 +118,14 @@ void clear_error();
 // Host-side fault injection (skim_debug_inject): the next `count` device
 // allocations (kFaultAlloc) or serving-loop copies and launches
 // (kFaultServe) are treated as failed, or IC-model sketch builds take their
-// counting path (kFaultIcRecords).  take_fault() consumes one.
-enum FaultKind : uint32_t { kFaultAlloc = 1, kFaultServe = 2, kFaultIcRecords = 3 };
+// counting path (kFaultIcRecords).  take_fault() consumes one.  Of
+// kFaultAllocNth's count only the last allocation fails: alloc_fault() is
+// whether the one about to be made does.
+enum FaultKind : uint32_t {
+    kFaultAlloc = 1, kFaultServe = 2, kFaultIcRecords = 3, kFaultAllocNth = 4
+};
 bool take_fault(FaultKind what);
+bool alloc_fault();
 
 struct Fail {
     skim_status st;

@@ -1156,7 +1156,7 @@ static void sketches_free(skim_sketches *h) {
 static skim_sketches *sketches_alloc(uint32_t n, uint32_t k, uint32_t ell) {
     SKIM_REQUIRE(n >= 1 && k >= 2 && k <= 256 && ell >= 1 && ell <= 64,
                  "need n >= 1, 2 <= k <= 256, 1 <= l <= 64");
-    if (take_fault(kFaultAlloc)) {
+    if (alloc_fault()) {
         set_error("device allocation for resident sketches failed: injected failure");
         throw Fail{SKIM_ENOMEM};
     }

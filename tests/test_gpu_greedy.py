@@ -296,3 +296,48 @@ def test_run_continues_after_a_failed_allocation(oracle_lib):
     ws, wg, _ = oracle_lib.skim(g, cfg["seed"], cfg["ell"], cfg["k"], 12)
     assert np.array_equal(a.cpu().numpy().view(np.uint32), ws)
     assert np.array_equal(b.cpu().numpy().view(np.uint64), wg)
+
+
+def test_order_steps_survive_a_failed_allocation(oracle_lib):
+    # more than 2^20 pairs, so the rank order is made in steps (here two, the
+    # second the last one): every allocation of the selection fails in turn,
+    # the call is made again on the same state, and the seeds and gains of both
+    # calls are the oracle's
+    import torch
+    import paper_1408_6282_amd as sk
+    from workloads.graphs import Graph, er_graph
+    n, ell, k, s = 20000, 64, 60, 5
+    rp, col = er_graph(n, n, n)
+    g = Graph(n, rp, col, np.full(col.size, 0xFFFFFFFF // 10, dtype=np.uint32))
+    ws, wg, _ = oracle_lib.skim(g, 5, ell, k, s)
+    G = sk.DeviceGraph.from_host(g, "cuda:0")
+    failed = 0
+    for nth in range(1, 100):
+        log(f"skim with allocation {nth} failing")
+        state = sk.GreedyState()
+        a = torch.empty(s, dtype=torch.int32, device="cuda:0")
+        b = torch.empty(s, dtype=torch.int64, device="cuda:0")
+        try:
+            sk.skim_greedy(G, ell, k, 5, 0, a, b, state=state)
+            sk.skim_debug_inject(sk.SKIM_FAULT_ALLOC_NTH, nth)
+            try:
+                sk.skim_greedy(G, ell, k, 5, s, a, b, state=state)
+                ok = True
+            except sk.SkimError as e:
+                assert e.status == sk.SKIM_ENOMEM
+                ok = False
+            sk.skim_debug_inject(sk.SKIM_FAULT_ALLOC_NTH, 0)
+            at = state.selected
+            assert at == s or not ok
+            if at < s:
+                sk.skim_greedy(G, ell, k, 5, s - at, a[at:], b[at:], state=state)
+            torch.cuda.synchronize()
+        finally:
+            sk.skim_debug_inject(sk.SKIM_FAULT_ALLOC_NTH, 0)
+            state.free()
+        assert np.array_equal(a.cpu().numpy().view(np.uint32), ws), nth
+        assert np.array_equal(b.cpu().numpy().view(np.uint64), wg), nth
+        if ok:
+            break
+        failed += 1
+    assert failed >= 12  # six allocations in each of two steps
