@@ -31,7 +31,8 @@ METRIC = "live-edge traversals/s (sketch build); batched vs plain queries/s, p99
 # The dominant work: the pruned reverse searches, run by three kernels (the
 # seed level of each window, whole-grid levels, and the workgroup tails);
 # they are timed and counted together.
-SEARCH_KERNELS = ["k_seed_window", "k_expand", "k_tails"]
+SEARCH_KERNELS = ["k_seed_window", "k_expand", "k_tails", "k_dense_seed", "k_dense_level",
+                  "k_dense_heavy"]  # the last three: windows of graphs with a dense core
 DOMINANT = "search"
 # Sources of the dominant kernel: measured HBM traffic is reported only while
 # these are unchanged since the counters were taken.
@@ -374,6 +375,8 @@ def bench_build(args, torch, sk, g, cfg):
     kms, klaunch, per_kernel = 0.0, 0, {}
     for name in SEARCH_KERNELS:
         ms_, n_ = sk.skim_timing_read(name)
+        if not n_:
+            continue
         per_kernel[name] = {"ms_per_step": ms_ / args.steps, "launches_per_step": n_ / args.steps}
         kms += ms_
         klaunch += n_

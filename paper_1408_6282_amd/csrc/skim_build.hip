@@ -515,9 +515,9 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t x, int m) {
 // each (per-wave atomics at the end of a launch would all queue on the
 // counters' lines).  Called by every thread; `scratch` holds 3 words per
 // wave of LDS that is free at this point.
-__device__ __forceinline__ void block_add3(uint64_t *scratch, unsigned long long *c0, uint32_t x0,
-                                           unsigned long long *c1, uint32_t x1,
-                                           unsigned long long *c2, uint32_t x2) {
+__device__ __forceinline__ void block_add3(uint64_t *scratch, unsigned long long *c0, uint64_t x0,
+                                           unsigned long long *c1, uint64_t x1,
+                                           unsigned long long *c2, uint64_t x2) {
     unsigned long long v[3] = {x0, x1, x2};
     for (int j = 0; j < 3; ++j)
         for (int off = 32; off > 0; off >>= 1) v[j] += shfl_xor_u64(v[j], off);
@@ -1264,7 +1264,7 @@ __global__ void __launch_bounds__(kBlock) k_dense_level(DenseArgs D, uint32_t L,
         D.ctl->size[16 * ((L + 1) % 3)] = 0;
         D.ctl->hsize[16 * ((L + 1) % 2)] = 0;
     }
-    uint32_t pairs = 0, scans = 0;
+    uint32_t pairs = 0;
     for (uint64_t v0 = (uint64_t)blockIdx.x * nodes; v0 < D.n; v0 += (uint64_t)gridDim.x * nodes) {
         if (wave == 0) {  // nodes <= 64
             uint64_t d = 0;
@@ -1339,13 +1339,12 @@ __global__ void __launch_bounds__(kBlock) k_dense_level(DenseArgs D, uint32_t L,
                 const uint32_t u = (lv & kLiveOne) ? (uint32_t)lv
                                                    : D.lsrc[(lv >> kLiveCountBits) + (e - s_ex[lo])];
                 dense_visit(D, u, s_inst[lo], s_m + lo, kBlock, next);
-                ++scans;
             }
             __syncthreads();  // the batch's LDS is reused
         }
         __syncthreads();  // s_mask and s_pair are refilled
     }
-    block_add3(s_scratch, &D.ctl->size[16 * (L % 3)], pairs, &D.ctl->scans, scans, nullptr, 0);
+    block_add3(s_scratch, &D.ctl->size[16 * (L % 3)], pairs, nullptr, 0, nullptr, 0);
 }
 
 // The long in-lists level L met, one chunk per wave.
@@ -1373,9 +1372,11 @@ __global__ void __launch_bounds__(kBlock) k_dense_heavy(DenseArgs D, uint32_t L)
 }
 
 // After the search, one wave per node: the visits of its pairs, their counts
-// into the state words, and its records, as far as there is room.  kFirst
-// false: only the records again, in a larger buffer (a pair's count before the
-// window reads the same before and after its update).
+// into the state words, and its records, as far as there is room.  The scans are
+// those of the visits, each of which stands for its pair's live in-edges (the
+// levels move many visits along an edge at once).  kFirst false: only the records
+// again, in a larger buffer (a pair's count before the window reads the same
+// before and after its update).
 template <bool kFirst> __global__ void __launch_bounds__(kBlock) k_dense_finish(DenseArgs D) {
     __shared__ uint64_t s_scratch[3 * (kBlock / 64)];
     __shared__ uint32_t s_sum[kBlock / 64];
@@ -1383,6 +1384,7 @@ template <bool kFirst> __global__ void __launch_bounds__(kBlock) k_dense_finish(
     constexpr uint32_t kPer = 8;  // nodes per wave between reservations
     const uint32_t lane = lane_id(), wave = threadIdx.x / 64;
     uint32_t visits = 0, again = 0;
+    uint64_t scans = 0;
     const uint64_t step = (uint64_t)gridDim.x * (kBlock / 64) * kPer;
     for (uint64_t v0 = (uint64_t)blockIdx.x * (kBlock / 64) * kPer; v0 < D.n; v0 += step) {
         uint32_t mine = 0, cs[kPer];  // records of this lane's pairs
@@ -1404,6 +1406,7 @@ template <bool kFirst> __global__ void __launch_bounds__(kBlock) k_dense_finish(
                                 ((uint64_t)prior_count(state, D.win) << 52);
             visits += c;
             again += c - 1;
+            scans += (uint64_t)c * ((live & kLiveOne) ? 1u : live_count(live));
             if (want) {
                 cs[r] = c;
                 mine += c;
@@ -1440,7 +1443,7 @@ template <bool kFirst> __global__ void __launch_bounds__(kBlock) k_dense_finish(
         }
     }
     if (kFirst)
-        block_add3(s_scratch, &D.ctl->visits, visits, &D.ctl->hinserts, again, nullptr, 0);
+        block_add3(s_scratch, &D.ctl->visits, visits, &D.ctl->hinserts, again, &D.ctl->scans, scans);
 }
 
 // Start of a window (or of its redo): clear the per-window fields and set
@@ -2009,7 +2012,7 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
             k_dense_init<<<grid_for(n, kBlock / 64, 16384), kBlock, 0, s>>>(D);
             SKIM_LAUNCH_CHECK();
             {
-                LaunchTimer t("k_seed_window", s);
+                LaunchTimer t("k_dense_seed", s);
                 k_dense_seed<<<grid_for(nw, kBlock, 1024), kBlock, 0, s>>>(D, sources, ws, we);
             }
             SKIM_LAUNCH_CHECK();
@@ -2017,10 +2020,13 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
             uint32_t L = 0;
             do {
                 for (int j = 0; j < kDenseBatch; ++j, ++L) {
-                    LaunchTimer t("k_expand", s);
-                    k_dense_level<<<grid_for(n, per, 8192), kBlock, 0, s>>>(D, L, per);
-                    SKIM_LAUNCH_CHECK();
+                    {
+                        LaunchTimer t("k_dense_level", s);
+                        k_dense_level<<<grid_for(n, per, 8192), kBlock, 0, s>>>(D, L, per);
+                        SKIM_LAUNCH_CHECK();
+                    }
                     if (D.heavy_cap) {
+                        LaunchTimer t("k_dense_heavy", s);
                         k_dense_heavy<<<1024, kBlock, 0, s>>>(D, L);
                         SKIM_LAUNCH_CHECK();
                     }

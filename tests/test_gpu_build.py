@@ -293,3 +293,28 @@ def test_scan_sizes(oracle_lib, n):
     g = from_edges(n, src, src + 1, 0xFFFFFFFF)
     log(f"scan sizes n={n}")
     _check(oracle_lib, g, 2, 4, 3)
+
+
+def test_dense_windows_count_the_same_work():
+    # windows of source bit sets report the visits and live-edge scans of the
+    # per-source search (out-lists for pulled levels keep the build to that one;
+    # no level is long enough to be pulled)
+    import paper_1408_6282_amd as sk
+    from workloads.graphs import Graph, rmat_graph, trivalency_thresholds
+    rp, col = rmat_graph(14, 1 << 18, (0.57, 0.19, 0.19, 0.05), 5)
+    g = Graph(1 << 14, rp, col, trivalency_thresholds(col.size, 5))
+    try:
+        sk.skim_timing_reset()
+        sk.skim_timing_enable("k_dense_level")
+        R, S, _, work, _ = gpu_build(g, 64, 32, 3)
+        dense = sk.skim_timing_read("k_dense_level")[1]
+        sk.skim_timing_reset()
+        sk.skim_set_build_params(dict(pull_frontier=0xFFFFFFFF))
+        R0, S0, _, work0, _ = gpu_build(g, 64, 32, 3)
+        assert dense and not sk.skim_timing_read("k_dense_level")[1]
+    finally:
+        sk.skim_timing_enable(None)
+        sk.skim_set_build_params(None)
+    log(f"work {work} by source {work0}")
+    assert np.array_equal(R, R0) and np.array_equal(S, S0)
+    assert work["visits"] == work0["visits"] and work["scans"] == work0["scans"]
