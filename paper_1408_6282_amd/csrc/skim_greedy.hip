@@ -37,6 +37,7 @@
 // seed's discrepancy with eq. (chernoff) on a grid of discrepancy values and
 // convolves the per-seed distributions pairwise in a tree of launches.
 #include "skim_internal.h"
+#include "skim_tail.h"
 #include "skim_wave.h"
 
 #include <mutex>
@@ -1513,7 +1514,6 @@ constexpr uint32_t kTailMaxBins = 1u << 16;
 constexpr uint64_t kTailMaxCells = 1ull << 30;  // seeds * (bins + 1)
 constexpr int kTailBlock = 256;
 
-constexpr uint32_t kTailCounters = 1024;  // arrival counters, cleared at the start of a tail
 __global__ void __launch_bounds__(kTailBlock) k_tail_total(uint32_t s, const uint64_t *gain,
                                                            uint64_t *total, uint32_t *arrived) {
     __shared__ unsigned long long acc;
@@ -1589,58 +1589,36 @@ __global__ void __launch_bounds__(kTailBlock) k_tail_survival(
 // 200 seeds, 4096 bins (3.34 GFLOP, 55 us at the 61 TFLOP/s that a large fp64
 // matrix product reaches here): vector units, 8 waves per 256 outputs, 0.58 ms;
 // this 0.18 ms (the first level 53 us, the last three 8 us each).
-constexpr int kTailTile = 256, kTailChunk = 32, kTailWaves = 4;
+constexpr int kTailWaves = 4;
 constexpr int kTailPairBlock = 64 * kTailWaves;
 constexpr int kTailBlocks = kTailChunk + 15;       // 16-cell blocks of a that a chunk meets
 constexpr int kTailPad = 18;
-constexpr uint64_t kTailSplit = kTailCounters;     // fewer tiles than this: split their D ranges
-constexpr uint64_t kTailPartials = 2 * kTailSplit;  // at most, kTailTile values each
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-// Tiles of a row and, with `part` D steps per workgroup, the workgroups of a
-// pair (tile t takes 16 t + 16 steps).
-__host__ __device__ inline uint32_t tail_tiles(uint64_t W) {
-    return (uint32_t)((W + kTailTile - 1) / kTailTile);
-}
-__host__ __device__ inline uint32_t tail_parts(uint32_t tile, uint32_t part) {
-    return (16 * tile + 16 + part - 1) / part;
-}
-
 __global__ void __launch_bounds__(kTailPairBlock) k_tail_pair(const double *in, double *out,
-                                                              uint32_t rows, uint32_t bins,
-                                                              uint32_t part, uint64_t per_pair,
+                                                              uint32_t bins, TailLevel L,
                                                               double *partial, uint32_t *arrived) {
     __shared__ double s_a[kTailBlocks * kTailPad];  // blocks of 16, padded: no bank conflicts
     __shared__ double s_b[16 * kTailChunk + 16];
     __shared__ double s_red[kTailWaves][kTailTile];
     __shared__ uint32_t s_last;
     const int64_t W = (int64_t)bins + 1;
-    const uint32_t T = tail_tiles((uint64_t)W);
-    const uint64_t pairs = rows / 2, items = pairs * per_pair + (rows % 2 ? T : 0);
     const int tid = (int)threadIdx.x, wave = tid / 64, lane = tid % 64;
     const int li = lane % 16, lk = lane / 16;
-    for (uint64_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const uint64_t p = item / per_pair;
-        if (p >= pairs) {  // the odd last row
-            const int64_t j = (int64_t)(item - pairs * per_pair) * kTailTile + tid;
-            if (j < W) out[pairs * W + j] = in[2 * pairs * W + j];
+    for (uint64_t item = blockIdx.x; item < L.items; item += gridDim.x) {
+        const TailItem work = tail_item(L, item);
+        const uint64_t p = work.pair;
+        uint32_t tile = work.tile;
+        int more = work.more;
+        if (p >= L.pairs) {  // the odd last row
+            const int64_t j = (int64_t)tile * kTailTile + tid;
+            if (j < W) out[p * W + j] = in[2 * p * W + j];
             continue;
         }
-        uint64_t rest = item - p * per_pair;
-        uint32_t tile = T - 1;  // the longest first
-        int more = -1;          // a second tile for this workgroup
-        if (part >= 16 * T) {   // whole tiles, a long one with a short one
-            more = (int)rest < (int)tile - (int)rest ? (int)rest : -1;
-            tile -= (uint32_t)rest;
-            rest = 0;
-        } else {
-            while (rest >= tail_parts(tile, part)) rest -= tail_parts(tile--, part);
-        }
-        const uint32_t nparts = tail_parts(tile, part);
         for (;; tile = (uint32_t)more, more = -1) {
         const int64_t c0 = 16 * (int64_t)tile;
-        const int64_t d0 = (int64_t)rest * part;
-        const int64_t d1 = d0 + part < c0 + 16 ? d0 + part : c0 + 16;
+        const int64_t d0 = (int64_t)work.part * L.part;
+        const int64_t d1 = d0 + L.part < c0 + 16 ? d0 + L.part : c0 + 16;
         const double *a = in + 2 * p * W, *b = a + W;
         v4d acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
         // the next chunk's values are on their way while this one is multiplied
@@ -1696,7 +1674,7 @@ __global__ void __launch_bounds__(kTailPairBlock) k_tail_pair(const double *in, 
         double v = 0.0;
         for (int w = 0; w < kTailWaves; ++w) v += s_red[w][tid];
         const int64_t j = 16 * c0 + tid;
-        if (nparts > 1) {
+        if (work.nparts > 1) {
             // item numbers of a tile's parts are consecutive
             // (agent-scope stores and loads reach the memory all XCDs see, so
             // no fence has to write back or invalidate a whole cache; the
@@ -1706,16 +1684,16 @@ __global__ void __launch_bounds__(kTailPairBlock) k_tail_pair(const double *in, 
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
             if (tid == 0) {
-                uint32_t *cnt = arrived + p * T + tile;
+                uint32_t *cnt = arrived + p * L.tiles + tile;
                 const uint32_t before = atomicAdd(cnt, 1u);
-                s_last = before + 1 == nparts;
+                s_last = before + 1 == work.nparts;
                 if (s_last) atomicExch(cnt, 0u);  // ready for the next level
             }
             __syncthreads();
             if (!s_last) break;  // uniform
-            const double *first = partial + (item - rest) * kTailTile;
+            const double *first = partial + (item - work.part) * kTailTile;
             v = 0.0;
-            for (uint32_t q = 0; q < nparts; ++q)
+            for (uint32_t q = 0; q < work.nparts; ++q)
                 v += ld<kAgent>(first + (uint64_t)q * kTailTile + tid);
         }
         if (j < W) out[p * W + j] = v + (j + 1 < W ? a[j + 1] : 0.0);
@@ -1744,24 +1722,11 @@ void tail_enqueue(uint32_t s, const uint64_t *tau, const uint32_t *second, const
     k_tail_survival<<<grid_for((uint64_t)s * W, kTailBlock), kTailBlock, 0, hs>>>(
         s, tau, second, gain, T.total, bins, max_rel, in);
     SKIM_LAUNCH_CHECK();
-    const uint32_t tiles = tail_tiles(W);
     for (uint32_t rows = s; rows > 1; rows = (rows + 1) / 2) {
-        const uint64_t pairs = rows / 2;
-        uint32_t part = 16 * tiles;
-        uint64_t per_pair = (tiles + 1) / 2;
-        if (pairs * tiles < kTailSplit) {
-            // about kTailSplit parts in all, none below one chunk of steps: a
-            // tile adds at most one more than its share, so there are at most
-            // kTailPartials of them
-            const uint64_t steps = pairs * 8 * tiles * (tiles + 1);
-            part = (uint32_t)std::max<uint64_t>(kTailChunk, (steps + kTailSplit - 1) / kTailSplit);
-            per_pair = 0;
-            for (uint32_t t = 0; t < tiles; ++t) per_pair += tail_parts(t, part);
-        }
-        const uint64_t items = pairs * per_pair + (rows % 2 ? tiles : 0);
+        const TailLevel L = tail_level(rows, W);
         if (rows == 2) out = tail;
-        k_tail_pair<<<(unsigned)std::min<uint64_t>(items, 1u << 20), kTailPairBlock, 0, hs>>>(
-            in, out, rows, bins, part, per_pair, T.partial, T.arrived);
+        k_tail_pair<<<(unsigned)std::min<uint64_t>(L.items, 1u << 20), kTailPairBlock, 0, hs>>>(
+            in, out, bins, L, T.partial, T.arrived);
         SKIM_LAUNCH_CHECK();
         std::swap(in, out);
     }
