@@ -176,6 +176,9 @@ __global__ void __launch_bounds__(kEvalBlock) k_eval(EvalArgs A) {
 // most of it the lists.
 constexpr uint32_t kSetsLdsNodes = 26000;   // 6.125 n + 2 KiB of LDS
 constexpr uint32_t kSetsSmallNodes = 4096;  // up to here 256 threads: several units per CU
+constexpr size_t sets_lds(uint64_t n, uint64_t threads) {
+    return 4 * n + 4 * ((n + 31) / 32) + 2 * (n + threads);
+}
 
 struct SetsArgs {
     uint32_t n, ell;
@@ -588,10 +591,14 @@ extern "C" skim_status skim_influence_batch(const skim_graph *g, uint32_t ell, u
         if (n <= kSetsLdsNodes) {
             const bool small = n <= kSetsSmallNodes;
             const uint64_t nt = small ? 256 : 1024;
-            const size_t lds = 4ull * n + 4ull * ((n + 31) / 32) + 2ull * (n + nt);
+            const size_t lds = sets_lds(n, nt);
             const void *f = small ? (const void *)k_eval_sets<true, 256>
                                   : (const void *)k_eval_sets<true, 1024>;
-            SKIM_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            // the limit belongs to the kernel, not to this call: always the
+            // largest, which no thread with a smaller graph lowers for another
+            SKIM_HIP(hipFuncSetAttribute(
+                f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                (int)sets_lds(small ? kSetsSmallNodes : kSetsLdsNodes, nt)));
             const unsigned grid = (unsigned)std::min<uint64_t>(units, 4096);  // multiples of 8
             if (small) k_eval_sets<true, 256><<<grid, 256, lds, hs>>>(A);
             else k_eval_sets<true, 1024><<<grid, 1024, lds, hs>>>(A);

@@ -201,3 +201,41 @@ def test_words_of_32_queries_at_state_limits(oracle_lib, n, q):
                 continue
             assert st[j] == 0
             assert int(got[j]) == oracle_lib.influence(g, 11, ell, sorted(set(S))), (j, S)
+
+
+def test_sizes_of_two_threads_do_not_meet(oracle_lib):
+    # two threads evaluate graphs of different sizes, each on a stream of its
+    # own: the LDS that one needs is not limited by the other's call
+    import threading
+    import torch
+    import paper_1408_6282_amd as sk
+    from workloads.graphs import Graph, er_graph
+    work = []
+    for n in (4200, 26000):
+        rp, col = er_graph(n, 2 * n, n)
+        g = Graph(n, rp, col, np.full(col.size, 0xFFFFFFFF // 4, dtype=np.uint32))
+        sets = [[v] for v in range(8)]
+        work.append((sk.DeviceGraph.from_host(g, "cuda:0"), sets,
+                     [oracle_lib.influence(g, 9, 2, s) for s in sets]))
+    errors = []
+
+    def run(G, sets, want):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                off = torch.arange(len(sets) + 1, dtype=torch.int64, device="cuda:0")
+                nodes = torch.tensor([s[0] for s in sets], dtype=torch.int32, device="cuda:0")
+                out = torch.empty(len(sets), dtype=torch.int64, device="cuda:0")
+                for _ in range(50):
+                    sk.skim_influence_batch(G, 2, 9, off, nodes, out, stream=stream)
+                    if out.cpu().tolist() != [int(w) for w in want]:
+                        errors.append("wrong counts")
+        except Exception as e:  # noqa: BLE001 - reported by the test
+            errors.append(repr(e))
+
+    threads = [threading.Thread(target=run, args=w) for w in work]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors[:3]
