@@ -25,6 +25,7 @@
 #include "skim_internal.h"
 
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 namespace skim {
@@ -158,7 +159,7 @@ __global__ void __launch_bounds__(kEvalBlock) k_eval(EvalArgs A) {
 }
 
 // --------------------------------------------- batches: 32 queries at once
-// A unit is one instance i and one word of 32 queries.  Its workgroup keeps a
+// A unit is one instance i and one word of up to 32 queries.  Its workgroup keeps a
 // 32-bit mask per node, the queries of the word that reach the node, and a
 // queue of the nodes whose mask grew since they were last expanded (a node is
 // in the queue at most once: its `dirty` bit).  Expanding v sends its mask
@@ -184,7 +185,9 @@ struct SetsArgs {
     uint32_t n, ell;
     const uint64_t *fptr;  // [l n + 1] live out-lists, instance-major
     const uint32_t *fadj;
-    uint64_t q, words;     // queries, words of 32 of them
+    uint64_t q, words;     // queries, words of `width` of them
+    uint32_t width;        // queries of a word (<= 32)
+    uint32_t shift;        // instances side by side: 8, or with fewer instances 4, 2 or 1
     const uint64_t *qoff;
     const uint32_t *qnodes;
     const uint8_t *bad;    // [q] the query names a node >= n
@@ -193,6 +196,22 @@ struct SetsArgs {
     uint32_t *dirty;       // [slots][(n + 31) / 32], zero between units
     uint32_t *ring;        // [slots][n + NT]
 };
+
+__host__ __device__ inline uint64_t sets_units(uint32_t ell, uint32_t shift, uint64_t words) {
+    return ((((uint64_t)ell - 1) >> shift) + 1) * words << shift;
+}
+
+// Queries of a word: as few as make no more than kSetsUnits units, where queries
+// that meet are walked more than once but side by side; 32 when there are more units
+// anyway.  100 pairs of nodes on a giant component (20,000 nodes, l = 1), a call:
+// words of 32 0.49 ms, so 0.19; with 256 units the 30 sets of an R-MAT graph of 2^17
+// nodes, l = 64, took 1.7 ms for 1.35 (device atomics).
+constexpr uint64_t kSetsUnits = 64;
+inline uint32_t sets_width(uint32_t ell, uint64_t q) {
+    uint32_t w = 32;
+    while (w > 1 && ell * ((q + w / 2 - 1) / (w / 2)) <= kSetsUnits) w /= 2;
+    return w;
+}
 
 // Per query: the status and a zero count (one wave each).
 __global__ void __launch_bounds__(256) k_sets_begin(uint32_t n, uint64_t q, const uint64_t *qoff,
@@ -273,14 +292,16 @@ __global__ void __launch_bounds__(NT) k_eval_sets(SetsArgs A) {
     Id *R = kLds ? (Id *)(s_mem + n + dwords) : (Id *)(A.ring + (uint64_t)blockIdx.x * cap);
     if (kLds)
         for (uint32_t v = tid; v < n + dwords; v += NT) s_mem[v] = 0;
-    // Workgroups go to the 8 XCDs in turn: every unit of instance i runs on
-    // XCD i mod 8, whose L2 then holds that instance's lists.
-    const uint64_t units = 8ull * ((A.ell + 7) / 8) * A.words;
+    // Workgroups go to the 8 XCDs in turn: with 8 instances or more every unit of
+    // instance i runs on XCD i mod 8, whose L2 then holds that instance's lists;
+    // with fewer an instance's units go to all XCDs.
+    const uint64_t units = sets_units(A.ell, A.shift, A.words);
     for (uint64_t u = blockIdx.x; u < units; u += gridDim.x) {
-        const uint32_t inst = (uint32_t)(u % 8 + 8 * (u / 8 / A.words));
+        const uint64_t r = u >> A.shift;
+        const uint32_t inst = (uint32_t)((u & ((1u << A.shift) - 1u)) + ((r / A.words) << A.shift));
         if (inst >= A.ell) continue;  // uniform
-        const uint64_t j0 = 32 * (u / 8 % A.words);
-        const uint32_t nq = A.q - j0 < 32 ? (uint32_t)(A.q - j0) : 32u;
+        const uint64_t j0 = A.width * (r % A.words);
+        const uint32_t nq = A.q - j0 < A.width ? (uint32_t)(A.q - j0) : A.width;
         const uint64_t *ptr = A.fptr + (uint64_t)inst * n;
         __syncthreads();  // the previous unit is done (and the first one's state is clear)
         if (tid <= 32) s_off[tid] = A.qoff[j0 + (tid < nq ? tid : nq)];
@@ -577,7 +598,9 @@ extern "C" skim_status skim_influence_batch(const skim_graph *g, uint32_t ell, u
         A.fptr = fwd.ptr;
         A.fadj = fwd.adj;
         A.q = q;
-        A.words = (q + 31) / 32;
+        A.width = sets_width(ell, q);
+        A.words = (q + A.width - 1) / A.width;
+        A.shift = ell >= 8 ? 3 : ell >= 4 ? 2 : ell >= 2 ? 1 : 0;
         A.qoff = qoff;
         A.qnodes = qnodes;  // never read when every set is empty
         A.reach = reach_pairs;
@@ -586,7 +609,7 @@ extern "C" skim_status skim_influence_batch(const skim_graph *g, uint32_t ell, u
         k_sets_begin<<<grid_for(q, 4, 4096), 256, 0, hs>>>(n, q, qoff, qnodes, bad, reach_pairs,
                                                            qstatus);
         SKIM_LAUNCH_CHECK();
-        const uint64_t units = 8ull * ((ell + 7) / 8) * A.words;
+        const uint64_t units = sets_units(ell, A.shift, A.words);
         LaunchTimer t("k_eval_sets", hs);
         if (n <= kSetsLdsNodes) {
             const bool small = n <= kSetsSmallNodes;
@@ -596,9 +619,14 @@ extern "C" skim_status skim_influence_batch(const skim_graph *g, uint32_t ell, u
                                   : (const void *)k_eval_sets<true, 1024>;
             // the limit belongs to the kernel, not to this call: always the
             // largest, which no thread with a smaller graph lowers for another
-            SKIM_HIP(hipFuncSetAttribute(
-                f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                (int)sets_lds(small ? kSetsSmallNodes : kSetsLdsNodes, nt)));
+            static std::atomic<uint64_t> have[2];  // by device
+            const uint64_t dev_bit = 1ull << T.device();
+            if (!(have[small].load() & dev_bit)) {
+                SKIM_HIP(hipFuncSetAttribute(
+                    f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                    (int)sets_lds(small ? kSetsSmallNodes : kSetsLdsNodes, nt)));
+                have[small] |= dev_bit;
+            }
             const unsigned grid = (unsigned)std::min<uint64_t>(units, 4096);  // multiples of 8
             if (small) k_eval_sets<true, 256><<<grid, 256, lds, hs>>>(A);
             else k_eval_sets<true, 1024><<<grid, 1024, lds, hs>>>(A);

@@ -164,6 +164,7 @@ class Arena {
     template <class T> T *alloc(size_t count) { return (T *)get(count * sizeof(T)); }
     void release(void *p);  // give one buffer back early (reused by this arena)
     hipStream_t stream() const { return s_; }
+    int device() const { return dev_; }
 
   private:
     struct Block {

@@ -239,3 +239,21 @@ def test_sizes_of_two_threads_do_not_meet(oracle_lib):
     for t in threads:
         t.join()
     assert not errors, errors[:3]
+
+
+@pytest.mark.parametrize("n", [300, 27000])
+def test_few_instances_and_word_widths(oracle_lib, n):
+    """Fewer instances than XCDs, and batches at the sizes where a word of queries
+    changes its width, on LDS and on global state."""
+    rng = np.random.default_rng(n)
+    e = np.unique(rng.integers(0, n, size=(4 * n, 2)), axis=0)
+    e = e[e[:, 0] != e[:, 1]]
+    g = from_edges(n, e[:, 0], e[:, 1], 0xFFFFFFFF // 3)
+    for ell, qs in [(1, (1, 64, 65, 129)), (2, (32, 33)), (3, (22,)), (5, (13, 26)), (9, (7, 8, 33))]:
+        for q in qs:
+            sets = [rng.integers(0, n, size=int(rng.integers(0, 4))).tolist() for _ in range(q)]
+            log(f"influence n={n} ell={ell} q={q}")
+            got, st = gpu_influence(g, ell, 7, sets)
+            assert not st.any()
+            for j in rng.permutation(q)[:12]:
+                assert int(got[j]) == oracle_lib.influence(g, 7, ell, sorted(set(sets[j]))), (j, ell)
