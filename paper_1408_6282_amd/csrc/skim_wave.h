@@ -57,6 +57,12 @@ template <int kMask> __device__ __forceinline__ uint64_t lane_xor64(uint64_t x) 
     return ((uint64_t)lane_xor<kMask>((uint32_t)(x >> 32)) << 32) | lane_xor<kMask>((uint32_t)x);
 }
 
+// Lane i's value, for an i that is the same in all lanes.
+__device__ __forceinline__ uint64_t lane_u64(uint64_t x, uint32_t i) {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), (int)i) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, (int)i);
+}
+
 // Minimum over each aligned group of G lanes, in every lane.
 template <int G> __device__ __forceinline__ uint32_t group_min_u32(uint32_t x) {
     if constexpr (G >= 2) x = min(x, lane_xor<1>(x));

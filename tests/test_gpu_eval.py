@@ -257,3 +257,19 @@ def test_few_instances_and_word_widths(oracle_lib, n):
             assert not st.any()
             for j in rng.permutation(q)[:12]:
                 assert int(got[j]) == oracle_lib.influence(g, 7, ell, sorted(set(sets[j]))), (j, ell)
+
+
+@pytest.mark.parametrize("fan", [1, 7, 8, 9, 33, 63, 64, 65, 200])
+def test_out_lists_of_sources_in_one_wave(oracle_lib, fan):
+    """Sources of `fan` edges each: waves of one source, of a few and of more than
+    are counted from the transposed masks, with a ragged last wave."""
+    rng = np.random.default_rng(fan)
+    n, hubs = 900, 40
+    src = np.repeat(np.arange(hubs), fan)
+    dst = np.concatenate([hubs + rng.choice(n - hubs, fan, replace=False) for _ in range(hubs)])
+    g = from_edges(n, src, dst, rng.integers(0, 1 << 32, size=src.size, dtype=np.uint32))
+    sets = [[h] for h in range(hubs)]
+    for ell in (1, 16, 64):
+        log(f"out-lists fan={fan} ell={ell}")
+        got, _ = gpu_influence(g, ell, 13, sets)
+        assert [int(x) for x in got] == [int(oracle_lib.influence(g, 13, ell, s)) for s in sets]
