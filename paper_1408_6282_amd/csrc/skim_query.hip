@@ -404,17 +404,24 @@ __device__ __forceinline__ void run_class(const QArgs &Q, const Run &run, bool i
     }
 }
 
-// Offsets of query j0 + lane (lane < cnt).  Offsets are validated before a
-// batch; a replayed plan re-checks its own sets here (non-decreasing, within
-// qoff[q]) and never reads outside.  Empty sets and bad offsets are answered;
-// returns whether a set with members is left.
+// Offsets of set j.  They are validated before a batch; a replayed plan
+// re-checks its own sets here (non-decreasing, within qoff[q]) and never reads
+// outside.
+__device__ __forceinline__ bool set_bounds(const QArgs &Q, uint64_t j, uint64_t &a, uint64_t &b) {
+    a = Q.qoff[j];
+    b = Q.qoff[j + 1];
+    return !(b < a || b > Q.qoff[Q.q] || b > Q.nodes_cap || (j == 0 && a != 0));
+}
+
+// Offsets of query j0 + lane (lane < cnt).  Empty sets and bad offsets are
+// answered; returns whether a set with members is left.
 __device__ __forceinline__ bool load_run(const QArgs &Q, uint32_t cnt, Run &run) {
     const uint32_t lane = lane_id();
     run.a = run.S = 0;
     if (lane >= cnt) return false;
     const uint64_t j = run.j0 + lane;
-    const uint64_t a = Q.qoff[j], b = Q.qoff[j + 1];
-    if (b < a || b > Q.qoff[Q.q] || b > Q.nodes_cap || (j == 0 && a != 0)) {
+    uint64_t a, b;
+    if (!set_bounds(Q, j, a, b)) {
         put_answer(Q, j, 0.0, -3);
         return false;
     }
@@ -427,6 +434,17 @@ __device__ __forceinline__ bool load_run(const QArgs &Q, uint32_t cnt, Run &run)
     return true;
 }
 
+// Bottom-k answer of query j, one node, by the calling lane.
+__device__ __forceinline__ void single_node(const QArgs &Q, uint64_t j, uint32_t u) {
+    if (u >= Q.n) {
+        put_answer(Q, j, 0.0, -1);
+        return;
+    }
+    const uint32_t sz = Q.size[u];
+    const uint64_t T = sz >= Q.k ? Q.ranks[(uint64_t)u * Q.k + Q.k - 1] : 0;
+    put_answer(Q, j, union_estimate(Q, sz, T), 0);
+}
+
 // Bottom-k answers of queries j0 .. j0 + cnt (cnt <= 64), by set size: one
 // lane for a single node, groups of 4, 8 and 16 lanes up to 64 members (16
 // lanes with 2 or 4 members each measured faster than a wave with one each),
@@ -435,16 +453,7 @@ __device__ __forceinline__ void answer_bottomk(const QArgs &Q, uint64_t j0, uint
                                                MergeLds &X, uint8_t *list) {
     Run run{j0, 0, 0, list};
     const bool set = load_run(Q, cnt, run);
-    if (set && run.S == 1) {
-        const uint32_t u = Q.qnodes[run.a];
-        if (u >= Q.n) {
-            put_answer(Q, j0 + lane_id(), 0.0, -1);
-        } else {
-            const uint32_t sz = Q.size[u];
-            const uint64_t T = sz >= Q.k ? Q.ranks[(uint64_t)u * Q.k + Q.k - 1] : 0;
-            put_answer(Q, j0 + lane_id(), union_estimate(Q, sz, T), 0);
-        }
-    }
+    if (set && run.S == 1) single_node(Q, j0 + lane_id(), Q.qnodes[run.a]);
     run_class<4, 1>(Q, run, set && run.S >= 2 && run.S <= 4);
     run_class<8, 1>(Q, run, set && run.S >= 5 && run.S <= 8);
     run_class<16, 1>(Q, run, set && run.S >= 9 && run.S <= 16);
@@ -757,7 +766,9 @@ __global__ void __launch_bounds__(kQBlock, 2) k_query_each(QArgs Q, uint64_t j0)
         const uint64_t a = shfl_u64(run.a, 0), S = shfl_u64(run.S, 0);
         uint64_t *rows = (uint64_t *)&X.merge;
         if (S == 0) return;
-        if (S <= 16) merge_staged<16>(Q, j, Q.qnodes + a, (uint32_t)S, rows);
+        if (S == 1) {  // (stepping to the k-th rank of the one row, k = 256: 97 us a call for 39)
+            if (threadIdx.x == 0) single_node(Q, j, Q.qnodes[a]);
+        } else if (S <= 16) merge_staged<16>(Q, j, Q.qnodes + a, (uint32_t)S, rows);
         else if (S <= 64) merge_staged<64>(Q, j, Q.qnodes + a, (uint32_t)S, rows);
         else bottomk_wave(Q, j, a, S, X.merge);
     } else {

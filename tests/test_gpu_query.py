@@ -237,3 +237,21 @@ def test_batch_sizes_at_kernel_edges(oracle_lib, k, q):
     got, status = gpu_query(to_dev_u64(R.reshape(-1)), to_dev_u32(S), n, k, ell, off, nodes, 0)
     assert np.array_equal(status, wst)
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("k", [65, 256])
+def test_single_nodes_over_long_sketches(oracle_lib, k):
+    """Sets of one node, a workgroup each, over sketches of more than 64 ranks: full
+    ones, short ones and empty ones, and a bad id."""
+    from gpu_util import to_dev_u32, to_dev_u64
+    n, ell = 120, 8
+    rng = np.random.default_rng(k)
+    R, S = _pool_tables(rng, n, k, 0)
+    S[5], R[5] = 0, 2 ** 64 - 1
+    sets = [[v] for v in range(n)] + [[n], [3, 3]]
+    off, nodes = _sets(sets)
+    want, wst = oracle_lib.union_query(R, S, k, ell, off, nodes)
+    for mode in (0, 1):
+        got, status = gpu_query(to_dev_u64(R.reshape(-1)), to_dev_u32(S), n, k, ell, off, nodes, 0,
+                                mode)
+        assert np.array_equal(status, wst) and np.array_equal(got, want)
