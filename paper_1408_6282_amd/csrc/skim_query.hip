@@ -30,6 +30,7 @@ constexpr int kQBlock = 64;             // one wave per block
 constexpr int kPerLane = kMaxMembers / 64;
 constexpr uint32_t kRun = 64;           // most queries a wave takes at once
 constexpr uint64_t kTakeMembers = 48;   // mean set size from which the counter balances
+constexpr uint64_t kSetWeight = 4;      // a set weighs as much as its members and this many more
 
 using QArgs = QueryArgs;
 
@@ -716,39 +717,81 @@ __device__ __forceinline__ void answer_run(const QArgs &Q, uint64_t j0, uint32_t
     else answer_ck<kCk>(Q, j0, cnt, X.merge, X.ck, X.list);
 }
 
+// The sets [j0, j1) of this wave where every wave of the grid takes a contiguous
+// share of equal weight: set j begins at weight qoff[j] + kSetWeight j, and wave w
+// takes those that begin in [w, w + 1) times the w-th part of the whole.  Both
+// ends are searched for together, 32 places of the offsets at a time.  (Offsets
+// out of order, which only a replayed plan can meet, give some share or other; the
+// shares begin at 0, end at q and follow each other, so no set is left out.)
+__device__ __forceinline__ void wave_share(const QArgs &Q, uint64_t q, uint64_t &j0, uint64_t &j1) {
+    const uint32_t lane = lane_id(), half = lane >> 5, hl = lane & 31u;
+    const uint64_t target = (Q.qoff[q] + kSetWeight * q) * (blockIdx.x + half) / gridDim.x;
+    uint64_t lo = 0, hi = q;  // the first place of weight `target` or more lies in [lo, hi]
+    while (__any(lo < hi)) {
+        const uint64_t step = (hi - lo + 31) / 32, x = lo + step * (hl + 1) - 1;
+        const bool in = lo < hi && x < hi;
+        const bool below = in && Q.qoff[x] + kSetWeight * x < target;
+        const uint32_t m = (uint32_t)(__ballot(below) >> (32 * half));
+        const uint32_t c = ~m ? (uint32_t)__ffs((int)~m) - 1u : 32u;  // places below the target
+        if (lo < hi) {
+            lo += step * c;
+            if (c < 32 && lo + step - 1 < hi) hi = lo + step - 1;  // that place is not below it
+            lo = lo < hi ? lo : hi;
+        }
+    }
+    j0 = shfl_u64(lo, 0);
+    j1 = blockIdx.x + 1 == gridDim.x ? q : shfl_u64(lo, 32);
+}
+
+// Whether the sets' weight is spread over the batch: no 64th part of it holds half
+// as much again as its share.
+__device__ __forceinline__ bool balanced(const QArgs &Q, uint64_t q) {
+    const uint64_t x0 = q * lane_id() / 64, x1 = q * (lane_id() + 1) / 64;
+    const uint64_t w = Q.qoff[x1] - Q.qoff[x0] + kSetWeight * (x1 - x0);
+    return !__any(128 * w > 3 * (Q.qoff[q] + kSetWeight * q));
+}
+
 template <int kCk>
-__global__ void __launch_bounds__(kQBlock, kCk < 0 ? 4 : 2) k_query_persistent(
+__global__ void __launch_bounds__(kQBlock, kCk < 0 ? 4 : kCk == 16 ? 3 : 2) k_query_persistent(
     QArgs Q, uint64_t q, unsigned long long *next) {
     __shared__ QueryLds<kCk> X;
     // Takes from different waves on the one counter are serialised by the
     // hardware (about 12 ns each).  Sets of less than kTakeMembers members on
-    // average cost less than that, so they go in equal runs, every wave the
-    // same number of them, spread over the batch (10^6 lognormal sets, mean
-    // 12: 1.08 ms taken from the counter, 0.81 ms in equal runs).  Batches of
-    // larger sets are taken from the counter, in runs that shrink as it drains
-    // (at most kRun, about a quarter of an even share of what is left), which
-    // balances sets of uneven size.
-    const uint64_t share = 4ull * gridDim.x;
-    const bool even = Q.qoff[q] < kTakeMembers * q;
-    uint64_t g = q / share, step = 0, j0 = 0;
+    // average cost less than that.  They go in equal runs, every wave the same
+    // number of them, spread over the batch, if that is balanced (see there), and
+    // else, or if a large set costs far more than its members' share (Cohen-Kaplan),
+    // each wave takes a share of equal weight.  10^6 lognormal sets, mean 12, a call:
+    // 0.51 ms in runs, 0.61 in shares (a share's ends are looked for in cold lines);
+    // sorted by size 0.85 and 0.54; 1000 sets of 1024 nodes before 99,000 of one, k =
+    // 64: 1.73 and 0.15.  Batches of larger sets are taken from the counter, in runs
+    // that shrink as it drains (at most kRun, about a quarter of an even share of
+    // what is left).
+    const uint64_t part = 4ull * gridDim.x;
+    const bool counter = Q.qoff[q] >= kTakeMembers * q;
+    uint64_t g = q / part, j0 = 0, end = q, step = 0;
     g = g < 1 ? 1 : g > kRun ? kRun : g;
-    if (even) {
-        const uint64_t rounds = (q + (uint64_t)gridDim.x * kRun - 1) / ((uint64_t)gridDim.x * kRun);
-        g = (q + gridDim.x * rounds - 1) / (gridDim.x * rounds);  // <= kRun
-        step = gridDim.x * g;
-        j0 = blockIdx.x * g;
+    if (!counter) {
+        if (kCk < 0 && balanced(Q, q)) {
+            const uint64_t rounds = (q + (uint64_t)gridDim.x * kRun - 1) / ((uint64_t)gridDim.x * kRun);
+            g = (q + gridDim.x * rounds - 1) / (gridDim.x * rounds);  // <= kRun
+            step = gridDim.x * g;
+            j0 = blockIdx.x * g;
+        } else {
+            step = g = kRun;
+            wave_share(Q, q, j0, end);
+        }
     }
     for (;; j0 += step) {  // one call site: the answering code is large
-        if (!even) {
+        if (counter) {
             unsigned long long at = 0;
             if (threadIdx.x == 0) at = atomicAdd(next, (unsigned long long)g);
             j0 = shfl_u64(at, 0);
         }
-        if (j0 >= q) break;
-        const uint64_t j1 = j0 + g < q ? j0 + g : q;
+        if (j0 >= end) break;
+        const uint64_t j1 = j0 + g < end ? j0 + g : end;
         answer_run<kCk>(Q, j0, (uint32_t)(j1 - j0), X);
-        if (!even) {
-            g = (q - j1) / share;
+        if (counter) {
+            g = (q - j1) / part;
             g = g < 1 ? 1 : g > kRun ? kRun : g;
         }
     }

@@ -255,3 +255,78 @@ def test_single_nodes_over_long_sketches(oracle_lib, k):
         got, status = gpu_query(to_dev_u64(R.reshape(-1)), to_dev_u32(S), n, k, ell, off, nodes, 0,
                                 mode)
         assert np.array_equal(status, wst) and np.array_equal(got, want)
+
+
+def _uneven(kind, q, rng):
+    sizes = np.clip(np.floor(np.exp(1.5 + 1.5 * rng.standard_normal(q))), 0, 1024).astype(int)
+    if kind == "ascending":
+        sizes = np.sort(sizes)
+    elif kind == "descending":
+        sizes = np.sort(sizes)[::-1]
+    elif kind == "front":  # the large sets next to each other
+        sizes = np.concatenate([np.full(q // 100, 700), rng.integers(0, 3, size=q - q // 100)])
+    elif kind == "one":
+        sizes = np.ones(q, dtype=int)
+        sizes[q // 2] = 1024
+    return sizes
+
+
+@pytest.mark.parametrize("kind", ["ascending", "descending", "front", "one"])
+@pytest.mark.parametrize("k", [16, 33, 64])
+def test_uneven_batches(oracle_lib, kind, k):
+    """Batches above the grid whose large sets stand together, of both estimators:
+    every set is answered, whichever wave's share it falls into."""
+    from gpu_util import to_dev_u32, to_dev_u64
+    n, ell, q = 300, 16, 4097 if kind == "one" else 7001
+    rng = np.random.default_rng(k)
+    R, S = _pool_tables(rng, n, k, 0)
+    off, nodes = _sets([rng.integers(0, n, size=s).tolist() for s in _uneven(kind, q, rng)])
+    rt, st = to_dev_u64(R.reshape(-1)), to_dev_u32(S)
+    for estimator, fn in [(0, oracle_lib.union_query), (1, oracle_lib.ck_query)]:
+        log(f"uneven {kind} k={k} est={estimator}")
+        want, wst = fn(R, S, k, ell, off, nodes)
+        got, status = gpu_query(rt, st, n, k, ell, off, nodes, estimator)
+        assert np.array_equal(status, wst) and np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("estimator", [0, 1])
+def test_replayed_plan_with_offsets_out_of_order(oracle_lib, estimator):
+    """A plan above the grid, replayed after some of its offsets were moved: the sets
+    they bound get status -3 and estimate 0, every other set its answer."""
+    import torch
+    import paper_1408_6282_amd as sk
+    from gpu_util import to_dev_u32, to_dev_u64
+    n, ell, k, q = 300, 16, 16, 9000
+    rng = np.random.default_rng(8)
+    R, S = _pool_tables(rng, n, k, 0)
+    sizes = rng.integers(0, 6, size=q)
+    sizes[::500] = 70
+    off, nodes = _sets([rng.integers(0, n, size=s).tolist() for s in sizes])
+    rt, st, qo, qn = to_dev_u64(R.reshape(-1)), to_dev_u32(S), to_dev_u64(off), to_dev_u32(nodes)
+    est = torch.full((q,), -1.0, dtype=torch.float64, device="cuda:0")
+    status = torch.full((q,), 7, dtype=torch.int32, device="cuda:0")
+    plan = sk.QueryPlan(rt, st, n, k, ell, qo, qn, est, status, estimator=estimator)
+    try:
+        for moved in ([], [1, 2000, 2001, 6500], list(range(100, 400, 7)) + [q - 1]):
+            o = off.astype(np.int64).copy()
+            for x in moved:  # back to the start, or past the end
+                o[x] = 0 if x % 2 else int(off[-1]) + 5
+            qo.copy_(torch.from_numpy(o).to(qo.device))
+            est.fill_(-1.0)
+            status.fill_(7)
+            log(f"plan est={estimator} with {len(moved)} offsets moved")
+            plan.launch()
+            torch.cuda.synchronize()
+            bad = (o[1:] < o[:-1]) | (o[1:] > o[-1])
+            bad[0] |= o[0] != 0
+            big = ~bad & (np.diff(o) > 1024)
+            good = np.flatnonzero(~bad & ~big)
+            o2, n2 = _sets([nodes[o[j]:o[j + 1]].tolist() for j in good])
+            fn = oracle_lib.ck_query if estimator else oracle_lib.union_query
+            want, _ = fn(R, S, k, ell, o2, n2)
+            got, code = est.cpu().numpy(), status.cpu().numpy()
+            assert np.all(code[bad] == -3) and np.all(got[bad] == 0.0)
+            assert np.all(code[big] == -2) and np.all(got[big] == 0.0)
+            assert np.all(code[good] == 0) and np.array_equal(got[good], want)
+    finally:
+        plan.free()
