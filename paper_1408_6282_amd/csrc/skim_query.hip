@@ -660,13 +660,14 @@ __device__ __forceinline__ double ck_sorted(const QArgs &Q, uint32_t LG, uint32_
     return sum;
 }
 
+// small_only: sets of more than 64 members are left to k_ck_large.
 template <int R>
 __device__ __forceinline__ void answer_ck(const QArgs &Q, uint64_t j0, uint32_t cnt, MergeLds &X,
-                                          CkLds &L, uint8_t *list) {
+                                          CkLds &L, uint8_t *list, bool small_only) {
     const uint32_t lane = lane_id();
     Run run{j0, 0, 0, list};
     const bool set = load_run(Q, cnt, run);
-    unsigned long long rest = __ballot(set && (R == 0 || run.S > 64));
+    unsigned long long rest = __ballot(set && (R == 0 || (run.S > 64 && !small_only)));
     if constexpr (R > 0) {
         for (uint32_t LG = 0; LG <= 6; ++LG) {
             const uint32_t G = 1u << LG;
@@ -712,9 +713,9 @@ template <int kCk> struct QueryLds {
 };
 template <int kCk>
 __device__ __forceinline__ void answer_run(const QArgs &Q, uint64_t j0, uint32_t cnt,
-                                           QueryLds<kCk> &X) {
+                                           QueryLds<kCk> &X, bool small_only) {
     if constexpr (kCk < 0) answer_bottomk(Q, j0, cnt, X.merge, X.list);
-    else answer_ck<kCk>(Q, j0, cnt, X.merge, X.ck, X.list);
+    else answer_ck<kCk>(Q, j0, cnt, X.merge, X.ck, X.list, small_only);
 }
 
 // The sets [j0, j1) of this wave where every wave of the grid takes a contiguous
@@ -753,7 +754,7 @@ __device__ __forceinline__ bool balanced(const QArgs &Q, uint64_t q) {
 
 template <int kCk>
 __global__ void __launch_bounds__(kQBlock, kCk < 0 ? 4 : kCk == 16 ? 3 : 2) k_query_persistent(
-    QArgs Q, uint64_t q, unsigned long long *next) {
+    QArgs Q, uint64_t q, unsigned long long *next, bool small_only) {
     __shared__ QueryLds<kCk> X;
     // Takes from different waves on the one counter are serialised by the
     // hardware (about 12 ns each).  Sets of less than kTakeMembers members on
@@ -789,7 +790,7 @@ __global__ void __launch_bounds__(kQBlock, kCk < 0 ? 4 : kCk == 16 ? 3 : 2) k_qu
         }
         if (j0 >= end) break;
         const uint64_t j1 = j0 + g < end ? j0 + g : end;
-        answer_run<kCk>(Q, j0, (uint32_t)(j1 - j0), X);
+        answer_run<kCk>(Q, j0, (uint32_t)(j1 - j0), X, small_only);
         if (counter) {
             g = (q - j1) / part;
             g = g < 1 ? 1 : g > kRun ? kRun : g;
@@ -800,7 +801,7 @@ __global__ void __launch_bounds__(kQBlock, kCk < 0 ? 4 : kCk == 16 ? 3 : 2) k_qu
 // One query per workgroup, queries j0 on: a batch within the grid (no counter
 // to reset), or the plain path's launch for one query.
 template <int kCk>
-__global__ void __launch_bounds__(kQBlock, 2) k_query_each(QArgs Q, uint64_t j0) {
+__global__ void __launch_bounds__(kQBlock, 2) k_query_each(QArgs Q, uint64_t j0, bool small_only) {
     __shared__ QueryLds<kCk> X;
     const uint64_t j = j0 + blockIdx.x;
     if constexpr (kCk < 0) {
@@ -815,7 +816,28 @@ __global__ void __launch_bounds__(kQBlock, 2) k_query_each(QArgs Q, uint64_t j0)
         else if (S <= 64) merge_staged<64>(Q, j, Q.qnodes + a, (uint32_t)S, rows);
         else bottomk_wave(Q, j, a, S, X.merge);
     } else {
-        answer_run<kCk>(Q, j, 1, X);
+        answer_run<kCk>(Q, j, 1, X, small_only);
+    }
+}
+
+// The Cohen-Kaplan answers of a batch's sets of more than 64 members, in a launch
+// of their own: their merge is a chain of dependent accesses (S (k - 1) steps at
+// most), which wants as many waves as fit, and the kernels that sort the small
+// sets in registers hold two per SIMD.  A set per wave, or shares of equal
+// weight.  20,000 sets of 200 over k = 64: 74 ms; among the sorted sets 132, and 103
+// with a wave-wide reduction by LDS permutes in each step.
+__global__ void __launch_bounds__(kQBlock, 4) k_ck_large(QArgs Q, uint64_t q) {
+    __shared__ MergeLds X;
+    const uint32_t lane = lane_id();
+    uint64_t j0 = blockIdx.x, end = j0 + 1;
+    if (q > gridDim.x) wave_share(Q, q, j0, end);
+    for (; j0 < end; j0 += 64) {
+        uint64_t a = 0, b = 0;
+        const bool big = j0 + lane < end && set_bounds(Q, j0 + lane, a, b) && b - a > 64;
+        for (unsigned long long rest = __ballot(big); rest; rest &= rest - 1) {
+            const uint32_t src = (uint32_t)__ffsll((long long)rest) - 1;
+            ck_wave(Q, j0 + src, shfl_u64(a, src), shfl_u64(b - a, src), X);
+        }
     }
 }
 
@@ -934,25 +956,33 @@ __global__ void __launch_bounds__(64 * kFewWaves) k_query_few(QArgs Q, uint64_t 
     }
 }
 
-template <int kCk> void launch_each(const QArgs &Q, uint64_t j0, unsigned grid, hipStream_t s) {
-    k_query_each<kCk><<<grid, kQBlock, 0, s>>>(Q, j0);
+template <int kCk> void launch_each(const QArgs &Q, uint64_t j0, unsigned grid, bool small_only,
+                                    hipStream_t s) {
+    k_query_each<kCk><<<grid, kQBlock, 0, s>>>(Q, j0, small_only);
 }
-void launch_each(const QArgs &Q, uint64_t j0, unsigned grid, hipStream_t s) {
+void launch_each(const QArgs &Q, uint64_t j0, unsigned grid, bool small_only, hipStream_t s) {
     if (Q.estimator == 0 && few_queries(Q.k, grid))
         k_query_few<<<grid, 64 * kFewWaves, 0, s>>>(Q, j0);
-    else if (Q.estimator == 0) launch_each<-1>(Q, j0, grid, s);
-    else if (Q.k <= 16) launch_each<16>(Q, j0, grid, s);
-    else if (Q.k <= 32) launch_each<32>(Q, j0, grid, s);
-    else if (Q.k <= 64) launch_each<64>(Q, j0, grid, s);
-    else launch_each<0>(Q, j0, grid, s);
+    else if (Q.estimator == 0) launch_each<-1>(Q, j0, grid, false, s);
+    else if (Q.k <= 16) launch_each<16>(Q, j0, grid, small_only, s);
+    else if (Q.k <= 32) launch_each<32>(Q, j0, grid, small_only, s);
+    else if (Q.k <= 64) launch_each<64>(Q, j0, grid, small_only, s);
+    else launch_each<0>(Q, j0, grid, false, s);
     SKIM_LAUNCH_CHECK();
 }
 
+// err: 1 and 2 for bad offsets, 4 if some set has more than 64 entries.
+constexpr uint32_t kBadOffsets = 3u, kLargeSets = 4u;
 __global__ void k_check_offsets(const uint64_t *qoff, uint64_t q, uint32_t *err) {
+    uint32_t seen = 0;
     for (uint64_t j = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; j <= q;
          j += (uint64_t)gridDim.x * blockDim.x) {
         if (j == 0 && qoff[0] != 0) atomicOr(err, 1u);
         if (j < q && qoff[j + 1] < qoff[j]) atomicOr(err, 2u);
+        if (__any(j < q && qoff[j + 1] - qoff[j] > 64) && !(seen & 4u)) {
+            if (lane_id() == 0) atomicOr(err, 4u);
+            seen = 4u;
+        }
     }
 }
 
@@ -973,17 +1003,24 @@ unsigned query_grid(uint64_t q) {
 
 void launch_queries_async(const QueryArgs &Q, uint64_t q, unsigned long long *next, hipStream_t s) {
     const unsigned grid = query_grid(q);
+    // Cohen-Kaplan: large sets apart once the waves are more than fit on the
+    // chip at two per SIMD (half the grid of a long batch)
+    const bool apart = Q.estimator == 1 && Q.k <= 64 && Q.large && q > query_grid(~0ull) / 2;
     if (q <= grid) {
-        launch_each(Q, 0, (unsigned)q, s);
-        return;
+        launch_each(Q, 0, (unsigned)q, apart, s);
+    } else {
+        fill_u64((uint64_t *)next, 0, 1, s);
+        if (Q.estimator == 0) k_query_persistent<-1><<<grid, kQBlock, 0, s>>>(Q, q, next, false);
+        else if (Q.k <= 16) k_query_persistent<16><<<grid, kQBlock, 0, s>>>(Q, q, next, apart);
+        else if (Q.k <= 32) k_query_persistent<32><<<grid, kQBlock, 0, s>>>(Q, q, next, apart);
+        else if (Q.k <= 64) k_query_persistent<64><<<grid, kQBlock, 0, s>>>(Q, q, next, apart);
+        else k_query_persistent<0><<<grid, kQBlock, 0, s>>>(Q, q, next, false);
+        SKIM_LAUNCH_CHECK();
     }
-    fill_u64((uint64_t *)next, 0, 1, s);
-    if (Q.estimator == 0) k_query_persistent<-1><<<grid, kQBlock, 0, s>>>(Q, q, next);
-    else if (Q.k <= 16) k_query_persistent<16><<<grid, kQBlock, 0, s>>>(Q, q, next);
-    else if (Q.k <= 32) k_query_persistent<32><<<grid, kQBlock, 0, s>>>(Q, q, next);
-    else if (Q.k <= 64) k_query_persistent<64><<<grid, kQBlock, 0, s>>>(Q, q, next);
-    else k_query_persistent<0><<<grid, kQBlock, 0, s>>>(Q, q, next);
-    SKIM_LAUNCH_CHECK();
+    if (apart) {
+        k_ck_large<<<grid, kQBlock, 0, s>>>(Q, q);
+        SKIM_LAUNCH_CHECK();
+    }
 }
 
 static void query_batch(const uint64_t *ranks, const uint32_t *size, uint32_t n, uint32_t k,
@@ -1004,19 +1041,20 @@ static void query_batch(const uint64_t *ranks, const uint32_t *size, uint32_t n,
     SKIM_LAUNCH_CHECK();
     uint32_t herr = 0;
     read_back(&herr, err, sizeof herr, s);
-    SKIM_REQUIRE(herr == 0, "qoff must start at 0 and be non-decreasing");
+    SKIM_REQUIRE(!(herr & kBadOffsets), "qoff must start at 0 and be non-decreasing");
     uint64_t total = 0;
     read_back(&total, qoff + q, sizeof total, s);
     SKIM_REQUIRE(total == 0 || qnodes, "qnodes is NULL");
     QArgs Q{ranks, size, n, k, ell, q, qoff, qnodes, est, qstatus, estimator};
     if (permutation) Q.perm_d = (uint64_t)n * ell;
+    Q.large = herr & kLargeSets;
     if (mode == 0) {
         unsigned long long *next = A.alloc<unsigned long long>(1);
         LaunchTimer t("k_query_persistent", s);
         launch_queries_async(Q, q, next, s);
     } else {
         for (uint64_t j = 0; j < q; ++j) {
-            launch_each(Q, j, 1, s);
+            launch_each(Q, j, 1, false, s);
         }
     }
     SKIM_HIP(hipStreamSynchronize(s));
@@ -1099,7 +1137,7 @@ static skim_query_plan *plan_create(const uint64_t *ranks, const uint32_t *size,
         SKIM_LAUNCH_CHECK();
         uint32_t herr = 0;
         read_back(&herr, err, sizeof herr, s);
-        SKIM_REQUIRE(herr == 0, "qoff must start at 0 and be non-decreasing");
+        SKIM_REQUIRE(!(herr & kBadOffsets), "qoff must start at 0 and be non-decreasing");
         uint64_t total = 0;
         read_back(&total, qoff + q, sizeof total, s);
         SKIM_REQUIRE(total == 0 || qnodes, "qnodes is NULL");
