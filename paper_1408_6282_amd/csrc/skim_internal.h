@@ -271,6 +271,7 @@ struct QueryArgs {
     uint64_t nodes_cap = ~0ull;  // entries qnodes holds (a set reaching past them: status -3)
     uint64_t perm_d = 0;  // n l for sketches of permutation positions, 0 for hashed ranks
     bool large = true;    // some set may have more than 64 members
+    uint64_t members = 0; // entries of all sets; 0: not known to the host
 };
 // Per-node estimates of sketches (perm_d = 0: hashed ranks; else sketches of
 // permutation positions over perm_d = n l pairs), enqueued on `s`.

@@ -330,3 +330,22 @@ def test_replayed_plan_with_offsets_out_of_order(oracle_lib, estimator):
             assert np.all(code[good] == 0) and np.array_equal(got[good], want)
     finally:
         plan.free()
+
+
+@pytest.mark.parametrize("k,q,members", [(33, 128, 1024), (33, 129, 1024), (64, 40, 1024),
+                                         (64, 700, 190), (16, 60, 900)])
+def test_few_large_sets(oracle_lib, k, q, members):
+    """Few sets of many members, whose heads are often equal, around the number of
+    entries from which they go to the kernel for larger batches, a bad member among
+    them."""
+    from gpu_util import to_dev_u32, to_dev_u64
+    n, ell = 300, 16
+    rng = np.random.default_rng(k + q)
+    R, S = _pool_tables(rng, n, k, 0)
+    sets = [rng.integers(0, n, size=members).tolist() for _ in range(q)]
+    sets[3][members // 2] = n
+    sets[7] = rng.integers(0, n, size=65).tolist()
+    off, nodes = _sets(sets)
+    want, wst = oracle_lib.union_query(R, S, k, ell, off, nodes)
+    got, status = gpu_query(to_dev_u64(R.reshape(-1)), to_dev_u32(S), n, k, ell, off, nodes, 0)
+    assert np.array_equal(status, wst) and np.array_equal(got, want)
