@@ -975,10 +975,16 @@ constexpr uint64_t kTailRecords = 1ull << 20;  // record room the host adds befo
 // reads only counts from before the window, and every (pair, source) visit is
 // claimed exactly once, on the device), so waves at different levels stay
 // exact.  A wave hands its stack back to global memory (appended to the next
-// level's array, which the host then continues level by level) when it could
-// outgrow its LDS or the visits reserved by all tails could outgrow the room
-// for records or hash-set inserts that the host gave.  There is no barrier
-// between waves: every wave leaves its loop on its own.
+// level's array, which the host then continues level by level) when a full step
+// could outgrow its LDS, at a list of more than kTailsList sources, or when the
+// visits reserved by all tails could outgrow the room for records or hash-set
+// inserts that the host gave.  There is no barrier between waves: every wave
+// leaves its loop on its own.
+//
+// (A stack nearly full that took as many edges a step as it had room for, one or
+// two, went on alone for hundreds of steps where a search met a giant component,
+// and a hub's list is 64 edges a step: 25,000 in-edges of each of four hubs, 160,000
+// nodes, 19 ms a build for 2.0 with the hub taken by the whole grid.)
 //
 // What bounds it: the longest chain of visits, three dependent accesses each
 // (live source, pair, claim), so nothing else is on the chain: records are
@@ -986,7 +992,8 @@ constexpr uint64_t kTailRecords = 1ull << 20;  // record room the host adds befo
 // the room, and no step has a barrier.  20,000 nodes, weighted cascade: 265 us
 // a window with a workgroup's level-synchronous search (eight barriers and a
 // reservation of visits and of records per level), 116 us so.
-constexpr uint32_t kTailsCap = 192;    // stack entries per wave (LDS)
+constexpr uint32_t kTailsCap = 256;    // stack entries per wave (LDS)
+constexpr uint32_t kTailsList = 512;   // longest live in-list a wave walks by itself
 constexpr int kTailsBlock = 256;
 constexpr int kTailsWaves = kTailsBlock / 64;
 constexpr uint32_t kTailsGrid = 1024;  // workgroups that fit on the device at once (4 per CU)
@@ -1036,20 +1043,21 @@ __global__ void __launch_bounds__(kTailsBlock) k_tails(WinArgs A, uint32_t L, ui
         nrec = 0;
     };
     while (n) {
-        // the entries at the top of the stack, their live edges end to end:
-        // up to 64 edges, and no more than the stack has room for
+        // the entries at the top of the stack, their live edges end to end, up
+        // to 64 edges
         const uint32_t take = min(n, 64u);
         uint64_t key = 0, live = 0;
         uint32_t c = 0;
+        bool hub = false;
         if (lane < take) {
             key = T.key[n - 1 - lane];
             live = T.live[n - 1 - lane];
             c = (live & kLiveOne) ? 1u : min(live_count(live), 64u);
+            hub = !(live & kLiveOne) && live_count(live) > kTailsList;
         }
         const uint32_t incl = wave_scan_sum(c);
-        const uint32_t E = min(min((uint32_t)__builtin_amdgcn_readlane((int)incl, 63), 64u),
-                               kTailsCap - n);
-        bool dump = E == 0;
+        const uint32_t E = min((uint32_t)__builtin_amdgcn_readlane((int)incl, 63), 64u);
+        bool dump = __any(hub) || E > kTailsCap - n;
         if (credit < E) {
             unsigned long long old = 0;
             uint32_t fl = 0;

@@ -318,3 +318,24 @@ def test_dense_windows_count_the_same_work():
     log(f"work {work} by source {work0}")
     assert np.array_equal(R, R0) and np.array_equal(S, S0)
     assert work["visits"] == work0["visits"] and work["scans"] == work0["scans"]
+
+
+@pytest.mark.parametrize("n,fan,denom,ell,k", [
+    (2000, 512, 1, 4, 8),    # the longest list a wave of the tails walks by itself
+    (2000, 513, 1, 4, 8),    # ... and past it
+    (2500, 1200, 2, 16, 16),
+    (3000, 300, 1, 16, 4),   # stacks that fill in few steps
+])
+def test_tails_hand_back_hubs_and_full_stacks(oracle_lib, n, fan, denom, ell, k):
+    """Small frontiers that meet hubs, as in-lists (every 100th node of a cycle) and
+    as sources all over: what the tails hand back goes on level by level."""
+    rng = np.random.default_rng(n + fan)
+    e = [np.stack([np.arange(n), (np.arange(n) + 1) % n], 1)]
+    for v in range(0, n, 100):
+        e.append(np.stack([rng.choice(n, fan, replace=False), np.full(fan, v)], 1))
+        e.append(np.stack([np.full(20, v), rng.choice(n, 20, replace=False)], 1))
+    e = np.unique(np.concatenate(e), axis=0)
+    e = e[e[:, 0] != e[:, 1]]
+    g = from_edges(n, e[:, 0], e[:, 1], 0xFFFFFFFF // denom)
+    log(f"tails hand back n={n} fan={fan} ell={ell} k={k}")
+    _check(oracle_lib, g, ell, k, 9)
