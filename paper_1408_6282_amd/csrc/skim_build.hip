@@ -1166,6 +1166,14 @@ constexpr uint32_t kDenseHeavy = 32;      // longer in-lists are cut into chunks
 constexpr int kDenseBatch = 4;            // levels launched without reading back
 constexpr uint32_t kDenseDeep = 48;       // a window of more levels: no dense window after it
 constexpr double kDenseVisits = 8.0;      // least visits per pair expected of a dense window
+// Its passes and levels cost 0.3 to 1.3 ms whatever is visited, so it has to be
+// expected to make kDenseLeast visits, and the pairs visited so far must not be
+// full: past kDensePruned k arrivals a pair, most are turned away (R-MAT of 2^18
+// nodes, l = 64, k = 32: 7.8 M visits in the window from 1.14 k on, 20 thousand from
+// 2.1 k; 6536 nodes, live degree 1.4, k = 24: 4 thousand from 1.9 k).  32,768-node
+// R-MAT graph, l = 32, k = 7, a window of 15 thousand visits: 1.3 ms dense, 0.5 not.
+constexpr double kDenseLeast = 524288.0;
+constexpr double kDensePruned = 1.25;
 
 struct DenseArgs {
     uint64_t *prec;         // pair records (state, live-list word)
@@ -1963,6 +1971,7 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
         return true;
     };
     bool dense_deep = false;   // a dense window took more than kDenseDeep levels
+    double arrivals = 0.0;     // a visited pair's arrivals so far (means of the windows)
     double expect = cap.dense ? kDenseVisits : 0.0;  // visits per pair expected of the next window
     // Window w covers buckets [bb, be): bucket 0 alone; then, unless that
     // was heavy, as many buckets as keep the arrivals per pair below k; then
@@ -2335,7 +2344,8 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
                 per_pair > kHeavy * (merged ? std::max(1.0, span / 2.0) : 1.0);
             uint32_t next = heavy ? 1u : sh.window_span;
             // until pruning takes hold, a pair's arrivals grow with the sources
-            expect = heavy || dense ? per_pair : 0.0;
+            arrivals += per_pair;
+            expect = (heavy || dense) && arrivals < kDensePruned * k ? per_pair : 0.0;
             merged = false;
             if (w == 0 && span == 1 && !heavy) {
                 // Bucket 0 gave each visited pair per_pair arrivals; with no
@@ -2354,8 +2364,11 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
             }
             prev_visits = h.visits;
             span_next = next;
-            if (bb + span < W && nw)
-                expect *= (double)(wb[std::min(bb + span + next, W)] - wb[bb + span]) / (double)nw;
+            if (bb + span < W && nw) {
+                const double more =
+                    (double)(wb[std::min(bb + span + next, W)] - wb[bb + span]) / (double)nw;
+                expect = (double)v * more >= kDenseLeast ? expect * more : 0.0;
+            }
         }
         if (debug)
             std::fprintf(stderr, "skim window %u: sources %llu visits-so-far %llu hashed %llu "

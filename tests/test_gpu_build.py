@@ -306,6 +306,7 @@ def test_dense_windows_count_the_same_work():
     try:
         sk.skim_timing_reset()
         sk.skim_timing_enable("k_dense_level")
+        sk.skim_set_build_params(dict(first_span=1))
         R, S, _, work, _ = gpu_build(g, 64, 32, 3)
         dense = sk.skim_timing_read("k_dense_level")[1]
         sk.skim_timing_reset()
@@ -339,3 +340,21 @@ def test_tails_hand_back_hubs_and_full_stacks(oracle_lib, n, fan, denom, ell, k)
     g = from_edges(n, e[:, 0], e[:, 1], 0xFFFFFFFF // denom)
     log(f"tails hand back n={n} fan={fan} ell={ell} k={k}")
     _check(oracle_lib, g, ell, k, 9)
+
+
+def test_no_dense_windows_where_pairs_are_full():
+    # few visits are left once the core's pairs hold k: those windows search by
+    # source (the first windows of this graph visit a pair five times on average)
+    import paper_1408_6282_amd as sk
+    from workloads.graphs import Graph, rmat_graph, trivalency_thresholds
+    rp, col = rmat_graph(15, 1 << 17, (0.57, 0.19, 0.19, 0.05), 5)
+    g = Graph(1 << 15, rp, col, trivalency_thresholds(col.size, 5))
+    try:
+        sk.skim_timing_reset()
+        sk.skim_timing_enable("k_dense_seed")
+        _, _, _, work, _ = gpu_build(g, 32, 7, 5)
+        dense = sk.skim_timing_read("k_dense_seed")[1]
+    finally:
+        sk.skim_timing_enable(None)
+    log(f"work {work}, dense windows {dense}")
+    assert work["restarts"] or dense == 0
