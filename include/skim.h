@@ -80,7 +80,8 @@ const char *skim_last_error(void);
  * is done wrong on the device.  what = SKIM_FAULT_ALLOC: the next `count`
  * device allocations the library makes fail as if the device were out of
  * memory (the call that makes one returns SKIM_ENOMEM and writes no
- * result); SKIM_FAULT_SERVE: the next `count` batch copies or launches of
+ * result, except that a sketch build goes on without its windows of source
+ * bit sets where it is those that it has no memory for); SKIM_FAULT_SERVE: the next `count` batch copies or launches of
  * the serving loop are treated as failed (the batch's requests complete
  * with status -5 and its slot is freed); SKIM_FAULT_IC_RECORDS: the next
  * `count` skim_build_ic_sketches calls give their single record-appending
@@ -112,7 +113,14 @@ skim_status skim_debug_inject(uint32_t what, uint32_t count);
  *   work  [6]   out, HOST, may be NULL: work the device did, in order:
  *         accepted visits (node-instance-source), live-edge scans, records
  *         kept for the merge, rank windows processed, restarts of the
- *         window phase after a buffer overflow, and the overflow bits.
+ *         window phase (after a buffer overflow, or without source bit sets
+ *         after an allocation failed), and the overflow bits.
+ * Scratch, besides the graph's live lists: 1 KiB per node for the pairs, as
+ * much again where a window may have to be redone, the records (24 n k bytes
+ * and more) and a hash set of 4 GiB or what a window needs; on graphs with
+ * large reach sets, windows of source bit sets of up to 64 bytes per node and
+ * instance, at most a sixth of the device's memory (a build that has no memory
+ * left for those goes on without them).
  */
 skim_status skim_build_sketches(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t seed,
                                 uint64_t *ranks, uint32_t *size, double *est,

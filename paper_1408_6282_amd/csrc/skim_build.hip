@@ -1832,6 +1832,7 @@ struct Capacity {
     uint64_t hash_min;    // least hash-set size of a window (raised after an overflow)
     uint32_t first_span;  // buckets of window 0 (1 after an optimistic one overflowed)
     bool dense;           // an optimistic first window overflowed its hash set
+    bool no_dense;        // an attempt with dense windows ran out of memory
 };
 
 }  // namespace
@@ -1852,7 +1853,7 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
                         const RankSource &rs, const PairLists &live, const LiveLists *fwd,
                         const uint32_t *sources, const unsigned long long *wb, uint32_t W,
                         const Capacity &cap, const Shapes &sh, uint64_t *ranks_out,
-                        uint32_t *size_out, uint64_t *work, Arena &A) {
+                        uint32_t *size_out, uint64_t *work, bool &dense_used, Arena &A) {
     hipStream_t s = A.stream();
     const uint32_t n = g->n;
     const uint64_t npairs = (uint64_t)n * kPairStride;
@@ -2006,7 +2007,9 @@ static void run_windows(const skim_graph *g, uint32_t ell, uint32_t k, uint64_t 
         // overflow there costs one redo of the window with more room instead
         // of a restart of all windows.  The first window restores the pair
         // records from scratch, the others from a copy taken here.
-        const bool dense = expect >= kDenseVisits && !dense_deep && !fwd && dense_setup(ws, we);
+        const bool dense = expect >= kDenseVisits && !dense_deep && !fwd && !cap.no_dense &&
+                           dense_setup(ws, we);
+        dense_used |= dense;
         const bool guard = !dense && (w == 0 || span_next == 1);
         if (guard && w > 0) {
             if (!snap) snap = A.alloc<uint64_t>(2 * npairs);
@@ -2509,15 +2512,21 @@ static void build_sketches(const skim_graph *g, uint32_t ell, uint32_t k, uint64
     Capacity cap{std::max<uint64_t>(1ull << 20, 3 * (uint64_t)n * k),
                  std::max<uint64_t>(1ull << 20, 3 * biggest),
                  next_pow2(std::max<uint64_t>(1ull << 16, 8 * bucket_max)), 1ull << 16,
-                 shapes.first_span, false};
+                 shapes.first_span, false, false};
     uint32_t retry_flags = 0;
     int attempt = 0;
     for (;; ++attempt) {
+        bool dense_used = false;
         try {
             Arena B(s);
             run_windows(g, ell, k, seed, rs, live, shapes.pull_frontier ? &fwd : nullptr, sources, wb,
-                        W, cap, shapes, ranks_out, size_out, work, B);
+                        W, cap, shapes, ranks_out, size_out, work, dense_used, B);
             break;
+        } catch (const Fail &f) {
+            // the bit sets take memory that the windows by source do not need
+            if (f.st != SKIM_ENOMEM || !dense_used) throw;
+            cap.no_dense = true;
+            clear_error();
         } catch (const Retry &r) {
             retry_flags |= r.flags;
             if (std::getenv("SKIM_DEBUG"))

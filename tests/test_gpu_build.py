@@ -358,3 +358,55 @@ def test_no_dense_windows_where_pairs_are_full():
         sk.skim_timing_enable(None)
     log(f"work {work}, dense windows {dense}")
     assert work["restarts"] or dense == 0
+
+
+def test_build_with_an_allocation_failing():
+    # each allocation of a build with dense windows fails in turn: the call
+    # returns SKIM_ENOMEM with its outputs untouched or, from the bit sets on,
+    # makes the same sketches without them
+    import torch
+    import paper_1408_6282_amd as sk
+    from workloads.graphs import Graph, rmat_graph, trivalency_thresholds
+    rp, col = rmat_graph(14, 1 << 18, (0.57, 0.19, 0.19, 0.05), 5)
+    g = Graph(1 << 14, rp, col, trivalency_thresholds(col.size, 5))
+    G = sk.DeviceGraph.from_host(g, "cuda:0")
+    ell, k = 64, 32
+    ranks = torch.empty(g.n * k, dtype=torch.int64, device="cuda:0")
+    size = torch.empty(g.n, dtype=torch.int32, device="cuda:0")
+
+    def build(nth):
+        ranks.fill_(7)
+        size.fill_(7)
+        sk.skim_timing_reset()
+        sk.skim_debug_inject(sk.SKIM_FAULT_ALLOC_NTH, nth)
+        try:
+            sk.skim_build_sketches(G, ell, k, 3, ranks, size)
+            ok = True
+        except sk.SkimError as e:
+            assert e.status == sk.SKIM_ENOMEM
+            ok = False
+        finally:
+            sk.skim_debug_inject(sk.SKIM_FAULT_ALLOC_NTH, 0)
+        torch.cuda.synchronize()
+        return ok, sk.skim_timing_read("k_dense_seed")[1]
+
+    try:
+        sk.skim_set_build_params(dict(first_span=1))
+        sk.skim_timing_enable("k_dense_seed")
+        ok, dense = build(0)
+        assert ok and dense
+        wr, ws = ranks.clone(), size.clone()
+        refused, without = 0, 0
+        for nth in range(1, 120):
+            log(f"build with allocation {nth} failing")
+            ok, d = build(nth)
+            if ok:
+                assert torch.equal(ranks, wr) and torch.equal(size, ws), nth
+                without += d < dense
+            else:
+                assert (ranks == 7).all() and (size == 7).all(), nth
+                refused += 1
+        assert refused and without
+    finally:
+        sk.skim_timing_enable(None)
+        sk.skim_set_build_params(None)
