@@ -1520,13 +1520,6 @@ __global__ void k_bounds(const uint64_t *seg, uint64_t nrec, uint64_t *start, ui
 
 // ------------------------------------------------------------- 5. merge
 
-// LDS written by some lanes of a wave, then read by others of the same wave.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // A step of a bitonic sort of 64 R 32-bit keys held in registers by one wave
 // (key r of lane l is element r * 64 + l), on the vector unit alone: a lane
 // move and one med3 (with 0 the smaller of the two, with all ones the larger).
@@ -1572,7 +1565,7 @@ __device__ void lds_bitonic(uint64_t *buf, uint32_t count, uint32_t lane) {
                     buf[i + stride] = a;
                 }
             }
-            wave_lds_sync();
+            wave_sync();
         }
 }
 
@@ -1616,7 +1609,7 @@ __device__ __forceinline__ void wave_sort(uint64_t (&x)[R], uint64_t *buf, uint3
         if (lane == 63) next = r + 1 < R ? over : 0xFFFFFFFFu;
         tie |= next != 0xFFFFFFFFu && y[r] >> kPlace == next >> kPlace;
     }
-    wave_lds_sync();
+    wave_sync();
     if (__any(tie)) {
         lds_bitonic(buf, 64u * R, lane);
 #pragma unroll
@@ -1626,7 +1619,7 @@ __device__ __forceinline__ void wave_sort(uint64_t (&x)[R], uint64_t *buf, uint3
         for (int r = 0; r < R; ++r)
             x[r] = y[r] != 0xFFFFFFFFu ? buf[y[r] & ((1u << kPlace) - 1)] : kNone;
     }
-    wave_lds_sync();  // buf may be written again
+    wave_sync();  // buf may be written again
 }
 
 // The k smallest of the S <= 64 R ranks of segment `a` (records sorted by
@@ -1679,7 +1672,7 @@ __device__ __forceinline__ void select_long(uint64_t (*lbuf)[kSelectSmall], uint
             // in by one sort of the 512 slots when the next 256 records, four
             // loads in flight, would outgrow their room.
             for (uint32_t j = lane; j < 512; j += 64) buf[j] = kNone;
-            wave_lds_sync();
+            wave_sync();
             uint64_t tau = kNone;
             uint32_t nc = 0;
             // phase 0: the wave's quarter; 1 and 2: pairs of waves, then of
@@ -1705,7 +1698,7 @@ __device__ __forceinline__ void select_long(uint64_t (*lbuf)[kSelectSmall], uint
                         for (uint32_t j = lane; j < 256; j += 64) buf[256 + j] = lbuf[wave + phase][j];
                 }
                 if (sort) {  // the 512 slots in order, the upper 256 given up
-                    wave_lds_sync();
+                    wave_sync();
                     uint64_t y[8];
 #pragma unroll
                     for (int r = 0; r < 8; ++r) y[r] = buf[r * 64 + lane];
@@ -1714,7 +1707,7 @@ __device__ __forceinline__ void select_long(uint64_t (*lbuf)[kSelectSmall], uint
                     for (int r = 0; r < 4; ++r) buf[r * 64 + lane] = y[r];
 #pragma unroll
                     for (int r = 4; r < 8; ++r) buf[r * 64 + lane] = kNone;
-                    wave_lds_sync();
+                    wave_sync();
                     tau = buf[k - 1];
                     nc = 0;
                 }

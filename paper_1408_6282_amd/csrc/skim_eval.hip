@@ -44,11 +44,10 @@ struct EvalArgs {
     const uint64_t *qoff;
     const uint32_t *qnodes;
     uint64_t *reach;       // [q] out
-    int32_t *status;       // [q] out, may be NULL
     uint32_t *bitmaps;     // [slots][2 n]
     uint32_t *queues;      // [slots][qcap]
     uint64_t qcap;         // l n
-    const uint32_t *covered;  // [2 n] pairs not to enter, or NULL
+    const uint32_t *covered;  // [2 n] pairs not to enter
 };
 
 template <class T> __device__ __forceinline__ T ld(const T *p) {
@@ -74,34 +73,18 @@ __device__ __forceinline__ bool mark(uint32_t *bm, uint64_t p) {
 }
 
 __device__ __forceinline__ bool is_covered(const uint32_t *cov, uint64_t p) {
-    return cov != nullptr && ((cov[p >> 5] >> (p & 31)) & 1u) != 0;
+    return ((cov[p >> 5] >> (p & 31)) & 1u) != 0;
 }
 
 __global__ void __launch_bounds__(kEvalBlock) k_eval(EvalArgs A) {
     __shared__ unsigned long long s_tail;
-    __shared__ uint32_t s_bad;
     const uint32_t tid = threadIdx.x;
     uint32_t *bm = A.bitmaps + (uint64_t)blockIdx.x * 2 * A.n;
     uint32_t *Q = A.queues + (uint64_t)blockIdx.x * A.qcap;
     for (uint64_t j = blockIdx.x; j < A.q; j += gridDim.x) {
-        const uint64_t b = A.qoff[j], e = A.qoff[j + 1];  // validated by the host
-        if (tid == 0) {
-            s_tail = 0;
-            s_bad = 0;
-        }
+        const uint64_t b = A.qoff[j], e = A.qoff[j + 1];
+        if (tid == 0) s_tail = 0;
         __syncthreads();
-        if (s_bad == 0)
-            for (uint64_t t = b + tid; t < e; t += kEvalBlock)
-                if (A.qnodes[t] >= A.n) s_bad = 1u;  // any writer: same value
-        __syncthreads();
-        if (s_bad) {
-            if (tid == 0) {
-                A.reach[j] = 0;
-                if (A.status) A.status[j] = -(int32_t)s_bad;
-            }
-            __syncthreads();
-            continue;
-        }
         // seeds: every (s, i) with s in S, i < l (duplicates in S act once)
         const uint64_t seeds = (e - b) * A.ell;
         for (uint64_t t0 = 0; t0 < seeds; t0 += kEvalBlock) {
@@ -148,10 +131,7 @@ __global__ void __launch_bounds__(kEvalBlock) k_eval(EvalArgs A) {
             __syncthreads();  // appends of this chunk are in the queue and s_tail
         }
         const uint64_t total = s_tail;
-        if (tid == 0) {
-            A.reach[j] = total;
-            if (A.status) A.status[j] = 0;
-        }
+        if (tid == 0) A.reach[j] = total;
         // clean the bitmap words this query set
         for (uint64_t t = tid; t < total; t += kEvalBlock) st(bm + (ld(Q + t) >> 5), 0u);
         __syncthreads();
@@ -520,7 +500,6 @@ extern "C" skim_status skim_greedy_exact(const skim_graph *g, uint32_t ell, uint
         A.bitmaps = T.alloc<uint32_t>(slots * 2 * n);
         A.queues = T.alloc<uint32_t>(slots * qcap);
         A.qcap = qcap;
-        A.status = nullptr;
         uint32_t *covered = T.alloc<uint32_t>(2ull * n);
         uint32_t *sel = T.alloc<uint32_t>(n);
         uint64_t *gain = T.alloc<uint64_t>(n);

@@ -275,18 +275,8 @@ __device__ __forceinline__ uint32_t run_of(const T *ex, T t) {
     return lo;
 }
 
-// Inclusive prefix sum over the wave's 64 lanes, and the lane whose range
-// holds flat position j of the wave's items laid end to end (binary lifting
-// over the prefix sums; j below the wave's total).
-__device__ __forceinline__ uint32_t wave_incl(uint32_t v) {
-    const uint32_t lane = threadIdx.x & 63u;
-#pragma unroll
-    for (uint32_t off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(v, off);
-        if (lane >= off) v += y;
-    }
-    return v;
-}
+// The lane whose range holds flat position j of the wave's items laid end to end
+// (binary lifting over the lanes' inclusive prefix sums; j below the wave's total).
 __device__ __forceinline__ uint32_t wave_owner(uint32_t incl, uint32_t j) {
     uint32_t r = 0;
 #pragma unroll
@@ -1844,7 +1834,8 @@ skim_greedy_state *greedy_create(const skim_graph *g, uint32_t ell, uint32_t k, 
     SKIM_REQUIRE(k >= 2 && k <= 65535, "k must be in [2, 65535]");
     SKIM_REQUIRE(g != nullptr, "graph is NULL");
     if ((uint64_t)g->n > (1ull << 22)) {
-        set_error("skim_greedy supports n <= 4194304 (per-thread search queues of n entries)");
+        set_error("skim_greedy supports n <= 4194304 (its searches take 2.5 KiB per node, at 32-bit "
+                  "offsets)");
         throw Fail{SKIM_EUNSUPPORTED};
     }
     auto st = std::make_unique<skim_greedy_state>();

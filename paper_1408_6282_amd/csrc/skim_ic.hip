@@ -122,7 +122,6 @@ __global__ void k_ic_ties(const uint64_t *keys, uint32_t *vals, uint32_t n, uint
 
 struct IcArgs {
     uint32_t n, k;
-    uint64_t seed;
     const uint64_t *rptr;
     const IcEdge *redge;
     const uint32_t *node_at;  // [k n] node at position t = index + 1
@@ -148,13 +147,6 @@ template <class T> __device__ __forceinline__ T ic_ld(const T *p) {
 }
 template <class T> __device__ __forceinline__ void ic_st(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// LDS accesses of one wave, in program order for the compiler too.
-__device__ __forceinline__ void ic_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Phase of position index x: chunk 0 is phase 0, chunks 4^(p-1) .. 4^p - 1 are
@@ -198,7 +190,7 @@ __global__ void __launch_bounds__(64) k_ic_wave(IcArgs A, uint64_t x0, uint64_t 
     const unsigned long long lower = (1ull << lane) - 1ull;
     uint32_t staged = 0;  // uniform
     auto flush = [&]() {
-        ic_sync();
+        wave_sync();
         unsigned long long base = 0;
         if (lane == 0) base = atomicAdd(A.rcount, (unsigned long long)staged);
         base = ((unsigned long long)(uint32_t)__shfl((int)(uint32_t)(base >> 32), 0) << 32) |
@@ -209,11 +201,11 @@ __global__ void __launch_bounds__(64) k_ic_wave(IcArgs A, uint64_t x0, uint64_t 
             atomicOr(A.ovf, 1u);
         }
         staged = 0;
-        ic_sync();
+        wave_sync();
     };
     for (uint64_t b = x0 + (uint64_t)blockIdx.x * kB; b < x1; b += (uint64_t)gridDim.x * kB) {
         const uint32_t m = x1 - b < kB ? (uint32_t)(x1 - b) : kB;
-        ic_sync();
+        wave_sync();
         for (uint32_t j = lane; j < kHash; j += 64) H[j] = 0xFFFFFFFFu;
         if (lane < m) {
             const uint32_t x = list ? list[b + lane] : (uint32_t)(b + lane);
@@ -222,7 +214,7 @@ __global__ void __launch_bounds__(64) k_ic_wave(IcArgs A, uint64_t x0, uint64_t 
             s_cnt[lane] = 0;
             F[lane] = lane << kIcNodeBits | A.node_at[x];
         }
-        ic_sync();
+        wave_sync();
         // true if `e` is new to the visited set
         auto insert = [&](uint32_t e) {
             uint32_t h = (e * 0x9E3779B1u) >> 16;
@@ -258,10 +250,10 @@ __global__ void __launch_bounds__(64) k_ic_wave(IcArgs A, uint64_t x0, uint64_t 
                 // before a position owns it
 #pragma unroll
                 for (uint32_t w = 0; w < kIcAhead; ++w) s_mark[64 * w + lane] = 0;
-                ic_sync();
+                wave_sync();
                 if (d && first >= base && first - base < 64 * kIcAhead)
                     s_mark[first - base] = (uint8_t)(lane + 1);
-                ic_sync();
+                wave_sync();
                 // the round's edges, all loads in flight before the first coin
                 IcEdge e[kIcAhead];
                 uint32_t rr[kIcAhead];
@@ -296,7 +288,7 @@ __global__ void __launch_bounds__(64) k_ic_wave(IcArgs A, uint64_t x0, uint64_t 
                     tail += c;
                 }
             }
-            ic_sync();
+            wave_sync();
         }
         if (over) {
             uint32_t *out = kB == 1 ? A.heavy : A.more;
@@ -334,7 +326,7 @@ __global__ void __launch_bounds__(64) k_ic_wave(IcArgs A, uint64_t x0, uint64_t 
             }
         }
         if (kPass == 0) {
-            ic_sync();
+            wave_sync();
             if (lane < m) A.counts[s_t[lane] - 1] = s_cnt[lane];
         }
     }
@@ -644,7 +636,6 @@ extern "C" skim_status skim_build_ic_sketches(const skim_graph *g, uint32_t k, u
         IcArgs A{};
         A.n = n;
         A.k = k;
-        A.seed = seed;
         A.rptr = rptr;
         A.redge = redge;
         A.node_at = node_at;

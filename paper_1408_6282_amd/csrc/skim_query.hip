@@ -41,14 +41,6 @@ struct MergeLds {
     uint16_t mlim[kMaxMembers];
 };
 
-// LDS written by some lanes of the wave, then read by others of it (the
-// block is one wave).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ uint64_t shfl_u64(uint64_t x, uint32_t src) {
     const uint32_t lo = __shfl((uint32_t)x, (int)src), hi = __shfl((uint32_t)(x >> 32), (int)src);
     return ((uint64_t)hi << 32) | lo;

@@ -12,6 +12,14 @@
 
 namespace skim {
 
+// LDS written by some lanes of a wave, then read by others of it: in program order
+// for the compiler too.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <int kCtrl> __device__ __forceinline__ uint32_t dpp_move(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, kCtrl, 0xF, 0xF, true);
 }
