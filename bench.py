@@ -289,7 +289,8 @@ def bench_rmat(torch, sk, steps=2):
     torch.cuda.empty_cache()
     # the searches' random accesses at the rates plain gathers and atomics
     # reach on a table the size of this build's pair records (17 GB: no
-    # cache holds it)
+    # cache holds it); a floor for a search by source: windows of source bit
+    # sets move many scans along an edge at once and go below it
     try:
         ra = random_access_rates(torch, table_log2=31)
         floor_s = work["scans"] / ra["gather_per_s"] + work["visits"] / ra["atomic_add_per_s"]

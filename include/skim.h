@@ -185,7 +185,8 @@ skim_status skim_estimates(const uint64_t *ranks, const uint32_t *size, uint32_t
  *   entries, or -3 when its offsets are out of order (only a replayed plan
  *   can see that; that query's est is 0, the rest of the batch is
  *   unaffected).  An empty set gives est 0, status 0.
- *   mode 0: one persistent launch for the whole batch (default);
+ *   mode 0: one persistent launch for the whole batch (default; a second one
+ *   for the Cohen-Kaplan sets of more than 64 entries of a long batch);
  *   mode 1: one launch per query (the plain path, for comparison).
  * The call validates qoff, launches, and waits for the stream.
  */
@@ -341,9 +342,13 @@ skim_status skim_greedy_state_load(const skim_graph *g, uint32_t ell, uint32_t k
  * k in [2, 256], k n < 2^32; same graph conventions and validation as
  * skim_build_sketches.  Every position runs a complete reverse search (an
  * instance has one source, so nothing prunes): the work is about k times
- * the sum of all nodes' influence.  Scratch: up to 2 GiB of records and
- * about 30 bytes per position, plus n / 8 + 4 n bytes per workgroup for the
- * searches that reach more than 1024 nodes, at most 2 GiB.
+ * the sum of all nodes' influence.  Scratch: about 40 bytes per position
+ * and per edge, the records (8 bytes each, up to 2 GiB appended in one pass, in which a
+ * node that has k takes few more), as much again and a sort's temporaries to
+ * order them, plus n / 8 + 4 n bytes per workgroup for the searches that reach
+ * more than 1024 nodes, at most 2 GiB.  Records that outgrow the 2 GiB, and
+ * those of such searches, are counted first and then written, every reached
+ * (node, position): twice 8 bytes for each, without a bound.
  */
 skim_status skim_build_ic_sketches(const skim_graph *g, uint32_t k, uint64_t seed,
                                    uint32_t *positions, double *est, void *stream);

@@ -683,7 +683,7 @@ __global__ void __launch_bounds__(kAheadGiantBlock) k_ahead_giant(SkArgs A) {
 // What bounds it: the chain of accesses and barriers, about 3 us per batch,
 // 3 us per seed's first filling prefix and 2 us per residual level.  1000
 // nodes, l = k = 64, 200 seeds: 6.0 ms with a search per thread in each batch
-// and six barriers per level, 2.6 ms now; 10^6 nodes, 50 seeds: 20 and 5 ms.
+// and six barriers per level, 2.7 ms now (a call 3.0); 10^6 nodes, 50 seeds: 20 and 5 ms.
 template <bool kLds, bool kLdsState>
 __global__ void __launch_bounds__(kSkimBlock) k_skim(SkArgs A, uint32_t goal, bool begin, uint64_t handoff,
                                                      uint32_t *seeds, uint64_t *gains,

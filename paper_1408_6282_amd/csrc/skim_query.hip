@@ -12,9 +12,10 @@
 //    member counting as rho = 1; the weights are added in increasing order of
 //    the value.  Sets of up to 64 members over sketches of k <= 64 are sorted
 //    in registers (ck_sorted); others are merged by the whole wave.
-// The batched path is one persistent launch whose waves pull runs of queries
-// from a device counter; the plain path launches the same device code once
-// per query.
+// The batched path is one persistent launch whose waves take shares of the batch or
+// pull runs of queries from a device counter (Cohen-Kaplan's large sets of a long
+// batch: a second launch); the plain path launches the same device code once per
+// query.
 #include "skim_internal.h"
 #include "skim_wave.h"
 
@@ -220,9 +221,9 @@ __device__ __forceinline__ void merge_group(const QArgs &Q, uint64_t j, const ui
 // One set alone in its workgroup (k_query_each), S <= G members: the
 // first ranks of every row go to LDS at once, one memory latency instead of
 // one in most steps (a member takes about k / S steps in a row's order, so
-// the rest is rarely reached), and lane t merges member t from there.  16
-// lognormal sets over k = 64 (20,000 nodes), bound by the chain of 64 steps:
-// 24.2 us a call when the steps read global memory, 22.7 us so.
+// the rest is rarely reached), and lane t merges member t from there.  Bound by
+// the chain of k steps: 16 lognormal sets over k = 256 (20,000 nodes), a batch
+// call, 159 us with steps in global memory and LDS permutes, 102 so.
 constexpr uint32_t kStagedRanks = sizeof(MergeLds) / sizeof(uint64_t);
 template <uint32_t G>
 __device__ __forceinline__ void merge_staged(const QArgs &Q, uint64_t j, const uint32_t *nodes,
@@ -480,7 +481,8 @@ __device__ __forceinline__ void answer_bottomk(const QArgs &Q, uint64_t j0, uint
 // in 10^9 for hashed ranks) is answered by the merge instead.
 //
 // What bounds it: vector-unit instructions (24,000 per set of 50 over k = 64)
-// at two waves per SIMD.  The merge it replaces made one serial step of two
+// at two waves per SIMD; with 64 ranks a lane part of the keys is in scratch (300
+// to 372 bytes a lane), with up to 32 none.  The merge it replaces made one serial step of two
 // wave-wide reductions and three dependent loads per distinct value: 20,000
 // sets of 50 over a 10^6-node table, 23.9 -> 1.16 ms.
 struct CkLds {
@@ -870,15 +872,15 @@ __device__ __forceinline__ uint64_t merge_rows(uint64_t x, uint64_t down, uint64
 
 // Few bottom-k queries over sketches of k <= 64, a workgroup each: its waves
 // merge the members' rows (of more than 64 members those that can matter) two
-// at a time, a rank per lane, and then
-// each other's results, so the chain is S / kFewWaves + 3 merges of about 0.4
-// us where stepping through the union is k steps of 0.2 us.  Lognormal sets
-// (20,000 nodes, mean 12, the largest of a batch 50 to 500 members), k = 64: 16
-// of them 26.9 us a call by the kernel for larger batches, 11.4 so; 64: 27.5
-// and 15.7, 1024: 30.3 and 22.7, 2048: 31.0 and 29.8.  With k = 16 the steps
-// are few: 64 sets 8.9 and 8.6 us, 256 sets 9.5 and 9.7.
+// at a time, a rank per lane, and then each other's results, so the chain is
+// S / kFewWaves + 3 merges of about 0.4 us where stepping through the union is k
+// steps of 0.2 us.  Lognormal sets (20,000 nodes, mean 12), k = 64: 16 of them 22.7
+// us a call by the kernel for larger batches, 7.6 to 8.4 so.  Batches whose largest
+// set has 50 to 500 members: 64 sets 27.5 and 15.7, 1024 30.3 and 22.7, 2048 31.0
+// and 29.8.  With k = 16 the steps are few: 64 sets 8.9 and 8.6 us, 256 sets 9.5 and
+// 9.7.
 constexpr int kFewWaves = 8;
-//
+
 // Where the entries of all sets are known and more than kFewMembers, most sets are
 // far above 64 members: if many of those begin with the same rank (20,000 nodes)
 // little is filtered, and the workgroups merge whole rows of which the steps read a
@@ -1249,7 +1251,7 @@ extern "C" void skim_query_plan_free(skim_query_plan *plan) { skim::plan_free(pl
 
 // -------------------------------------------------------- resident sketches
 // A library-owned copy of a sketch table (ranks, sizes, per-node estimates)
-// answering union queries with one enqueue-only launch: no host check of the
+// answering union queries by launches that are only enqueued: no host check of the
 // offsets (the query kernel checks every set on the device, status -3) and
 // no wait, so the call can be captured into a HIP graph.  The persistent
 // kernel's work counter is reset by a fill kernel on the stream (no memset
